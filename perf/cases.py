@@ -1,0 +1,288 @@
+"""Performance cases of the Locret chunk step: what a program that serves one attention layer has it do.
+
+Four kinds of work, all through the public binding (paper_2410_01805_amd.binding):
+  request   a prompt from an empty cache: evicting chunk steps, optionally the trailing non-evicting pass and a few
+            generated tokens (Algorithm 1 from its first chunk to the generation that follows it)
+  generate  tokens generated on a full cache, then rolled back (the appended units carry NaN scores, so one
+            evicting call drops exactly them): several continuations sampled from the same retained prompt
+  score     the retaining head alone
+  evict     append + top-b + compaction alone over a prompt from an empty cache, on scores that the caller has
+
+Head layouts, budgets, chunk sizes and hidden widths are those of `synth.WORKLOADS`, of the tests and of bench.py.
+"""
+import math
+
+import torch
+
+from paper_2410_01805_amd import binding as B
+
+DEV = "cuda:0"
+
+# (query heads, KV heads, head dim, rotary base); base 0: no rotary embedding
+LLAMA = dict(h=32, h_kv=8, d=128, theta=500000.0)
+PHI3 = dict(h=32, h_kv=32, d=96, theta=10000.0)
+NARROW = dict(h=32, h_kv=8, d=64, theta=500000.0)
+SMALL_F32 = dict(h=8, h_kv=2, d=64, theta=0.0)
+
+DEFAULTS = dict(kind="request", dtype="bf16", d_R=1024, expand=0, kv_bits=0, planted=False, N=0, n_s=0, n_pin=0, pyramid=False,
+                tail=0, gen=0, scored=False, T=0)
+
+
+def _case(name=None, **kw):
+    c = dict(DEFAULTS, **kw)
+    if name is not None:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # The float32 layer of the test configuration, a whole 4096-token stream in chunks of 512.
+        _case("f32_stream", **SMALL_F32, dtype="f32", B=512, b=1024, n_s=64, d_R=256, expand=1, N=4096),
+        # A short prompt in one ragged chunk and a few scored tokens after it: launches and latency.
+        _case("short_prompt", **LLAMA, B=1024, b=1024, n_s=256, N=611, gen=8, scored=True),
+        # Prompts at 32K-context settings (b = 6144, chunks of 2048), the last chunk ragged.
+        _case("llama_32k", **LLAMA, B=2048, b=6144, n_s=2048, N=15900),
+        # The headline workload's chunk step (b = 16384, chunks of 4096; 1 % of the keys 4 times as large), to the steady state.
+        _case("llama_128k", **LLAMA, B=4096, b=16384, n_s=2048, N=32768, planted=True),
+        # Many KV heads of 96 dims (b = 8192, chunks of 4096).
+        _case("phi3_128k", **PHI3, B=4096, b=8192, n_s=1024, N=20480),
+        # The paper's own Llama setting: chunks of 1024, n_s = 2500, last 100 tokens not evicting, then generation.
+        _case("llama_paper_row", **LLAMA, B=1024, b=16384, n_s=2500, N=20100, tail=100, gen=8),
+        # bf16 heads of 64 dims.
+        _case("narrow_heads", **NARROW, B=2048, b=4096, n_s=512, N=10000),
+        # 4-bit cache rows, prompt and generation.
+        _case("q4_request", **LLAMA, B=2048, b=6144, n_s=1024, N=8192, kv_bits=4, gen=32),
+        # A budget per KV head.
+        _case("head_budgets", **LLAMA, B=2048, b=14336, n_s=1024, N=16384, pyramid=True),
+        # Generation on the full 16K cache.
+        _case("llama_generate", **LLAMA, kind="generate", B=1024, b=16384, gen=16, planted=True),
+        # The retaining head alone on a ragged block of tokens.
+        _case("score_block", **LLAMA, kind="score", B=4096, b=1024, T=1500),
+        # Eviction alone with a large budget (the scores come from elsewhere), the last chunk ragged.
+        _case("evict_large", **LLAMA, kind="evict", B=4096, b=32768, n_s=2048, N=48000),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case: sizes spread over what the listed cases stand for, odd ones among them."""
+    kind = rng.choice(["request"] * 5 + ["generate"] * 2 + ["score", "evict"])
+    f32 = kind != "score" and rng.random() < 0.15
+    if f32:
+        layout = dict(h=8, h_kv=2, d=rng.choice([64, 64, 128]), theta=rng.choice([0.0, 10000.0]))
+        d_R, big_B, big_b = 256, 1024, 2048
+    else:
+        layout = dict(rng.choice([LLAMA, LLAMA, PHI3, NARROW, dict(h=16, h_kv=4, d=128, theta=500000.0),
+                                  dict(h=16, h_kv=8, d=128, theta=10000.0)]))
+        d_R, big_B, big_b = rng.choice([512, 1024, 1024]), 4096, 16384
+    kw = dict(layout, dtype="f32" if f32 else "bf16", d_R=d_R)
+    b = _log(rng, 1024, big_b)
+    if kind == "generate":
+        return _case(**kw, kind=kind, B=1024, b=b, gen=rng.randint(8, 32), planted=rng.random() < 0.5,
+                     kv_bits=4 if not f32 and rng.random() < 0.25 else 0)
+    if kind == "score":
+        T = _log(rng, 32, 4096)
+        return _case(**kw, kind=kind, B=T, b=1024, T=T)
+    if kind == "evict":
+        b = _log(rng, 1024, 8192 if layout["h_kv"] > 8 else 32768)
+        chunk = _log(rng, 256, min(4096, b))
+        return _case(**kw, kind=kind, B=chunk, b=b, n_s=rng.randint(0, b // 4), N=min(48 * chunk, b + rng.randint(chunk, 4 * chunk)))
+    chunk = _log(rng, 256, min(big_B, b))
+    n_s = rng.randint(0, b // 8)
+    pyramid = not f32 and layout["h_kv"] > 2 and rng.random() < 0.2
+    # tokens: about a budget and a few chunks more, as far as the largest listed case's work goes
+    N = b + rng.randint(0, 4 * chunk)
+    most = _request_flops(listed()[3]) * 0.9
+    if f32:
+        most /= 50
+    c = _case(**kw, B=chunk, b=b, n_s=n_s, N=N, pyramid=pyramid, planted=rng.random() < 0.3,
+              kv_bits=4 if not f32 and not pyramid and rng.random() < 0.2 else 0,
+              tail=rng.choice([0, 0, rng.randint(16, 128)]), gen=rng.choice([0, 0, rng.randint(4, 32)]), scored=rng.random() < 0.3,
+              n_pin=rng.choice([0, 0, rng.randint(1, b // 16)]) if not pyramid else 0)
+    while _request_flops(c) > most or c["N"] / c["B"] > 48:
+        c["N"] = c["N"] * 3 // 4
+    return c
+
+
+def _budgets(c):
+    """Head-wise budgets from b down to b / 7, the same total as a single budget of 4/7 b."""
+    n = c["h_kv"]
+    return [int(round(c["b"] * (1 - 6 / 7 * m / max(1, n - 1)))) for m in range(n)]
+
+
+def _chunks(c):
+    return [(lo, min(c["N"], lo + c["B"])) for lo in range(0, c["N"], c["B"])]
+
+
+# ---- inputs ----------------------------------------------------------------------------------------------------------
+def _tokens(c, n, gen):
+    dt = torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+    q = torch.randn(n, c["h"], c["d"], device=DEV, generator=gen).to(dt)
+    k = torch.randn(n, c["h_kv"], c["d"], device=DEV, generator=gen)
+    v = torch.randn(n, c["h_kv"], c["d"], device=DEV, generator=gen).to(dt)
+    if c["planted"]:
+        k *= torch.where(torch.rand(n, 1, 1, device=DEV, generator=gen) < 0.01, 4.0, 1.0)
+    return q, k.to(dt), v
+
+
+def prepare(case, seed):
+    c = case
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    rope = c["theta"] > 0
+    layer = B.LocretLayer(B.locret_config(c["h"], c["h_kv"], c["d"], c["B"], c["b"], c["d_R"], c["expand"],
+                                          B.LOCRET_F32 if c["dtype"] == "f32" else B.LOCRET_BF16, int(rope), c["theta"], 0.0, c["kv_bits"]), DEV)
+    d_in = 3 * c["h"] * c["d"] if c["expand"] else (c["h"] + 2 * c["h_kv"]) * c["d"]
+    W1 = (0.02 * torch.randn(d_in, c["d_R"], device=DEV, generator=gen)).to(layer.tdtype)
+    W2 = (0.02 * torch.randn(c["d_R"], c["h_kv"], device=DEV, generator=gen)).to(layer.tdtype)
+    layer.set_weights(W1, W2)
+    s = dict(case=c, layer=layer, weights=(W1, W2))
+    if c["kind"] == "request":
+        if c["pyramid"]:
+            layer.set_head_budgets(_budgets(c))
+        if c["n_pin"]:
+            layer.set_pinned_prefix(c["n_pin"])
+        n = c["N"] + c["tail"] + c["gen"]
+        q, k, v = _tokens(c, n, gen)
+        out = torch.empty_like(q)
+        steps = _chunks(c) + ([(c["N"], c["N"] + c["tail"])] if c["tail"] else [])
+        scores = torch.zeros(c["h_kv"] * (n + 4) + 4 * len(steps) + 4, device=DEV)      # every step's part starts at a multiple of 16 bytes
+        s["out"], at = [out, scores], 0
+        s["steps"], s["tokens"] = [], []
+        for lo, hi in steps + [(i, i + 1) for i in range(n - c["gen"], n)]:
+            size = c["h_kv"] * (hi - lo)
+            part = (q[lo:hi], k[lo:hi], v[lo:hi], out[lo:hi], scores[at:at + size])
+            if lo < c["N"] + c["tail"]:
+                s["steps"].append((*part, hi - lo, int(lo < c["N"])))
+            else:
+                s["tokens"].append(part if c["scored"] else (*part[:4], None))
+            at += (size + 3) // 4 * 4
+    elif c["kind"] == "generate":
+        # the cache as a prompt left it: b units with the scores they were kept for
+        for lo in range(0, c["b"], c["B"]):
+            _, k, v = _tokens(c, min(c["B"], c["b"] - lo), gen)
+            B.locret_evict_compact(layer.ctx, torch.randn(c["h_kv"], k.shape[0], device=DEV, generator=gen), k, v, k.shape[0], 0, None)
+        q, k, v = _tokens(c, c["gen"], gen)
+        s["out"] = torch.empty_like(q)
+        s["tokens"] = [(q[i:i + 1], k[i:i + 1], v[i:i + 1], s["out"][i:i + 1]) for i in range(c["gen"])]
+        s["none"] = torch.full((c["h_kv"], 1), float("nan"), device=DEV)
+    elif c["kind"] == "score":
+        s["qkv"] = _tokens(c, c["T"], gen)
+        s["out"] = torch.empty(c["h_kv"], c["T"], device=DEV)
+    else:
+        _, k, v = _tokens(c, c["N"], gen)
+        s["steps"] = [(torch.randn(c["h_kv"], hi - lo, device=DEV, generator=gen), k[lo:hi], v[lo:hi], hi - lo) for lo, hi in _chunks(c)]
+        s["kept"] = torch.zeros(c["h_kv"], c["b"], device=DEV, dtype=torch.int32)
+    return s
+
+
+# ---- one pass --------------------------------------------------------------------------------------------------------
+def _cache(layer):
+    """The live cache as the binding shows it, in place: K, V, scores, original positions."""
+    view, c = B.locret_cache_view(layer.ctx), layer.cfg
+    base, rows = layer.workspace.data_ptr(), c.n_kv_heads * view["row_stride"]
+
+    def at(addr, dtype, inner):
+        size = rows * inner * dtype.itemsize
+        return layer.workspace[addr - base:addr - base + size].view(dtype).view(c.n_kv_heads, view["row_stride"], inner)[:, :view["len"]]
+    return [at(view["K"], layer.tdtype, c.head_dim), at(view["V"], layer.tdtype, c.head_dim), at(view["score"], torch.float32, 1),
+            at(view["orig_pos"], torch.int32, 1)]
+
+
+def run(state):
+    s = state
+    c, ctx = s["case"], s["layer"].ctx
+    if c["kind"] == "request":
+        B.locret_reset(ctx)
+        for q, k, v, out, scores, T, evict in s["steps"]:
+            B.locret_prefill_chunk(ctx, q, k, v, T, c["n_s"], evict, None, out, scores, None)
+        for q, k, v, out, scores in s["tokens"]:
+            B.locret_decode_step(ctx, q, k, v, c["scored"], out, scores)
+        return s["out"]
+    if c["kind"] == "generate":
+        for q, k, v, out in s["tokens"]:
+            B.locret_decode_step(ctx, q, k, v, False, out, None)
+        B.locret_evict_compact(ctx, s["none"], k, v, 1, 0, None)
+        return s["out"]
+    if c["kind"] == "score":
+        B.locret_score(ctx, *s["qkv"], c["T"], s["out"])
+        return s["out"]
+    B.locret_reset(ctx)
+    for scores, k, v, T in s["steps"]:
+        B.locret_evict_compact(ctx, scores, k, v, T, c["n_s"], s["kept"])
+    return [s["kept"], *_cache(s["layer"])]
+
+
+# ---- what a pass cannot do without -----------------------------------------------------------------------------------
+def _sizes(c):
+    """Bytes of an element, of a cached K and V row pair with its score and position, and the retaining head's input width."""
+    es = 4 if c["dtype"] == "f32" else 2
+    row = 2 * (c["d"] // 2 + 4 * (c["d"] // 32)) if c["kv_bits"] else 2 * c["d"] * es
+    return es, row + 8, (c["h"] + 2 * c["h_kv"]) * c["d"]
+
+
+def _step(c, lens, T, scored=True):
+    """(bytes, flops) of attention, append and retaining head over T tokens on caches of lens[m] units."""
+    es, row, K = _sizes(c)
+    g = c["h"] // c["h_kv"]
+    flops = sum(4 * g * c["d"] * (T * n + T * (T + 1) // 2) for n in lens)
+    size = 2 * T * c["h"] * c["d"] * es + 2 * T * c["h_kv"] * c["d"] * es + sum(n * (row - 8) + T * row for n in lens)
+    if scored:
+        flops += 2 * T * K * c["d_R"] + 2 * T * c["d_R"] * c["h_kv"]
+        size += K * c["d_R"] * es + T * c["h_kv"] * 4
+    return size, flops
+
+
+def _request(c):
+    budgets = _budgets(c) if c["pyramid"] else [c["b"]] * c["h_kv"]
+    lens, size, flops, row = [0] * c["h_kv"], 0, 0, _sizes(c)[1]
+    for lo, hi in _chunks(c):
+        a, f = _step(c, lens, hi - lo)
+        size, flops = size + a, flops + f
+        over = any(n + hi - lo > b for n, b in zip(lens, budgets))
+        lens = [min(n + hi - lo, b) for n, b in zip(lens, budgets)]
+        if over:
+            size += 2 * sum(lens) * row          # the kept units move together
+    for T, scored in ([(c["tail"], True)] if c["tail"] else []) + [(1, c["scored"])] * c["gen"]:
+        a, f = _step(c, lens, T, scored)
+        size, flops = size + a, flops + f
+        lens = [n + T for n in lens]
+    return size, flops
+
+
+def _request_flops(c):
+    return _request(c)[1]
+
+
+def work(case):
+    c = case
+    es, row, K = _sizes(c)
+    if c["kind"] == "request":
+        size, flops = _request(c)
+    elif c["kind"] == "generate":
+        size, flops = 2 * c["h_kv"] * c["b"] * row, 0      # the roll-back's move
+        for i in range(c["gen"]):
+            a, f = _step(c, [c["b"] + i] * c["h_kv"], 1, False)
+            size, flops = size + a, flops + f
+    elif c["kind"] == "score":
+        size = c["T"] * K * es + K * c["d_R"] * es + c["T"] * c["h_kv"] * 4
+        flops = 2 * c["T"] * K * c["d_R"] + 2 * c["T"] * c["d_R"] * c["h_kv"]
+    else:
+        n, size, flops = 0, 0, 0
+        for lo, hi in _chunks(c):
+            size += 2 * c["h_kv"] * (hi - lo) * row
+            n, over = min(n + hi - lo, c["b"]), n + hi - lo > c["b"]
+            if over:
+                size += 2 * c["h_kv"] * n * row + 4 * c["h_kv"] * n
+    return {"bytes": size, "flops": flops}
+
+
+def tolerance(case):
+    if case["kind"] == "evict":
+        return "exact"
+    # Against the same chunk in float64 (first chunks, scores and attention): float32 5e-7 (sums of a few thousand terms), bf16 2.7e-3
+    # to 4.7e-3 (queries, keys, probabilities and outputs rounded to 8 bits once each; the upper end with planted keys).
+    return {"rel": 2e-6} if case["dtype"] == "f32" else {"rel": 1.5e-2}
