@@ -119,8 +119,18 @@ def _chunks(c):
 
 
 # ---- inputs ----------------------------------------------------------------------------------------------------------
+def _dtype(c):
+    return torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+
+
+def _weights(c, gen):
+    d_in = 3 * c["h"] * c["d"] if c["expand"] else (c["h"] + 2 * c["h_kv"]) * c["d"]
+    return ((0.02 * torch.randn(d_in, c["d_R"], device=DEV, generator=gen)).to(_dtype(c)),
+            (0.02 * torch.randn(c["d_R"], c["h_kv"], device=DEV, generator=gen)).to(_dtype(c)))
+
+
 def _tokens(c, n, gen):
-    dt = torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+    dt = _dtype(c)
     q = torch.randn(n, c["h"], c["d"], device=DEV, generator=gen).to(dt)
     k = torch.randn(n, c["h_kv"], c["d"], device=DEV, generator=gen)
     v = torch.randn(n, c["h_kv"], c["d"], device=DEV, generator=gen).to(dt)
@@ -135,9 +145,7 @@ def prepare(case, seed):
     rope = c["theta"] > 0
     layer = B.LocretLayer(B.locret_config(c["h"], c["h_kv"], c["d"], c["B"], c["b"], c["d_R"], c["expand"],
                                           B.LOCRET_F32 if c["dtype"] == "f32" else B.LOCRET_BF16, int(rope), c["theta"], 0.0, c["kv_bits"]), DEV)
-    d_in = 3 * c["h"] * c["d"] if c["expand"] else (c["h"] + 2 * c["h_kv"]) * c["d"]
-    W1 = (0.02 * torch.randn(d_in, c["d_R"], device=DEV, generator=gen)).to(layer.tdtype)
-    W2 = (0.02 * torch.randn(c["d_R"], c["h_kv"], device=DEV, generator=gen)).to(layer.tdtype)
+    W1, W2 = _weights(c, gen)
     layer.set_weights(W1, W2)
     s = dict(case=c, layer=layer, weights=(W1, W2))
     if c["kind"] == "request":
@@ -214,6 +222,106 @@ def run(state):
     for scores, k, v, T in s["steps"]:
         B.locret_evict_compact(ctx, scores, k, v, T, c["n_s"], s["kept"])
     return [s["kept"], *_cache(s["layer"])]
+
+
+# ---- the same in 64 bits ---------------------------------------------------------------------------------------------
+def _rotated(c, x, first):
+    """Rows of x [n, ..., d] at positions first, first + 1, ...: pair (i, i + d/2) turned by position * theta^(-2i/d)."""
+    if c["theta"] <= 0:
+        return x
+    half = c["d"] // 2
+    freq = c["theta"] ** (-2.0 * torch.arange(half, device=DEV, dtype=torch.float64) / c["d"])
+    angle = (first + torch.arange(x.shape[0], device=DEV, dtype=torch.float64))[:, None] * freq
+    angle = angle.view(x.shape[0], *[1] * (x.dim() - 2), half)
+    lo, hi = x[..., :half], x[..., half:]
+    return torch.cat([lo * angle.cos() - hi * angle.sin(), hi * angle.cos() + lo * angle.sin()], -1)
+
+
+def _rows4(x):
+    """Rows as 4-bit codes hold them: groups of 32, step (max - min) / 15 in bf16, codes rounded to even, decided in 32 bits."""
+    g = x.float().reshape(*x.shape[:-1], -1, 32)
+    lo, hi = g.amin(-1, keepdim=True), g.amax(-1, keepdim=True)
+    step = ((hi - lo) / torch.full_like(hi, 15.0)).bfloat16().float()
+    step = torch.where(step > 0, step, torch.ones_like(step))
+    codes = ((g - lo) / step).round().clamp(0, 15)
+    return (lo.double() + codes.double() * step.double()).reshape(x.shape)
+
+
+def _scores64(c, W1, W2, q, k, v):
+    """[h_kv, T] = SiLU([q, k, v] W1) W2."""
+    if c["expand"]:
+        k, v = (x.repeat_interleave(c["h"] // c["h_kv"], dim=1) for x in (k, v))
+    z = torch.cat([x.flatten(1).double() for x in (q, k, v)], 1) @ W1.double()
+    return (z * z.sigmoid() @ W2.double()).T.contiguous()
+
+
+def _attend64(c, q, K, V):
+    """q [T, h, d] as the last T of the rows K[m], V[m] [n, d] of each KV head."""
+    T, g = q.shape[0], c["h"] // c["h_kv"]
+    out = torch.empty(q.shape, device=DEV, dtype=torch.float64)
+    for m in range(c["h_kv"]):
+        n = K[m].shape[0]
+        keys = _rotated(c, K[m], 0).T.contiguous()
+        x = _rotated(c, q[:, m * g:(m + 1) * g].double(), n - T).transpose(0, 1)
+        hidden = torch.arange(n, device=DEV)[None] > torch.arange(n - T, n, device=DEV)[:, None]
+        for j in range(g):
+            p = torch.softmax((x[j].contiguous() @ keys / math.sqrt(c["d"])).masked_fill_(hidden, -math.inf), 1)
+            out[:, m * g + j] = p @ V[m]
+    return out
+
+
+def exact(case, seed):
+    c = case
+    if c["kind"] == "evict":
+        return None                     # rows and whole numbers, moved and not computed
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    W1, W2 = _weights(c, gen)
+    stored = _rows4 if c["kv_bits"] else torch.Tensor.double
+    heads = range(c["h_kv"])
+    if c["kind"] == "score":
+        return _scores64(c, W1, W2, *_tokens(c, c["T"], gen))
+    K, V = ([torch.empty(0, c["d"], device=DEV, dtype=torch.float64)] * c["h_kv"] for _ in range(2))
+    S = [torch.empty(0, device=DEV)] * c["h_kv"]
+
+    def append(k, v):
+        for rows, x in ((K, stored(k)), (V, stored(v))):
+            rows[:] = [torch.cat([rows[m], x[:, m]]) for m in heads]
+
+    if c["kind"] == "generate":
+        for lo in range(0, c["b"], c["B"]):
+            _, k, v = _tokens(c, min(c["B"], c["b"] - lo), gen)
+            torch.randn(c["h_kv"], k.shape[0], device=DEV, generator=gen)
+            append(k, v)
+        q, k, v = _tokens(c, c["gen"], gen)
+        out = torch.empty(q.shape, device=DEV, dtype=torch.float64)
+        for i in range(c["gen"]):
+            append(k[i:i + 1], v[i:i + 1])
+            out[i:i + 1] = _attend64(c, q[i:i + 1], K, V)
+        return out
+    n = c["N"] + c["tail"] + c["gen"]
+    q, k, v = _tokens(c, n, gen)
+    steps = _chunks(c) + ([(c["N"], c["N"] + c["tail"])] if c["tail"] else [])
+    out, scores, at = torch.empty(q.shape, device=DEV, dtype=torch.float64), [], 0
+    budgets = _budgets(c) if c["pyramid"] else [c["b"]] * c["h_kv"]
+    for lo, hi in steps + [(i, i + 1) for i in range(n - c["gen"], n)]:
+        append(k[lo:hi], v[lo:hi])
+        out[lo:hi] = _attend64(c, q[lo:hi], K, V)
+        part = _scores64(c, W1, W2, q[lo:hi], k[lo:hi], v[lo:hi])
+        S = [torch.cat([S[m], part[m].float()]) for m in heads]
+        scores.append(part.flatten() if lo < c["N"] + c["tail"] or c["scored"] else torch.zeros_like(part.flatten()))
+        scores.append(scores[-1].new_zeros(-part.numel() % 4))
+        for m in heads if lo < c["N"] else ():
+            L = S[m].shape[0]
+            if L > budgets[m]:
+                # the pinned first units, the best of the others, the last n_s; in the order they have
+                order = S[m][c["n_pin"]:L - c["n_s"]].sort(descending=True, stable=True).indices + c["n_pin"]
+                kept = torch.cat([torch.arange(c["n_pin"], device=DEV), order[:budgets[m] - c["n_s"] - c["n_pin"]].sort().values,
+                                  torch.arange(L - c["n_s"], L, device=DEV)])
+                K[m], V[m], S[m] = K[m][kept], V[m][kept], S[m][kept]
+    scores = torch.cat(scores)
+    whole = torch.zeros(c["h_kv"] * (n + 4) + 4 * len(steps) + 4, device=DEV, dtype=torch.float64)
+    whole[:scores.numel()] = scores
+    return [out, whole]
 
 
 # ---- what a pass cannot do without -----------------------------------------------------------------------------------
