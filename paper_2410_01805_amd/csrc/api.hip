@@ -391,10 +391,6 @@ static void run_evict(locret_ctx* c, int L, int n_stab, int32_t* kept_idx_out, h
   const int b = c->cfg.budget;
   const SelectArgs a = select_args(c, L, n_stab, kept_idx_out);
   CacheBuf A = c->buf(c->cur);
-  c->mark(3, 0, st);
-  if (!select_done) launch_select(a, c->D.h_kv, st);
-  c->mark(3, 1, st);
-  c->mark(4, 0, st);
   // the other copy becomes the live one as soon as one head is over its budget; the heads that are not
   // are then copied as they are (their kept lists are 0, 1, 2, ...)
   bool over = L > b;
@@ -402,6 +398,12 @@ static void run_evict(locret_ctx* c, int L, int n_stab, int32_t* kept_idx_out, h
     over = false;
     for (int m = 0; m < c->D.h_kv; ++m) over = over || a.L_h.v[m] > c->b_h[m];
   }
+  c->mark(3, 0, st);
+  // a step that evicts nothing has no list to find: the caller's copy, if asked for, is 0, 1, 2, ...
+  if (!select_done && over) launch_select(a, c->D.h_kv, st);
+  else if (!select_done && a.kept2) launch_keep_all(a.kept2, a.stride2, c->D.h_kv, L, a.L_h, st);
+  c->mark(3, 1, st);
+  c->mark(4, 0, st);
   if (over) {
     CacheBuf B = c->buf(c->cur ^ 1);
     const float2* tab = c->D.rope ? (const float2*)(c->ws + c->L.tab) : nullptr;

@@ -225,6 +225,8 @@ void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_s
                    int kept_stride, int32_t* kept2, int stride2, hipStream_t st);
 // The same from a filled SelectArgs (head-wise budgets: L and n_keep are the largest over the heads).
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st);
+// out[m][i] = i for i < L (per head with head-wise budgets): the kept lists of a step that evicts nothing.
+void launch_keep_all(int32_t* out, int stride, int h_kv, int L, const HeadLens& L_h, hipStream_t st);
 
 // dst[m][r] = src[m][kept[m][r]] for K, V, S, P; dst.Kr[m][r] = K rotated to position r.
 // keep_h: per-head row counts (n_keep then being the largest), or NULL.

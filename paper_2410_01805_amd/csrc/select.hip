@@ -3,21 +3,22 @@
 // placed at the start of the sequence, visible to every eviction).
 //
 // One 1024-thread workgroup per KV head.  Scores become order-preserving 32-bit keys (NaN lowest,
-// -0 == +0) held in LDS; a 4-pass, 8-bit-per-pass radix select finds the key tau of the k-th best
-// candidate and how many units equal to tau still fit; a ballot-based ordered compaction then emits
-// the kept indices ascending, taking equal keys from the lowest index up.  Integer work only, so
-// the result is exact and deterministic.
+// -0 == +0); a radix select finds the key tau of the k-th best candidate and how many units equal to
+// tau still fit; a ballot-based ordered compaction then emits the kept indices ascending, taking equal
+// keys from the lowest index up.  Integer work only, so the result is exact and deterministic.
 //
-// Up to 24576 candidates per head the keys never leave registers (select_reg_kernel): wavefront w
+// Up to 65536 candidates per head the keys never leave registers (select_reg_kernel): wavefront w
 // owns a contiguous index range, lane-interleaved in rounds of 64, so every global read is a
 // 256-byte line, the radix passes touch LDS only for the histogram, and the final ordered
-// compaction is ballots over registers.  Longer inputs use select_kernel (keys in LDS, or re-read
-// from global memory when they do not fit).
+// compaction is ballots over registers.  64 keys per thread is what 16 wavefronts on one CU (128
+// registers each) hold.  Longer inputs use select_kernel, whose four passes re-read the scores: a stream of 48000
+// tokens into 8 budgets of 32768 units (eviction alone) takes 760 us with the register form up to 24576
+// candidates only, 538 us with it up to 65536.
 //
-// Histogram counters are replicated 32 times (bin * 32 + lane % 32): every lane of a wavefront then
-// updates its own LDS bank whatever digit it holds.  Score keys share their top bits (same sign
-// and exponent range), so without the replicas almost all 1024 threads of the first pass would
-// queue on two or three counters.
+// select_kernel replicates its histogram counters 32 times (bin * 32 + lane % 32): every lane of a
+// wavefront then updates its own LDS bank whatever digit it holds.  Score keys share their top bits
+// (same sign and exponent range), so without the replicas almost all 1024 threads of the first pass
+// would queue on two or three counters.
 #include "device_util.h"
 #include "kernels.h"
 #include "select_body.h"
@@ -28,14 +29,12 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WAVES = SEL_THREADS / 64;
 constexpr int SEL_HDR = 256 * SEL_REP + 256 + 128;   // words of LDS before the keys: hist[256][32] tot[256] wsum[64] bc[64]
 
-template <bool IN_LDS>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
-  extern __shared__ uint32_t smem[];
+  __shared__ uint32_t smem[SEL_HDR];
   uint32_t* hist = smem;                       // [256][SEL_REP]
   uint32_t* tot = smem + 256 * SEL_REP;        // [256] per-bin totals
   uint32_t* wsum = tot + 256;
   uint32_t* bc = wsum + 64;
-  uint32_t* keys = smem + SEL_HDR;
 
   const int m = blockIdx.x;
   const HeadSel hs = head_sel(a, m);
@@ -50,9 +49,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
   const int n_cand = L - hs.n_stab - n_pin;
   const int kk = hs.n_keep - hs.n_stab - n_pin;    // candidates to keep, 0 <= kk <= n_cand
 
-  if (IN_LDS)
-    for (int i = tid; i < n_cand; i += SEL_THREADS) keys[i] = score_key(s[i]);
-  auto key_at = [&](int i) -> uint32_t { return IN_LDS ? keys[i] : score_key(s[i]); };
+  auto key_at = [&](int i) -> uint32_t { return score_key(s[i]); };
 
   uint32_t tau, need_eq;
   if (kk >= n_cand) {          // everything fits
@@ -171,18 +168,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_reg_kernel(SelectArgs a) {
   select_reg_body<MAXR, SEL_THREADS, 2>(a, blockIdx.x, smem);
 }
 
-// bytes of dynamic LDS the in-LDS variant may use: asked for once (thread-safe static initialisation)
-static int lds_limit() {
-  static const int limit = [] {
-    if (hipFuncSetAttribute((const void*)select_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            160 * 1024) == hipSuccess)
-      return 160 * 1024;
-    (void)hipGetLastError();
-    return 64 * 1024;
-  }();
-  return limit;
-}
-
 void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_stab, int n_pin, int32_t* kept,
                    int kept_stride, int32_t* kept2, int stride2, hipStream_t st) {
   SelectArgs a = {S, cap, L, n_keep, n_stab, n_pin, kept, kept_stride, kept2, stride2,
@@ -198,19 +183,28 @@ void launch_select(const SelectArgs& a, int h_kv, hipStream_t st) {
   const int npin = a.n_pin < a.L - ns ? a.n_pin : a.L - ns;
   const int n_cand = a.L - ns - npin;
   const int wseg = ((n_cand + SEL_WAVES - 1) / SEL_WAVES + 63) & ~63;
-  if (wseg <= 12 * 64) {
-    launch_kernel(select_reg_kernel<12>, dim3(h_kv), dim3(SEL_THREADS), 0, st, a);
-    return;
+#define LOCRET_SEL_REG(R)                                                                         \
+  if (wseg <= R * 64) {                                                                           \
+    launch_kernel(select_reg_kernel<R>, dim3(h_kv), dim3(SEL_THREADS), 0, st, a);                 \
+    return;                                                                                       \
   }
-  if (wseg <= 24 * 64) {
-    launch_kernel(select_reg_kernel<24>, dim3(h_kv), dim3(SEL_THREADS), 0, st, a);
-    return;
-  }
-  size_t need = (size_t)(SEL_HDR + n_cand) * sizeof(uint32_t);
-  if (need <= (size_t)lds_limit())
-    launch_kernel(select_kernel<true>, dim3(h_kv), dim3(SEL_THREADS), need, st, a);
-  else
-    launch_kernel(select_kernel<false>, dim3(h_kv), dim3(SEL_THREADS), SEL_HDR * sizeof(uint32_t), st, a);
+  LOCRET_SEL_REG(12)
+  LOCRET_SEL_REG(24)
+  LOCRET_SEL_REG(36)
+  LOCRET_SEL_REG(48)
+  LOCRET_SEL_REG(64)
+#undef LOCRET_SEL_REG
+  launch_kernel(select_kernel, dim3(h_kv), dim3(SEL_THREADS), 0, st, a);
+}
+
+// Nothing is over its budget: every head's kept list is 0, 1, 2, ... (only a caller's copy wants it).
+__global__ __launch_bounds__(256) void keep_all_kernel(int32_t* __restrict__ out, int stride, int L_common, HeadLens L_h) {
+  const int m = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+  if (i < head_len(L_h, m, L_common)) out[(int64_t)m * stride + i] = i;
+}
+
+void launch_keep_all(int32_t* out, int stride, int h_kv, int L, const HeadLens& L_h, hipStream_t st) {
+  launch_kernel(keep_all_kernel, dim3((L + 255) / 256, h_kv), dim3(256), 0, st, out, stride, L, L_h);
 }
 
 }  // namespace locret

@@ -86,6 +86,23 @@ def test_evict_compact_bit_exact(name, kw, sizes, kind):
     layer.close()
 
 
+@pytest.mark.parametrize("n_cand", [12288, 12289, 24576, 24577, 36864, 36865, 49152, 49153, 65535, 65536, 65537])
+def test_select_at_the_edges_of_its_forms(n_cand):
+    """One chunk into an empty cache: n_cand candidates per head, at the most each register-resident form holds and one more
+    (12, 24, 36, 48, 64 keys per thread; beyond them the scores are re-read).  Heads of normal, tied and special scores."""
+    n_s, b, h_kv = 5, n_cand // 3 + 5, 3
+    w = synth.tiny(name="sel_edge", dtype="f32", h=h_kv, h_kv=h_kv, d=16, N=n_cand + n_s, B=n_cand + n_s, b=b, n_s=n_s, d_R=64, rope=False)
+    layer, W1, W2 = make_layer(w)
+    o = make_oracle(w, W1, W2)
+    rng = np.random.default_rng(n_cand)
+    sc = np.concatenate([_scores(rng, 1, n_cand + n_s, kind) for kind in ("normal", "ties", "specials")])
+    k = rng.standard_normal((n_cand + n_s, h_kv, 16)).astype(np.float32)
+    kept_ref = o.evict_compact(sc, k, k, n_s)
+    kept = layer.evict_compact(torch.from_numpy(sc).to(DEV), dev(k, w), dev(k, w), n_s)
+    np.testing.assert_array_equal(kept.cpu().numpy(), kept_ref)
+    layer.close()
+
+
 def test_select_is_deterministic_and_reset_works():
     w = synth.tiny(dtype="bf16", h=2, h_kv=2, d=64, N=4096, B=1024, b=1536, n_s=16)
     layer, _, _ = make_layer(w)
