@@ -446,7 +446,7 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
   const HeadLens* hl = c->lens(&hl_tmp);      // per-head cache lengths before this chunk, or NULL
   c->mark(0, 0, st);
   if (D.kv_bits) launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st, false);
-  else launch_append(D, fused_q ? nullptr : q, k, v, T, c->n_c, c->seen, A, qr, tab, st, false, hl);
+  else launch_append(D, fused_q ? nullptr : q, k, v, T, c->n_c, c->seen, A, qr, tab, st, nullptr, hl);
   c->mark(0, 1, st);
   const void* qx = (D.rope && !fused_q) ? qr : q;
   const void* Kx = D.rope ? A.Kr : A.K;
@@ -585,9 +585,12 @@ int locret_evict_compact(locret_ctx* c, const float* chunk_scores, const void* k
   const float2* tab = D.rope ? (const float2*)(c->ws + c->L.tab) : nullptr;
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);
-  if (D.kv_bits) launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st, false);
-  else launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, false, hl);
-  launch_score_reduce(chunk_scores, 1, T, D.h_kv, T, A.S, D.cap, c->n_c, nullptr, st, hl);
+  if (D.kv_bits) {
+    launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st, false);
+    launch_score_reduce(chunk_scores, 1, T, D.h_kv, T, A.S, D.cap, c->n_c, nullptr, st, hl);
+  } else {
+    launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, chunk_scores, hl);
+  }
   run_evict(c, c->n_c + T, n_stab, kept_idx_out, st);
   c->seen += T;
   return hipGetLastError() == hipSuccess ? LOCRET_OK : LOCRET_EHIP;

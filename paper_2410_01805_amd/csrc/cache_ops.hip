@@ -71,101 +71,6 @@ void launch_prep_weights(const Dims& D, int expand, const void* W1, const void* 
 }
 
 // ------------------------------------------------------------------------------------------------
-// rotate VEC pairs held as (lo, hi) by the table row of `pos`
-template <typename T>
-__device__ __forceinline__ void rotate_pairs(const Vec16<T>& lo, const Vec16<T>& hi, Vec16<T>& olo, Vec16<T>& ohi,
-                                             const float2* __restrict__ tab_row) {
-#pragma unroll
-  for (int i = 0; i < Vec16<T>::N; ++i) {
-    float2 cs = tab_row[i];
-    float a = lo.get(i), b = hi.get(i);
-    olo.set(i, a * cs.x - b * cs.y);
-    ohi.set(i, b * cs.x + a * cs.y);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, const T* __restrict__ k,
-                                                     const T* __restrict__ v, int Tn, int n_c, int seen, int h,
-                                                     int h_kv, int d, int cap, T* __restrict__ Kc,
-                                                     T* __restrict__ Vc, T* __restrict__ Krc,
-                                                     int32_t* __restrict__ Pc, T* __restrict__ qr,
-                                                     const float2* __restrict__ tab, int rope, int q_rows,
-                                                     float* __restrict__ S_unscored, HeadLens n_c_h) {
-  constexpr int VEC = Vec16<T>::N;
-  const int half = d / 2;
-  const int tpr = half / VEC;
-  int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t row = gid / tpr;
-  int part = (int)(gid % tpr);
-  const int rows_per_tok = q_rows + 2 * h_kv;   // q_rows = h when queries are rotated here, else 0
-  if (row >= (int64_t)Tn * rows_per_tok) return;
-  int t = (int)(row / rows_per_tok);
-  int r = (int)(row % rows_per_tok);
-  int off = part * VEC;
-  typedef Vec16<T> V16;
-  if (r < q_rows) {
-    const T* src = q + ((int64_t)t * h + r) * d;
-    V16 lo, hi, olo, ohi;
-    lo.raw = *(const decltype(lo.raw)*)(src + off);
-    hi.raw = *(const decltype(hi.raw)*)(src + half + off);
-    const int n_c_q = head_len(n_c_h, r / (h / h_kv), n_c);   // a query sits behind its own KV head's cache
-    rotate_pairs<T>(lo, hi, olo, ohi, tab + (int64_t)(n_c_q + t) * half + off);
-    T* dst = qr + ((int64_t)t * h + r) * d;
-    *(decltype(lo.raw)*)(dst + off) = olo.raw;
-    *(decltype(lo.raw)*)(dst + half + off) = ohi.raw;
-    return;
-  }
-  r -= q_rows;
-  const bool is_k = r < h_kv;
-  int m = is_k ? r : r - h_kv;
-  n_c = head_len(n_c_h, m, n_c);
-  const T* src = (is_k ? k : v) + ((int64_t)t * h_kv + m) * d;
-  V16 lo, hi;
-  lo.raw = *(const decltype(lo.raw)*)(src + off);
-  hi.raw = *(const decltype(hi.raw)*)(src + half + off);
-  int64_t drow = ((int64_t)m * cap + n_c + t) * d;
-  T* dst = (is_k ? Kc : Vc) + drow;
-  *(decltype(lo.raw)*)(dst + off) = lo.raw;
-  *(decltype(lo.raw)*)(dst + half + off) = hi.raw;
-  if (is_k) {
-    if (rope) {
-      V16 olo, ohi;
-      rotate_pairs<T>(lo, hi, olo, ohi, tab + (int64_t)(n_c + t) * half + off);
-      *(decltype(lo.raw)*)(Krc + drow + off) = olo.raw;
-      *(decltype(lo.raw)*)(Krc + drow + half + off) = ohi.raw;
-    }
-    if (part == 0) {
-      Pc[(int64_t)m * cap + n_c + t] = seen + t;
-      if (S_unscored) S_unscored[(int64_t)m * cap + n_c + t] = __uint_as_float(0x7fc00000u);   // NaN: ranks last
-    }
-  }
-}
-
-void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c, int64_t seen,
-                   const CacheBuf& c, void* qr, const float2* tab, hipStream_t st, bool mark_unscored,
-                   const HeadLens* n_c_h) {
-  float* Su = mark_unscored ? c.S : nullptr;
-  const HeadLens hl = head_lens_or_common(n_c_h);
-  const int vec = D.bf16 ? 8 : 4;
-  const int tpr = (D.d / 2) / vec;
-  const int q_rows = (D.rope && q != nullptr) ? D.h : 0;
-  int64_t threads = (int64_t)T * (q_rows + 2 * D.h_kv) * tpr;
-  dim3 grid((unsigned)((threads + 255) / 256));
-  if (D.bf16)
-    launch_kernel(append_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k,
-                       (const bf16_t*)v, T, n_c, (int)seen, D.h, D.h_kv, D.d, D.cap, (bf16_t*)c.K, (bf16_t*)c.V,
-                       (bf16_t*)c.Kr, c.P, (bf16_t*)qr, tab, D.rope, q_rows, Su, hl);
-  else
-    launch_kernel(append_kernel<float>, grid, dim3(256), 0, st, (const float*)q, (const float*)k,
-                       (const float*)v, T, n_c, (int)seen, D.h, D.h_kv, D.d, D.cap, (float*)c.K, (float*)c.V,
-                       (float*)c.Kr, c.P, (float*)qr, tab, D.rope, q_rows, Su, hl);
-}
-
-// ------------------------------------------------------------------------------------------------
-// Compaction: dst[m][r] = src[m][kept[m][r]].  A thread owns slot r (and VEC rotary pairs of it)
-// for ALL KV heads: the rotary table row of slot r is read once and reused for every head, and
-// the loads of HB heads are issued together before anything is stored (memory-level parallelism).
 // 16-byte loads and stores that bypass the caches' retention: compaction touches every byte once
 typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4)));
 template <typename R>
@@ -180,6 +85,127 @@ __device__ __forceinline__ void nt_store16(void* p, R r) {
   __builtin_nontemporal_store(__builtin_bit_cast(nt_u32x4, r), (nt_u32x4*)p);
 }
 
+// Append: a thread owns token t and VEC rotary pairs of its rows, for `hpb` consecutive KV heads (blockIdx.y), so
+// the rotary-table row of the token's slot is read once for all of them and the loads of two heads are in flight
+// together.  Bound by HBM: 12 us for 4096 tokens x 8 heads x 128 dims = 42 MB.  Scores that the caller has already
+// (S_src) travel with the rows.  With one thread per row piece, each with its own table reads, that cost as much as
+// the launch of their own it saves: 48000 tokens in 12 eviction-only steps 538 us with the separate launch, 537 us
+// with one thread per piece, 500 us in this form.  With q != NULL further blocks of blockIdx.y rotate the queries
+// into qr (storage types whose attention kernel does not do it itself).
+// K un-rotated is next read by a compaction, long after it has left the caches: its stores do not stay in them.
+template <typename T, bool RAGGED>
+__global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, const T* __restrict__ k,
+                                                     const T* __restrict__ v, int Tn, int n_c_common, int seen, int h,
+                                                     int h_kv, int d, int cap, T* __restrict__ Kc,
+                                                     T* __restrict__ Vc, T* __restrict__ Krc,
+                                                     int32_t* __restrict__ Pc, T* __restrict__ qr,
+                                                     const float2* __restrict__ tab, int rope, int hpb, int kv_blocks,
+                                                     float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h) {
+  constexpr int VEC = Vec16<T>::N;
+  typedef Vec16<T> V16;
+  typedef decltype(V16().raw) raw_t;
+  const int half = d / 2;
+  const int tpr = half / VEC;
+  const int rows = 256 / tpr;                    // tokens per workgroup
+  const int lr = (int)threadIdx.x / tpr, part = (int)threadIdx.x % tpr;
+  const int t = (int)blockIdx.x * rows + lr;
+  if (lr >= rows || t >= Tn) return;
+  const int off = part * VEC;
+  float2 cs[VEC];
+  auto table_row = [&](int n_c) {
+    const float2* tr = tab + (int64_t)(n_c + t) * half + off;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) cs[i] = tr[i];
+  };
+  auto rotate = [&](const V16& lo, const V16& hi, V16& olo, V16& ohi) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      const float a = lo.get(i), b = hi.get(i);
+      olo.set(i, a * cs[i].x - b * cs[i].y);
+      ohi.set(i, b * cs[i].x + a * cs[i].y);
+    }
+  };
+  if (rope && !RAGGED) table_row(n_c_common);
+  if ((int)blockIdx.y >= kv_blocks) {
+    const int j0 = ((int)blockIdx.y - kv_blocks) * hpb;
+    for (int j = j0; j < min(h, j0 + hpb); ++j) {
+      if (RAGGED) table_row(n_c_h.v[j / (h / h_kv)]);      // a query sits behind its own KV head's cache
+      const int64_t row = ((int64_t)t * h + j) * d;
+      V16 lo, hi, olo, ohi;
+      lo.raw = *(const raw_t*)(q + row + off);
+      hi.raw = *(const raw_t*)(q + row + half + off);
+      rotate(lo, hi, olo, ohi);
+      *(raw_t*)(qr + row + off) = olo.raw;
+      *(raw_t*)(qr + row + half + off) = ohi.raw;
+    }
+    return;
+  }
+  const int m_lo = (int)blockIdx.y * hpb, m_hi = min(h_kv, m_lo + hpb);
+  for (int m0 = m_lo; m0 < m_hi; m0 += 2) {
+    V16 klo[2], khi[2], vlo[2], vhi[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int64_t row = ((int64_t)t * h_kv + min(m0 + u, m_hi - 1)) * d;    // a spare head repeats the last one (not stored)
+      klo[u].raw = *(const raw_t*)(k + row + off);
+      khi[u].raw = *(const raw_t*)(k + row + half + off);
+      vlo[u].raw = *(const raw_t*)(v + row + off);
+      vhi[u].raw = *(const raw_t*)(v + row + half + off);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int m = m0 + u;
+      if (m >= m_hi) break;
+      const int n_c = RAGGED ? n_c_h.v[m] : n_c_common;
+      const int64_t slot = (int64_t)m * cap + n_c + t, drow = slot * d;
+      *(raw_t*)(Vc + drow + off) = vlo[u].raw;
+      *(raw_t*)(Vc + drow + half + off) = vhi[u].raw;
+      if (rope) {
+        if (RAGGED) table_row(n_c);
+        V16 olo, ohi;
+        rotate(klo[u], khi[u], olo, ohi);
+        *(raw_t*)(Krc + drow + off) = olo.raw;
+        *(raw_t*)(Krc + drow + half + off) = ohi.raw;
+        nt_store16(Kc + drow + off, klo[u].raw);
+        nt_store16(Kc + drow + half + off, khi[u].raw);
+      } else {
+        *(raw_t*)(Kc + drow + off) = klo[u].raw;
+        *(raw_t*)(Kc + drow + half + off) = khi[u].raw;
+      }
+      if (part == 0) {
+        Pc[slot] = seen + t;
+        if (S_src) S[slot] = S_src[(int64_t)m * Tn + t];
+      }
+    }
+  }
+}
+
+void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c, int64_t seen,
+                   const CacheBuf& c, void* qr, const float2* tab, hipStream_t st, const float* scores,
+                   const HeadLens* n_c_h) {
+  const HeadLens hl = head_lens_or_common(n_c_h);
+  const int vec = D.bf16 ? 8 : 4;
+  const int tpr = (D.d / 2) / vec;
+  const int rows = 256 / tpr;
+  const int q_rows = (D.rope && q != nullptr) ? D.h : 0;
+  const int gx = (T + rows - 1) / rows;
+  // as few heads per thread as give the chip about three workgroups per CU
+  int hpb = D.h_kv;
+  while (hpb > 1 && (int64_t)gx * ((D.h_kv + hpb - 1) / hpb) < 768) hpb = (hpb + 1) / 2;
+  const int kv_blocks = (D.h_kv + hpb - 1) / hpb;
+  dim3 grid((unsigned)gx, (unsigned)(kv_blocks + (q_rows + hpb - 1) / hpb));
+#define LOCRET_APPEND(TT, RG)                                                                                          \
+  launch_kernel((append_kernel<TT, RG>), grid, dim3(256), 0, st, (const TT*)q, (const TT*)k, (const TT*)v, T, n_c,     \
+                (int)seen, D.h, D.h_kv, D.d, D.cap, (TT*)c.K, (TT*)c.V, (TT*)c.Kr, c.P, (TT*)qr, tab, D.rope, hpb,     \
+                kv_blocks, c.S, scores, hl)
+  if (D.bf16) { if (hl.ragged) LOCRET_APPEND(bf16_t, true); else LOCRET_APPEND(bf16_t, false); }
+  else { if (hl.ragged) LOCRET_APPEND(float, true); else LOCRET_APPEND(float, false); }
+#undef LOCRET_APPEND
+}
+
+// ------------------------------------------------------------------------------------------------
+// Compaction: dst[m][r] = src[m][kept[m][r]].  A thread owns slot r (and VEC rotary pairs of it)
+// for ALL KV heads: the rotary table row of slot r is read once and reused for every head, and
+// the loads of HB heads are issued together before anything is stored (memory-level parallelism).
 // RAGGED: head m has keep_h.v[m] rows (head-wise budgets); rows beyond that are neither read nor written.
 template <typename T, int HB, bool RAGGED>
 __global__ __launch_bounds__(256) void compact_kernel(const T* __restrict__ Ks, const T* __restrict__ Vs,

@@ -145,13 +145,13 @@ void launch_prep_weights(const Dims& D, int expand, const void* W1, const void* 
 
 // Append the chunk at slots [n_c, n_c+T) of `c`: K, V copied, Kr = K rotated to n_c+t,
 // P = seen + t; qr [T][h][d] = q rotated to n_c+t (rope only; q may be NULL to skip).
-// mark_unscored: also store NaN as the score of the appended units (no score will be computed).
+// scores [h_kv][T], or NULL: the units' scores when the caller has them already.
 void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c,
                    int64_t seen, const CacheBuf& c, void* qr, const float2* tab, hipStream_t st,
-                   bool mark_unscored = false, const HeadLens* n_c_h = nullptr);
+                   const float* scores = nullptr, const HeadLens* n_c_h = nullptr);
 
 // 4-bit rows.  Append: quantize the chunk's k, v rows into the packed arrays of `c` at slots [n_c, n_c+T) and write
-// their dequantized values (K rotated to n_c+t) into the staging arrays; P and optional NaN scores as launch_append.
+// their dequantized values (K rotated to n_c+t) into the staging arrays; P as launch_append; mark_unscored: also a NaN score (none will be computed).
 // Compact: dst packed rows r = src packed rows kept[m][r], S, P likewise, staging rows r rewritten for slot r.
 bool q4_head_dim(int d);
 int q4_row_bytes(int d);      // d/2 code bytes + 4 bytes (scale, minimum as bf16) per group of 32 dims
