@@ -63,16 +63,62 @@ constexpr int PP_KPRE = 4;                     // K fragments fetched ahead of t
 constexpr int PP_VPRE = 4;                     // V^T fragments in flight ahead of their MFMA
 constexpr int PP_YTAIL = 4;                    // MFMAs of group A's S block issued behind barrier Y
 constexpr int PP_SEL_MAXR = 48;                // keys per thread of a selection workgroup (512 threads)
-constexpr int PP_MAX_SPLIT = 8;                // key ranges per (head group, token tile) item at most
-constexpr int PP_SPLIT_TOKENS = 2048;          // token rows (times splits) the partial-result buffer holds at most
+constexpr int PP_MAX_PARTS = 16;               // key ranges per (head group, token tile) item at most
+constexpr int PP_MAX_SLOTS = 256;              // partial results (256 query rows each) the buffer holds at most
+constexpr int PP_CUT_SLACK = 4;                // key tiles by which the last part may exceed the part length
+constexpr int PP_CUS = 256, PP_XCD_CUS = 32;   // compute units of the device and of one XCD
+
+// Where a launch cuts items (head group, token tile) into parts along the keys.  Only the first n_donors items of the
+// dispatch order, the longest, are cut: into k equal parts, or (k == 0) into parts of tau key tiles, the last one
+// taking what is left.  Part 0 of every item comes first in the launch, then part 1 of the donors, and so on.
+struct PPCut {
+  int n_items;        // items, padded to whole rounds of the 8 XCDs in the spread order
+  int n_donors;
+  int k, tau;
+  int n_slots;        // n_donors * (parts at most): part p of donor i leaves its partial result in slot p * n_donors + i
+  __host__ __device__ int parts(int i, int tiles) const {
+    if (i >= n_donors) return 1;
+    if (k > 0) return k;
+    return tiles <= tau + PP_CUT_SLACK ? 1 : (tiles - PP_CUT_SLACK + tau - 1) / tau;
+  }
+};
+
+// Dispatch order: item i of the launch -> head group and token tile; false: padding.
+struct PPOrder {
+  int n_hgroups, n_ttiles, gph, n_sel, spread;      // gph: head groups per KV head
+  HeadOrder heads;
+};
+__device__ __forceinline__ bool pp_item(const PPOrder& o, bool spread, int i, int& hgroup, int& tt) {
+  if (spread) {
+    // Head-wise budgets: with one KV head per XCD the XCD of the longest head would set the launch's time.
+    // Instead every XCD takes every eighth token tile of every head, the heads from the longest cache to
+    // the shortest, so that all XCDs hold the same work and each hands out its long items first.
+    // (Measured on 8 heads of 28672 ... 4096 units, mean 16384: 1.61 ms per step with one head
+    // per XCD, 1.39 ms with the heads interleaved item by item, 1.14 ms in this order; equal heads 1.07 ms.)
+    const int x = i >> 3, per_head = (o.n_ttiles + 7) >> 3;
+    const int r = x / per_head;                            // rank of the head group, longest first
+    hgroup = o.heads.v[r / o.gph] * o.gph + r % o.gph;
+    tt = (x % per_head) * 8 + (i & 7);
+    if (tt >= o.n_ttiles) return false;                    // the launch is padded to whole rounds of the 8 XCDs
+  } else if ((o.n_hgroups & 7) == 0) {                     // one KV head per XCD (workgroup ids go round the XCDs)
+    const int g8 = o.n_hgroups >> 3;
+    hgroup = ((i + o.n_sel) & 7) * g8 + (i >> 3) % g8;
+    tt = i / o.n_hgroups;
+  } else {
+    hgroup = i % o.n_hgroups;
+    tt = i / o.n_hgroups;
+  }
+  tt = o.n_ttiles - 1 - tt;                                // longest key ranges first
+  return true;
+}
 
 #define LOCRET_TR_READ(dst, addr, off) \
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "i"(off) : "memory")
 #define LOCRET_LGKM_WAIT(a, b, n) asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "i"(n))
 
 // GENERAL = false is the common case: every KV head holds n_c_common units, one KV head per XCD, the whole key
-// range per workgroup (n_c_h, spread_arg, order, n_split_arg and part_arg are ignored, so nothing of head-wise
-// lengths, the spread launch order or the key split remains in its code).
+// range per workgroup (n_c_h, order.spread, cut and part are ignored, so nothing of head-wise lengths, the spread
+// launch order or the cut items remains in its code).
 // D = 128 or 96.  The tile layout in LDS is that of 128 dims for both (rows of 256 bytes): with 96 dims the lanes
 // of a direct load that would fetch the last four 16-byte chunks of a row point outside the buffer instead and
 // bring zeros, which nothing reads; every fragment address stays as it is, S takes 6 contraction steps and O^T
@@ -81,12 +127,8 @@ template <int D, bool GENERAL>
 __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __restrict__ q, const float2* __restrict__ tab, const bf16_t* __restrict__ Kx,
                                                              const bf16_t* __restrict__ V, bf16_t* __restrict__ out,
                                                              int Tn, int h, int g, int cap, int n_c_common, float c_log2,
-                                                             int hpw, int n_hgroups, int n_ttiles, SelectArgs sel, int n_sel,
-                                                             HeadLens n_c_h, int spread_arg, HeadOrder order,
-                                                             int n_split_arg, float* __restrict__ part_arg) {
-  const int n_split = GENERAL ? n_split_arg : 1;
-  float* const part = GENERAL ? part_arg : nullptr;
-  const int spread = GENERAL ? spread_arg : 0;
+                                                             int hpw, PPOrder order, SelectArgs sel, int n_sel,
+                                                             HeadLens n_c_h, PPCut cut, float* __restrict__ part) {
   constexpr int NW = PP_NW;
   static_assert(D == 128 || D == 96, "head dims of this kernel");
   constexpr int NKS = D / 16;
@@ -108,31 +150,14 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
     static_assert(select_body_smem_words(PP_NW * 64, 4) * 4 <= (int)sizeof(ring), "the selection's scratch fits the ring");
     return;
   }
-  const int bid = blockIdx.x - n_sel;
-  int hgroup, tt;
-  if (spread) {
-    // Head-wise budgets: with one KV head per XCD the XCD of the longest head would set the launch's time.
-    // Instead every XCD takes every eighth token tile of every head, the heads from the longest cache to
-    // the shortest, so that all XCDs hold the same work and each hands out its long items first.
-    // (Measured on 8 heads of 28672 ... 4096 units, mean 16384: 1.61 ms per step with one head per XCD,
-    // 1.39 ms with the heads interleaved item by item, 1.14 ms in this order; equal heads 1.07 ms.)
-    const int i = bid >> 3, per_head = (n_ttiles + 7) >> 3;
-    const int r = i / per_head;                            // rank of the head group, longest first
-    const int gph = g / hpw;                               // head groups per KV head
-    hgroup = order.v[r / gph] * gph + r % gph;
-    tt = (i % per_head) * 8 + (bid & 7);
-    if (tt >= n_ttiles) return;                            // the launch is padded to whole rounds of the 8 XCDs
-  } else if ((n_hgroups & 7) == 0) {                  // one KV head per XCD (workgroup ids go round the XCDs)
-    const int g8 = n_hgroups >> 3;
-    hgroup = (blockIdx.x & 7) * g8 + (bid >> 3) % g8;
-    tt = bid / n_hgroups;
-  } else {
-    hgroup = bid % n_hgroups;
-    tt = bid / n_hgroups;
+  int item = blockIdx.x - n_sel, layer = 0;
+  if (GENERAL && item >= cut.n_items) {
+    const int x = item - cut.n_items;
+    layer = 1 + x / cut.n_donors;
+    item = x % cut.n_donors;
   }
-  // n_split > 1: n_ttiles counts (token tile, key split) pairs, the split being the fast index
-  const int split = tt % n_split;
-  tt = n_ttiles / n_split - 1 - tt / n_split;  // longest key ranges first
+  int hgroup, tt;
+  if (!pp_item(order, GENERAL && order.spread, item, hgroup, tt)) return;
   const int wph = NW / hpw;
   const int TW = wph * 32;
   const int t0 = tt * TW;
@@ -143,11 +168,18 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
   const int t_last_wg = min(Tn, t0 + TW) - 1;
   const int n_keys = n_c + t_last_wg + 1;
   const int n_tiles_all = (n_keys + KT - 1) / KT;
-  // Key split (short chunks leave most CUs without a workgroup otherwise): this workgroup takes the key tiles
-  // [t_lo, t_lo + n_tiles) of its queries' range and leaves un-normalised partial results for the merge kernel.
-  const int per_split = (n_tiles_all + n_split - 1) / n_split;
-  const int t_lo = split * per_split;
-  const int n_tiles = max(0, min(n_tiles_all, t_lo + per_split) - t_lo);
+  // A cut item: this workgroup takes the key tiles [t_lo, t_lo + n_tiles) of its queries' range and leaves
+  // un-normalised partial results for the merge kernel.
+  int t_lo = 0, n_tiles = n_tiles_all, n_parts = 1;
+  if (GENERAL) {
+    n_parts = cut.parts(item, n_tiles_all);
+    if (layer >= n_parts) return;
+    if (n_parts > 1) {
+      const int len = cut.k > 0 ? (n_tiles_all + n_parts - 1) / n_parts : cut.tau;
+      t_lo = layer * len;
+      n_tiles = max(0, (layer == n_parts - 1 ? n_tiles_all : min(n_tiles_all, t_lo + len)) - t_lo);
+    }
+  }
   const int n_keys_s = min(n_keys, (t_lo + n_tiles) * KT);
   const int wave_last_slot = n_c + min(Tn - 1, tw0 + 31);
   const int my_t = min(tw0 + n32, Tn - 1);
@@ -342,7 +374,7 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
 #pragma unroll
           for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[kb][r]);
         mx = max_across_halves(mx);
-        // Key-split launches only: in the split that holds the diagonal a query may see none of the split's keys
+        // Cut items only: in the part that holds the diagonal a query may see none of the part's keys
         // (its row of the first tile is wholly masked, and every later tile lies further right).  Such a lane keeps
         // max 0 and sum 0, and the merge kernel drops partials whose sum is 0; without the test it would form
         // -inf - (-inf).  In unsplit launches every query sees key 0, which lies in the first tile.
@@ -445,23 +477,18 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
   {
     const int t = tw0 + n32;
     float l = l_run + __shfl_xor(l_run, 32, 64);
-    if (part != nullptr) {
-      // partial result of this key split: O un-normalised, running max (log2 units) and sum; a wavefront that saw
-      // no key leaves sum 0
-      if (t < Tn) {
-        const int64_t row = ((int64_t)split * Tn + t) * h + j;
-        float* op = part + row * D;
+    if (GENERAL && n_parts > 1) {
+      // partial result of this part: O un-normalised, running max (log2 units) and sum; a query that saw no key
+      // leaves sum 0.  The accumulators go out as they lie in the registers, 1 KB in a row per store.
+      const int64_t slot = (int64_t)layer * cut.n_donors + item;
+      float4* op = (float4*)part + (slot * NW + wave) * (NDB * 4 * 64) + lane;
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
-          for (int rq = 0; rq < 4; ++rq)
-            *(float4*)(op + db * 32 + rq * 8 + hi * 4) =
-                make_float4(oacc[db][rq * 4 + 0], oacc[db][rq * 4 + 1], oacc[db][rq * 4 + 2], oacc[db][rq * 4 + 3]);
-        if (hi == 0) {
-          float* ml = part + (int64_t)n_split * Tn * h * D + row * 2;
-          *(float2*)ml = make_float2(m_run, l);
-        }
-      }
+        for (int rq = 0; rq < 4; ++rq)
+          op[(db * 4 + rq) * 64] =
+              make_float4(oacc[db][rq * 4 + 0], oacc[db][rq * 4 + 1], oacc[db][rq * 4 + 2], oacc[db][rq * 4 + 3]);
+      if (hi == 0) ((float2*)(part + (int64_t)cut.n_slots * (NW * 32) * D))[slot * (NW * 32) + wave * 32 + n32] = make_float2(m_run, l);
     } else if (t < Tn) {
       const float inv = 1.f / l;
       bf16_t* op = out + ((int64_t)t * h + j) * D;
@@ -478,46 +505,135 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
   }
 }
 
-// out[t][j][:] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m) over the key splits of a row (t, j);
-// a split whose sum is 0 saw no key of that row.  A thread owns 4 elements of a row.
-__global__ __launch_bounds__(256) void attn_pp_merge_kernel(const float* __restrict__ part, bf16_t* __restrict__ out,
-                                                            int rows, int n_split, int D) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t row = gid / (D / 4);
-  const int e = (int)(gid % (D / 4)) * 4;
-  if (row >= rows) return;
-  const float* ml = part + (int64_t)n_split * rows * D;
+// out[t][j][:] = sum_p w_p O_p / sum_p w_p l_p with w_p = 2^(m_p - max m) over the parts of a cut item; a part whose
+// sum is 0 saw no key of that row.  One workgroup per (donor, 32 dims), its threads as in the attention kernel.
+template <int D>
+__global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* __restrict__ part, bf16_t* __restrict__ out,
+                                                                   int Tn, int h, int g, int n_c_common, int hpw, PPOrder order,
+                                                                   HeadLens n_c_h, PPCut cut) {
+  constexpr int NW = PP_NW, NDB = D / 32;
+  const int item = blockIdx.x, db = blockIdx.y;
+  int hgroup, tt;
+  if (!pp_item(order, order.spread, item, hgroup, tt)) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n32 = lane & 31, hi = lane >> 5;
+  const int wph = NW / hpw, TW = wph * 32;
+  const int n_c = head_len(n_c_h, (hgroup * hpw) / g, n_c_common);
+  const int n_parts = cut.parts(item, (n_c + min(Tn, (tt + 1) * TW) + KT - 1) / KT);
+  if (n_parts == 1) return;
+  const float2* ml = (const float2*)(part + (int64_t)cut.n_slots * (NW * 32) * D) + wave * 32 + n32;
+  const float4* op = (const float4*)part + (int64_t)wave * (NDB * 4 * 64) + db * (4 * 64) + lane;
   float M = -INFINITY;
-  for (int s = 0; s < n_split; ++s) {
-    const float2 x = *(const float2*)(ml + ((int64_t)s * rows + row) * 2);
+  for (int p = 0; p < n_parts; ++p) {
+    const float2 x = ml[((int64_t)p * cut.n_donors + item) * (NW * 32)];
     if (x.y > 0.f) M = fmaxf(M, x.x);
   }
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f, den = 0.f;
-  for (int s = 0; s < n_split; ++s) {
-    const float2 x = *(const float2*)(ml + ((int64_t)s * rows + row) * 2);
-    if (!(x.y > 0.f)) continue;
-    const float w = __builtin_amdgcn_exp2f(x.x - M);
-    const float4 o = *(const float4*)(part + ((int64_t)s * rows + row) * D + e);
+  float acc[16], den = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int p = 0; p < n_parts; ++p) {
+    const int64_t slot = (int64_t)p * cut.n_donors + item;
+    const float2 x = ml[slot * (NW * 32)];
+    float4 o[4];
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) o[rq] = op[slot * (NW * NDB * 4 * 64) + rq * 64];
+    const float w = x.y > 0.f ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;     // such a part's O is 0 too
     den = fmaf(w, x.y, den);
-    a0 = fmaf(w, o.x, a0);
-    a1 = fmaf(w, o.y, a1);
-    a2 = fmaf(w, o.z, a2);
-    a3 = fmaf(w, o.w, a3);
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      acc[rq * 4 + 0] = fmaf(w, o[rq].x, acc[rq * 4 + 0]);
+      acc[rq * 4 + 1] = fmaf(w, o[rq].y, acc[rq * 4 + 1]);
+      acc[rq * 4 + 2] = fmaf(w, o[rq].z, acc[rq * 4 + 2]);
+      acc[rq * 4 + 3] = fmaf(w, o[rq].w, acc[rq * 4 + 3]);
+    }
   }
+  const int t = tt * TW + (wave % wph) * 32 + n32;
+  if (t >= Tn) return;
   const float inv = 1.f / den;      // every query sees at least its own key
-  uint2 wd;
-  wd.x = pack_bf16(a0 * inv, a1 * inv);
-  wd.y = pack_bf16(a2 * inv, a3 * inv);
-  *(uint2*)(out + row * D + e) = wd;
+  bf16_t* dst = out + ((int64_t)t * h + hgroup * hpw + wave / wph) * D + db * 32 + hi * 4;
+#pragma unroll
+  for (int rq = 0; rq < 4; ++rq) {
+    uint2 w;
+    w.x = pack_bf16(acc[rq * 4 + 0] * inv, acc[rq * 4 + 1] * inv);
+    w.y = pack_bf16(acc[rq * 4 + 2] * inv, acc[rq * 4 + 3] * inv);
+    *(uint2*)(dst + rq * 8) = w;
+  }
 }
 
 static bool pp_head_dim(int d) { return d == 128 || d == 96; }
 
-// Floats of workspace for the partial results of key-split launches (0: this shape never splits).
+static int pp_heads_per_wg(int g) { return g % 8 == 0 ? 8 : g % 4 == 0 ? 4 : g % 2 == 0 ? 2 : 1; }
+
+// Floats of workspace for the partial results of cut items: room for every item of the longest chunk in 8 parts, up to
+// PP_MAX_SLOTS (34 MB at 128 dims).  0: this shape never cuts.
 size_t attention_pp_split_floats(const Dims& Dm, int chunk_max) {
   if (!pp_head_dim(Dm.d) || !Dm.bf16) return 0;
-  const int tokens = chunk_max < PP_SPLIT_TOKENS / 2 ? 2 * chunk_max : PP_SPLIT_TOKENS;
-  return (size_t)tokens * Dm.h * (Dm.d + 2);
+  const int hpw = pp_heads_per_wg(Dm.g), TW = PP_NW / hpw * 32;
+  const int64_t slots = (int64_t)8 * (Dm.h / hpw) * ((chunk_max + TW - 1) / TW);
+  return (size_t)(slots < PP_MAX_SLOTS ? slots : PP_MAX_SLOTS) * (PP_NW * 32) * (Dm.d + 2);
+}
+
+// Which items of a launch to cut.  The unit is the key tile (1.7 us of a workgroup).  Workgroups occupy a CU each, so a
+// short chunk, whose I items are at most half as many as the P CUs (both per XCD where the order deals items to XCDs),
+// leaves most of the chip idle: the items longer than tau, about the mean load of a CU, are cut there, and the
+// remainders come last in the launch and go to the CUs that had nothing or are done first.
+// A cut costs the writing, reading and merging of partial results and a second prologue, about PP_CUT_COST tiles at
+// the end of a launch; without that much gain nothing is cut.  With more items nothing is cut either, however
+// uneven they are: the chip is limited by power there, the busy CUs of an uneven launch run faster, and cutting 256
+// items of 97 ... 128 tiles to equal loads (or 256 items of 32 ... 256 tiles) took as long as leaving them whole
+// (222 us against 215, 298 against 300), plus 9-13 us for the merge.
+// Tuning::pp_split: 0 = never, k = every item into k parts (both bounded by the buffer).
+constexpr int PP_CUT_COST = 6;
+static PPCut plan_cut(const Dims& Dm, const PPOrder& o, const HeadLens& hl, int T, int n_c, int TW, size_t floats) {
+  PPCut cut = {};
+  const int lists = o.spread || (o.n_hgroups & 7) == 0 ? 8 : 1;           // item lists that share no CU
+  const int P = lists == 8 ? PP_XCD_CUS : PP_CUS;
+  const int per_head = (o.n_ttiles + 7) / 8;
+  cut.n_items = o.spread ? o.n_hgroups * per_head * 8 : o.n_hgroups * o.n_ttiles;
+  const int max_slots = (int)(floats / ((size_t)(PP_NW * 32) * (Dm.d + 2)));
+  if (max_slots == 0 || Dm.tune.pp_split == 0 || Dm.tune.pp_split == 1) return cut;
+  if (Dm.tune.pp_split > 1) {
+    int k = Dm.tune.pp_split < PP_MAX_PARTS ? Dm.tune.pp_split : PP_MAX_PARTS;
+    while (k > 1 && (int64_t)k * cut.n_items > max_slots) --k;
+    if (k > 1) { cut.k = k; cut.n_donors = cut.n_items; cut.n_slots = k * cut.n_items; }
+    return cut;
+  }
+  const int I = cut.n_items / lists;
+  auto tiles = [&](int nc, int tt) { const int e = (tt + 1) * TW; return (nc + (T < e ? T : e) + KT - 1) / KT; };
+  auto rank_len = [&](int r) { return hl.ragged ? hl.v[o.spread ? o.heads.v[r] : r] : n_c; };     // r-th KV head of the order
+  const int heads = hl.ragged ? Dm.h_kv : 1;
+  int64_t sum = 0;                          // tiles of all items (a KV head has gph head groups)
+  int longest = 0;
+  for (int r = 0; r < heads; ++r)
+    for (int tt = 0; tt < o.n_ttiles; ++tt) {
+      const int c = tiles(rank_len(r), tt);
+      sum += c;
+      longest = c > longest ? c : longest;
+    }
+  sum *= hl.ragged ? o.gph : o.n_hgroups;
+  const int mean = (int)((sum + (int64_t)lists * P - 1) / ((int64_t)lists * P));        // load of a CU
+  if (2 * I <= P) {
+    int tau = mean + 2 > 8 ? mean + 2 : 8;
+    if (tau < (longest + PP_MAX_PARTS - 1) / PP_MAX_PARTS) tau = (longest + PP_MAX_PARTS - 1) / PP_MAX_PARTS;
+    for (;; tau += 1 + tau / 8) {
+      if (longest < tau + PP_CUT_SLACK + PP_CUT_COST) return cut;
+      int donors = 0;
+      if (o.spread) {                       // whole heads of the order, up to the last one with an item to cut
+        for (int r = 0; r < heads; ++r)
+          if (tiles(rank_len(r), o.n_ttiles - 1) > tau + PP_CUT_SLACK) donors = (r + 1) * o.gph * per_head * 8;
+      } else {                              // the order goes through the token tiles from the longest on
+        int nt = 0;
+        for (int r = 0; r < heads; ++r)
+          for (int tt = 0; tt < o.n_ttiles; ++tt)
+            if (tiles(rank_len(r), tt) > tau + PP_CUT_SLACK) { nt = nt > o.n_ttiles - tt ? nt : o.n_ttiles - tt; break; }
+        donors = nt * o.n_hgroups;
+      }
+      const int parts = (longest - PP_CUT_SLACK + tau - 1) / tau;
+      if ((int64_t)parts * donors > max_slots) continue;
+      cut.tau = tau; cut.n_donors = donors; cut.n_slots = parts * donors;
+      return cut;
+    }
+  }
+  return cut;
 }
 
 // `tab` non-null: q holds un-rotated queries and the kernel rotates them (table row n_c + t).
@@ -535,51 +651,41 @@ bool launch_attention_bf16_pp(const Dims& Dm, LaunchTimer tm, const void* q, con
   if ((int64_t)Dm.cap * Dm.d * 2 >= (1ll << 31)) return false;   // 32-bit byte offsets inside one head
   constexpr int NW = PP_NW;
   const int g = Dm.g;
-  const int hpw = (g % 8 == 0) ? 8 : (g % 4 == 0) ? 4 : (g % 2 == 0) ? 2 : 1;
-  const int wph = NW / hpw;
-  const int TW = wph * 32;
+  const int hpw = pp_heads_per_wg(g);
+  const int TW = NW / hpw * 32;
   const int n_hgroups = Dm.h / hpw;
   const int n_ttiles = (T + TW - 1) / TW;
   const float c_log2 = scale * 1.4426950408889634f;
   const int n_sel = sel ? Dm.h_kv : 0;
   const HeadLens hl = head_lens_or_common(n_c_h);
   const SelectArgs sa = sel ? *sel : SelectArgs{};
-  // Key split: a short chunk has too few (head group, token tile) items for the 256 CUs (chunks of 1024 tokens of
-  // a 32-head layer: 128), so each item is cut into n_split key ranges, as many as bring the launch to about one
-  // workgroup per CU, and a second kernel merges the partial results.  Only while every split still has a
-  // few key tiles in every head and the partials fit their buffer.  Tuning::pp_split: 0 = never,
-  // k = always k ranges (bounded by the buffer only).
-  int n_split = 1;
-  if (split_part != nullptr) {
-    const int forced = Dm.tune.pp_split;
-    int min_nc = n_c;
-    if (hl.ragged) for (int m = 0; m < Dm.h_kv; ++m) min_nc = hl.v[m] < min_nc ? hl.v[m] : min_nc;
-    const int items = n_hgroups * n_ttiles;
-    int want = forced >= 0 ? forced : 256 / items;
-    want = want > PP_MAX_SPLIT ? PP_MAX_SPLIT : want;
-    const int min_tiles = (min_nc + 1 + KT - 1) / KT;
-    while (want > 1 && ((size_t)want * T * Dm.h * (Dm.d + 2) > split_floats || (forced < 0 && min_tiles / want < 8))) --want;
-    n_split = want < 1 ? 1 : want;
-  }
-  const int n_tt_eff = n_ttiles * n_split;
-  const int spread = (hl.ragged && Dm.tune.pp_spread != 0) || Dm.tune.pp_spread == 1;
-  const int n_wg = spread ? n_hgroups * ((n_tt_eff + 7) / 8) * 8 : n_hgroups * n_tt_eff;
-  float* part = n_split > 1 ? split_part : nullptr;
+  PPOrder order;
+  order.n_hgroups = n_hgroups;
+  order.n_ttiles = n_ttiles;
+  order.gph = g / hpw;
+  order.n_sel = n_sel;
+  order.spread = (hl.ragged && Dm.tune.pp_spread != 0) || Dm.tune.pp_spread == 1;
+  order.heads = longest_first(hl, Dm.h_kv);
+  const PPCut cut = plan_cut(Dm, order, hl, T, n_c, TW, split_part ? split_floats : 0);
+  const bool parted = cut.n_donors > 0;
+  const unsigned n_wg = (unsigned)(n_sel + cut.n_items + (parted ? cut.n_slots - cut.n_donors : 0));
 #define LOCRET_PP_LAUNCH(SP)                                                                                          \
   do { if (Dm.d == 96) LOCRET_PP_LAUNCH_D(96, SP); else LOCRET_PP_LAUNCH_D(128, SP); } while (0)
 #define LOCRET_PP_LAUNCH_D(DD, SP)                                                                                    \
-  hipExtLaunchKernelGGL((attn_pp_kernel<DD, SP>), dim3(n_sel + n_wg), dim3(NW * 64), 0, st, tm.start,                   \
-                        part ? nullptr : tm.stop, 0, (const bf16_t*)q, tab, (const bf16_t*)Kx, (const bf16_t*)V,        \
-                        (bf16_t*)out, T, Dm.h, g, Dm.cap, n_c, c_log2, hpw, n_hgroups, n_tt_eff, sa, n_sel, hl, spread, \
-                        longest_first(hl, Dm.h_kv), n_split, part)
-  if (part || spread || hl.ragged) LOCRET_PP_LAUNCH(true); else LOCRET_PP_LAUNCH(false);
+  hipExtLaunchKernelGGL((attn_pp_kernel<DD, SP>), dim3(n_wg), dim3(NW * 64), 0, st, tm.start,                          \
+                        parted ? nullptr : tm.stop, 0, (const bf16_t*)q, tab, (const bf16_t*)Kx, (const bf16_t*)V,      \
+                        (bf16_t*)out, T, Dm.h, g, Dm.cap, n_c, c_log2, hpw, order, sa, n_sel, hl, cut, split_part)
+  if (parted || order.spread || hl.ragged) LOCRET_PP_LAUNCH(true); else LOCRET_PP_LAUNCH(false);
 #undef LOCRET_PP_LAUNCH
 #undef LOCRET_PP_LAUNCH_D
-  if (part) {
-    const int rows = T * Dm.h;
-    const int64_t threads = (int64_t)rows * (Dm.d / 4);
-    hipExtLaunchKernelGGL(attn_pp_merge_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, nullptr, tm.stop, 0,
-                          (const float*)part, (bf16_t*)out, rows, n_split, Dm.d);
+  if (parted) {
+    const dim3 grid((unsigned)cut.n_donors, (unsigned)(Dm.d / 32));
+    if (Dm.d == 96)
+      hipExtLaunchKernelGGL(attn_pp_merge_kernel<96>, grid, dim3(NW * 64), 0, st, nullptr, tm.stop, 0, (const float*)split_part,
+                            (bf16_t*)out, T, Dm.h, g, n_c, hpw, order, hl, cut);
+    else
+      hipExtLaunchKernelGGL(attn_pp_merge_kernel<128>, grid, dim3(NW * 64), 0, st, nullptr, tm.stop, 0, (const float*)split_part,
+                            (bf16_t*)out, T, Dm.h, g, n_c, hpw, order, hl, cut);
   }
   return true;
 }

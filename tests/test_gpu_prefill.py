@@ -154,6 +154,20 @@ def test_key_split_chosen_for_short_chunks_behind_a_long_cache():
     layer.close()
 
 
+@pytest.mark.parametrize("h,h_kv,d,sizes", [
+    (8, 2, 128, [1, 64, 65, 300, 17, 1]),        # global item list; up to 16 parts per item
+    (32, 8, 128, [64, 100, 129]),                # one list per XCD
+    (4, 4, 96, [255, 256, 257, 40]),             # 256-token tiles, 96 dims
+])
+def test_items_of_short_chunks_cut_to_the_mean_load(h, h_kv, d, sizes):
+    """Chunks with few items behind a cache of 3000 units: the longest items are cut, and near the mean load some items of a
+    launch stay whole beside cut ones (last parts longer than the others, query rows past the chunk, parts that see only
+    a few keys)."""
+    w = synth.tiny(name="cut", dtype="bf16", h=h, h_kv=h_kv, d=d, N=3000 + sum(sizes), B=1000, b=5000, n_s=50, d_R=128)
+    layer, o, _ = _run_stream(w, teacher_forced=True, chunk_sizes=[1000] * 3 + sizes)
+    layer.close()
+
+
 @pytest.mark.parametrize("n_z", ["0", "2", "5", "8"])
 def test_contraction_split_of_the_retaining_head(n_z, monkeypatch):
     # short chunks give the retaining head too few tiles for the CUs; the launcher then slices the
