@@ -1,7 +1,7 @@
-// Plain-VALU float kernels for the chunk attention (Eq. 1) and the retaining head (Section 3.3).
-// They serve the float32 configuration (where bf16 matrix cores would break the 1e-5 bar) and any
-// head_dim the MFMA kernels do not cover.  All arithmetic is float32 with float32 accumulation;
-// storage may be float or bf16.
+// Plain-VALU float kernels for the chunk attention (Eq. 1) and the retaining head (Section 3.3) of
+// bf16 layers that the bf16 matrix-core kernels do not cover (head dims 16 and 32, hidden widths that
+// are no multiple of 128).  All arithmetic is float32 with float32 accumulation.  float32 layers run on
+// f32_kernels.hip.
 #include "device_util.h"
 #include "kernels.h"
 
@@ -145,7 +145,7 @@ void launch_attention_simple(const Dims& D, const void* q, const void* Kx, const
                              int n_c, float scale, hipStream_t st, const HeadLens* n_c_h) {
   const HeadLens hl = head_lens_or_common(n_c_h);
   if (D.bf16) attn_simple_dispatch<bf16_t>(D, q, Kx, V, out, T, n_c, scale, st, hl);
-  else attn_simple_dispatch<float>(D, q, Kx, V, out, T, n_c, scale, st, hl);
+  else launch_attention_f32(D, q, Kx, V, out, T, n_c, scale, st, hl);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -215,18 +215,17 @@ __global__ __launch_bounds__(256) void score_simple_kernel(const T* __restrict__
   }
 }
 
-int score_parts_simple(const Dims& D) { return (D.d_R + SC_TN - 1) / SC_TN; }
+int score_parts_simple(const Dims& D) { return D.bf16 ? (D.d_R + SC_TN - 1) / SC_TN : score_parts_f32(D); }
 
 void launch_score_simple(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
                          const float* W2f, float* part, hipStream_t st) {
+  if (!D.bf16) {
+    launch_score_f32(D, q, k, v, T, W1t, W2f, part, st);
+    return;
+  }
   dim3 grid((T + SC_TM - 1) / SC_TM, (D.d_R + SC_TN - 1) / SC_TN);
-  const int hd = D.h * D.d, kvd = D.h_kv * D.d;
-  if (D.bf16)
-    launch_kernel(score_simple_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k,
-                       (const bf16_t*)v, T, hd, kvd, (const bf16_t*)W1t, W2f, D.K, D.d_R, D.h_kv, part, T);
-  else
-    launch_kernel(score_simple_kernel<float>, grid, dim3(256), 0, st, (const float*)q, (const float*)k,
-                       (const float*)v, T, hd, kvd, (const float*)W1t, W2f, D.K, D.d_R, D.h_kv, part, T);
+  launch_kernel(score_simple_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, T,
+                D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, W2f, D.K, D.d_R, D.h_kv, part, T);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -168,6 +168,16 @@ def test_items_of_short_chunks_cut_to_the_mean_load(h, h_kv, d, sizes):
     layer.close()
 
 
+@pytest.mark.parametrize("d", [16, 32, 64, 96, 128])
+def test_float32_attention_at_the_edges_of_its_tiles(d):
+    """32 heads x 250 tokens take two query blocks per workgroup, the short chunks one; single tokens, chunks one off a block and
+    key ranges shorter than the workgroup's wavefronts; a hidden width that is no multiple of its tile."""
+    w = synth.tiny(name="f32_edges", dtype="f32", h=32, h_kv=8, d=d, N=250 + 1 + 15 + 17 + 249, B=250, b=400, n_s=20, d_R=72,
+                   rope=d >= 64, theta=10000.0)
+    layer, o, _ = _run_stream(w, teacher_forced=True, chunk_sizes=[1, 15, 17, 250, 249])
+    layer.close()
+
+
 @pytest.mark.parametrize("n_z", ["0", "2", "5", "8"])
 def test_contraction_split_of_the_retaining_head(n_z, monkeypatch):
     # short chunks give the retaining head too few tiles for the CUs; the launcher then slices the
