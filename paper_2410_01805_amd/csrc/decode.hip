@@ -20,7 +20,8 @@
 // The step is two launches.  The split kernel goes over the units already in the cache and rotates the
 // (un-rotated) query itself; one more workgroup per KV head takes the new token: one more partial (logit from
 // the rotated query and key, value row, sum 1) and the append to the cache (K, V, the rotated-key shadow, the
-// original position, and a NaN score when the caller does not score generated tokens).  The merge kernel
+// original position, and a NaN score when the caller does not score generated tokens, or else the score from
+// the token's hidden activations, which score_token_kernel left in front of this launch).  The merge kernel
 // combines the partials.  A separate append launch cost 15 % of the step.
 #include <stdlib.h>
 
@@ -28,6 +29,7 @@
 
 #include "attn_common.h"
 #include "kernels.h"
+#include "token_score.h"
 
 namespace locret {
 
@@ -52,6 +54,7 @@ struct DecodeToken {
   int g, cap, n_c, seen, mark_unscored;
   int pre;                // 1: the token is already at slot n_c; attend over n_c + 1 units, no token workgroup
   float c_log2;
+  TokenScore score;       // act NULL: no score to form
   HeadLens n_c_h;         // units per head before the token (ragged), else n_c
 };
 
@@ -301,6 +304,15 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   if (!token_wg) return;
   __shared__ float ks[D];                              // its key, rotated to position n_keys and rounded as stored
   __shared__ float dots[G][DEC_THREADS / 64];
+  static_assert(DEC_THREADS == 256, "token_score's workgroup");
+  __shared__ float score_red[4];
+  if (g0 == 0 && tk.score.act != nullptr) {
+    const float s = token_score(tk.score.act, tk.score.d_R, tk.score.W2f, tk.score.h_kv, m, score_red);
+    if (tid == 0) {
+      tk.S[(int64_t)m * cap + n_keys] = s;
+      if (tk.score.out) tk.score.out[m] = s;
+    }
+  }
   if (tid < D) {
     const T* kp = (const T*)tk.k + (int64_t)m * D;
     float ke = Elem<T>::ld(kp + tid);
@@ -480,7 +492,7 @@ static void decode_launch(const Dims& D, const DecodeToken& tk, T* out, float* p
 
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
                         const float2* tab, void* out, int n_c, int64_t seen, float scale, float* part, hipStream_t st,
-                        bool mark_unscored, const HeadLens* n_c_h, bool pre_appended) {
+                        bool mark_unscored, const HeadLens* n_c_h, bool pre_appended, const TokenScore* score) {
   DecodeToken tk;
   tk.pre = pre_appended ? 1 : 0;
   tk.q = q; tk.k = k; tk.v = v;
@@ -488,6 +500,7 @@ void launch_decode_step(const Dims& D, const void* q, const void* k, const void*
   tk.K = c.K; tk.V = c.V; tk.Kr = c.Kr; tk.S = c.S; tk.P = c.P;
   tk.g = D.g; tk.cap = D.cap; tk.n_c = n_c; tk.seen = (int)seen; tk.mark_unscored = mark_unscored ? 1 : 0;
   tk.c_log2 = scale * 1.4426950408889634f;
+  tk.score = score ? *score : TokenScore{};
   tk.n_c_h = head_lens_or_common(n_c_h);
 #define LOCRET_DEC(DD)                                                                  \
   case DD:                                                                              \

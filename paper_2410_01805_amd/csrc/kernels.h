@@ -202,11 +202,19 @@ bool attention_bf16_attaches_timer(const Dims& D);
 // `part` holds h * decode_max_splits(D) * (d + 2) floats of split-K partials.
 int decode_keys_per_split(const Dims& D, int n_keys);
 int decode_max_splits(const Dims& D);
+// score (bf16 storage, not with pre_appended): the launch also forms the token's scores from its activations.
+struct TokenScore {
+  const float* act;       // [d_R] of launch_score_token
+  const float* W2f;       // [d_R][h_kv]
+  int d_R, h_kv;
+  float* out;             // [h_kv], or NULL: into the cache only
+};
 // pre_appended: the token already sits at slot n_c of the arrays (4-bit rows: launch_append_q4 put it there as the
 // cache stores it); the launch then attends over n_c + 1 units and appends nothing.
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
                         const float2* tab, void* out, int n_c, int64_t seen, float scale, float* part, hipStream_t st,
-                        bool mark_unscored, const HeadLens* n_c_h = nullptr, bool pre_appended = false);
+                        bool mark_unscored, const HeadLens* n_c_h = nullptr, bool pre_appended = false,
+                        const TokenScore* score = nullptr);
 
 // Retaining head: partial scores part[nb][h_kv][T] over hidden-unit blocks; returns the number of
 // blocks nb through *n_parts.  `part` must hold (d_R/score_part_width) * h_kv * chunk_max floats.
@@ -219,6 +227,8 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
                       const void* W1t, const float* W2f, float* part, hipStream_t st, float* zpart = nullptr,
                       size_t zpart_floats = 0);
 size_t score_bf16_split_floats(const Dims& D, int chunk_max);
+// One token's hidden activations act[d_R] (shapes of launch_score_bf16); its scores are act . W2.
+void launch_score_token(const Dims& D, const void* q, const void* k, const void* v, const void* W1t, float* act, hipStream_t st);
 // scores[m][t] = sum over nb (fixed order) -> S[m*cap + n_c + t] (if S) and out[m*T + t] (if out).
 // With n_parts == 1 this is a strided copy (used for caller-supplied scores).
 void launch_score_reduce(const float* part, int n_parts, int part_stride_T, int h_kv, int T, float* S,

@@ -60,6 +60,32 @@ def test_decode_tokens_with_scores(kw):
     layer.close()
 
 
+@pytest.mark.parametrize("h,h_kv,d,d_R", [(1, 1, 64, 128), (4, 2, 64, 256), (8, 2, 128, 384), (6, 6, 96, 128), (33, 33, 64, 128)])
+def test_scores_of_one_token(h, h_kv, d, d_R):
+    """The single-token form of the retaining head: contractions shorter than and no multiple of a wavefront's 512 elements, more
+    than 32 KV heads; locret_score, locret_score_static, a decode step and a chunk of one token give the same score.
+    All sums are float32 over exact products of bf16 values, so the float32 bound applies."""
+    from paper_2410_01805_amd import binding as B
+    w = synth.tiny(name="one_token", dtype="bf16", h=h, h_kv=h_kv, d=d, N=3, B=4, b=8, n_s=1, d_R=d_R)
+    layer, W1, W2 = make_layer(w)
+    o = make_oracle(w, W1, W2)
+    q, k, v = synth.tokens(w, 0, 1)
+    ref = o.score(q, k, v)
+    x = [dev(t, w) for t in (q, k, v)]
+    sc = layer.score(*x).cpu().numpy()
+    assert_close(sc, ref, "f32", "one token")
+    static = torch.empty(h_kv, 1, device=DEV)
+    B.locret_score_static(layer.ctx, *x, 1, static)
+    np.testing.assert_array_equal(static.cpu().numpy(), sc)
+    _, chunk, _ = layer.prefill_chunk(*x, 0)
+    np.testing.assert_array_equal(chunk.cpu().numpy(), sc)
+    _, token = layer.decode_step(*x, with_score=True)
+    np.testing.assert_array_equal(token.cpu().numpy(), sc[:, 0])
+    S = layer.cache_tensors()[2].cpu().numpy()
+    np.testing.assert_array_equal(S, np.repeat(sc, 2, axis=1))
+    layer.close()
+
+
 def test_decode_without_scores_then_evicting_chunk():
     # generated units carry NaN scores; a later evicting chunk drops them before any scored unit
     w = synth.tiny(name="dec_nan", dtype="bf16", h=8, h_kv=2, d=128, N=1400, B=200, b=500, n_s=40, d_R=128)
