@@ -417,11 +417,11 @@ static void attn_launch(const Dims& Dm, LaunchTimer tm, const void* q, const flo
                      n_hgroups, n_ttiles, hl, spread, longest_first(hl, Dm.h_kv));
 }
 
-// The direct-to-LDS kernel (attention_pp.hip) serves head dims 128 and 96 while byte offsets inside one head's
+// The direct-to-LDS kernel (attention_pp.hip) serves head dims 128, 96 and 64 while byte offsets inside one head's
 // cache fit 31 bits; everything else, and every shape when the context's switches ask for it, runs on the
 // register-staged kernel above.
 static bool pp_applies(const Dims& Dm) {
-  return !Dm.tune.attn_regstaged && (Dm.d == 128 || Dm.d == 96) && (int64_t)Dm.cap * Dm.d * 2 < (1ll << 31);
+  return !Dm.tune.attn_regstaged && (Dm.d == 128 || Dm.d == 96 || Dm.d == 64) && (int64_t)Dm.cap * Dm.d * 2 < (1ll << 31);
 }
 
 // true when launch_attention_bf16 hands its LaunchTimer to the kernel's own dispatch

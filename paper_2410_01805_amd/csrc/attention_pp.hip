@@ -1,4 +1,4 @@
-// Chunk attention (Eq. 1) on the bf16 matrix cores of gfx950, head_dim 128 (and 96): K and V tiles go
+// Chunk attention (Eq. 1) on the bf16 matrix cores of gfx950, head_dim 128, 96 and 64: K and V tiles go
 // global -> LDS directly (buffer_load ... lds), and the two wavefronts of every SIMD are held in anti-phase.
 //
 // Products are formed transposed with v_mfma_f32_32x32x16_bf16: S^T = K Q^T (A = 32 key rows from LDS, B = the
@@ -55,12 +55,13 @@ typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int PP_ROWB = 256;                   // bytes of a key's row in LDS: 128 bf16; head_dim 96 leaves the last quarter unused
-constexpr int PP_TILE_B = KT * PP_ROWB;        // 16 KB per operand tile
+constexpr int PP_ROWB = 256;                   // bytes of a row in LDS: 128 bf16; head_dim 96 leaves the last quarter unused
+constexpr int PP_ROWS = 64;                    // rows of a tile: its keys, or with head_dim 64 two keys each
+constexpr int PP_TILE_B = PP_ROWS * PP_ROWB;   // 16 KB per operand tile
+__host__ __device__ constexpr int pp_tile_keys(int d) { return d == 64 ? 2 * PP_ROWS : PP_ROWS; }
 constexpr int PP_STAGE_B = 2 * PP_TILE_B;      // K then V
 constexpr int PP_NW = 8;
 constexpr int PP_KPRE = 4;                     // K fragments fetched ahead of the S block
-constexpr int PP_VPRE = 4;                     // V^T fragments in flight ahead of their MFMA
 constexpr int PP_YTAIL = 4;                    // MFMAs of group A's S block issued behind barrier Y
 constexpr int PP_SEL_MAXR = 48;                // keys per thread of a selection workgroup (512 threads)
 constexpr int PP_MAX_PARTS = 16;               // key ranges per (head group, token tile) item at most
@@ -119,10 +120,15 @@ __device__ __forceinline__ bool pp_item(const PPOrder& o, bool spread, int i, in
 // GENERAL = false is the common case: every KV head holds n_c_common units, one KV head per XCD, the whole key
 // range per workgroup (n_c_h, order.spread, cut and part are ignored, so nothing of head-wise lengths, the spread
 // launch order or the cut items remains in its code).
-// D = 128 or 96.  The tile layout in LDS is that of 128 dims for both (rows of 256 bytes): with 96 dims the lanes
+// D = 128, 96 or 64.  The tile layout in LDS is that of 128 dims for both (rows of 256 bytes): with 96 dims the lanes
 // of a direct load that would fetch the last four 16-byte chunks of a row point outside the buffer instead and
 // bring zeros, which nothing reads; every fragment address stays as it is, S takes 6 contraction steps and O^T
-// has 3 blocks of 32 dims.
+// has 3 blocks of 32 dims.  With 64 dims a tile is 128 keys: row r holds key r in its first and key r + 64 in its second
+// half, so the addresses stay as they are again: the K fragment of contraction step ks >= 4 is step ks - 4 of
+// keys 64 .. 127, the V^T fragment of dim block db >= 2 is block db - 2 of those keys.  A tile then takes as many MFMAs
+// as with 128 dims and twice the softmax, which bounds it.  (32q/8kv x 64, chunks of 2048 on 0 .. 4096 units: 99 us a launch
+// on the register-staged kernel with the selection and a reduction in launches of their own, 12 us; 87 us here with both
+// inside.)
 template <int D, bool GENERAL>
 __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __restrict__ q, const float2* __restrict__ tab, const bf16_t* __restrict__ Kx,
                                                              const bf16_t* __restrict__ V, bf16_t* __restrict__ out,
@@ -130,9 +136,14 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
                                                              int hpw, PPOrder order, SelectArgs sel, int n_sel,
                                                              HeadLens n_c_h, PPCut cut, float* __restrict__ part) {
   constexpr int NW = PP_NW;
-  static_assert(D == 128 || D == 96, "head dims of this kernel");
-  constexpr int NKS = D / 16;
-  constexpr int NDB = D / 32;
+  static_assert(D == 128 || D == 96 || D == 64, "head dims of this kernel");
+  constexpr int NKS = D / 16;                  // contraction steps of S
+  constexpr int NDB = D / 32;                  // 32-dim blocks of O^T
+  constexpr int KT = pp_tile_keys(D);
+  constexpr int KH = KT / PP_ROWS;             // keys per LDS row
+  constexpr int NKB = KT / 32;                 // 32-key blocks of a tile
+  constexpr int PP_VPRE = KH == 2 ? 2 : 4;     // V^T fragments in flight ahead of their MFMA (64 dims: no registers for more)
+  constexpr int NKF = KH * NKS, NVF = KH * NDB;     // K fragments per row block, V^T fragments per 16-row chunk
   __shared__ __attribute__((aligned(1024))) unsigned char ring[4 * PP_STAGE_B];
 
   const int tid = threadIdx.x;
@@ -255,8 +266,10 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
   constexpr int NCH = D / 8;                     // 16-byte chunks of a row in memory
   constexpr int OUTSIDE = 0x7ffff000;            // an offset no buffer reaches: the load brings zeros
   const int k_ch = l_pos ^ l_row ^ (w4 << 2), v_ch = l_pos ^ (l_row << 2);
-  const int k_vo = k_ch < NCH ? (w4 * 4 + l_row) * (D * 2) + k_ch * 16 : OUTSIDE;   // + u * 16 rows (scalar offset)
-  const int v_vo = v_ch < NCH ? (w4 * 4 + l_row) * (D * 2) + v_ch * 16 : OUTSIDE;
+  auto offset = [&](int ch) {                    // + u * 16 rows (scalar offset)
+    return ch < KH * NCH ? ((ch / NCH) * PP_ROWS + w4 * 4 + l_row) * (D * 2) + (ch % NCH) * 16 : OUTSIDE;
+  };
+  const int k_vo = offset(k_ch), v_vo = offset(v_ch);
   auto issue = [&](int tile, int stage) __attribute__((always_inline)) {
     const int tile_u = __builtin_amdgcn_readfirstlane(tile);
     const int left = __builtin_amdgcn_readfirstlane(max(n_keys_s - tile_u * KT, 0) * (D * 2));   // 0 past the end
@@ -280,38 +293,53 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
   // ---- fragment addresses (bytes inside a stage) ---------------------------------------------------
   const int kx = n32 & 15;
   const int k_base = n32 * 256 + ((kx >> 1) << 5) + ((hi ^ (kx & 1)) << 4);
-  int k_rd[NKS];
+  // the address of a step's fragment, base ^ (step << 5), is kept in a register per step, except with 64 dims: the
+  // probabilities of 128 keys leave no room, and the reload of a spilled register would wait for the loads in flight
+  int k_rd[NKF];
 #pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) k_rd[ks] = k_base ^ (ks << 5);
+  for (int ks = 0; ks < NKF; ++ks) k_rd[ks] = k_base ^ (ks << 5);
+  auto k_at = [&](int base, int ks) __attribute__((always_inline)) { return KH == 2 ? base ^ (ks << 5) : base + k_rd[ks]; };
+  auto k_stage = [&](int sb_off) __attribute__((always_inline)) {
+    int base = sb_off;
+    if (KH == 2) {
+      base += k_base;                            // k_base < 16 KB, the stage's offset is a multiple of 32 KB
+      asm volatile("" : "+v"(base));             // formed anew for every tile
+    }
+    return base;
+  };
   const int vs = lane & 15, vG = lane >> 4;
   const int v_base = PP_TILE_B + (((vG >> 1) * 4 + (vs >> 2)) * 256) + ((vs >> 2) << 6) +
                      ((((vG & 1) << 1) + ((vs & 3) >> 1)) << 4) + ((vs & 1) << 3);
   // LDS byte addresses of stage 0 for the asm reads
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_u8_ptr)ring;
-  uint32_t v_ad[NDB];
+  uint32_t v_ad[NVF];
 #pragma unroll
-  for (int db = 0; db < NDB; ++db) v_ad[db] = ring_lds + (uint32_t)(v_base ^ (db << 6));
+  for (int db = 0; db < NVF; ++db) v_ad[db] = ring_lds + (uint32_t)(v_base ^ (db << 6));
 
   bf16x8 kpre[PP_KPRE];                          // fragment f = ks * 2 + kb of the tile whose S block comes next
   auto prefetch_k = [&](int sb_off) __attribute__((always_inline)) {
-    const unsigned char* sb = ring + sb_off;
+    const int base = k_stage(sb_off);
 #pragma unroll
-    for (int f = 0; f < PP_KPRE; ++f) kpre[f] = *(const bf16x8*)(sb + k_rd[f >> 1] + (f & 1) * 32 * 256);
+    for (int f = 0; f < PP_KPRE; ++f) kpre[f] = *(const bf16x8*)(ring + k_at(base, f >> 1) + (f & 1) * 32 * 256);
   };
 
-  // `mid` runs before the last `tail` MFMAs are issued (all fragment reads are out by then)
-  auto s_block = [&](f32x16 (&sacc)[2], int sb_off, auto mid, auto tail_c) __attribute__((always_inline)) {
+  // `mid` runs before the last `tail` MFMAs are issued (all fragment reads are out by then).  Fragment f: step f / 2 of
+  // row block f % 2.
+  auto s_block = [&](f32x16 (&sacc)[NKB], int sb_off, auto mid, auto tail_c) __attribute__((always_inline)) {
     constexpr int TAIL = decltype(tail_c)::value;    // 0: no split
-    const unsigned char* sb = ring + sb_off;
-    bf16x8 kf[NKS][2];
+    const int base = k_stage(sb_off);
+    bf16x8 kf[NKF][2];
 #pragma unroll
-    for (int f = 0; f < 2 * NKS; ++f)
-      kf[f >> 1][f & 1] = f < PP_KPRE ? kpre[f] : *(const bf16x8*)(sb + k_rd[f >> 1] + (f & 1) * 32 * 256);
+    for (int f = 0; f < 2 * NKF; ++f)
+      kf[f >> 1][f & 1] = f < PP_KPRE ? kpre[f] : *(const bf16x8*)(ring + k_at(base, f >> 1) + (f & 1) * 32 * 256);
+    auto mfma = [&](int f) __attribute__((always_inline)) {
+      const int ks = (f >> 1) % NKS, kb = (f >> 1) / NKS * 2 + (f & 1);
+      sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f >> 1][f & 1], qf[ks], ks == 0 ? negm : sacc[kb], 0, 0, 0);   // the S chain starts from -(running max)
+    };
 #pragma unroll
-    for (int f = 0; f < 2 * NKS - TAIL; ++f)
-      sacc[f & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f >> 1][f & 1], qf[f >> 1], f < 2 ? negm : sacc[f & 1], 0, 0, 0);   // the S chain starts from -(running max)
+    for (int f = 0; f < 2 * NKF - TAIL; ++f) mfma(f);
 #pragma unroll
-    for (int i = 0; i < 2 * NKS - PP_KPRE; ++i) {
+    for (int i = 0; i < 2 * NKF - PP_KPRE; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
@@ -319,40 +347,39 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
     if (TAIL > 0) {
       mid();
 #pragma unroll
-      for (int f = 2 * NKS - TAIL; f < 2 * NKS; ++f)
-        sacc[f & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f >> 1][f & 1], qf[f >> 1], sacc[f & 1], 0, 0, 0);
+      for (int f = 2 * NKF - TAIL; f < 2 * NKF; ++f) mfma(f);
     }
   };
 
   // softmax and PV of one tile; the S accumulators are in sacc
-  auto softmax_pv = [&](f32x16 (&sacc)[2], int tile, int sb_off) __attribute__((always_inline)) {
+  auto softmax_pv = [&](f32x16 (&sacc)[NKB], int tile, int sb_off) __attribute__((always_inline)) {
     const int base = tile * KT;
-    uint32_t va[NDB];
+    uint32_t va[NVF];
 #pragma unroll
-    for (int db = 0; db < NDB; ++db) va[db] = v_ad[db] + (uint32_t)sb_off;
-    // V^T fragment f = kc * NDB + db: two transposing 8-byte reads (keys +0..3 and +8..11 of the 16-key chunk)
-    s16x4 vlo[4 * NDB], vhi[4 * NDB];
+    for (int db = 0; db < NVF; ++db) va[db] = v_ad[db] + (uint32_t)sb_off;
+    // V^T fragment f = kc * NVF + db: two transposing 8-byte reads (rows +0..3 and +8..11 of the 16-row chunk kc)
+    s16x4 vlo[4 * NVF], vhi[4 * NVF];
 #pragma unroll
     for (int f = 0; f < PP_VPRE; ++f) {
-      LOCRET_TR_READ(vlo[f], va[f % NDB], (f / NDB) * 4096);
-      LOCRET_TR_READ(vhi[f], va[f % NDB], (f / NDB) * 4096 + 2048);
+      LOCRET_TR_READ(vlo[f], va[f % NVF], (f / NVF) * 4096);
+      LOCRET_TR_READ(vhi[f], va[f % NVF], (f / NVF) * 4096 + 2048);
     }
     if (base + KT - 1 > n_c + tw0) {           // wave-uniform: tile crosses the diagonal
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           int slot = base + kb * 32 + (r >> 2) * 8 + hi * 4 + (r & 3);
           if (slot > limit) sacc[kb][r] = -INFINITY;
         }
     }
-    uint4 pb[4];
+    uint4 pb[2 * NKB];                          // probabilities of keys 16 kc .. + 15
     {
       float ps;
       auto exp_pack_sum = [&]() __attribute__((always_inline)) {
         float ps0 = 0.f, ps1 = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
+        for (int kb = 0; kb < NKB; ++kb) {
           uint32_t w[8];
 #pragma unroll
           for (int r = 0; r < 16; r += 2) {
@@ -370,7 +397,7 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
       if (fresh || __any(!(ps < RESCALE_SUM))) {     // rare: set or raise the running max
         float mx = -INFINITY;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
           for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[kb][r]);
         mx = max_across_halves(mx);
@@ -389,7 +416,7 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
 #pragma unroll
         for (int r = 0; r < 16; ++r) negm[r] = -m_run;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
           for (int r = 0; r < 16; ++r) sacc[kb][r] -= delta;
         fresh = false;
@@ -399,8 +426,8 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int f = 0; f < 4 * NDB; ++f) {
-      constexpr int LASTF = 4 * NDB - 1;
+    for (int f = 0; f < 4 * NVF; ++f) {
+      constexpr int LASTF = 4 * NVF - 1;
       const int newest = f + PP_VPRE - 1 < LASTF ? f + PP_VPRE - 1 : LASTF;   // newest fragment already requested
       // reads issued after fragment f's: two per fragment
       static_assert(PP_VPRE <= 6, "lgkmcnt cases");
@@ -413,12 +440,13 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
         default: LOCRET_LGKM_WAIT(vlo[f], vhi[f], 0); break;
       }
       const s16x8 both = __builtin_shufflevector(vlo[f], vhi[f], 0, 1, 2, 3, 4, 5, 6, 7);
-      oacc[f % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), *(const bf16x8*)&pb[f / NDB],
+      oacc[f % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both),
+                                                              *(const bf16x8*)&pb[f / NVF + 4 * (f % NVF / NDB)],
                                                               oacc[f % NDB], 0, 0, 0);
-      if (f + PP_VPRE < 4 * NDB) {
+      if (f + PP_VPRE < 4 * NVF) {
         const int fn = f + PP_VPRE;
-        LOCRET_TR_READ(vlo[fn], va[fn % NDB], (fn / NDB) * 4096);
-        LOCRET_TR_READ(vhi[fn], va[fn % NDB], (fn / NDB) * 4096 + 2048);
+        LOCRET_TR_READ(vlo[fn], va[fn % NVF], (fn / NVF) * 4096);
+        LOCRET_TR_READ(vhi[fn], va[fn % NVF], (fn / NVF) * 4096 + 2048);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -444,7 +472,7 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
       issue(t_lo + t + 3, (t + 3) & 3);
       prefetch_k(sb_off);
       wg_barrier();                                              // Y(t)
-      f32x16 sacc[2];
+      f32x16 sacc[NKB];
       s_block(sacc, sb_off, []() {}, IntC<0>());
       softmax_pv(sacc, t_lo + t, sb_off);
       asm volatile("s_waitcnt vmcnt(8)" ::: "memory");          // own loads of tile t+2 have landed
@@ -461,7 +489,7 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
     for (int t = 0; t < n_active; ++t) {
       const int sb_off = (t & 3) * PP_STAGE_B;
       wg_barrier();                                              // X(t)
-      f32x16 sacc[2];
+      f32x16 sacc[NKB];
       s_block(sacc, sb_off, wg_barrier, IntC<PP_YTAIL>());        // Y(t), passed PP_YTAIL MFMAs before the end of the block
       softmax_pv(sacc, t_lo + t, sb_off);
       prefetch_k(((t + 1) & 3) * PP_STAGE_B);
@@ -511,7 +539,7 @@ template <int D>
 __global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* __restrict__ part, bf16_t* __restrict__ out,
                                                                    int Tn, int h, int g, int n_c_common, int hpw, PPOrder order,
                                                                    HeadLens n_c_h, PPCut cut) {
-  constexpr int NW = PP_NW, NDB = D / 32;
+  constexpr int NW = PP_NW, NDB = D / 32, KT = pp_tile_keys(D);
   const int item = blockIdx.x, db = blockIdx.y;
   int hgroup, tt;
   if (!pp_item(order, order.spread, item, hgroup, tt)) return;
@@ -559,7 +587,7 @@ __global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* 
   }
 }
 
-static bool pp_head_dim(int d) { return d == 128 || d == 96; }
+static bool pp_head_dim(int d) { return d == 128 || d == 96 || d == 64; }
 
 static int pp_heads_per_wg(int g) { return g % 8 == 0 ? 8 : g % 4 == 0 ? 4 : g % 2 == 0 ? 2 : 1; }
 
@@ -587,7 +615,7 @@ static PPCut plan_cut(const Dims& Dm, const PPOrder& o, const HeadLens& hl, int 
   PPCut cut = {};
   const int lists = o.spread || (o.n_hgroups & 7) == 0 ? 8 : 1;           // item lists that share no CU
   const int P = lists == 8 ? PP_XCD_CUS : PP_CUS;
-  const int per_head = (o.n_ttiles + 7) / 8;
+  const int per_head = (o.n_ttiles + 7) / 8, KT = pp_tile_keys(Dm.d);
   cut.n_items = o.spread ? o.n_hgroups * per_head * 8 : o.n_hgroups * o.n_ttiles;
   const int max_slots = (int)(floats / ((size_t)(PP_NW * 32) * (Dm.d + 2)));
   if (max_slots == 0 || Dm.tune.pp_split == 0 || Dm.tune.pp_split == 1) return cut;
@@ -670,7 +698,11 @@ bool launch_attention_bf16_pp(const Dims& Dm, LaunchTimer tm, const void* q, con
   const bool parted = cut.n_donors > 0;
   const unsigned n_wg = (unsigned)(n_sel + cut.n_items + (parted ? cut.n_slots - cut.n_donors : 0));
 #define LOCRET_PP_LAUNCH(SP)                                                                                          \
-  do { if (Dm.d == 96) LOCRET_PP_LAUNCH_D(96, SP); else LOCRET_PP_LAUNCH_D(128, SP); } while (0)
+  do {                                                                                                                 \
+    if (Dm.d == 64) LOCRET_PP_LAUNCH_D(64, SP);                                                                         \
+    else if (Dm.d == 96) LOCRET_PP_LAUNCH_D(96, SP);                                                                    \
+    else LOCRET_PP_LAUNCH_D(128, SP);                                                                                   \
+  } while (0)
 #define LOCRET_PP_LAUNCH_D(DD, SP)                                                                                    \
   hipExtLaunchKernelGGL((attn_pp_kernel<DD, SP>), dim3(n_wg), dim3(NW * 64), 0, st, tm.start,                          \
                         parted ? nullptr : tm.stop, 0, (const bf16_t*)q, tab, (const bf16_t*)Kx, (const bf16_t*)V,      \
@@ -680,12 +712,13 @@ bool launch_attention_bf16_pp(const Dims& Dm, LaunchTimer tm, const void* q, con
 #undef LOCRET_PP_LAUNCH_D
   if (parted) {
     const dim3 grid((unsigned)cut.n_donors, (unsigned)(Dm.d / 32));
-    if (Dm.d == 96)
-      hipExtLaunchKernelGGL(attn_pp_merge_kernel<96>, grid, dim3(NW * 64), 0, st, nullptr, tm.stop, 0, (const float*)split_part,
-                            (bf16_t*)out, T, Dm.h, g, n_c, hpw, order, hl, cut);
-    else
-      hipExtLaunchKernelGGL(attn_pp_merge_kernel<128>, grid, dim3(NW * 64), 0, st, nullptr, tm.stop, 0, (const float*)split_part,
-                            (bf16_t*)out, T, Dm.h, g, n_c, hpw, order, hl, cut);
+#define LOCRET_PP_MERGE(DD)                                                                                            \
+  hipExtLaunchKernelGGL(attn_pp_merge_kernel<DD>, grid, dim3(NW * 64), 0, st, nullptr, tm.stop, 0, (const float*)split_part,   \
+                        (bf16_t*)out, T, Dm.h, g, n_c, hpw, order, hl, cut)
+    if (Dm.d == 64) LOCRET_PP_MERGE(64);
+    else if (Dm.d == 96) LOCRET_PP_MERGE(96);
+    else LOCRET_PP_MERGE(128);
+#undef LOCRET_PP_MERGE
   }
   return true;
 }

@@ -173,7 +173,7 @@ int score_parts_f32(const Dims& D);
 void launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
                       float* part, hipStream_t st);
 // bf16 MFMA kernel with K/V staged global -> LDS directly and the two wavefronts of every SIMD held one S block
-// apart (attention_pp.hip; d = 128 or 96); false if the shape is not covered.
+// apart (attention_pp.hip; d = 128, 96 or 64); false if the shape is not covered.
 bool launch_attention_bf16_pp(const Dims& D, LaunchTimer tm, const void* q, const float2* tab, const void* Kx,
                               const void* V, void* out, int T, int n_c, float scale, hipStream_t st,
                               const SelectArgs* sel = nullptr, const HeadLens* n_c_h = nullptr,

@@ -158,6 +158,8 @@ def test_key_split_chosen_for_short_chunks_behind_a_long_cache():
     (8, 2, 128, [1, 64, 65, 300, 17, 1]),        # global item list; up to 16 parts per item
     (32, 8, 128, [64, 100, 129]),                # one list per XCD
     (4, 4, 96, [255, 256, 257, 40]),             # 256-token tiles, 96 dims
+    (8, 8, 64, [255, 129, 64, 1]),               # key tiles of 128
+    (16, 2, 64, [127, 31, 33]),
 ])
 def test_items_of_short_chunks_cut_to_the_mean_load(h, h_kv, d, sizes):
     """Chunks with few items behind a cache of 3000 units: the longest items are cut, and near the mean load some items of a
