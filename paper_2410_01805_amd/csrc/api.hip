@@ -445,7 +445,7 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);      // per-head cache lengths before this chunk, or NULL
   c->mark(0, 0, st);
-  if (D.kv_bits) launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st, false);
+  if (D.kv_bits) launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st);
   else launch_append(D, fused_q ? nullptr : q, k, v, T, c->n_c, c->seen, A, qr, tab, st, nullptr, hl);
   c->mark(0, 1, st);
   const void* qx = (D.rope && !fused_q) ? qr : q;
@@ -540,17 +540,15 @@ int locret_decode_step(locret_ctx* c, const void* q, const void* k, const void* 
   // The retaining head of one token is two short launches and a reduction by itself; here the token's workgroup of the
   // attention launch does everything behind the hidden activations.
   TokenScore score = {};
-  if (with_score && c->mfma_score && !D.kv_bits && D.tune.score_nt == 0 && D.tune.score_split < 0 && c->L.zpart_floats > 0) {
+  if (with_score && c->mfma_score && D.tune.score_nt == 0 && D.tune.score_split < 0 && c->L.zpart_floats > 0) {
     float* act = (float*)(c->ws + c->L.zpart);
     launch_score_token(D, q, k, v, c->ws + c->L.W1t, act, st);
     score = {act, (const float*)(c->ws + c->L.W2f), D.d_R, D.h_kv, scores_out};
   } else if (with_score) {
     run_score(c, q, k, v, 1, A.S, c->n_c, scores_out, st);
   }
-  // 4-bit rows: the token enters the cache first (packed row + staging), then attention reads it like any unit
-  if (D.kv_bits) launch_append_q4(D, k, v, 1, c->n_c, c->seen, A, tab, st, /*mark_unscored=*/!with_score);
   launch_decode_step(D, q, k, v, A, tab, attn_out, c->n_c, c->seen, c->scale, (float*)(c->ws + c->L.dpart), st,
-                     /*mark_unscored=*/!with_score, c->lens(&hl_tmp), /*pre_appended=*/D.kv_bits != 0, score.act ? &score : nullptr);
+                     /*mark_unscored=*/!with_score, c->lens(&hl_tmp), score.act ? &score : nullptr);
   grow(c, 1);
   c->seen += 1;
   return hipGetLastError() == hipSuccess ? LOCRET_OK : LOCRET_EHIP;
@@ -595,7 +593,7 @@ int locret_evict_compact(locret_ctx* c, const float* chunk_scores, const void* k
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);
   if (D.kv_bits) {
-    launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st, false);
+    launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st);
     launch_score_reduce(chunk_scores, 1, T, D.h_kv, T, A.S, D.cap, c->n_c, nullptr, st, hl);
   } else {
     launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, chunk_scores, hl);

@@ -29,6 +29,7 @@
 
 #include "attn_common.h"
 #include "kernels.h"
+#include "quant_row.h"
 #include "token_score.h"
 
 namespace locret {
@@ -52,7 +53,9 @@ struct DecodeToken {
   float* S;
   int32_t* P;
   int g, cap, n_c, seen, mark_unscored;
-  int pre;                // 1: the token is already at slot n_c; attend over n_c + 1 units, no token workgroup
+  uint8_t* Kq;            // 4-bit rows: the packed arrays (K, Kr and V are then the staging copy), else NULL
+  uint8_t* Vq;
+  int qstride;
   float c_log2;
   TokenScore score;       // act NULL: no score to form
   HeadLens n_c_h;         // units per head before the token (ragged), else n_c
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   // read, the partial carries max -inf and sum 0, which the merge weighs with 0)
   const int n_keys = head_len(tk.n_c_h, m, tk.n_c);   // units of this head in the cache = the new token's slot and position
   const int k0 = split * keys_per_wg;
-  const int k1 = min(n_keys + tk.pre, k0 + keys_per_wg);
+  const int k1 = min(n_keys, k0 + keys_per_wg);
   const T* Kb = Kx + (int64_t)m * cap * D;
   const T* Vb = V + (int64_t)m * cap * D;
   const int off = (act ? sub : 0) * VEC;
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     }
   }
   __syncthreads();
-  const bool token_wg = !tk.pre && split == n_splits - 1;
+  const bool token_wg = split == n_splits - 1;
   for (int idx = tid; idx < G * PW && !token_wg; idx += DEC_THREADS) {
     const int u = idx / PW, e = idx % PW;
     if (g0 + u >= g) continue;
@@ -313,7 +316,45 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
       if (tk.score.out) tk.score.out[m] = s;
     }
   }
-  if (tid < D) {
+  __shared__ float vs[D];                              // its value as stored
+  bool quantized = false;
+  if constexpr (std::is_same<T, bf16_t>::value && (D == 64 || D == 96 || D == 128)) {
+    // 4-bit rows: attention sees the token as the cache holds it, so it is quantized first (wavefront 0 the key,
+    // wavefront 1 the value).  As a launch of its own in front of this kernel that took 6 us a token.
+    quantized = tk.Kq != nullptr;
+    if (quantized && wave < 2) {
+      constexpr int NP = Q4Lanes<D>::NP;
+      const int p = min(lane, NP - 1);
+      Q4Pieces r = quantize_pieces<D>((const bf16_t*)(wave == 0 ? tk.k : tk.v) + (int64_t)m * D, p, 0);
+      if (wave == 0 && tab != nullptr) {
+        float2 cs[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) cs[e] = tab[(int64_t)n_keys * (D / 2) + 8 * p + e];
+        r.rotate(cs);
+      }
+      if (lane < NP) {
+        const q4_u32x4 ra = pack8_bf16(r.a), rb = pack8_bf16(r.b);
+        if (g0 == 0) {                                 // one launch per step appends
+          const int64_t slot = (int64_t)m * cap + n_keys;
+          store_pieces<D>(r, (wave == 0 ? tk.Kq : tk.Vq) + slot * tk.qstride, p);
+          bf16_t* st = (bf16_t*)(wave == 0 ? tk.Kr : tk.V) + slot * D;
+          *(q4_u32x4*)(st + 8 * p) = ra;
+          *(q4_u32x4*)(st + D / 2 + 8 * p) = rb;
+        }
+        float a[8], b[8];
+        unpack8_bf16(ra, a);
+        unpack8_bf16(rb, b);
+        float* dst = wave == 0 ? ks : vs;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { dst[8 * p + e] = a[e]; dst[D / 2 + 8 * p + e] = b[e]; }
+      }
+    }
+  }
+  if (g0 == 0 && tid == 0) {
+    tk.P[(int64_t)m * cap + n_keys] = tk.seen;
+    if (tk.mark_unscored) tk.S[(int64_t)m * cap + n_keys] = __uint_as_float(0x7fc00000u);   // NaN: ranks last
+  }
+  if (!quantized && tid < D) {
     const T* kp = (const T*)tk.k + (int64_t)m * D;
     float ke = Elem<T>::ld(kp + tid);
     if (tab != nullptr) {
@@ -326,15 +367,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
       ke = Elem<T>::ld(&rounded);
     }
     ks[tid] = ke;
-    if (g0 == 0) {                                     // one launch per step appends
+    vs[tid] = Elem<T>::ld((const T*)tk.v + (int64_t)m * D + tid);
+    if (g0 == 0) {
       const int64_t row = ((int64_t)m * cap + n_keys) * D + tid;
       ((T*)tk.K)[row] = kp[tid];
       ((T*)tk.V)[row] = ((const T*)tk.v)[(int64_t)m * D + tid];
       if (tab != nullptr) Elem<T>::st((T*)tk.Kr + row, ke);
-      if (tid == 0) {
-        tk.P[(int64_t)m * cap + n_keys] = tk.seen;
-        if (tk.mark_unscored) tk.S[(int64_t)m * cap + n_keys] = __uint_as_float(0x7fc00000u);   // NaN: ranks last
-      }
     }
   }
   __syncthreads();
@@ -356,7 +394,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     if (g0 + u >= g) continue;
     float val;
     if (e < D) {
-      val = Elem<T>::ld((const T*)tk.v + (int64_t)m * D + e);
+      val = vs[e];
     } else if (e == D) {
       val = 0.f;
       for (int w2 = 0; w2 < (D + 63) / 64; ++w2) val += dots[u][w2];     // the wavefronts that hold dims, in order
@@ -473,9 +511,9 @@ int decode_max_splits(const Dims& D) {
 template <typename T, int DD>
 static void decode_launch(const Dims& D, const DecodeToken& tk, T* out, float* part, hipStream_t st) {
   const int kpw = decode_keys_per_split(D, tk.n_c);
-  const int n_attn = (tk.n_c + tk.pre + kpw - 1) / kpw;   // splits over the units already in the cache (the longest head's)
+  const int n_attn = (tk.n_c + kpw - 1) / kpw;   // splits over the units already in the cache (the longest head's)
   const T* Kx = (const T*)(D.rope ? tk.Kr : tk.K);
-  const int n_part = n_attn + (tk.pre ? 0 : 1);           // + the workgroup of the new token
+  const int n_part = n_attn + 1;                          // + the workgroup of the new token
   const dim3 grid(n_part, D.h_kv);
   for (int g0 = 0; g0 < D.g; g0 += 4) {
     const int left = D.g - g0;
@@ -492,9 +530,9 @@ static void decode_launch(const Dims& D, const DecodeToken& tk, T* out, float* p
 
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
                         const float2* tab, void* out, int n_c, int64_t seen, float scale, float* part, hipStream_t st,
-                        bool mark_unscored, const HeadLens* n_c_h, bool pre_appended, const TokenScore* score) {
+                        bool mark_unscored, const HeadLens* n_c_h, const TokenScore* score) {
   DecodeToken tk;
-  tk.pre = pre_appended ? 1 : 0;
+  tk.Kq = (uint8_t*)c.Kq; tk.Vq = (uint8_t*)c.Vq; tk.qstride = c.qstride;
   tk.q = q; tk.k = k; tk.v = v;
   tk.tab = D.rope ? tab : nullptr;
   tk.K = c.K; tk.V = c.V; tk.Kr = c.Kr; tk.S = c.S; tk.P = c.P;

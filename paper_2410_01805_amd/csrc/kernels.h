@@ -151,13 +151,13 @@ void launch_append(const Dims& D, const void* q, const void* k, const void* v, i
                    const float* scores = nullptr, const HeadLens* n_c_h = nullptr);
 
 // 4-bit rows.  Append: quantize the chunk's k, v rows into the packed arrays of `c` at slots [n_c, n_c+T) and write
-// their dequantized values (K rotated to n_c+t) into the staging arrays; P as launch_append; mark_unscored: also a NaN score (none will be computed).
+// their dequantized values (K rotated to n_c+t) into the staging arrays; P as launch_append.
 // Compact: dst packed rows r = src packed rows kept[m][r], S, P likewise, staging rows r rewritten for slot r.
 bool q4_head_dim(int d);
 int q4_row_bytes(int d);      // d/2 code bytes + 4 bytes (scale, minimum as bf16) per group of 32 dims
 int q4_row_stride(int d);     // the same, padded to a multiple of 16
 void launch_append_q4(const Dims& D, const void* k, const void* v, int T, int n_c, int64_t seen, const CacheBuf& c,
-                      const float2* tab, hipStream_t st, bool mark_unscored);
+                      const float2* tab, hipStream_t st);
 void launch_compact_q4(const Dims& D, const CacheBuf& src, const CacheBuf& dst, const int32_t* kept, int kept_stride,
                        int n_keep, const float2* tab, hipStream_t st);
 
@@ -202,18 +202,16 @@ bool attention_bf16_attaches_timer(const Dims& D);
 // `part` holds h * decode_max_splits(D) * (d + 2) floats of split-K partials.
 int decode_keys_per_split(const Dims& D, int n_keys);
 int decode_max_splits(const Dims& D);
-// score (bf16 storage, not with pre_appended): the launch also forms the token's scores from its activations.
+// score (bf16 storage): the launch also forms the token's scores from its activations.
 struct TokenScore {
   const float* act;       // [d_R] of launch_score_token
   const float* W2f;       // [d_R][h_kv]
   int d_R, h_kv;
   float* out;             // [h_kv], or NULL: into the cache only
 };
-// pre_appended: the token already sits at slot n_c of the arrays (4-bit rows: launch_append_q4 put it there as the
-// cache stores it); the launch then attends over n_c + 1 units and appends nothing.
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
                         const float2* tab, void* out, int n_c, int64_t seen, float scale, float* part, hipStream_t st,
-                        bool mark_unscored, const HeadLens* n_c_h = nullptr, bool pre_appended = false,
+                        bool mark_unscored, const HeadLens* n_c_h = nullptr,
                         const TokenScore* score = nullptr);
 
 // Retaining head: partial scores part[nb][h_kv][T] over hidden-unit blocks; returns the number of

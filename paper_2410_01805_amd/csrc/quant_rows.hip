@@ -16,65 +16,9 @@
 // read once.
 #include "device_util.h"
 #include "kernels.h"
+#include "quant_row.h"
 
 namespace locret {
-
-
-__device__ __forceinline__ uint32_t pack2_bf16(float a, float b) { return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16); }
-
-typedef unsigned int q4_u32x4 __attribute__((ext_vector_type(4)));
-
-// A row of D bf16 values is shared by NP = D/16 lanes (a power-of-two block of NPP lanes is reserved for it); lane p
-// owns two pieces of 8 dims, [8p, 8p+8) and [D/2 + 8p, D/2 + 8p + 8): eight rotary pairs (i, i + D/2).  Piece ids
-// run 0 .. 2 NP - 1 in dim order (piece q = dims [8q, 8q+8)); a quantization group is four consecutive pieces.
-template <int D>
-struct Q4Lanes {
-  static constexpr int NP = D / 16;
-  static constexpr int NPP = NP <= 4 ? 4 : 8;
-};
-
-// min and max of the group that piece `piece` belongs to, gathered from the lanes of the row (lane block starts at
-// lane `base`): every lane offers the (min, max) of its two pieces.
-template <int D>
-__device__ __forceinline__ void group_min_max(int piece, int base, float mn0, float mx0, float mn1, float mx1, float& lo, float& hi) {
-  constexpr int NP = Q4Lanes<D>::NP;
-  const int g = piece >> 2;
-  lo = INFINITY;
-  hi = -INFINITY;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int q = 4 * g + j;                      // a member piece: slot q / NP of lane q % NP
-    const int src = base + q % NP;
-    const float a0 = __shfl(mn0, src, 64), a1 = __shfl(mn1, src, 64);
-    const float b0 = __shfl(mx0, src, 64), b1 = __shfl(mx1, src, 64);
-    lo = fminf(lo, q / NP ? a1 : a0);
-    hi = fmaxf(hi, q / NP ? b1 : b0);
-  }
-}
-
-// codes of 8 values against (lo, s); returns the packed dword (dim e in nibble e) and leaves the dequantized values
-__device__ __forceinline__ uint32_t quant8(float (&x)[8], float lo, float s) {
-  uint32_t w = 0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float c = fminf(fmaxf(rintf(__fdiv_rn(x[e] - lo, s)), 0.f), 15.f);
-    w |= (uint32_t)c << (4 * e);
-    x[e] = fmaf(c, s, lo);
-  }
-  return w;
-}
-
-__device__ __forceinline__ void unpack8_bf16(q4_u32x4 v, float (&x)[8]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    x[2 * i] = bf2f((bf16_t)(v[i] & 0xffffu));
-    x[2 * i + 1] = bf2f((bf16_t)(v[i] >> 16));
-  }
-}
-__device__ __forceinline__ q4_u32x4 pack8_bf16(const float (&x)[8]) {
-  q4_u32x4 r = {pack2_bf16(x[0], x[1]), pack2_bf16(x[2], x[3]), pack2_bf16(x[4], x[5]), pack2_bf16(x[6], x[7])};
-  return r;
-}
 
 // Append: thread (t, p) quantizes its two pieces of the K row and of the V row of token t for the KV heads of its
 // block, writes the code dwords and (first lane of every group) the group's (scale, minimum), and the staging
@@ -85,7 +29,7 @@ __global__ __launch_bounds__(256) void append_q4_kernel(const bf16_t* __restrict
                                                         uint8_t* __restrict__ Kq, uint8_t* __restrict__ Vq, int qstride,
                                                         bf16_t* __restrict__ Kst, bf16_t* __restrict__ Vst,
                                                         int32_t* __restrict__ P, const float2* __restrict__ tab,
-                                                        float* __restrict__ S_unscored, int hpb) {
+                                                        int hpb) {
   constexpr int NP = Q4Lanes<D>::NP, NPP = Q4Lanes<D>::NPP;
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int t_raw = (int)(gid / NPP), p_raw = (int)(gid % NPP);
@@ -105,45 +49,17 @@ __global__ __launch_bounds__(256) void append_q4_kernel(const bf16_t* __restrict
 #pragma unroll
     for (int kv = 0; kv < 2; ++kv) {
       const bf16_t* src = (kv == 0 ? k : v) + ((int64_t)t * h_kv + m) * D;
-      float a[8], b[8];
-      unpack8_bf16(*(const q4_u32x4*)(src + 8 * p), a);
-      unpack8_bf16(*(const q4_u32x4*)(src + D / 2 + 8 * p), b);
-      float mn0 = a[0], mx0 = a[0], mn1 = b[0], mx1 = b[0];
-#pragma unroll
-      for (int e = 1; e < 8; ++e) {
-        mn0 = fminf(mn0, a[e]); mx0 = fmaxf(mx0, a[e]);
-        mn1 = fminf(mn1, b[e]); mx1 = fmaxf(mx1, b[e]);
-      }
-      float lo0, hi0, lo1, hi1;
-      group_min_max<D>(p, base, mn0, mx0, mn1, mx1, lo0, hi0);
-      group_min_max<D>(NP + p, base, mn0, mx0, mn1, mx1, lo1, hi1);
-      float s0 = bf2f(f2bf(__fdiv_rn(hi0 - lo0, 15.0f))), s1 = bf2f(f2bf(__fdiv_rn(hi1 - lo1, 15.0f)));
-      s0 = s0 > 0.f ? s0 : 1.0f;
-      s1 = s1 > 0.f ? s1 : 1.0f;
-      const uint32_t w0 = quant8(a, lo0, s0), w1 = quant8(b, lo1, s1);     // a, b now hold the dequantized values
-      if (kv == 0 && tab != nullptr) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float lo = a[e] * cs[e].x - b[e] * cs[e].y, hi = b[e] * cs[e].x + a[e] * cs[e].y;
-          a[e] = lo;
-          b[e] = hi;
-        }
-      }
+      Q4Pieces r = quantize_pieces<D>(src, p, base);
+      if (kv == 0 && tab != nullptr) r.rotate(cs);
       if (act) {
         uint8_t* qrow = (kv == 0 ? Kq : Vq) + slot * qstride;
-        *(uint32_t*)(qrow + 4 * p) = w0;
-        *(uint32_t*)(qrow + D / 4 + 4 * p) = w1;
-        if ((p & 3) == 0) *(uint32_t*)(qrow + D / 2 + 4 * (p >> 2)) = (uint32_t)f2bf(s0) | ((uint32_t)f2bf(lo0) << 16);
-        if (((NP + p) & 3) == 0) *(uint32_t*)(qrow + D / 2 + 4 * ((NP + p) >> 2)) = (uint32_t)f2bf(s1) | ((uint32_t)f2bf(lo1) << 16);
+        store_pieces<D>(r, qrow, p);
         bf16_t* st = (kv == 0 ? Kst : Vst) + slot * D;
-        *(q4_u32x4*)(st + 8 * p) = pack8_bf16(a);
-        *(q4_u32x4*)(st + D / 2 + 8 * p) = pack8_bf16(b);
+        *(q4_u32x4*)(st + 8 * p) = pack8_bf16(r.a);
+        *(q4_u32x4*)(st + D / 2 + 8 * p) = pack8_bf16(r.b);
       }
     }
-    if (act && p == 0) {
-      P[slot] = seen + t;
-      if (S_unscored) S_unscored[slot] = __uint_as_float(0x7fc00000u);   // NaN: ranks last
-    }
+    if (act && p == 0) P[slot] = seen + t;
   }
 }
 
@@ -243,18 +159,17 @@ int q4_row_bytes(int d) { return d / 2 + 4 * (d / 32); }
 int q4_row_stride(int d) { return (q4_row_bytes(d) + 15) / 16 * 16; }
 
 void launch_append_q4(const Dims& D, const void* k, const void* v, int T, int n_c, int64_t seen, const CacheBuf& c,
-                      const float2* tab, hipStream_t st, bool mark_unscored) {
+                      const float2* tab, hipStream_t st) {
   const int npp = D.d / 16 <= 4 ? 4 : 8;
   const int64_t threads = (int64_t)T * npp;
   const unsigned gx = (unsigned)((threads + 255) / 256);
   int hpb = D.h_kv;
   while (hpb > 1 && (int64_t)gx * ((D.h_kv + hpb - 1) / hpb) < 768) hpb = (hpb + 1) / 2;
   const dim3 grid(gx, (unsigned)((D.h_kv + hpb - 1) / hpb));
-  float* Su = mark_unscored ? c.S : nullptr;
 #define LOCRET_Q4A(DD)                                                                                              \
   launch_kernel(append_q4_kernel<DD>, grid, dim3(256), 0, st, (const bf16_t*)k, (const bf16_t*)v, T, n_c,            \
                 (int)seen, D.h_kv, D.cap, (uint8_t*)c.Kq, (uint8_t*)c.Vq, c.qstride, (bf16_t*)c.Kr, (bf16_t*)c.V,    \
-                c.P, D.rope ? tab : nullptr, Su, hpb)
+                c.P, D.rope ? tab : nullptr, hpb)
   if (D.d == 128) LOCRET_Q4A(128); else if (D.d == 96) LOCRET_Q4A(96); else LOCRET_Q4A(64);
 #undef LOCRET_Q4A
 }

@@ -72,6 +72,31 @@ def test_teacher_forced_stream_with_4bit_rows(kw):
     layer.close()
 
 
+@pytest.mark.parametrize("h,h_kv,d,rope", [(8, 1, 64, True), (6, 2, 96, True), (16, 2, 128, True), (4, 4, 128, False)])
+def test_generated_tokens_from_an_empty_cache(h, h_kv, d, rope):
+    """Every row of the cache was quantized by a decode step: one to four heads a launch (groups of 8 take two launches, of which the
+    first appends), packed rows bit-exact, and a chunk behind them attends over the staging copy."""
+    w = synth.tiny(name="q4_generated", kv_bits=4, dtype="bf16", h=h, h_kv=h_kv, d=d, N=80, B=70, b=100, n_s=4, d_R=128, rope=rope)
+    layer, W1, W2 = make_layer(w)
+    o = _oracle(w, W1, W2)
+    for i in range(10):
+        q, k, v = synth.tokens(w, i, i + 1)
+        out_ref, sc_ref, _ = o.prefill_chunk(q, k, v, 0, evict=False)
+        out, sc = layer.decode_step(dev(q, w), dev(k, w), dev(v, w), with_score=True)
+        assert_close(host(out), out_ref, w.dtype, f"token {i} attention", per_row=True)
+        assert_close(sc.cpu().numpy(), sc_ref[:, 0], w.dtype, f"token {i} score")
+    q, k, v = synth.tokens(w, 10, 80)
+    out_ref, _, _ = o.prefill_chunk(q, k, v, 0, evict=False)
+    out, _, _ = layer.prefill_chunk(dev(q, w), dev(k, w), dev(v, w), 0, evict=False)
+    assert_close(host(out), out_ref, w.dtype, "chunk attention", per_row=True)
+    Kq, Vq, _, P = layer.cache_tensors()
+    for m in range(h_kv):
+        np.testing.assert_array_equal(Kq[m].cpu().numpy(), o.Kq[m])
+        np.testing.assert_array_equal(Vq[m].cpu().numpy(), o.Vq[m])
+        np.testing.assert_array_equal(P[m].cpu().numpy(), o.P[m])
+    layer.close()
+
+
 def test_evict_compact_entry_point_moves_packed_rows_bit_exactly():
     w = synth.tiny(name="q4_evict", kv_bits=4, dtype="bf16", h=8, h_kv=4, d=128, N=6000, B=1000, b=2200, n_s=300, d_R=128)
     layer, W1, W2 = make_layer(w)
