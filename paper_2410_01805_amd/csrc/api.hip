@@ -385,23 +385,25 @@ static SelectArgs select_args(locret_ctx* c, int L, int n_stab, int32_t* kept_id
   return a;
 }
 
+// Some head is over its budget: the other copy then becomes the live one, and the heads that are not over are copied
+// as they are (their kept lists are 0, 1, 2, ...).
+static bool over_budget(const locret_ctx* c, const SelectArgs& a) {
+  if (!c->ragged) return a.L > c->cfg.budget;
+  bool over = false;
+  for (int m = 0; m < c->D.h_kv; ++m) over = over || a.L_h.v[m] > c->b_h[m];
+  return over;
+}
+
 // select + compact on the live copy, whose rows [0, L) are filled; updates the host bookkeeping.
 // select_done: the selection has already been launched (inside the attention launch).
-static void run_evict(locret_ctx* c, int L, int n_stab, int32_t* kept_idx_out, hipStream_t st, bool select_done = false) {
+static void run_evict(locret_ctx* c, const SelectArgs& a, hipStream_t st, bool select_done = false) {
   const int b = c->cfg.budget;
-  const SelectArgs a = select_args(c, L, n_stab, kept_idx_out);
   CacheBuf A = c->buf(c->cur);
-  // the other copy becomes the live one as soon as one head is over its budget; the heads that are not
-  // are then copied as they are (their kept lists are 0, 1, 2, ...)
-  bool over = L > b;
-  if (c->ragged) {
-    over = false;
-    for (int m = 0; m < c->D.h_kv; ++m) over = over || a.L_h.v[m] > c->b_h[m];
-  }
+  const bool over = over_budget(c, a);
   c->mark(3, 0, st);
   // a step that evicts nothing has no list to find: the caller's copy, if asked for, is 0, 1, 2, ...
   if (!select_done && over) launch_select(a, c->D.h_kv, st);
-  else if (!select_done && a.kept2) launch_keep_all(a.kept2, a.stride2, c->D.h_kv, L, a.L_h, st);
+  else if (!select_done && a.kept2) launch_keep_all(a.kept2, a.stride2, c->D.h_kv, a.L, a.L_h, st);
   c->mark(3, 1, st);
   c->mark(4, 0, st);
   if (over) {
@@ -496,26 +498,25 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
   // rides in the first workgroups of the attention launch (Tuning::fuse_select = 0 keeps the separate launch).
   bool fuse_select = false;
   SelectArgs sa{};
-  if (evict && !c->overlap && c->mfma_attn) {
-    sa = select_args(c, L, n_stab, kept_idx_out);
-    fuse_select = attention_bf16_fuses_select(D, sa.L - sa.n_stab - sa.n_pin);
-  }
+  if (evict) sa = select_args(c, L, n_stab, kept_idx_out);
+  if (evict && !c->overlap && c->mfma_attn) fuse_select = attention_bf16_fuses_select(D, sa.L - sa.n_stab - sa.n_pin);
   if (evict && c->overlap) {
     scores(nullptr);
     ok = ok && hipEventRecord(c->ev_fork, st) == hipSuccess;
     ok = ok && hipStreamWaitEvent(c->side, c->ev_fork, 0) == hipSuccess;
-    run_evict(c, L, n_stab, kept_idx_out, c->side);
+    run_evict(c, sa, c->side);
     ok = ok && hipEventRecord(c->ev_join, c->side) == hipSuccess;
     attention(nullptr);
     ok = ok && hipStreamWaitEvent(st, c->ev_join, 0) == hipSuccess;
   } else if (fuse_select) {
     scores(&sa);
     attention(&sa);
-    run_evict(c, L, n_stab, kept_idx_out, st, /*select_done=*/true);
+    run_evict(c, sa, st, /*select_done=*/true);
   } else {
     attention(nullptr);
-    scores(nullptr);
-    if (evict) run_evict(c, L, n_stab, kept_idx_out, st);
+    // a selection of its own sums the partial scores too, where its form allows
+    scores(evict && over_budget(c, sa) && select_sums_partials(sa.L - sa.n_stab - sa.n_pin) ? &sa : nullptr);
+    if (evict) run_evict(c, sa, st);
     else {
       grow(c, T);
       c->mark(3, 0, st); c->mark(3, 1, st); c->mark(4, 0, st); c->mark(4, 1, st);
@@ -598,7 +599,7 @@ int locret_evict_compact(locret_ctx* c, const float* chunk_scores, const void* k
   } else {
     launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, chunk_scores, hl);
   }
-  run_evict(c, c->n_c + T, n_stab, kept_idx_out, st);
+  run_evict(c, select_args(c, c->n_c + T, n_stab, kept_idx_out), st);
   c->seen += T;
   return hipGetLastError() == hipSuccess ? LOCRET_OK : LOCRET_EHIP;
 }

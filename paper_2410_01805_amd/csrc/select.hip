@@ -177,14 +177,18 @@ void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_s
   launch_select(a, h_kv, st);
 }
 
+// keys of a thread in the register-resident form
+static int select_reg_rounds(int n_cand) { return ((n_cand + SEL_WAVES - 1) / SEL_WAVES + 63) / 64; }
+bool select_sums_partials(int n_cand) { return select_reg_rounds(n_cand) <= 64; }
+
 // The path is chosen for the longest head; every path takes shorter heads as they come.
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st) {
   const int ns = a.n_stab < a.L ? a.n_stab : a.L;
   const int npin = a.n_pin < a.L - ns ? a.n_pin : a.L - ns;
   const int n_cand = a.L - ns - npin;
-  const int wseg = ((n_cand + SEL_WAVES - 1) / SEL_WAVES + 63) & ~63;
+  const int rounds = select_reg_rounds(n_cand);
 #define LOCRET_SEL_REG(R)                                                                         \
-  if (wseg <= R * 64) {                                                                           \
+  if (rounds <= R) {                                                                              \
     launch_kernel(select_reg_kernel<R>, dim3(h_kv), dim3(SEL_THREADS), 0, st, a);                 \
     return;                                                                                       \
   }
