@@ -190,6 +190,15 @@ def test_workgroup_order_of_the_other_head_dims_with_head_budgets():
     layer.close()
 
 
+@pytest.mark.parametrize("tail", [45, 300])
+def test_short_chunk_on_long_caches_with_head_budgets(tail):
+    # one and two token tiles on caches of very different lengths: the longest items are cut along the keys
+    w = synth.tiny(name=f"hb_cut_{tail}", dtype="bf16", h=12, h_kv=12, d=96, N=3 * 1024 + tail, B=1024, b=3000, n_s=8, d_R=128)
+    layer, o = _run_stream(w, [3000, 8, 2900, 640, 1500, 64, 2000, 300, 700, 1024, 2500, 100])
+    _assert_caches_equal(layer, o, w)
+    layer.close()
+
+
 def test_key_split_with_head_budgets(monkeypatch):
     monkeypatch.setenv("LOCRET_PP_SPLIT", "4")         # 8 token tiles x 4 key ranges, dealt over the XCDs longest head first
     w = synth.tiny(**SPREAD)
