@@ -538,13 +538,12 @@ int locret_decode_step(locret_ctx* c, const void* q, const void* k, const void* 
   CacheBuf A = c->buf(c->cur);
   const float2* tab = D.rope ? (const float2*)(c->ws + c->L.tab) : nullptr;
   HeadLens hl_tmp;
-  // The retaining head of one token is two short launches and a reduction by itself; here the token's workgroup of the
-  // attention launch does everything behind the hidden activations.
+  // The retaining head of one token is two short launches and a reduction by itself; here its hidden activations are
+  // formed beside the attention, their product with W2 beside the merge.
   TokenScore score = {};
   if (with_score && c->mfma_score && D.tune.score_nt == 0 && D.tune.score_split < 0 && c->L.zpart_floats > 0) {
-    float* act = (float*)(c->ws + c->L.zpart);
-    launch_score_token(D, q, k, v, c->ws + c->L.W1t, act, st);
-    score = {act, (const float*)(c->ws + c->L.W2f), D.d_R, D.h_kv, scores_out};
+    score = {(float*)(c->ws + c->L.zpart), c->ws + c->L.W1t, (const float*)(c->ws + c->L.W2f), D.d_R, D.K, D.h_kv, D.h * D.d,
+             D.h_kv * D.d, scores_out};
   } else if (with_score) {
     run_score(c, q, k, v, 1, A.S, c->n_c, scores_out, st);
   }

@@ -20,9 +20,14 @@
 // The step is two launches.  The split kernel goes over the units already in the cache and rotates the
 // (un-rotated) query itself; one more workgroup per KV head takes the new token: one more partial (logit from
 // the rotated query and key, value row, sum 1) and the append to the cache (K, V, the rotated-key shadow, the
-// original position, and a NaN score when the caller does not score generated tokens, or else the score from
-// the token's hidden activations, which score_token_kernel left in front of this launch).  The merge kernel
-// combines the partials.  A separate append launch cost 15 % of the step.
+// original position, and a NaN score when the caller does not score generated tokens).  The merge kernel
+// combines the partials.  For a scored token further workgroups of the first launch form its hidden activations and
+// further ones of the second its scores: with the activations in a launch of their own in front (5 us) and their
+// product in the token's workgroup, a 611-token prompt and 8 scored tokens took 181 us, 145 us in this form, and an
+// unscored token gained too (16 tokens on 32 heads x 8192 units x 96: 407 -> 396 us; 8 x 6144 x 128: 231 -> 227 us).
+// (Requesting the first keys and values in front of the query's rotation, or those of the next iteration before the
+// current one is worked on, costs the fourth workgroup of a CU: 8 x 16384 x 128 337 to 357 us against 360, but
+// 8 x 16384 x 64 280 against 268 and 8 x 6144 x 128 233 against 231.)  A separate append launch cost 15 % of the step.
 #include <stdlib.h>
 
 #include <type_traits>
@@ -57,19 +62,21 @@ struct DecodeToken {
   uint8_t* Vq;
   int qstride;
   float c_log2;
+  int n_part;             // partials per query head
   TokenScore score;       // act NULL: no score to form
   HeadLens n_c_h;         // units per head before the token (ragged), else n_c
 };
 
-template <typename T, int D, int G>
+template <typename T, int D, int G, bool SCORED>
 __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __restrict__ Kx, int g0, int keys_per_wg,
                                                                   float* __restrict__ part, DecodeToken tk) {
-  // n_splits partials per query head: gridDim.x - 1 splits over the cached units, then the new token's, which the
-  // last workgroup of a head forms (it has no units of its own, so it is done long before the others)
+  // n_splits partials per query head: n_splits - 1 splits over the cached units, then the new token's, which the
+  // last of these workgroups forms (it has no units of its own, so it is done long before the others).
+  // SCORED: the workgroups behind them form the token's hidden activations.
   const T* __restrict__ q = (const T*)tk.q;
   const T* __restrict__ V = (const T*)tk.V;
   const float2* __restrict__ tab = tk.tab;
-  const int g = tk.g, cap = tk.cap, n_splits = (int)gridDim.x;
+  const int g = tk.g, cap = tk.cap, n_splits = SCORED ? tk.n_part : (int)gridDim.x;
   const float c_log2 = tk.c_log2;
   constexpr int VEC = Vec16<T>::N;
   constexpr int LPR = D / VEC;                       // lanes that hold data of one row
@@ -89,6 +96,15 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
 
   const int split = blockIdx.x, m = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if constexpr (SCORED) {
+    if (split >= n_splits) {
+      const TokenScore& sc = tk.score;
+      const int r = ((split - n_splits) * (int)gridDim.y + m) * (DEC_THREADS / 64) + wave;
+      if (r < sc.d_R)
+        token_hidden((const bf16_t*)tk.q, (const bf16_t*)tk.k, (const bf16_t*)tk.v, sc.hd, sc.kvd, (const bf16_t*)sc.W1t, sc.K, r, sc.act);
+      return;
+    }
+  }
   const int sub = lane % LPRP, grp = lane / LPRP;
   const bool act = sub < LPR;
   // head-wise budgets: a head shorter than the longest leaves its last splits empty (k1 <= k0: no row is
@@ -307,15 +323,6 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   if (!token_wg) return;
   __shared__ float ks[D];                              // its key, rotated to position n_keys and rounded as stored
   __shared__ float dots[G][DEC_THREADS / 64];
-  static_assert(DEC_THREADS == 256, "token_score's workgroup");
-  __shared__ float score_red[4];
-  if (g0 == 0 && tk.score.act != nullptr) {
-    const float s = token_score(tk.score.act, tk.score.d_R, tk.score.W2f, tk.score.h_kv, m, score_red);
-    if (tid == 0) {
-      tk.S[(int64_t)m * cap + n_keys] = s;
-      if (tk.score.out) tk.score.out[m] = s;
-    }
-  }
   __shared__ float vs[D];                              // its value as stored
   bool quantized = false;
   if constexpr (std::is_same<T, bf16_t>::value && (D == 64 || D == 96 || D == 128)) {
@@ -413,9 +420,11 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
 constexpr int DEC_MERGE_THREADS = 1024;
 constexpr int DEC_MERGE_PRE = 12;       // vector elements a thread requests before anything else
 constexpr int DEC_MERGE_WS = 2048;      // splits whose weights are kept in LDS
-template <typename T>
+// SCORED: one more workgroup per KV head multiplies the token's hidden activations with W2.
+template <typename T, bool SCORED>
 __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const float* __restrict__ part, int n_splits,
-                                                                         int d, T* __restrict__ out) {
+                                                                         int d, T* __restrict__ out, int h, TokenScore score,
+                                                                         float* __restrict__ S, int cap, int n_c, HeadLens n_c_h) {
   // The kernel is a chain of memory latencies, not of bytes (45 KB per head): every load that does not depend on
   // another is requested up front.  Thread (e, r) owns element e of splits r, r + R, ...; the first
   // DEC_MERGE_PRE of them are in flight while the maxima and sums of the splits are reduced.
@@ -423,6 +432,15 @@ __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const f
   __shared__ float wsm[DEC_MERGE_WS];
   __shared__ float acc_s[DEC_MERGE_THREADS];
   const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (SCORED && j >= h) {
+    const int m = j - h;
+    const float s = token_score(score.act, score.d_R, score.W2f, score.h_kv, m, red);
+    if (tid == 0) {
+      S[(int64_t)m * cap + head_len(n_c_h, m, n_c)] = s;
+      if (score.out) score.out[m] = s;
+    }
+    return;
+  }
   const int pw = d + 2;
   const float* p = part + (int64_t)j * n_splits * pw;
   constexpr int R = DEC_MERGE_THREADS / 128;   // d <= 128
@@ -508,24 +526,39 @@ int decode_max_splits(const Dims& D) {
   return (D.cap + kmin - 1) / kmin + 1;
 }
 
-template <typename T, int DD>
-static void decode_launch(const Dims& D, const DecodeToken& tk, T* out, float* part, hipStream_t st) {
+template <typename T, int DD, int G, bool SCORED>
+static void decode_attn_launch(const T* Kx, int g0, int kpw, float* part, const DecodeToken& tk, dim3 grid, hipStream_t st) {
+  hipLaunchKernelGGL((decode_attn_kernel<T, DD, G, SCORED>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk);
+}
+
+// SCORED: tk.score is set (bf16 storage only)
+template <typename T, int DD, bool SCORED>
+static void decode_launch(const Dims& D, DecodeToken& tk, T* out, float* part, hipStream_t st) {
   const int kpw = decode_keys_per_split(D, tk.n_c);
   const int n_attn = (tk.n_c + kpw - 1) / kpw;   // splits over the units already in the cache (the longest head's)
   const T* Kx = (const T*)(D.rope ? tk.Kr : tk.K);
   const int n_part = n_attn + 1;                          // + the workgroup of the new token
-  const dim3 grid(n_part, D.h_kv);
+  tk.n_part = n_part;
   for (int g0 = 0; g0 < D.g; g0 += 4) {
     const int left = D.g - g0;
-    if (left >= 3)
-      hipLaunchKernelGGL((decode_attn_kernel<T, DD, 4>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk);
-    else if (left == 2)
-      hipLaunchKernelGGL((decode_attn_kernel<T, DD, 2>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk);
-    else
-      hipLaunchKernelGGL((decode_attn_kernel<T, DD, 1>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk);
+    const dim3 grid(n_part, D.h_kv);
+    if (SCORED && g0 == 0) {
+      // a wavefront per hidden unit in further columns of h_kv workgroups
+      const int per_x = D.h_kv * (DEC_THREADS / 64);
+      const dim3 more(n_part + (D.d_R + per_x - 1) / per_x, D.h_kv);
+      if (left >= 3) decode_attn_launch<T, DD, 4, SCORED>(Kx, g0, kpw, part, tk, more, st);
+      else if (left == 2) decode_attn_launch<T, DD, 2, SCORED>(Kx, g0, kpw, part, tk, more, st);
+      else decode_attn_launch<T, DD, 1, SCORED>(Kx, g0, kpw, part, tk, more, st);
+    } else if (left >= 3) {
+      decode_attn_launch<T, DD, 4, false>(Kx, g0, kpw, part, tk, grid, st);
+    } else if (left == 2) {
+      decode_attn_launch<T, DD, 2, false>(Kx, g0, kpw, part, tk, grid, st);
+    } else {
+      decode_attn_launch<T, DD, 1, false>(Kx, g0, kpw, part, tk, grid, st);
+    }
   }
-  hipLaunchKernelGGL(decode_merge_kernel<T>, dim3(D.h), dim3(DEC_MERGE_THREADS), 0, st, (const float*)part, n_part, D.d,
-                     out);
+  hipLaunchKernelGGL((decode_merge_kernel<T, SCORED>), dim3(D.h + (SCORED ? D.h_kv : 0)), dim3(DEC_MERGE_THREADS), 0, st,
+                     (const float*)part, n_part, D.d, out, D.h, tk.score, tk.S, D.cap, tk.n_c, tk.n_c_h);
 }
 
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
@@ -542,8 +575,9 @@ void launch_decode_step(const Dims& D, const void* q, const void* k, const void*
   tk.n_c_h = head_lens_or_common(n_c_h);
 #define LOCRET_DEC(DD)                                                                  \
   case DD:                                                                              \
-    if (D.bf16) decode_launch<bf16_t, DD>(D, tk, (bf16_t*)out, part, st);               \
-    else decode_launch<float, DD>(D, tk, (float*)out, part, st);                        \
+    if (!D.bf16) decode_launch<float, DD, false>(D, tk, (float*)out, part, st);         \
+    else if (score) decode_launch<bf16_t, DD, true>(D, tk, (bf16_t*)out, part, st);     \
+    else decode_launch<bf16_t, DD, false>(D, tk, (bf16_t*)out, part, st);               \
     break;
   switch (D.d) {
     LOCRET_DEC(16)

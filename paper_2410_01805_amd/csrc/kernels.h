@@ -202,11 +202,12 @@ bool attention_bf16_attaches_timer(const Dims& D);
 // `part` holds h * decode_max_splits(D) * (d + 2) floats of split-K partials.
 int decode_keys_per_split(const Dims& D, int n_keys);
 int decode_max_splits(const Dims& D);
-// score (bf16 storage): the launch also forms the token's scores from its activations.
+// score (bf16 storage, the shapes of score_parts_bf16): the launches also form the token's scores.
 struct TokenScore {
-  const float* act;       // [d_R] of launch_score_token
+  float* act;             // [d_R] of workspace for the hidden activations; NULL: no score
+  const void* W1t;        // [d_R][K]
   const float* W2f;       // [d_R][h_kv]
-  int d_R, h_kv;
+  int d_R, K, h_kv, hd, kvd;      // hd, kvd: elements of the token's q and of its k or v
   float* out;             // [h_kv], or NULL: into the cache only
 };
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
@@ -225,8 +226,6 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
                       const void* W1t, const float* W2f, float* part, hipStream_t st, float* zpart = nullptr,
                       size_t zpart_floats = 0);
 size_t score_bf16_split_floats(const Dims& D, int chunk_max);
-// One token's hidden activations act[d_R] (shapes of launch_score_bf16); its scores are act . W2.
-void launch_score_token(const Dims& D, const void* q, const void* k, const void* v, const void* W1t, float* act, hipStream_t st);
 // scores[m][t] = sum over nb (fixed order) -> S[m*cap + n_c + t] (if S) and out[m*T + t] (if out).
 // With n_parts == 1 this is a strided copy (used for caller-supplied scores).
 void launch_score_reduce(const float* part, int n_parts, int part_stride_T, int h_kv, int T, float* S,

@@ -396,41 +396,23 @@ __global__ __launch_bounds__(FIN_THREADS) void score_finish_kernel(const float* 
   }
 }
 
-// One token (a generated one): act[r] = SiLU(W1t[r][:] . x).  A matrix-vector product, bound by reading W1 (12.6 MB at
+// One token: act[r] = SiLU(W1t[r][:] . x).  A matrix-vector product, bound by reading W1 (12.6 MB at
 // 32q/8kv x 128, d_R = 1024): a wavefront takes a hidden unit, its row and the token 16 bytes per lane at a time.  The
 // matrix-core kernel spends a 64-token tile on the token and reads W1 from 64 workgroups only; with its finish kernel and
-// the reduction behind it it took 8 + 9.6 + 3.7 us a token, this kernel 5.1.
+// the reduction behind it it took 8 + 9.6 + 3.7 us a token, this kernel 5.1.  (A generated token's hidden activations
+// are formed in the decode launch.)
 __global__ __launch_bounds__(256) void score_token_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                           const bf16_t* __restrict__ v, int hd, int kvd,
                                                           const bf16_t* __restrict__ W1t, int K, float* __restrict__ act) {
-  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);      // d_R is a multiple of 128
-  const bf16_t* w = W1t + (int64_t)r * K;
-  float acc = 0.f;
-#pragma unroll 4
-  for (int c = lane * 8; c < K; c += 512) {            // hd, kvd and K are multiples of 64: 8 elements lie in one of q, k, v
-    const bf16_t* x = c < hd ? q + c : c < hd + kvd ? k + (c - hd) : v + (c - hd - kvd);
-    Vec16<bf16_t> a, b;
-    a.raw = *(const uint4*)(w + c);
-    b.raw = *(const uint4*)x;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc = fmaf(a.get(e), b.get(e), acc);
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (lane == 0) act[r] = acc * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(acc * -1.4426950408889634f));
+  token_hidden(q, k, v, hd, kvd, W1t, K, blockIdx.x * 4 + (threadIdx.x >> 6), act);      // d_R is a multiple of 128
 }
 
-// scores[m] = act . W2[:][m], one workgroup per KV head (a generated token's score is formed by the decode kernel itself)
+// scores[m] = act . W2[:][m], one workgroup per KV head
 __global__ __launch_bounds__(256) void score_token_finish_kernel(const float* __restrict__ act, int d_R,
                                                                  const float* __restrict__ W2f, int h_kv, float* __restrict__ part) {
   __shared__ float red[4];
   const float s = token_score(act, d_R, W2f, h_kv, blockIdx.x, red);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-void launch_score_token(const Dims& D, const void* q, const void* k, const void* v, const void* W1t, float* act, hipStream_t st) {
-  launch_kernel(score_token_kernel, dim3(D.d_R / 4), dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v,
-                D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, D.K, act);
 }
 
 // Floats of workspace for the partial pre-activations of contraction-split launches.
@@ -458,7 +440,8 @@ int score_parts_bf16(const Dims& D) {
 int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
                       const float* W2f, float* part, hipStream_t st, float* zpart, size_t zpart_floats) {
   if (T == 1 && zpart != nullptr && D.tune.score_nt == 0 && D.tune.score_split < 0) {
-    launch_score_token(D, q, k, v, W1t, zpart, st);
+    launch_kernel(score_token_kernel, dim3(D.d_R / 4), dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v,
+                  D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, D.K, zpart);
     launch_kernel(score_token_finish_kernel, dim3(D.h_kv), dim3(256), 0, st, (const float*)zpart, D.d_R, W2f, D.h_kv, part);
     return 1;
   }

@@ -60,7 +60,7 @@ def test_decode_tokens_with_scores(kw):
     layer.close()
 
 
-@pytest.mark.parametrize("h,h_kv,d,d_R", [(1, 1, 64, 128), (4, 2, 64, 256), (8, 2, 128, 384), (6, 6, 96, 128), (33, 33, 64, 128)])
+@pytest.mark.parametrize("h,h_kv,d,d_R", [(1, 1, 64, 128), (4, 2, 64, 256), (8, 2, 128, 384), (6, 6, 96, 128), (33, 33, 64, 128), (16, 2, 64, 128)])
 def test_scores_of_one_token(h, h_kv, d, d_R):
     """The single-token form of the retaining head: contractions shorter than and no multiple of a wavefront's 512 elements, more
     than 32 KV heads; locret_score, locret_score_static, a decode step and a chunk of one token give the same score.
