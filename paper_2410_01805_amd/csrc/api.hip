@@ -470,7 +470,7 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     c->mark(1, 0, st);
     if (c->mfma_attn) launch_attention_bf16(D, qx, Kx, A.V, attn_out, T, n_c, c->scale, st, fused_q ? tab : nullptr, LaunchTimer(), sel, hl,
                                             split_part, c->L.apart_floats);
-    else launch_attention_simple(D, qx, Kx, A.V, attn_out, T, n_c, c->scale, st, hl);
+    else launch_attention_simple(D, qx, Kx, A.V, attn_out, T, n_c, c->scale, st, hl, sel);
     c->mark(1, 1, st);
   };
   auto scores = [&](SelectArgs* fused) {
@@ -493,13 +493,16 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     c->mark(2, 1, st);
   };
   bool ok = true;
-  // The selection depends on the scores only.  Where the attention launch can carry it (direct-to-LDS kernel, head_dim 128 or 96,
+  // The selection depends on the scores only.  Where the attention launch can carry it (direct-to-LDS kernel, float32 kernel,
   // few enough candidates for its register-resident form) the retaining head runs first and the selection
   // rides in the first workgroups of the attention launch (Tuning::fuse_select = 0 keeps the separate launch).
   bool fuse_select = false;
   SelectArgs sa{};
   if (evict) sa = select_args(c, L, n_stab, kept_idx_out);
-  if (evict && !c->overlap && c->mfma_attn) fuse_select = attention_bf16_fuses_select(D, sa.L - sa.n_stab - sa.n_pin);
+  if (evict && !c->overlap) {
+    const int n_cand = sa.L - sa.n_stab - sa.n_pin;
+    fuse_select = c->mfma_attn ? attention_bf16_fuses_select(D, n_cand) : attention_f32_fuses_select(D, n_cand);
+  }
   if (evict && c->overlap) {
     scores(nullptr);
     ok = ok && hipEventRecord(c->ev_fork, st) == hipSuccess;

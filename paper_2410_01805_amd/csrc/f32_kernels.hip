@@ -10,6 +10,7 @@
 // heads are 256 workgroups of 8 wavefronts.
 #include "device_util.h"
 #include "kernels.h"
+#include "select_body.h"
 
 namespace locret {
 
@@ -33,21 +34,32 @@ template <int N> __device__ __forceinline__ void load_floats(const float* p, flo
 // one query block, by the L2 (a key row is read once per 16 queries): 512 tokens on 1024 + 512 units,
 // 8 heads x 64: 21 us against 199 of a vector-ALU kernel with K, V and P tiles in LDS; the error against 64 bits halved.
 // QB = 2 where that still gives every CU a workgroup.
+// The first n_sel workgroups of the launch do not attend: each carries out the selection of one KV head, which depends on
+// the scores only, and sums their partials.  As a launch of its own it took 8.4 us behind 20 us of attention (2 heads, 1472
+// candidates): 4096 tokens in chunks of 512 333 us, 279 us in this form.
+constexpr int F32_SEL_MAXR = 24;               // keys per thread of a selection workgroup: up to 12288 candidates per head
 template <int D, int QB>
 __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ Kx,
                                                                const float* __restrict__ V, float* __restrict__ out, int Tn,
-                                                               int h, int g, int cap, int n_c_common, float c_log2, HeadLens n_c_h) {
+                                                               int h, int g, int cap, int n_c_common, float c_log2, HeadLens n_c_h, int n_ttiles,
+                                                               SelectArgs sel, int n_sel) {
   constexpr int NC = D / 16;                   // 16-dim pieces of a row = dim blocks of O^T
   constexpr int V4 = D / 64 * 64;              // dims fetched four (then two, one) per lane
   constexpr int V2 = (D - V4) / 32 * 32;
   constexpr int ROW = D + 2;
-  __shared__ float red[F32_NW][16 * QB][ROW];  // O, max, sum of every wavefront
+  constexpr int RED = F32_NW * 16 * QB * ROW, SEL = select_body_smem_words(F32_NW * 64, 1);
+  __shared__ __attribute__((aligned(16))) float smem[RED > SEL ? RED : SEL];
+  if ((int)blockIdx.x < n_sel) {
+    select_reg_body<F32_SEL_MAXR, F32_NW * 64, 1>(sel, blockIdx.x, (uint32_t*)smem);
+    return;
+  }
+  float (*red)[16 * QB][ROW] = (float (*)[16 * QB][ROW])smem;             // O, max, sum of every wavefront
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, kg = lane >> 4;
-  const int j = blockIdx.y, m = j / g;
+  const int item = (int)blockIdx.x - n_sel, j = item / n_ttiles, m = j / g;
   const int n_c = head_len(n_c_h, m, n_c_common);
-  const int t0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * (16 * QB);      // longest key ranges first
+  const int t0 = (n_ttiles - 1 - item % n_ttiles) * (16 * QB);            // longest key ranges first
   const int n_keys = n_c + min(Tn, t0 + 16 * QB);
   const float* Kb = Kx + (int64_t)m * cap * D;
   const float* Vb = V + (int64_t)m * cap * D;
@@ -178,21 +190,31 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
 
 template <int D>
 static void attn_f32_launch(const Dims& Dm, const float* q, const float* Kx, const float* V, float* out, int T, int n_c,
-                            float scale, hipStream_t st, const HeadLens& hl) {
+                            float scale, hipStream_t st, const HeadLens& hl, const SelectArgs* sel) {
   const float c_log2 = scale * 1.4426950408889634f;
-  if ((int64_t)((T + 31) / 32) * Dm.h >= 256)
-    hipLaunchKernelGGL((attn_f32_kernel<D, 2>), dim3((T + 31) / 32, Dm.h), dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g,
-                       Dm.cap, n_c, c_log2, hl);
+  const SelectArgs sa = sel ? *sel : SelectArgs{};
+  const int n_sel = sel ? Dm.h_kv : 0;
+  const bool two = (int64_t)((T + 31) / 32) * Dm.h >= 256;
+  const int n_ttiles = two ? (T + 31) / 32 : (T + 15) / 16;
+  const dim3 grid((unsigned)(n_sel + n_ttiles * Dm.h));
+  if (two)
+    hipLaunchKernelGGL((attn_f32_kernel<D, 2>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2,
+                       hl, n_ttiles, sa, n_sel);
   else
-    hipLaunchKernelGGL((attn_f32_kernel<D, 1>), dim3((T + 15) / 16, Dm.h), dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g,
-                       Dm.cap, n_c, c_log2, hl);
+    hipLaunchKernelGGL((attn_f32_kernel<D, 1>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2,
+                       hl, n_ttiles, sa, n_sel);
+}
+
+bool attention_f32_fuses_select(const Dims& Dm, int n_cand) {
+  const int wseg = ((n_cand + F32_NW - 1) / F32_NW + 63) & ~63;
+  return !Dm.bf16 && Dm.tune.fuse_select && wseg <= F32_SEL_MAXR * 64;
 }
 
 void launch_attention_f32(const Dims& Dm, const void* q, const void* Kx, const void* V, void* out, int T, int n_c, float scale,
-                          hipStream_t st, const HeadLens& hl) {
+                          hipStream_t st, const HeadLens& hl, const SelectArgs* sel) {
 #define LOCRET_CASE(DD)                                                                                          \
   case DD:                                                                                                       \
-    attn_f32_launch<DD>(Dm, (const float*)q, (const float*)Kx, (const float*)V, (float*)out, T, n_c, scale, st, hl); \
+    attn_f32_launch<DD>(Dm, (const float*)q, (const float*)Kx, (const float*)V, (float*)out, T, n_c, scale, st, hl, sel); \
     break;
   switch (Dm.d) {
     LOCRET_CASE(16)

@@ -162,13 +162,16 @@ void launch_compact_q4(const Dims& D, const CacheBuf& src, const CacheBuf& dst, 
                        int n_keep, const float2* tab, hipStream_t st);
 
 // Attention of T queries (already rotated if rope) over slots [0, n_c+T) of Kx/V, query t seeing
-// slots <= n_c+t (Eq. 1).  bf16 storage: plain VALU kernel; float32 storage: launch_attention_f32.
+// slots <= n_c+t (Eq. 1).  bf16 storage: plain VALU kernel (`sel` must be NULL); float32 storage: launch_attention_f32.
 // n_c_h (every attention launcher): per-head cache lengths, or NULL when all heads hold n_c units.
 void launch_attention_simple(const Dims& D, const void* q, const void* Kx, const void* V, void* out,
-                             int T, int n_c, float scale, hipStream_t st, const HeadLens* n_c_h = nullptr);
+                             int T, int n_c, float scale, hipStream_t st, const HeadLens* n_c_h = nullptr,
+                             const SelectArgs* sel = nullptr);
 // float32 storage (f32_kernels.hip): the launchers above and launch_score_simple below hand over to these.
 void launch_attention_f32(const Dims& D, const void* q, const void* Kx, const void* V, void* out, int T, int n_c, float scale,
-                          hipStream_t st, const HeadLens& n_c_h);
+                          hipStream_t st, const HeadLens& n_c_h, const SelectArgs* sel);
+// True when launch_attention_f32 carries out a selection over n_cand candidates per head inside its launch (pass `sel`).
+bool attention_f32_fuses_select(const Dims& D, int n_cand);
 int score_parts_f32(const Dims& D);
 void launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
                       float* part, hipStream_t st);

@@ -142,10 +142,10 @@ static void attn_simple_dispatch(const Dims& D, const void* q, const void* Kx, c
 }
 
 void launch_attention_simple(const Dims& D, const void* q, const void* Kx, const void* V, void* out, int T,
-                             int n_c, float scale, hipStream_t st, const HeadLens* n_c_h) {
+                             int n_c, float scale, hipStream_t st, const HeadLens* n_c_h, const SelectArgs* sel) {
   const HeadLens hl = head_lens_or_common(n_c_h);
   if (D.bf16) attn_simple_dispatch<bf16_t>(D, q, Kx, V, out, T, n_c, scale, st, hl);
-  else launch_attention_f32(D, q, Kx, V, out, T, n_c, scale, st, hl);
+  else launch_attention_f32(D, q, Kx, V, out, T, n_c, scale, st, hl, sel);
 }
 
 // ------------------------------------------------------------------------------------------------

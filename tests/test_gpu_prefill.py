@@ -373,3 +373,21 @@ def test_selection_inside_attention_at_its_size_limit(n_s):
     K, V, S, P = layer.cache_tensors()
     np.testing.assert_array_equal(P[0].cpu().numpy(), o.P[0])
     layer.close()
+
+
+@pytest.mark.parametrize("n_s", [12, 11], ids=["fits_the_fused_selection", "one_candidate_too_many"])
+def test_selection_inside_float32_attention_at_its_size_limit(n_s, monkeypatch):
+    # 512 threads of 24 keys: 12288 candidates per head ride in the launch, one more takes the separate kernel.  The scores are the
+    # layer's own (the selection sums their partials); a context without the fusion gives the same bits throughout.
+    w = synth.tiny(name=f"f32_sel_limit_{n_s}", dtype="f32", h=2, h_kv=2, d=16, N=6 * 2300, B=2300, b=10000, n_s=n_s, d_R=128)
+    layer, W1, W2 = make_layer(w)
+    monkeypatch.setenv("LOCRET_FUSE_SELECT", "0")
+    plain, _, _ = make_layer(w)
+    for c in range(6):
+        x = [dev(t, w) for t in synth.chunk(w, c)]
+        for a, b in zip(layer.prefill_chunk(*x, w.n_s), plain.prefill_chunk(*x, w.n_s)):
+            np.testing.assert_array_equal(a.cpu().numpy()[:, :min((c + 1) * w.B, w.b)], b.cpu().numpy()[:, :min((c + 1) * w.B, w.b)])
+    for a, b in zip(layer.cache_tensors(), plain.cache_tensors()):
+        np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
+    layer.close()
+    plain.close()
