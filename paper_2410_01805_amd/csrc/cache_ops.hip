@@ -179,10 +179,94 @@ __global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, co
   }
 }
 
+// Rows of 96 bf16, whose halves are not whole 128-byte lines: a thread owns one 16-byte piece of the row
+// instead of a rotary pair of pieces, and fetches the partner piece of K as well (a line its neighbours have just
+// fetched).  A wavefront then stores 1 KB in a row; in pairs of pieces it stores runs of half a row, which end inside
+// lines.  (32 heads x 96: append of 4096 tokens 36 -> 32 us, compaction of 8192 units 70 -> 58 us.  Rows of 64 dims,
+// whose halves are half a line, gain nothing from it: append of 2048 tokens on 8 heads 5.3 against 5.8 us.)
+__device__ __forceinline__ uint4 rotate_piece(uint4 own, uint4 partner, const float2 (&cs)[8], bool low) {
+  Vec16<bf16_t> x, y, r;
+  x.raw = own;
+  y.raw = partner;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    r.set(i, low ? x.get(i) * cs[i].x - y.get(i) * cs[i].y : x.get(i) * cs[i].x + y.get(i) * cs[i].y);
+  return r.raw;
+}
+
+template <bool RAGGED>
+__global__ __launch_bounds__(256) void append_rows_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int Tn,
+                                                          int n_c_common, int seen, int h_kv, int d, int cap,
+                                                          bf16_t* __restrict__ Kc, bf16_t* __restrict__ Vc,
+                                                          bf16_t* __restrict__ Krc, int32_t* __restrict__ Pc,
+                                                          const float2* __restrict__ tab, int rope, int hpb,
+                                                          float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h) {
+  constexpr int HB = 2;
+  const int half = d / 2, ppr = d / 8, rows = 256 / ppr;       // pieces of a row, tokens per workgroup
+  const int lr = (int)threadIdx.x / ppr, piece = (int)threadIdx.x % ppr;
+  const int t = (int)blockIdx.x * rows + lr;
+  if (lr >= rows || t >= Tn) return;
+  const int off = piece * 8;
+  const bool low = off < half;
+  const int poff = low ? off + half : off - half, coff = low ? off : off - half;
+  float2 cs[8];
+  auto table_row = [&](int n_c) {
+    const float2* tr = tab + (int64_t)(n_c + t) * half + coff;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cs[i] = tr[i];
+  };
+  if (rope && !RAGGED) table_row(n_c_common);
+  const int m_lo = (int)blockIdx.y * hpb, m_hi = min(h_kv, m_lo + hpb);
+  for (int m0 = m_lo; m0 < m_hi; m0 += HB) {
+    uint4 kx[HB], ky[HB], vx[HB];
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const int64_t row = ((int64_t)t * h_kv + min(m0 + u, m_hi - 1)) * d;    // a spare head repeats the last one (not stored)
+      kx[u] = *(const uint4*)(k + row + off);
+      ky[u] = *(const uint4*)(k + row + poff);
+      vx[u] = *(const uint4*)(v + row + off);
+    }
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const int m = m0 + u;
+      if (m >= m_hi) break;
+      const int n_c = RAGGED ? n_c_h.v[m] : n_c_common;
+      const int64_t slot = (int64_t)m * cap + n_c + t, drow = slot * d;
+      *(uint4*)(Vc + drow + off) = vx[u];
+      if (rope) {
+        if (RAGGED) table_row(n_c);
+        *(uint4*)(Krc + drow + off) = rotate_piece(kx[u], ky[u], cs, low);
+        nt_store16(Kc + drow + off, kx[u]);
+      } else {
+        *(uint4*)(Kc + drow + off) = kx[u];
+      }
+      if (piece == 0) {
+        Pc[slot] = seen + t;
+        if (S_src) S[slot] = S_src[(int64_t)m * Tn + t];
+      }
+    }
+  }
+}
+
+// storage and head dim of the kernels above and below
+static bool row_pieces(const Dims& D) { return D.bf16 && D.d == 96; }
+
 void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c, int64_t seen,
                    const CacheBuf& c, void* qr, const float2* tab, hipStream_t st, const float* scores,
                    const HeadLens* n_c_h) {
   const HeadLens hl = head_lens_or_common(n_c_h);
+  if (row_pieces(D) && q == nullptr) {
+    const int rows = 256 / (D.d / 8), gx = (T + rows - 1) / rows;
+    int hpb = D.h_kv;
+    while (hpb > 2 && (int64_t)gx * ((D.h_kv + hpb - 1) / hpb) < 768) hpb = (hpb + 1) / 2;
+    const dim3 grid((unsigned)gx, (unsigned)((D.h_kv + hpb - 1) / hpb));
+#define LOCRET_APPEND_ROWS(RG)                                                                                           \
+  launch_kernel((append_rows_kernel<RG>), grid, dim3(256), 0, st, (const bf16_t*)k, (const bf16_t*)v, T, n_c, (int)seen,   \
+                D.h_kv, D.d, D.cap, (bf16_t*)c.K, (bf16_t*)c.V, (bf16_t*)c.Kr, c.P, tab, D.rope, hpb, c.S, scores, hl)
+    if (hl.ragged) LOCRET_APPEND_ROWS(true); else LOCRET_APPEND_ROWS(false);
+#undef LOCRET_APPEND_ROWS
+    return;
+  }
   const int vec = D.bf16 ? 8 : 4;
   const int tpr = (D.d / 2) / vec;
   const int rows = 256 / tpr;
@@ -280,13 +364,82 @@ __global__ __launch_bounds__(256) void compact_kernel(const T* __restrict__ Ks, 
   }
 }
 
+template <int HB, bool RAGGED>
+__global__ __launch_bounds__(256) void compact_rows_kernel(const bf16_t* __restrict__ Ks, const bf16_t* __restrict__ Vs,
+                                                           const float* __restrict__ Ss, const int32_t* __restrict__ Ps,
+                                                           bf16_t* __restrict__ Kd, bf16_t* __restrict__ Vd,
+                                                           bf16_t* __restrict__ Krd, float* __restrict__ Sd,
+                                                           int32_t* __restrict__ Pd, const int32_t* __restrict__ kept,
+                                                           int kept_stride, int n_keep, int h_kv, int d, int cap,
+                                                           const float2* __restrict__ tab, int rope, int hpb,
+                                                           HeadLens keep_h) {
+  const int half = d / 2, ppr = d / 8, rows = 256 / ppr;
+  const int lr = (int)threadIdx.x / ppr, piece = (int)threadIdx.x % ppr;
+  const int r = (int)blockIdx.x * rows + lr;
+  if (lr >= rows || r >= n_keep) return;
+  const int off = piece * 8;
+  const bool low = off < half;
+  const int poff = low ? off + half : off - half;
+  float2 cs[8];
+  if (rope) {
+    const float2* tr = tab + (int64_t)r * half + (low ? off : off - half);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cs[i] = tr[i];
+  }
+  const int m_lo = blockIdx.y * hpb, m_hi = min(h_kv, m_lo + hpb);
+  for (int m0 = m_lo; m0 < m_hi; m0 += HB) {
+    int src[HB];
+    uint4 kx[HB], ky[HB], vx[HB];
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const int m = min(m0 + u, m_hi - 1);          // spare iterations repeat the last head (stores are skipped)
+      if (RAGGED) src[u] = r < keep_h.v[m] ? kept[(int64_t)m * kept_stride + r] : 0;   // row 0: a valid address
+      else src[u] = kept[(int64_t)m * kept_stride + r];
+    }
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const int64_t srow = ((int64_t)min(m0 + u, m_hi - 1) * cap + src[u]) * d;
+      kx[u] = *(const uint4*)(Ks + srow + off);
+      if (rope) ky[u] = *(const uint4*)(Ks + srow + poff);
+      vx[u] = nt_load16<uint4>(Vs + srow + off);
+    }
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const int m = m0 + u;
+      if (m >= m_hi) break;
+      if (RAGGED && r >= keep_h.v[m]) continue;
+      const int64_t drow = ((int64_t)m * cap + r) * d;
+      nt_store16(Kd + drow + off, kx[u]);
+      nt_store16(Vd + drow + off, vx[u]);
+      if (rope) nt_store16(Krd + drow + off, rotate_piece(kx[u], ky[u], cs, low));
+      if (piece == 0) {
+        Sd[(int64_t)m * cap + r] = Ss[(int64_t)m * cap + src[u]];
+        Pd[(int64_t)m * cap + r] = Ps[(int64_t)m * cap + src[u]];
+      }
+    }
+  }
+}
+
 void launch_compact(const Dims& D, const CacheBuf& s, const CacheBuf& t, const int32_t* kept, int kept_stride,
                     int n_keep, const float2* tab, hipStream_t st, const HeadLens* keep_h) {
   const HeadLens hl = head_lens_or_common(keep_h);
+  if (n_keep == 0) return;
+  if (row_pieces(D)) {
+    const int rows = 256 / (D.d / 8), gx = (n_keep + rows - 1) / rows;
+    int hpb = D.h_kv;
+    while (hpb > 2 && (int64_t)gx * ((D.h_kv + hpb - 1) / hpb) < 768) hpb = (hpb + 1) / 2;
+    const dim3 grid((unsigned)gx, (unsigned)((D.h_kv + hpb - 1) / hpb));
+#define LOCRET_COMPACT_ROWS(RG)                                                                                          \
+  launch_kernel((compact_rows_kernel<2, RG>), grid, dim3(256), 0, st, (const bf16_t*)s.K, (const bf16_t*)s.V, s.S, s.P,   \
+                (bf16_t*)t.K, (bf16_t*)t.V, (bf16_t*)t.Kr, t.S, t.P, kept, kept_stride, n_keep, D.h_kv, D.d, D.cap, tab,   \
+                D.rope, hpb, hl)
+    if (hl.ragged) LOCRET_COMPACT_ROWS(true); else LOCRET_COMPACT_ROWS(false);
+#undef LOCRET_COMPACT_ROWS
+    return;
+  }
   const int vec = D.bf16 ? 8 : 4;
   const int tpr = (D.d / 2) / vec;
   int64_t threads = (int64_t)n_keep * tpr;
-  if (threads == 0) return;
   // A thread serves `hpb` KV heads (the rotary-table row is read once for all of them); with many heads
   // and a short cache that leaves too few workgroups, so the heads are then split over blockIdx.y.
   // (config 4, 32 heads x 8192 units: 192 workgroups took 85 us, 768 take 57 us)

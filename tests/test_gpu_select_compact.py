@@ -46,6 +46,9 @@ CASES = [
     ("odd_chunks", dict(dtype="bf16", h=4, h_kv=2, d=128, N=5000, B=1100, b=2000, n_s=33), [1, 1100, 7, 64, 65, 1023, 1, 1100, 1100, 538], "specials"),
     ("paper_phi3_row", dict(dtype="bf16", h=2, h_kv=2, d=96, N=20000, B=3072, b=6000, n_s=2500), None, "normal"),
     ("paper_llama_row", dict(dtype="bf16", h=2, h_kv=1, d=128, N=24000, B=1024, b=16384, n_s=2500), None, "normal"),
+    # rows of 96 dims: 21 rows per workgroup, heads in pairs with one left over
+    ("rows_of_96_dims", dict(dtype="bf16", h=5, h_kv=5, d=96, N=852, B=300, b=190, n_s=11), [1, 20, 21, 22, 63, 64, 1, 170, 190, 300], "normal"),
+    ("rows_of_96_dims_norope", dict(dtype="bf16", h=3, h_kv=3, d=96, N=1000, B=250, b=400, n_s=20, rope=False), None, "ties"),
     # more candidates than the register-resident select holds: keys staged in LDS ...
     ("keys_in_lds", dict(dtype="f32", h=1, h_kv=1, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False), None, "ties"),
     # ... and more than LDS holds: keys re-read from global memory in every pass
