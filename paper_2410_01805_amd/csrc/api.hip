@@ -396,14 +396,15 @@ static bool over_budget(const locret_ctx* c, const SelectArgs& a) {
 
 // select + compact on the live copy, whose rows [0, L) are filled; updates the host bookkeeping.
 // select_done: the selection has already been launched (inside the attention launch).
-static void run_evict(locret_ctx* c, const SelectArgs& a, hipStream_t st, bool select_done = false) {
+// keep_done: the caller's list of a step that evicts nothing has been written already.
+static void run_evict(locret_ctx* c, const SelectArgs& a, hipStream_t st, bool select_done = false, bool keep_done = false) {
   const int b = c->cfg.budget;
   CacheBuf A = c->buf(c->cur);
   const bool over = over_budget(c, a);
   c->mark(3, 0, st);
   // a step that evicts nothing has no list to find: the caller's copy, if asked for, is 0, 1, 2, ...
   if (!select_done && over) launch_select(a, c->D.h_kv, st);
-  else if (!select_done && a.kept2) launch_keep_all(a.kept2, a.stride2, c->D.h_kv, a.L, a.L_h, st);
+  else if (!select_done && !keep_done && a.kept2) launch_keep_all(a.kept2, a.stride2, c->D.h_kv, a.L, a.L_h, st);
   c->mark(3, 1, st);
   c->mark(4, 0, st);
   if (over) {
@@ -595,13 +596,17 @@ int locret_evict_compact(locret_ctx* c, const float* chunk_scores, const void* k
   const float2* tab = D.rope ? (const float2*)(c->ws + c->L.tab) : nullptr;
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);
+  const SelectArgs sa = select_args(c, c->n_c + T, n_stab, kept_idx_out);
+  // (the append's threads write the list of a step that evicts nothing while that is at most 16 entries each)
+  const bool keep = !D.kv_bits && !over_budget(c, sa) && sa.L <= 16 * T;
   if (D.kv_bits) {
     launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st);
     launch_score_reduce(chunk_scores, 1, T, D.h_kv, T, A.S, D.cap, c->n_c, nullptr, st, hl);
   } else {
-    launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, chunk_scores, hl);
+    launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, chunk_scores, hl, keep ? kept_idx_out : nullptr,
+                  sa.stride2);
   }
-  run_evict(c, select_args(c, c->n_c + T, n_stab, kept_idx_out), st);
+  run_evict(c, sa, st, false, keep);
   c->seen += T;
   return hipGetLastError() == hipSuccess ? LOCRET_OK : LOCRET_EHIP;
 }

@@ -92,7 +92,14 @@ __device__ __forceinline__ void nt_store16(void* p, R r) {
 // the launch of their own it saves: 48000 tokens in 12 eviction-only steps 538 us with the separate launch, 537 us
 // with one thread per piece, 500 us in this form.  With q != NULL further blocks of blockIdx.y rotate the queries
 // into qr (storage types whose attention kernel does not do it itself).
+// An eviction-only step that evicts nothing has the caller's list 0, 1, 2, ... written here as well (keep), every thread a
+// share of it: a launch of its own for that took 4.2 us
+// (48000 tokens into 8 x 32768 units in 12 steps, 8 of which evict nothing: 499 -> 486 us).
 // K un-rotated is next read by a compaction, long after it has left the caches: its stores do not stay in them.
+__device__ __forceinline__ void keep_all(int32_t* __restrict__ out, int n, int first, int step) {
+  for (int i = first; i < n; i += step) out[i] = i;
+}
+
 template <typename T, bool RAGGED>
 __global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                      const T* __restrict__ v, int Tn, int n_c_common, int seen, int h,
@@ -100,7 +107,8 @@ __global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, co
                                                      T* __restrict__ Vc, T* __restrict__ Krc,
                                                      int32_t* __restrict__ Pc, T* __restrict__ qr,
                                                      const float2* __restrict__ tab, int rope, int hpb, int kv_blocks,
-                                                     float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h) {
+                                                     float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h,
+                                                     int32_t* __restrict__ keep, int keep_stride) {
   constexpr int VEC = Vec16<T>::N;
   typedef Vec16<T> V16;
   typedef decltype(V16().raw) raw_t;
@@ -175,6 +183,7 @@ __global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, co
         Pc[slot] = seen + t;
         if (S_src) S[slot] = S_src[(int64_t)m * Tn + t];
       }
+      if (keep) keep_all(keep + (int64_t)m * keep_stride, n_c + Tn, t * tpr + part, Tn * tpr);
     }
   }
 }
@@ -182,7 +191,7 @@ __global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, co
 // Rows of 96 bf16, whose halves are not whole 128-byte lines: a thread owns one 16-byte piece of the row
 // instead of a rotary pair of pieces, and fetches the partner piece of K as well (a line its neighbours have just
 // fetched).  A wavefront then stores 1 KB in a row; in pairs of pieces it stores runs of half a row, which end inside
-// lines.  (32 heads x 96: append of 4096 tokens 36 -> 32 us, compaction of 8192 units 70 -> 58 us.  Rows of 64 dims,
+// lines.  (32 heads x 96: append of 4096 tokens 36 -> 30 us, compaction of 8192 units 70 -> 58 us.  Rows of 64 dims,
 // whose halves are half a line, gain nothing from it: append of 2048 tokens on 8 heads 5.3 against 5.8 us.)
 __device__ __forceinline__ uint4 rotate_piece(uint4 own, uint4 partner, const float2 (&cs)[8], bool low) {
   Vec16<bf16_t> x, y, r;
@@ -200,7 +209,8 @@ __global__ __launch_bounds__(256) void append_rows_kernel(const bf16_t* __restri
                                                           bf16_t* __restrict__ Kc, bf16_t* __restrict__ Vc,
                                                           bf16_t* __restrict__ Krc, int32_t* __restrict__ Pc,
                                                           const float2* __restrict__ tab, int rope, int hpb,
-                                                          float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h) {
+                                                          float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h,
+                                                          int32_t* __restrict__ keep, int keep_stride) {
   constexpr int HB = 2;
   const int half = d / 2, ppr = d / 8, rows = 256 / ppr;       // pieces of a row, tokens per workgroup
   const int lr = (int)threadIdx.x / ppr, piece = (int)threadIdx.x % ppr;
@@ -244,6 +254,7 @@ __global__ __launch_bounds__(256) void append_rows_kernel(const bf16_t* __restri
         Pc[slot] = seen + t;
         if (S_src) S[slot] = S_src[(int64_t)m * Tn + t];
       }
+      if (keep) keep_all(keep + (int64_t)m * keep_stride, n_c + Tn, t * ppr + piece, Tn * ppr);
     }
   }
 }
@@ -253,7 +264,7 @@ static bool row_pieces(const Dims& D) { return D.bf16 && D.d == 96; }
 
 void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c, int64_t seen,
                    const CacheBuf& c, void* qr, const float2* tab, hipStream_t st, const float* scores,
-                   const HeadLens* n_c_h) {
+                   const HeadLens* n_c_h, int32_t* keep, int keep_stride) {
   const HeadLens hl = head_lens_or_common(n_c_h);
   if (row_pieces(D) && q == nullptr) {
     const int rows = 256 / (D.d / 8), gx = (T + rows - 1) / rows;
@@ -262,7 +273,8 @@ void launch_append(const Dims& D, const void* q, const void* k, const void* v, i
     const dim3 grid((unsigned)gx, (unsigned)((D.h_kv + hpb - 1) / hpb));
 #define LOCRET_APPEND_ROWS(RG)                                                                                           \
   launch_kernel((append_rows_kernel<RG>), grid, dim3(256), 0, st, (const bf16_t*)k, (const bf16_t*)v, T, n_c, (int)seen,   \
-                D.h_kv, D.d, D.cap, (bf16_t*)c.K, (bf16_t*)c.V, (bf16_t*)c.Kr, c.P, tab, D.rope, hpb, c.S, scores, hl)
+                D.h_kv, D.d, D.cap, (bf16_t*)c.K, (bf16_t*)c.V, (bf16_t*)c.Kr, c.P, tab, D.rope, hpb, c.S, scores, hl,      \
+                keep, keep_stride)
     if (hl.ragged) LOCRET_APPEND_ROWS(true); else LOCRET_APPEND_ROWS(false);
 #undef LOCRET_APPEND_ROWS
     return;
@@ -280,7 +292,7 @@ void launch_append(const Dims& D, const void* q, const void* k, const void* v, i
 #define LOCRET_APPEND(TT, RG)                                                                                          \
   launch_kernel((append_kernel<TT, RG>), grid, dim3(256), 0, st, (const TT*)q, (const TT*)k, (const TT*)v, T, n_c,     \
                 (int)seen, D.h, D.h_kv, D.d, D.cap, (TT*)c.K, (TT*)c.V, (TT*)c.Kr, c.P, (TT*)qr, tab, D.rope, hpb,     \
-                kv_blocks, c.S, scores, hl)
+                kv_blocks, c.S, scores, hl, keep, keep_stride)
   if (D.bf16) { if (hl.ragged) LOCRET_APPEND(bf16_t, true); else LOCRET_APPEND(bf16_t, false); }
   else { if (hl.ragged) LOCRET_APPEND(float, true); else LOCRET_APPEND(float, false); }
 #undef LOCRET_APPEND

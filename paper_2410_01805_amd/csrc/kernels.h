@@ -146,9 +146,10 @@ void launch_prep_weights(const Dims& D, int expand, const void* W1, const void* 
 // Append the chunk at slots [n_c, n_c+T) of `c`: K, V copied, Kr = K rotated to n_c+t,
 // P = seen + t; qr [T][h][d] = q rotated to n_c+t (rope only; q may be NULL to skip).
 // scores [h_kv][T], or NULL: the units' scores when the caller has them already.
+// keep [h_kv][keep_stride], or NULL: filled with 0, 1, 2, ... over the units each head then holds.
 void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c,
                    int64_t seen, const CacheBuf& c, void* qr, const float2* tab, hipStream_t st,
-                   const float* scores = nullptr, const HeadLens* n_c_h = nullptr);
+                   const float* scores = nullptr, const HeadLens* n_c_h = nullptr, int32_t* keep = nullptr, int keep_stride = 0);
 
 // 4-bit rows.  Append: quantize the chunk's k, v rows into the packed arrays of `c` at slots [n_c, n_c+T) and write
 // their dequantized values (K rotated to n_c+t) into the staging arrays; P as launch_append.
