@@ -23,11 +23,13 @@
 // original position, and a NaN score when the caller does not score generated tokens).  The merge kernel
 // combines the partials.  For a scored token further workgroups of the first launch form its hidden activations and
 // further ones of the second its scores: with the activations in a launch of their own in front (5 us) and their
-// product in the token's workgroup, a 611-token prompt and 8 scored tokens took 181 us, 145 us in this form, and an
-// unscored token gained too (16 tokens on 32 heads x 8192 units x 96: 407 -> 396 us; 8 x 6144 x 128: 231 -> 227 us).
-// (Requesting the first keys and values in front of the query's rotation, or those of the next iteration before the
-// current one is worked on, costs the fourth workgroup of a CU: 8 x 16384 x 128 337 to 357 us against 360, but
-// 8 x 16384 x 64 280 against 268 and 8 x 6144 x 128 233 against 231.)  A separate append launch cost 15 % of the step.
+// product in the token's workgroup, a 611-token prompt and 8 scored tokens took 181 us, 152 us in this form.
+// The token's own row and the query are requested before anything is computed, and the token's workgroup skips the
+// merge of its empty row slots: 152 -> 145 us there, 16 tokens on 8 x 6144 x 128 units 231 -> 227 us, on
+// 8 x 16384 x 64 268 -> 266 us.  (Requesting the first keys and values there too, or those of the next iteration
+// before the current one is worked on, costs the fourth workgroup of a CU: 8 x 16384 x 128 337 to 357 us against 360, but
+// 8 x 16384 x 64 280 against 268 and 8 x 6144 x 128 233 against 231.)
+// A separate append launch cost 15 % of the step.
 #include <stdlib.h>
 
 #include <type_traits>
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   const T* __restrict__ q = (const T*)tk.q;
   const T* __restrict__ V = (const T*)tk.V;
   const float2* __restrict__ tab = tk.tab;
-  const int g = tk.g, cap = tk.cap, n_splits = SCORED ? tk.n_part : (int)gridDim.x;
+  const int g = tk.g, cap = tk.cap, n_splits = tk.n_part;
   const float c_log2 = tk.c_log2;
   constexpr int VEC = Vec16<T>::N;
   constexpr int LPR = D / VEC;                       // lanes that hold data of one row
@@ -96,12 +98,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
 
   const int split = blockIdx.x, m = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if constexpr (SCORED) {
+  if constexpr (SCORED && std::is_same<T, bf16_t>::value) {
     if (split >= n_splits) {
       const TokenScore& sc = tk.score;
       const int r = ((split - n_splits) * (int)gridDim.y + m) * (DEC_THREADS / 64) + wave;
       if (r < sc.d_R)
-        token_hidden((const bf16_t*)tk.q, (const bf16_t*)tk.k, (const bf16_t*)tk.v, sc.hd, sc.kvd, (const bf16_t*)sc.W1t, sc.K, r, sc.act);
+        token_hidden(q, (const bf16_t*)tk.k, (const bf16_t*)tk.v, sc.hd, sc.kvd, (const bf16_t*)sc.W1t, sc.K, r, sc.act);
       return;
     }
   }
@@ -116,6 +118,33 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   const T* Vb = V + (int64_t)m * cap * D;
   const int off = (act ? sub : 0) * VEC;
 
+  constexpr int BLK = (DEC_THREADS / 64) * DEC_UN * KPW;   // rows per workgroup iteration
+  struct Tile {
+    V16 kf[MM ? 1 : DEC_UN], vf[DEC_UN];
+    bf16x8 ka[NSB][NKS];
+  };
+  // (spare rows re-read the first row)
+  auto load_tile = [&](Tile& t, int kb) __attribute__((always_inline)) {
+    if (MM) {
+      // A operand: lane (row lane % 16 of the 16-row block, k group lane / 16) fetches 16 bytes of that key's row
+      const bf16_t* Kh = (const bf16_t*)Kb;
+#pragma unroll
+      for (int sb = 0; sb < NSB; ++sb) {
+        const int key = kb + wave * WROWS + sb * 16 + (lane & 15);
+        const bf16_t* kr = Kh + (int64_t)(key < k1 ? key : k0) * D + (lane >> 4) * 8;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) t.ka[sb][ks] = *(const bf16x8*)(kr + ks * 32);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < DEC_UN; ++i) {
+      const int key = kb + (wave * DEC_UN + i) * KPW + grp;
+      const int64_t row = (int64_t)(key < k1 ? key : k0) * D + off;
+      if (!MM) t.kf[i].raw = *(const raw_t*)(Kb + row);
+      t.vf[i].raw = *(const raw_t*)(Vb + row);
+    }
+  };
+
   // `tab` non-null: q is un-rotated and takes position n_keys (the slot the token is appended at).  One thread
   // per 16-byte chunk of the G query rows rotates its dims with the partner dims (+- D/2), rounds to the storage
   // type as the rotated query of a chunk is, and leaves the row in LDS for the whole workgroup: every workgroup
@@ -123,22 +152,39 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   // (with every lane rotating for itself the kernel took 26 us instead of 20).
   float qv[G][VEC];
   __shared__ float qs[G * D];
+  constexpr int CPR = D / VEC;                         // chunks per row
+  const int qu = tid / CPR, qoff = (tid % CPR) * VEC;  // the chunk this thread rotates
+  const bool q_thread = tab != nullptr && tid < G * CPR, qlow = qoff < D / 2;
+  V16 qx, qy;
+  float2 qcs[VEC];
+  if (q_thread) {
+    const T* qr = q + (int64_t)(m * g + min(g0 + qu, g - 1)) * D;
+    qx.raw = *(const raw_t*)(qr + qoff);
+    qy.raw = *(const raw_t*)(qr + (qlow ? qoff + D / 2 : qoff - D / 2));
+    const float2* tr = tab + (int64_t)n_keys * (D / 2) + (qlow ? qoff : qoff - D / 2);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) qcs[e] = tr[e];
+  }
+  // the new token's own row, in its workgroup (last of the head); 4-bit rows are read by the quantizer instead
+  const bool token_wg = split == n_splits - 1;
+  const bool token_row = token_wg && tid < D && tk.Kq == nullptr;
+  const bool klow = tid < D / 2;
+  T k_own, k_pair, v_own;
+  float2 k_cs;
+  if (token_row) {
+    const T* kp = (const T*)tk.k + (int64_t)m * D;
+    k_own = kp[tid];
+    k_pair = kp[klow ? tid + D / 2 : tid - D / 2];
+    v_own = ((const T*)tk.v)[(int64_t)m * D + tid];
+    if (tab != nullptr) k_cs = tab[(int64_t)n_keys * (D / 2) + (klow ? tid : tid - D / 2)];
+  }
   if (tab != nullptr) {
-    constexpr int CPR = D / VEC;                       // chunks per row
-    if (tid < G * CPR) {
-      const int u = tid / CPR, offc = (tid % CPR) * VEC;
-      const int j = m * g + min(g0 + u, g - 1);
-      const bool low = offc < D / 2;
-      V16 x, y;
-      x.raw = *(const raw_t*)(q + (int64_t)j * D + offc);
-      y.raw = *(const raw_t*)(q + (int64_t)j * D + (low ? offc + D / 2 : offc - D / 2));
-      const float2* tr = tab + (int64_t)n_keys * (D / 2) + (low ? offc : offc - D / 2);
+    if (q_thread) {
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        const float2 cs = tr[e];
         V16 r;
-        r.set(0, low ? x.get(e) * cs.x - y.get(e) * cs.y : x.get(e) * cs.x + y.get(e) * cs.y);
-        qs[u * D + offc + e] = r.get(0) * c_log2;      // logits in log2 units
+        r.set(0, qlow ? qx.get(e) * qcs[e].x - qy.get(e) * qcs[e].y : qx.get(e) * qcs[e].x + qy.get(e) * qcs[e].y);
+        qs[qu * D + qoff + e] = r.get(0) * c_log2;     // logits in log2 units
       }
     }
     __syncthreads();
@@ -164,6 +210,95 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
       __syncthreads();
     }
   }
+  // ---- the new token (last workgroup of the head): its partial for the G heads, and the append ------------------
+  if (token_wg) {
+    __shared__ float ks[D];                              // its key, rotated to position n_keys and rounded as stored
+    __shared__ float dots[G][DEC_THREADS / 64];
+    __shared__ float vs[D];                              // its value as stored
+    if constexpr (std::is_same<T, bf16_t>::value && (D == 64 || D == 96 || D == 128)) {
+      // 4-bit rows: attention sees the token as the cache holds it, so it is quantized first (wavefront 0 the key,
+      // wavefront 1 the value).  As a launch of its own in front of this kernel that took 6 us a token.
+      if (tk.Kq != nullptr && wave < 2) {
+        constexpr int NP = Q4Lanes<D>::NP;
+        const int p = min(lane, NP - 1);
+        Q4Pieces r = quantize_pieces<D>((const bf16_t*)(wave == 0 ? tk.k : tk.v) + (int64_t)m * D, p, 0);
+        if (wave == 0 && tab != nullptr) {
+          float2 cs[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) cs[e] = tab[(int64_t)n_keys * (D / 2) + 8 * p + e];
+          r.rotate(cs);
+        }
+        if (lane < NP) {
+          const q4_u32x4 ra = pack8_bf16(r.a), rb = pack8_bf16(r.b);
+          if (g0 == 0) {                                 // one launch per step appends
+            const int64_t slot = (int64_t)m * cap + n_keys;
+            store_pieces<D>(r, (wave == 0 ? tk.Kq : tk.Vq) + slot * tk.qstride, p);
+            bf16_t* st = (bf16_t*)(wave == 0 ? tk.Kr : tk.V) + slot * D;
+            *(q4_u32x4*)(st + 8 * p) = ra;
+            *(q4_u32x4*)(st + D / 2 + 8 * p) = rb;
+          }
+          float a[8], b[8];
+          unpack8_bf16(ra, a);
+          unpack8_bf16(rb, b);
+          float* dst = wave == 0 ? ks : vs;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { dst[8 * p + e] = a[e]; dst[D / 2 + 8 * p + e] = b[e]; }
+        }
+      }
+    }
+    if (g0 == 0 && tid == 0) {
+      tk.P[(int64_t)m * cap + n_keys] = tk.seen;
+      if (tk.mark_unscored) tk.S[(int64_t)m * cap + n_keys] = __uint_as_float(0x7fc00000u);   // NaN: ranks last
+    }
+    if (token_row) {
+      float ke = Elem<T>::ld(&k_own);
+      if (tab != nullptr) {
+        const float kpar = Elem<T>::ld(&k_pair);
+        T rounded;
+        Elem<T>::st(&rounded, klow ? ke * k_cs.x - kpar * k_cs.y : ke * k_cs.x + kpar * k_cs.y);
+        ke = Elem<T>::ld(&rounded);
+      }
+      ks[tid] = ke;
+      vs[tid] = Elem<T>::ld(&v_own);
+      if (g0 == 0) {
+        const int64_t row = ((int64_t)m * cap + n_keys) * D + tid;
+        ((T*)tk.K)[row] = k_own;
+        ((T*)tk.V)[row] = v_own;
+        if (tab != nullptr) Elem<T>::st((T*)tk.Kr + row, ke);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      float pr = 0.f;
+      if (tid < D) {
+        const int j = m * g + min(g0 + u, g - 1);
+        const float qe = tab != nullptr ? qs[u * D + tid] : Elem<T>::ld(q + (int64_t)j * D + tid) * c_log2;
+        pr = qe * ks[tid];
+      }
+#pragma unroll
+      for (int x = 32; x >= 1; x >>= 1) pr += __shfl_xor(pr, x, 64);
+      if (lane == 0) dots[u][wave] = pr;
+    }
+    __syncthreads();
+    for (int idx = tid; idx < G * PW; idx += DEC_THREADS) {
+      const int u = idx / PW, e = idx % PW;
+      if (g0 + u >= g) continue;
+      float val;
+      if (e < D) {
+        val = vs[e];
+      } else if (e == D) {
+        val = 0.f;
+        for (int w2 = 0; w2 < (D + 63) / 64; ++w2) val += dots[u][w2];     // the wavefronts that hold dims, in order
+      } else {
+        val = 1.f;
+      }
+      const int j = m * g + g0 + u;
+      part[((int64_t)j * n_splits + n_splits - 1) * PW + e] = val;
+    }
+    return;
+  }
+
   // B operand of S^T = K Q^T: lane (head n = lane % 16, k group lane / 16) holds q[n][32 ks + 8 (lane / 16) .. + 8],
   // scaled, rounded to bf16 (as the chunk kernels round their pre-scaled queries); heads past G are zero
   bf16x8 qb[NKS];
@@ -187,30 +322,10 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     for (int e = 0; e < VEC; ++e) o[u][e] = 0.f;
   }
 
-  constexpr int BLK = (DEC_THREADS / 64) * DEC_UN * KPW;   // rows per workgroup iteration
-  for (int kb = k0; kb < k1; kb += BLK) {
-    V16 kf[MM ? 1 : DEC_UN], vf[DEC_UN];
+  auto attend = [&](const Tile& t, int kb) __attribute__((always_inline)) {
     bool valid[DEC_UN];
-    bf16x8 ka[NSB][NKS];
-    if (MM) {
-      // A operand: lane (row lane % 16 of the 16-row block, k group lane / 16) fetches 16 bytes of that key's row
-      const bf16_t* Kh = (const bf16_t*)Kb;
 #pragma unroll
-      for (int sb = 0; sb < NSB; ++sb) {
-        const int key = kb + wave * WROWS + sb * 16 + (lane & 15);
-        const bf16_t* kr = Kh + (int64_t)(key < k1 ? key : k0) * D + (lane >> 4) * 8;    // spare rows re-read the first row
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) ka[sb][ks] = *(const bf16x8*)(kr + ks * 32);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < DEC_UN; ++i) {
-      const int key = kb + (wave * DEC_UN + i) * KPW + grp;
-      valid[i] = key < k1;
-      const int64_t row = (int64_t)(valid[i] ? key : k0) * D + off;   // spare slots re-read the first row
-      if (!MM) kf[i].raw = *(const raw_t*)(Kb + row);
-      vf[i].raw = *(const raw_t*)(Vb + row);
-    }
+    for (int i = 0; i < DEC_UN; ++i) valid[i] = kb + (wave * DEC_UN + i) * KPW + grp < k1;
     float s[DEC_UN][G];
     if (MM) {
       typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -219,7 +334,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
       for (int sb = 0; sb < NSB; ++sb) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[sb][ks], qb[ks], acc, 0, 0, 0);
+        for (int ks = 0; ks < NKS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.ka[sb][ks], qb[ks], acc, 0, 0, 0);
         // the lane holds rows 4 (lane / 16) + r of the block for head lane % 16
         if ((lane & 15) < G)
 #pragma unroll
@@ -241,7 +356,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
         for (int u = 0; u < G; ++u) {
           float a = 0.f;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) a = fmaf(kf[0 + (MM ? 0 : i)].get(e), qv[u][e], a);
+          for (int e = 0; e < VEC; ++e) a = fmaf(t.kf[0 + (MM ? 0 : i)].get(e), qv[u][e], a);
 #pragma unroll
           for (int x = 1; x < LPRP; x <<= 1) a += __shfl_xor(a, x, 64);
           s[i][u] = valid[i] ? a : -INFINITY;
@@ -278,8 +393,13 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
         const float p = valid[i] ? __builtin_amdgcn_exp2f(s[i][u] - muse[u]) : 0.f;
         lrun[u] += p;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) o[u][e] = fmaf(p, vf[i].get(e), o[u][e]);
+        for (int e = 0; e < VEC; ++e) o[u][e] = fmaf(p, t.vf[i].get(e), o[u][e]);
       }
+  };
+  for (int kb = k0; kb < k1; kb += BLK) {
+    Tile t;
+    load_tile(t, kb);
+    attend(t, kb);
   }
 
   // ---- merge the row slots of the workgroup ----------------------------------------------------
@@ -297,8 +417,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     }
   }
   __syncthreads();
-  const bool token_wg = split == n_splits - 1;
-  for (int idx = tid; idx < G * PW && !token_wg; idx += DEC_THREADS) {
+  for (int idx = tid; idx < G * PW; idx += DEC_THREADS) {
     const int u = idx / PW, e = idx % PW;
     if (g0 + u >= g) continue;
     float M = -INFINITY;
@@ -317,99 +436,6 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     }
     const int j = m * g + g0 + u;
     part[((int64_t)j * n_splits + split) * PW + e] = val;
-  }
-
-  // ---- the new token (last workgroup of the head): its partial for the G heads, and the append ------------------
-  if (!token_wg) return;
-  __shared__ float ks[D];                              // its key, rotated to position n_keys and rounded as stored
-  __shared__ float dots[G][DEC_THREADS / 64];
-  __shared__ float vs[D];                              // its value as stored
-  bool quantized = false;
-  if constexpr (std::is_same<T, bf16_t>::value && (D == 64 || D == 96 || D == 128)) {
-    // 4-bit rows: attention sees the token as the cache holds it, so it is quantized first (wavefront 0 the key,
-    // wavefront 1 the value).  As a launch of its own in front of this kernel that took 6 us a token.
-    quantized = tk.Kq != nullptr;
-    if (quantized && wave < 2) {
-      constexpr int NP = Q4Lanes<D>::NP;
-      const int p = min(lane, NP - 1);
-      Q4Pieces r = quantize_pieces<D>((const bf16_t*)(wave == 0 ? tk.k : tk.v) + (int64_t)m * D, p, 0);
-      if (wave == 0 && tab != nullptr) {
-        float2 cs[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cs[e] = tab[(int64_t)n_keys * (D / 2) + 8 * p + e];
-        r.rotate(cs);
-      }
-      if (lane < NP) {
-        const q4_u32x4 ra = pack8_bf16(r.a), rb = pack8_bf16(r.b);
-        if (g0 == 0) {                                 // one launch per step appends
-          const int64_t slot = (int64_t)m * cap + n_keys;
-          store_pieces<D>(r, (wave == 0 ? tk.Kq : tk.Vq) + slot * tk.qstride, p);
-          bf16_t* st = (bf16_t*)(wave == 0 ? tk.Kr : tk.V) + slot * D;
-          *(q4_u32x4*)(st + 8 * p) = ra;
-          *(q4_u32x4*)(st + D / 2 + 8 * p) = rb;
-        }
-        float a[8], b[8];
-        unpack8_bf16(ra, a);
-        unpack8_bf16(rb, b);
-        float* dst = wave == 0 ? ks : vs;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { dst[8 * p + e] = a[e]; dst[D / 2 + 8 * p + e] = b[e]; }
-      }
-    }
-  }
-  if (g0 == 0 && tid == 0) {
-    tk.P[(int64_t)m * cap + n_keys] = tk.seen;
-    if (tk.mark_unscored) tk.S[(int64_t)m * cap + n_keys] = __uint_as_float(0x7fc00000u);   // NaN: ranks last
-  }
-  if (!quantized && tid < D) {
-    const T* kp = (const T*)tk.k + (int64_t)m * D;
-    float ke = Elem<T>::ld(kp + tid);
-    if (tab != nullptr) {
-      const bool low = tid < D / 2;
-      const float kpar = Elem<T>::ld(kp + (low ? tid + D / 2 : tid - D / 2));
-      const float2 cs = tab[(int64_t)n_keys * (D / 2) + (low ? tid : tid - D / 2)];
-      ke = low ? ke * cs.x - kpar * cs.y : ke * cs.x + kpar * cs.y;
-      T rounded;
-      Elem<T>::st(&rounded, ke);
-      ke = Elem<T>::ld(&rounded);
-    }
-    ks[tid] = ke;
-    vs[tid] = Elem<T>::ld((const T*)tk.v + (int64_t)m * D + tid);
-    if (g0 == 0) {
-      const int64_t row = ((int64_t)m * cap + n_keys) * D + tid;
-      ((T*)tk.K)[row] = kp[tid];
-      ((T*)tk.V)[row] = ((const T*)tk.v)[(int64_t)m * D + tid];
-      if (tab != nullptr) Elem<T>::st((T*)tk.Kr + row, ke);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    float pr = 0.f;
-    if (tid < D) {
-      const int j = m * g + min(g0 + u, g - 1);
-      const float qe = tab != nullptr ? qs[u * D + tid] : Elem<T>::ld(q + (int64_t)j * D + tid) * c_log2;
-      pr = qe * ks[tid];
-    }
-#pragma unroll
-    for (int x = 32; x >= 1; x >>= 1) pr += __shfl_xor(pr, x, 64);
-    if (lane == 0) dots[u][wave] = pr;
-  }
-  __syncthreads();
-  for (int idx = tid; idx < G * PW; idx += DEC_THREADS) {
-    const int u = idx / PW, e = idx % PW;
-    if (g0 + u >= g) continue;
-    float val;
-    if (e < D) {
-      val = vs[e];
-    } else if (e == D) {
-      val = 0.f;
-      for (int w2 = 0; w2 < (D + 63) / 64; ++w2) val += dots[u][w2];     // the wavefronts that hold dims, in order
-    } else {
-      val = 1.f;
-    }
-    const int j = m * g + g0 + u;
-    part[((int64_t)j * n_splits + n_splits - 1) * PW + e] = val;
   }
 }
 
@@ -526,39 +552,31 @@ int decode_max_splits(const Dims& D) {
   return (D.cap + kmin - 1) / kmin + 1;
 }
 
-template <typename T, int DD, int G, bool SCORED>
-static void decode_attn_launch(const T* Kx, int g0, int kpw, float* part, const DecodeToken& tk, dim3 grid, hipStream_t st) {
-  hipLaunchKernelGGL((decode_attn_kernel<T, DD, G, SCORED>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk);
-}
-
-// SCORED: tk.score is set (bf16 storage only)
-template <typename T, int DD, bool SCORED>
+template <typename T, int DD>
 static void decode_launch(const Dims& D, DecodeToken& tk, T* out, float* part, hipStream_t st) {
   const int kpw = decode_keys_per_split(D, tk.n_c);
   const int n_attn = (tk.n_c + kpw - 1) / kpw;   // splits over the units already in the cache (the longest head's)
   const T* Kx = (const T*)(D.rope ? tk.Kr : tk.K);
   const int n_part = n_attn + 1;                          // + the workgroup of the new token
   tk.n_part = n_part;
+  const bool scored = tk.score.act != nullptr;
+  const int per_x = D.h_kv * (DEC_THREADS / 64);          // hidden units of one further column of workgroups
   for (int g0 = 0; g0 < D.g; g0 += 4) {
     const int left = D.g - g0;
-    const dim3 grid(n_part, D.h_kv);
-    if (SCORED && g0 == 0) {
-      // a wavefront per hidden unit in further columns of h_kv workgroups
-      const int per_x = D.h_kv * (DEC_THREADS / 64);
-      const dim3 more(n_part + (D.d_R + per_x - 1) / per_x, D.h_kv);
-      if (left >= 3) decode_attn_launch<T, DD, 4, SCORED>(Kx, g0, kpw, part, tk, more, st);
-      else if (left == 2) decode_attn_launch<T, DD, 2, SCORED>(Kx, g0, kpw, part, tk, more, st);
-      else decode_attn_launch<T, DD, 1, SCORED>(Kx, g0, kpw, part, tk, more, st);
-    } else if (left >= 3) {
-      decode_attn_launch<T, DD, 4, false>(Kx, g0, kpw, part, tk, grid, st);
-    } else if (left == 2) {
-      decode_attn_launch<T, DD, 2, false>(Kx, g0, kpw, part, tk, grid, st);
-    } else {
-      decode_attn_launch<T, DD, 1, false>(Kx, g0, kpw, part, tk, grid, st);
-    }
+    const dim3 grid(n_part + (scored && g0 == 0 ? (D.d_R + per_x - 1) / per_x : 0), D.h_kv);
+#define LOCRET_DEC_ATTN(GG, SC)                                                                                         \
+  hipLaunchKernelGGL((decode_attn_kernel<T, DD, GG, SC>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk)
+    const bool sc = scored && g0 == 0;
+    if (left >= 3) { if (sc) LOCRET_DEC_ATTN(4, true); else LOCRET_DEC_ATTN(4, false); }
+    else if (left == 2) { if (sc) LOCRET_DEC_ATTN(2, true); else LOCRET_DEC_ATTN(2, false); }
+    else { if (sc) LOCRET_DEC_ATTN(1, true); else LOCRET_DEC_ATTN(1, false); }
+#undef LOCRET_DEC_ATTN
   }
-  hipLaunchKernelGGL((decode_merge_kernel<T, SCORED>), dim3(D.h + (SCORED ? D.h_kv : 0)), dim3(DEC_MERGE_THREADS), 0, st,
-                     (const float*)part, n_part, D.d, out, D.h, tk.score, tk.S, D.cap, tk.n_c, tk.n_c_h);
+#define LOCRET_DEC_MERGE(SC)                                                                                              \
+  hipLaunchKernelGGL((decode_merge_kernel<T, SC>), dim3(D.h + (SC ? D.h_kv : 0)), dim3(DEC_MERGE_THREADS), 0, st,          \
+                     (const float*)part, n_part, D.d, out, D.h, tk.score, tk.S, D.cap, tk.n_c, tk.n_c_h)
+  if (scored) LOCRET_DEC_MERGE(true); else LOCRET_DEC_MERGE(false);
+#undef LOCRET_DEC_MERGE
 }
 
 void launch_decode_step(const Dims& D, const void* q, const void* k, const void* v, const CacheBuf& c,
@@ -575,9 +593,8 @@ void launch_decode_step(const Dims& D, const void* q, const void* k, const void*
   tk.n_c_h = head_lens_or_common(n_c_h);
 #define LOCRET_DEC(DD)                                                                  \
   case DD:                                                                              \
-    if (!D.bf16) decode_launch<float, DD, false>(D, tk, (float*)out, part, st);         \
-    else if (score) decode_launch<bf16_t, DD, true>(D, tk, (bf16_t*)out, part, st);     \
-    else decode_launch<bf16_t, DD, false>(D, tk, (bf16_t*)out, part, st);               \
+    if (D.bf16) decode_launch<bf16_t, DD>(D, tk, (bf16_t*)out, part, st);               \
+    else decode_launch<float, DD>(D, tk, (float*)out, part, st);                        \
     break;
   switch (D.d) {
     LOCRET_DEC(16)
