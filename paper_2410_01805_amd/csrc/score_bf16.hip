@@ -438,11 +438,12 @@ int score_parts_bf16(const Dims& D) {
 // slices; chunks of 1024 tokens 32.9 (128-token tiles, 4 slices), 33.3 (64-token tiles), 29.4 (64-token tiles,
 // 2 slices); chunks of 3072 or 4096 tokens are a third slower with 64-token tiles (more LDS traffic per MFMA).
 int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
-                      const float* W2f, float* part, hipStream_t st, float* zpart, size_t zpart_floats) {
+                      const float* W2f, float* part, hipStream_t st, float* zpart, size_t zpart_floats, float* single) {
   if (T == 1 && zpart != nullptr && D.tune.score_nt == 0 && D.tune.score_split < 0) {
     launch_kernel(score_token_kernel, dim3(D.d_R / 4), dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v,
                   D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, D.K, zpart);
-    launch_kernel(score_token_finish_kernel, dim3(D.h_kv), dim3(256), 0, st, (const float*)zpart, D.d_R, W2f, D.h_kv, part);
+    launch_kernel(score_token_finish_kernel, dim3(D.h_kv), dim3(256), 0, st, (const float*)zpart, D.d_R, W2f, D.h_kv,
+                  single ? single : part);
     return 1;
   }
   // Token tile: 64 when 128-token tiles would leave at least half of the 256 CUs without one (T <= 2048 at
@@ -461,6 +462,7 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
     if (n_z < 1) n_z = 1;
   }
   grid.z = n_z;
+  if (single && (n_z > 1 || D.d_R == RT_M)) part = single;
 #define LOCRET_SCORE_LAUNCH(KS, NTT)                                                                                  \
   launch_kernel(score_mfma_kernel<KS, NTT>, grid, dim3(512), 0, st, (const bf16_t*)q, (const bf16_t*)k,                \
                 (const bf16_t*)v, T, D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, W2f, D.K, D.h_kv, part, T,          \

@@ -391,3 +391,18 @@ def test_selection_inside_float32_attention_at_its_size_limit(n_s, monkeypatch):
         np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
     layer.close()
     plain.close()
+
+
+@pytest.mark.parametrize("d_R", [128, 512])
+def test_scores_for_the_caller_alone(d_R):
+    # split contractions and a single hidden block leave one partial, which goes straight to the caller: the same bits as the
+    # scores of a chunk step, whose partials are summed into the cache
+    w = synth.tiny(name="score_alone", dtype="bf16", h=8, h_kv=4, d=128, N=1500, B=1500, b=1500, n_s=1, d_R=d_R)
+    layer, W1, W2 = make_layer(w)
+    q, k, v = synth.tokens(w, 0, 1500)
+    for T in (2, 64, 65, 300, 1500):
+        x = [dev(t[:T], w) for t in (q, k, v)]
+        layer.reset()
+        _, sc, _ = layer.prefill_chunk(*x, 0, evict=False)
+        np.testing.assert_array_equal(layer.score(*x).cpu().numpy(), sc.cpu().numpy(), err_msg=f"T {T}")
+    layer.close()
