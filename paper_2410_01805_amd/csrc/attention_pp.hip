@@ -533,8 +533,9 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
   }
 }
 
-// out[t][j][:] = sum_p w_p O_p / sum_p w_p l_p with w_p = 2^(m_p - max m) over the parts of a cut item; a part whose
-// sum is 0 saw no key of that row.  One workgroup per (donor, 32 dims), its threads as in the attention kernel.
+// out[t][j][:] = sum_p w_p O_p / sum_p w_p l_p with w_p = 2^(m_p - max m) over the parts of a cut item.  A part whose
+// sum is 0 saw no key of that row and is left out: its O is 0, or NaN where a key that the row must not see has a value
+// that is not finite (0 times it).  One workgroup per (donor, 32 dims), its threads as in the attention kernel.
 template <int D>
 __global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* __restrict__ part, bf16_t* __restrict__ out,
                                                                    int Tn, int h, int g, int n_c_common, int hpw, PPOrder order,
@@ -564,7 +565,11 @@ __global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* 
     float4 o[4];
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) o[rq] = op[slot * (NW * NDB * 4 * 64) + rq * 64];
-    const float w = x.y > 0.f ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;     // such a part's O is 0 too
+    const bool seen = x.y != 0.f;                // (a sum that is NaN counts: the row's result is NaN)
+    const float w = seen ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;
+    // (the loads are not put behind a branch: the parts' chains overlap)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) o[rq] = seen ? o[rq] : make_float4(0.f, 0.f, 0.f, 0.f);
     den = fmaf(w, x.y, den);
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {

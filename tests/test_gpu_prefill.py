@@ -170,6 +170,29 @@ def test_items_of_short_chunks_cut_to_the_mean_load(h, h_kv, d, sizes):
     layer.close()
 
 
+@pytest.mark.parametrize("d,n_c,parts,bad", [(128, 552, 4, 30), (96, 552, 4, 30), (64, 488, 3, 30)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_a_part_without_visible_keys_takes_nothing_from_hidden_values(d, n_c, parts, bad, value, monkeypatch):
+    """The last part of every item is a single key tile that begins inside the chunk (slot 576, with 64 dims slot 512), so the first 24
+    tokens see none of its keys.  A value row of a later token in that tile that is not finite stays out of their
+    results: they are the same bits as with a finite one.  The tokens that see it are not finite in any dim."""
+    monkeypatch.setenv("LOCRET_PP_SPLIT", str(parts))
+    w = synth.tiny(name="hidden_values", dtype="bf16", h=8, h_kv=2, d=d, N=n_c + 64, B=n_c, b=2 * n_c, n_s=8, d_R=128)
+    outs = []
+    for bad_value in (None, value):
+        layer, _, _ = make_layer(w)
+        q, k, v = synth.tokens(w, 0, n_c)
+        layer.prefill_chunk(dev(q, w), dev(k, w), dev(v, w), 0, evict=False)
+        q, k, v = (dev(x, w) for x in synth.tokens(w, n_c, n_c + 64))
+        if bad_value is not None:
+            v[bad] = bad_value
+        outs.append(layer.prefill_chunk(q, k, v, 0, evict=False)[0].float().cpu().numpy())
+        layer.close()
+    assert np.isfinite(outs[0]).all()
+    np.testing.assert_array_equal(outs[1][:24], outs[0][:24])
+    assert not np.isfinite(outs[1][bad:]).any()
+
+
 @pytest.mark.parametrize("d", [16, 32, 64, 96, 128])
 def test_float32_attention_at_the_edges_of_its_tiles(d):
     """32 heads x 250 tokens take two query blocks per workgroup, the short chunks one; single tokens, chunks one off a block and
