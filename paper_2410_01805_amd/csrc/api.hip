@@ -523,8 +523,8 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     run_evict(c, sa, st, /*select_done=*/true);
   } else {
     attention(nullptr);
-    // a selection of its own sums the partial scores too, where its form allows
-    scores(evict && over_budget(c, sa) && select_sums_partials(sa.L - sa.n_stab - sa.n_pin) ? &sa : nullptr);
+    // a selection of its own sums the partial scores too
+    scores(evict && over_budget(c, sa) ? &sa : nullptr);
     if (evict) run_evict(c, sa, st);
     else {
       grow(c, T);

@@ -80,7 +80,7 @@ struct SelectArgs {
   int kept_stride;
   int32_t* kept2;       // optional second copy (caller's buffer), or NULL
   int stride2;
-  // Optional first step (register-resident form only, also inside the attention launch): sum the retaining
+  // Optional first step (also inside the attention launch): sum the retaining
   // head's partial scores part[p][m][t], p < n_parts in ascending order, into S_w[m][L - red_T + t] (the rows
   // of S that the selection then reads) and red_out[m][t]; part == NULL: the scores are already in S.
   const float* part;
@@ -243,8 +243,6 @@ void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_s
                    int kept_stride, int32_t* kept2, int stride2, hipStream_t st);
 // The same from a filled SelectArgs (head-wise budgets: L and n_keep are the largest over the heads).
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st);
-// True when launch_select can first sum partial scores (SelectArgs::part) over this many candidates per head.
-bool select_sums_partials(int n_cand);
 // out[m][i] = i for i < L (per head with head-wise budgets): the kept lists of a step that evicts nothing.
 void launch_keep_all(int32_t* out, int stride, int h_kv, int L, const HeadLens& L_h, hipStream_t st);
 

@@ -1,7 +1,8 @@
 // Exact top-k selection over the retaining-head scores of one KV head with the keys held in registers
-// (the body of select_reg_kernel, also run by workgroups of the head_dim-128 attention launch): see
-// select.hip for the method.  NT threads (512 or 1024), MAXR keys per thread, MAXR * 64 * (NT / 64) >= the
-// number of candidates.  smem: select_body_smem_words(NT, REP1) words.
+// (the body of select_reg_kernel, also run by workgroups of the direct-to-LDS bf16 and the float32 attention
+// launches): see select.hip for the method.  NT threads (512 or 1024), MAXR keys per thread in registers.  Without
+// TAIL, MAXR * 64 * (NT / 64) >= the number of candidates; with it, candidates beyond that are read again from
+// memory wherever the body goes over the keys.  smem: select_body_smem_words(NT, REP1) words.
 #pragma once
 #include "device_util.h"
 #include "kernels.h"
@@ -26,8 +27,6 @@ __device__ __forceinline__ HeadSel head_sel(const SelectArgs& a, int m) {
   r.n_pin = min(a.n_pin, r.L - r.n_stab);
   return r;
 }
-
-constexpr int SEL_REP = 32;    // counter replicas per bin of the 8-bit passes of select_kernel (= LDS banks)
 
 // Digits of the register-resident form: 12 + 10 + 10 bits, most significant first.  Score keys share their sign
 // and most exponent bits, so an 8-bit first digit leaves a third of the candidates in the threshold's bin and
@@ -56,10 +55,10 @@ __device__ __forceinline__ uint32_t sum_before(const uint32_t* ws, int wave) {
 // digit (k >> shift) & (NB - 1) in hist[NB][REP] (zero on entry), finds from the top the digit that holds the
 // remaining-th key and updates prefix / remaining.  Returns true when every key of that digit is wanted (the digit
 // holds exactly `remaining` keys): the lower bits then need no pass.  All NT threads call it; scratch: ws[16 + 3],
-// 16-byte aligned, private to the pass.
-template <int MAXR, int NT, int NB, int REP>
+// 16-byte aligned, private to the pass.  tail(f) calls f(round, key) for the thread's rounds that are not in registers.
+template <int MAXR, int NT, int NB, int REP, typename Tail>
 __device__ __forceinline__ bool select_radix_pass(const uint32_t (&k)[MAXR], int nvalid, int shift, uint32_t mask,
-                                                  uint32_t& prefix, uint32_t& remaining, uint32_t* hist, uint32_t* ws) {
+                                                  uint32_t& prefix, uint32_t& remaining, uint32_t* hist, uint32_t* ws, Tail tail) {
   constexpr int NWAVES = NT / 64;
   constexpr int BPT = NB / NT;                 // bins per thread in the scan
   static_assert(NB % NT == 0 && BPT >= 1, "bins per thread");
@@ -68,6 +67,9 @@ __device__ __forceinline__ bool select_radix_pass(const uint32_t (&k)[MAXR], int
 #pragma unroll
   for (int j = 0; j < MAXR; ++j)
     if (j < nvalid && (k[j] & mask) == prefix) atomicAdd(&hist[((k[j] >> shift) & (uint32_t)(NB - 1)) * REP + rep], 1u);
+  tail([&](int j, uint32_t key) {
+    if (j < nvalid && (key & mask) == prefix) atomicAdd(&hist[((key >> shift) & (uint32_t)(NB - 1)) * REP + rep], 1u);
+  });
   __syncthreads();
   // thread t owns bins NB-1 - t BPT - i, i < BPT: ascending thread order = descending digits
   uint32_t c[BPT];
@@ -111,7 +113,7 @@ __device__ __forceinline__ bool select_radix_pass(const uint32_t (&k)[MAXR], int
 }
 
 // REP1: replicas per bin of the first pass (4 where 64 KB of LDS are at hand, else 2)
-template <int MAXR, int NT, int REP1>
+template <int MAXR, int NT, int REP1, bool TAIL = false>
 __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint32_t* smem) {
   static_assert(NT == 512 || NT == 1024, "workgroup sizes of the two callers");
   constexpr int NWAVES = NT / 64;
@@ -139,7 +141,7 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
   const int L = hs.L, n_pin = hs.n_pin;
   const int n_cand = L - hs.n_stab - n_pin;
   const int kk = hs.n_keep - hs.n_stab - n_pin;
-  const int wseg = ((n_cand + NWAVES - 1) / NWAVES + 63) & ~63;     // <= MAXR * 64 (checked by the host)
+  const int wseg = ((n_cand + NWAVES - 1) / NWAVES + 63) & ~63;     // <= MAXR * 64 (checked by the host), or TAIL
   const int w_lo = wave * wseg;
   const int w_hi = min(n_cand, w_lo + wseg);
   const int first = w_lo + lane;
@@ -156,6 +158,22 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
     for (int j = 0; j < MAXR; ++j) k[j] = score_key(f[j]);
   }
 
+  // rounds MAXR, MAXR + 1, ... of this wavefront (TAIL): f(round, key) in groups whose loads are in flight together; f
+  // is called in whole wavefronts, also past the end (round >= nvalid, any key)
+  auto tail = [&](auto f) __attribute__((always_inline)) {
+    if constexpr (TAIL) {
+      constexpr int GRP = 8;
+      const int n_rounds = (w_hi - w_lo + 63) >> 6;
+      for (int j0 = MAXR; j0 < n_rounds; j0 += GRP) {
+        float x[GRP];
+#pragma unroll
+        for (int i = 0; i < GRP; ++i) x[i] = s[min(first + (j0 + i) * 64, n_cand - 1)];
+#pragma unroll
+        for (int i = 0; i < GRP; ++i) f(j0 + i, score_key(x[i]));
+      }
+    }
+  };
+
   uint32_t tau, need_eq;
   if (kk >= n_cand) {
     tau = 0u; need_eq = 0xffffffffu;
@@ -166,9 +184,9 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
     // A pass may end the search early: when the digit it settles on holds exactly the keys still wanted, all
     // keys with that prefix are kept, whatever their lower bits: tau = the prefix with zeros below, every key equal
     // to it kept.  (After the second pass the digit typically holds one key.)
-    bool all = select_radix_pass<MAXR, NT, SEL_NB1, REP1>(k, nvalid, 32 - SEL_BITS1, 0u, prefix, remaining, hist, ws);
-    if (!all) all = select_radix_pass<MAXR, NT, SEL_NB2, SEL_REP2>(k, nvalid, SEL_BITS2, ~0u << (32 - SEL_BITS1), prefix, remaining, hist + H1, ws + 20);
-    if (!all) all = select_radix_pass<MAXR, NT, SEL_NB2, SEL_REP2>(k, nvalid, 0, ~0u << SEL_BITS2, prefix, remaining, hist + H1 + H2, ws + 40);
+    bool all = select_radix_pass<MAXR, NT, SEL_NB1, REP1>(k, nvalid, 32 - SEL_BITS1, 0u, prefix, remaining, hist, ws, tail);
+    if (!all) all = select_radix_pass<MAXR, NT, SEL_NB2, SEL_REP2>(k, nvalid, SEL_BITS2, ~0u << (32 - SEL_BITS1), prefix, remaining, hist + H1, ws + 20, tail);
+    if (!all) all = select_radix_pass<MAXR, NT, SEL_NB2, SEL_REP2>(k, nvalid, 0, ~0u << SEL_BITS2, prefix, remaining, hist + H1 + H2, ws + 40, tail);
     tau = prefix;
     need_eq = remaining;
   }
@@ -181,6 +199,10 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
     tot_gt += __popcll(__ballot(j < nvalid && k[j] > tau));
     my_eq += (j < nvalid && k[j] == tau) ? 1u : 0u;
   }
+  tail([&](int j, uint32_t key) {
+    tot_gt += __popcll(__ballot(j < nvalid && key > tau));
+    my_eq += (j < nvalid && key == tau) ? 1u : 0u;
+  });
   uint32_t tot_eq = my_eq;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) tot_eq += __shfl_xor(tot_eq, o, 64);
@@ -198,9 +220,8 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
     // the common case, decided per wavefront: none of its keys equals tau, so a key is kept iff it is above tau and
     // its place is the count of kept keys before it (the equal keys of earlier wavefronts add a constant)
     uint32_t base = run_gt + min(run_eq, need_eq);
-#pragma unroll
-    for (int j = 0; j < MAXR; ++j) {
-      const bool gt = j < nvalid && k[j] > tau;
+    auto emit = [&](int j, uint32_t key) __attribute__((always_inline)) {
+      const bool gt = j < nvalid && key > tau;
       const uint64_t bg = __ballot(gt);
       if (gt) {
         const uint32_t pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, 0u));
@@ -208,13 +229,15 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
         if (out2) out2[pos] = n_pin + first + j * 64;
       }
       base += __popcll(bg);
-    }
+    };
+#pragma unroll
+    for (int j = 0; j < MAXR; ++j) emit(j, k[j]);
+    tail(emit);
   } else {
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-#pragma unroll
-    for (int j = 0; j < MAXR; ++j) {
-      const bool gt = j < nvalid && k[j] > tau;
-      const bool eq = j < nvalid && k[j] == tau;
+    auto emit = [&](int j, uint32_t key) __attribute__((always_inline)) {
+      const bool gt = j < nvalid && key > tau;
+      const bool eq = j < nvalid && key == tau;
       const uint64_t bg = __ballot(gt), be = __ballot(eq);
       const uint32_t gt_before = run_gt + __popcll(bg & lt_mask);
       const uint32_t eq_before = run_eq + __popcll(be & lt_mask);
@@ -225,7 +248,10 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
       }
       run_gt += __popcll(bg);
       run_eq += __popcll(be);
-    }
+    };
+#pragma unroll
+    for (int j = 0; j < MAXR; ++j) emit(j, k[j]);
+    tail(emit);
   }
   for (int i = n_cand + tid; i < L - n_pin; i += NT) {
     out[kk + (i - n_cand)] = n_pin + i;

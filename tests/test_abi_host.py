@@ -3,6 +3,8 @@ include/locret.h declares, and turns bad arguments into error codes before touch
 import ctypes as C
 import os
 import re
+import struct
+import subprocess
 
 import pytest
 
@@ -98,3 +100,35 @@ def test_strerror_names_every_code():
     with pytest.raises(B.LocretError) as e:
         B._check(B.LOCRET_ESTATE, "x")
     assert e.value.code == B.LOCRET_ESTATE
+
+
+def _kernels_with_scratch(tmp_path):
+    """{kernel: bytes of scratch memory a lane} of the library's gfx950 code objects, as their own metadata state them."""
+    from paper_2410_01805_amd import build
+    llvm = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC))), "llvm", "bin")
+    if not os.path.exists(os.path.join(llvm, "llvm-readelf")):
+        pytest.skip("no llvm-readelf beside hipcc")
+    fat, code = tmp_path / "fat", tmp_path / "code"
+    subprocess.run([os.path.join(llvm, "llvm-objcopy"), f"--dump-section=.hip_fatbin={fat}", build.LIB, str(tmp_path / "copy")], check=True)
+    raw, magic, found = fat.read_bytes(), b"__CLANG_OFFLOAD_BUNDLE__", {}
+    for at in (m.start() for m in re.finditer(magic, raw)):
+        # a bundle: magic, number of entries, then (offset, size, length of the name, name) of each
+        n, p = struct.unpack_from("<Q", raw, at + len(magic))[0], at + len(magic) + 8
+        for _ in range(n):
+            off, size, ln = struct.unpack_from("<QQQ", raw, p)
+            name = raw[p + 24:p + 24 + ln].decode()
+            p += 24 + ln
+            if not name.endswith("gfx950"):
+                continue
+            code.write_bytes(raw[at + off:at + off + size])
+            notes = subprocess.run([os.path.join(llvm, "llvm-readelf"), "--notes", str(code)], check=True, capture_output=True, text=True).stdout
+            found.update(re.findall(r"\.name: +(_Z\S+)\n +\.private_segment_fixed_size: (\d+)", notes))
+    return {k: int(v) for k, v in found.items()}
+
+
+def test_no_kernel_uses_scratch_memory(tmp_path):
+    # the first launch of a kernel that does has the runtime provide memory for the queue; compute calls never allocate
+    found = _kernels_with_scratch(tmp_path)
+    for part in ("attn_pp_kernel", "attn_f32_kernel", "decode_attn_kernel", "score_mfma_kernel", "select_reg_kernel", "compact_kernel"):
+        assert any(part in k for k in found), part
+    assert {k: v for k, v in found.items() if v} == {}

@@ -89,10 +89,11 @@ def test_evict_compact_bit_exact(name, kw, sizes, kind):
     layer.close()
 
 
-@pytest.mark.parametrize("n_cand", [12288, 12289, 24576, 24577, 36864, 36865, 49152, 49153, 65535, 65536, 65537])
+@pytest.mark.parametrize("n_cand", [12288, 12289, 24576, 24577, 36864, 36865, 45056, 45057, 49152, 49153, 65535, 65536, 65537, 100001])
 def test_select_at_the_edges_of_its_forms(n_cand):
-    """One chunk into an empty cache: n_cand candidates per head, at the most each register-resident form holds and one more
-    (12, 24, 36, 48, 64 keys per thread; beyond them the scores are re-read).  Heads of normal, tied and special scores."""
+    """One chunk into an empty cache: n_cand candidates per head, at the most each form holds in registers and one more
+    (12, 24, 36 keys per thread), and at the edges of the groups of 8 in which what is beyond them is read again (8192
+    candidates).  Heads of normal, tied and special scores."""
     n_s, b, h_kv = 5, n_cand // 3 + 5, 3
     w = synth.tiny(name="sel_edge", dtype="f32", h=h_kv, h_kv=h_kv, d=16, N=n_cand + n_s, B=n_cand + n_s, b=b, n_s=n_s, d_R=64, rope=False)
     layer, W1, W2 = make_layer(w)
