@@ -479,19 +479,25 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     else launch_attention_simple(D, qx, Kx, A.V, attn_out, T, n_c, c->scale, st, hl, sel);
     c->mark(1, 1, st);
   };
-  auto scores = [&](SelectArgs* fused) {
+  // sel: the selection that follows, or NULL.  Its workgroups sum the partial scores themselves where that is the
+  // shorter way (one workgroup per KV head there, the whole chip in the reduction, which is a launch more).
+  auto scores = [&](SelectArgs* sel, bool in_attention) {
     c->mark(2, 0, st);
-    if (fused && !scores_in) {
-      // the selection workgroups of the attention launch sum the partial scores themselves
+    if (sel && !scores_in) {
       int parts = 0;
       run_score(c, q, k, v, T, nullptr, n_c, nullptr, st, /*reduce=*/false, &parts);
-      fused->part = (const float*)(c->ws + c->L.part);
-      fused->n_parts = parts;
-      fused->part_T = T;
-      fused->h_kv = D.h_kv;
-      fused->red_T = T;
-      fused->S_w = A.S;
-      fused->red_out = scores_out;
+      const float* part = (const float*)(c->ws + c->L.part);
+      if (!in_attention ? select_sums_partials(T) : c->mfma_attn ? attention_bf16_sums_partials(parts, T) : attention_f32_sums_partials(D, parts, T)) {
+        sel->part = part;
+        sel->n_parts = parts;
+        sel->part_T = T;
+        sel->h_kv = D.h_kv;
+        sel->red_T = T;
+        sel->S_w = A.S;
+        sel->red_out = scores_out;
+      } else {
+        launch_score_reduce(part, parts, T, D.h_kv, T, A.S, D.cap, n_c, scores_out, st, hl);
+      }
     } else {
       run_score(c, q, k, v, T, scores_in ? nullptr : A.S, n_c, scores_out, st);
       if (scores_in) launch_score_reduce(scores_in, 1, T, D.h_kv, T, A.S, D.cap, n_c, nullptr, st, hl);
@@ -510,7 +516,7 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     fuse_select = c->mfma_attn ? attention_bf16_fuses_select(D, n_cand) : attention_f32_fuses_select(D, n_cand);
   }
   if (evict && c->overlap) {
-    scores(nullptr);
+    scores(nullptr, false);
     ok = ok && hipEventRecord(c->ev_fork, st) == hipSuccess;
     ok = ok && hipStreamWaitEvent(c->side, c->ev_fork, 0) == hipSuccess;
     run_evict(c, sa, c->side);
@@ -518,13 +524,12 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     attention(nullptr);
     ok = ok && hipStreamWaitEvent(st, c->ev_join, 0) == hipSuccess;
   } else if (fuse_select) {
-    scores(&sa);
+    scores(&sa, true);
     attention(&sa);
     run_evict(c, sa, st, /*select_done=*/true);
   } else {
     attention(nullptr);
-    // a selection of its own sums the partial scores too
-    scores(evict && over_budget(c, sa) ? &sa : nullptr);
+    scores(evict && over_budget(c, sa) ? &sa : nullptr, false);
     if (evict) run_evict(c, sa, st);
     else {
       grow(c, T);

@@ -676,6 +676,11 @@ bool attention_pp_fuses_select(const Dims& Dm, int n_cand) {
   return wseg <= PP_SEL_MAXR * 64;
 }
 
+// The selection's workgroups sum the partials as long as that hides behind the attention: a thread walks n_parts partials for
+// each of its tokens.  A step with 8 KV heads, summed there or reduced before it: T = 3072, 64 partials (384 a thread): 128 dims
+// 458.5, 475.5 us, 64 dims 272.5, 282.4; T = 4096, 64 partials (512 a thread): 128 dims 658.5, 629.8 us, 64 dims 385.1, 366.7.
+bool attention_bf16_sums_partials(int n_parts, int T) { return (T + PP_NW * 64 - 1) / (PP_NW * 64) * n_parts <= 384; }
+
 // `sel` non-null (and attention_pp_fuses_select true): the launch also performs that selection.
 bool launch_attention_bf16_pp(const Dims& Dm, LaunchTimer tm, const void* q, const float2* tab, const void* Kx, const void* V, void* out,
                               int T, int n_c, float scale, hipStream_t st, const SelectArgs* sel,

@@ -210,6 +210,14 @@ bool attention_f32_fuses_select(const Dims& Dm, int n_cand) {
   return !Dm.bf16 && Dm.tune.fuse_select && wseg <= F32_SEL_MAXR * 64;
 }
 
+// As long as the sum hides behind the attention, which takes about the longer the more dims there are (a thread walks n_parts
+// partials for each of its tokens).  A step with 2 KV heads, summed there or reduced before it: 16 dims, T = 1024: 16 partials 43.8,
+// 48.8 us, 64 partials 94.3, 89.1, 256 partials 293.1, 239.7; 64 dims, T = 2048: 32 partials 281.1, 291.8, 128 partials 629.2, 658.7,
+// 1024 partials 4529, 3995; 128 dims, T = 2048: 64 partials 746, 767.
+bool attention_f32_sums_partials(const Dims& Dm, int n_parts, int T) {
+  return (T + F32_NW * 64 - 1) / (F32_NW * 64) * n_parts <= 4 * Dm.d;
+}
+
 void launch_attention_f32(const Dims& Dm, const void* q, const void* Kx, const void* V, void* out, int T, int n_c, float scale,
                           hipStream_t st, const HeadLens& hl, const SelectArgs* sel) {
 #define LOCRET_CASE(DD)                                                                                          \

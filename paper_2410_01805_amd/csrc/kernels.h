@@ -173,6 +173,8 @@ void launch_attention_f32(const Dims& D, const void* q, const void* Kx, const vo
                           hipStream_t st, const HeadLens& n_c_h, const SelectArgs* sel);
 // True when launch_attention_f32 carries out a selection over n_cand candidates per head inside its launch (pass `sel`).
 bool attention_f32_fuses_select(const Dims& D, int n_cand);
+// True when that selection is also the place to sum n_parts partial scores of T tokens (SelectArgs::part).
+bool attention_f32_sums_partials(const Dims& D, int n_parts, int T);
 int score_parts_f32(const Dims& D);
 void launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
                       float* part, hipStream_t st);
@@ -194,6 +196,7 @@ void launch_attention_bf16(const Dims& D, const void* q, const void* Kx, const v
 // True when launch_attention_bf16 would carry out a selection over n_cand candidates per head inside its
 // own launch (pass `sel`); otherwise the caller launches launch_select itself.
 bool attention_bf16_fuses_select(const Dims& D, int n_cand);
+bool attention_bf16_sums_partials(int n_parts, int T);      // as attention_f32_sums_partials
 // True when launch_attention_bf16 takes un-rotated queries plus the rotary table for these
 // dimensions (the kernel rotates them itself); otherwise it expects rotated queries.
 bool attention_bf16_rotates_q(const Dims& D);
@@ -243,6 +246,8 @@ void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_s
                    int kept_stride, int32_t* kept2, int stride2, hipStream_t st);
 // The same from a filled SelectArgs (head-wise budgets: L and n_keep are the largest over the heads).
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st);
+// True when launch_select is the place to sum partial scores of T tokens (SelectArgs::part).
+bool select_sums_partials(int T);
 // out[m][i] = i for i < L (per head with head-wise budgets): the kept lists of a step that evicts nothing.
 void launch_keep_all(int32_t* out, int stride, int h_kv, int L, const HeadLens& L_h, hipStream_t st);
 

@@ -45,6 +45,13 @@ void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_s
 // keys of a thread
 static int select_reg_rounds(int n_cand) { return ((n_cand + SEL_WAVES - 1) / SEL_WAVES + 63) / 64; }
 
+// One token a thread: the thread's chain of loads is then the one a thread of the reduction has, and its launch (4 us) is
+// saved.  With a second token a thread it is lost again.  A step, selection in a launch of its own, summed there or
+// reduced before it: float32, 2 heads, T = 512: 32 partials 88.0, 89.1 us, 128 partials 199.4, 202.1; T = 1024, 32 partials 144.8,
+// 146.1; T = 1500, 4 partials 159.2, 156.8; T = 2048, 32 partials 306.7, 299.6.  bf16, 8 heads x 64, T = 1024, 32 partials
+// 105.8, 107.0 us; T = 1500, 8 partials 96.3, 95.5; T = 3072, 8 partials 158.8, 155.8, 32 partials 240.0, 226.4.
+bool select_sums_partials(int T) { return T <= SEL_THREADS; }
+
 // The form is chosen for the longest head; every form takes shorter heads as they come.
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st) {
   const int ns = a.n_stab < a.L ? a.n_stab : a.L;

@@ -429,3 +429,31 @@ def test_scores_for_the_caller_alone(d_R):
         _, sc, _ = layer.prefill_chunk(*x, 0, evict=False)
         np.testing.assert_array_equal(layer.score(*x).cpu().numpy(), sc.cpu().numpy(), err_msg=f"T {T}")
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,d,T,d_R", [("bf16", 64, 1024, 512), ("bf16", 64, 1025, 512), ("bf16", 64, 1536, 16384), ("bf16", 64, 1537, 16384),
+                                            ("f32", 16, 512, 4096), ("f32", 16, 513, 4096)])
+def test_partial_scores_are_summed_to_the_same_bits_wherever_that_is_done(dtype, d, T, d_R, monkeypatch):
+    """Partials on either side of what the selection workgroups of the attention launches sum (384 or 4 d terms a thread) and,
+    without the fusion, of what the selection's own launch does (1024 tokens); the reduction launch does the rest.  The scores of
+    locret_score always come from the reduction."""
+    w = synth.tiny(name="sum_place", dtype=dtype, h=2, h_kv=1, d=d, N=3 * T, B=T, b=T + 300, n_s=20, d_R=d_R)
+    fused, _, _ = make_layer(w)
+    monkeypatch.setenv("LOCRET_FUSE_SELECT", "0")
+    plain, _, _ = make_layer(w)
+    S_ref = np.empty(0, np.float32)
+    for c in range(3):
+        x = [dev(t, w) for t in synth.chunk(w, c)]
+        sc_ref = fused.score(*x).cpu().numpy()
+        S_cat = np.concatenate([S_ref, sc_ref[0]])
+        n_keep = min(len(S_cat), w.b)
+        kept = []
+        for layer in (fused, plain):
+            _, sc, k = layer.prefill_chunk(*x, w.n_s)
+            np.testing.assert_array_equal(sc.cpu().numpy(), sc_ref)
+            kept.append(k.cpu().numpy()[0, :n_keep])
+        np.testing.assert_array_equal(kept[0], kept[1])
+        S_ref = S_cat[kept[0]]
+    for layer in (fused, plain):
+        np.testing.assert_array_equal(layer.cache_tensors()[2][0].cpu().numpy(), S_ref)
+        layer.close()
