@@ -198,11 +198,11 @@ static void attn_f32_launch(const Dims& Dm, const float* q, const float* Kx, con
   const int n_ttiles = two ? (T + 31) / 32 : (T + 15) / 16;
   const dim3 grid((unsigned)(n_sel + n_ttiles * Dm.h));
   if (two)
-    hipLaunchKernelGGL((attn_f32_kernel<D, 2>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2,
-                       hl, n_ttiles, sa, n_sel);
+    launch_kernel((attn_f32_kernel<D, 2>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2, hl,
+                  n_ttiles, sa, n_sel);
   else
-    hipLaunchKernelGGL((attn_f32_kernel<D, 1>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2,
-                       hl, n_ttiles, sa, n_sel);
+    launch_kernel((attn_f32_kernel<D, 1>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2, hl,
+                  n_ttiles, sa, n_sel);
 }
 
 bool attention_f32_fuses_select(const Dims& Dm, int n_cand) {

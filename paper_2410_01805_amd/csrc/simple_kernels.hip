@@ -127,8 +127,8 @@ static void attn_simple_dispatch(const Dims& D, const void* q, const void* Kx, c
   dim3 grid((Tn + 31) / 32, D.h);
 #define LOCRET_ATTN_CASE(DD)                                                                                    \
   case DD:                                                                                                      \
-    hipLaunchKernelGGL((attn_simple_kernel<T, DD>), grid, dim3(256), 0, st, (const T*)q, (const T*)Kx,          \
-                       (const T*)V, (T*)out, Tn, D.h, D.g, D.cap, n_c, scale, hl);                              \
+    launch_kernel((attn_simple_kernel<T, DD>), grid, dim3(256), 0, st, (const T*)q, (const T*)Kx, (const T*)V,  \
+                  (T*)out, Tn, D.h, D.g, D.cap, n_c, scale, hl);                                                \
     break;
   switch (D.d) {
     LOCRET_ATTN_CASE(16)

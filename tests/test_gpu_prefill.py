@@ -375,6 +375,28 @@ def test_profile_modes():
     layer.close()
 
 
+@pytest.mark.parametrize("dtype,d,d_R,select_rides", [("f32", 64, 128, True), ("f32", 16, 100, True), ("bf16", 32, 128, False), ("bf16", 64, 100, True)])
+def test_stage_times_of_the_other_kernels(dtype, d, d_R, select_rides):
+    """Mode 2 times every stage through its kernels' own dispatches, also on float32 layers, on head dims and on hidden widths that the
+    bf16 matrix-core kernels do not take; a selection that rides in the attention launch is part of its entry."""
+    from paper_2410_01805_amd import binding as B
+    w = synth.tiny(name="stages", dtype=dtype, h=4, h_kv=2, d=d, N=4 * 300, B=300, b=500, n_s=20, d_R=d_R)
+    layer, _, _ = make_layer(w)
+    chunks = [tuple(dev(x, w) for x in synth.chunk(w, c)) for c in range(4)]
+    for q, k, v in chunks:                                # (the first launches of the kernels are not timed)
+        layer.prefill_chunk(q, k, v, w.n_s)
+    layer.reset()
+    B.locret_profile_mode(layer.ctx, 2)
+    B.locret_profile_enable(layer.ctx, 4)
+    for q, k, v in chunks:
+        layer.prefill_chunk(q, k, v, w.n_s)
+    ms, n = B.locret_profile_read(layer.ctx)
+    assert n == 4 and all(0.0 < x < 50.0 for x in (ms[0], ms[1], ms[2], ms[4]))
+    assert ms[3] == 0.0 if select_rides else 0.0 < ms[3] < 50.0
+    B.locret_profile_enable(layer.ctx, 0)
+    layer.close()
+
+
 @pytest.mark.parametrize("n_s", [24, 23], ids=["fits_the_fused_selection", "one_candidate_too_many"])
 def test_selection_inside_attention_at_its_size_limit(n_s):
     # the head_dim-128 attention launch carries the selection while a wavefront's share of the candidates fits
