@@ -18,6 +18,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int F32_NW = 8;                      // wavefronts per workgroup
 
+// Launches number their workgroups through, in rows of at most F32_ROW: one grid dimension of 512-thread workgroups ends at 2^23,
+// which 2^27 tokens of the retaining head (a few milliseconds' work) are beyond.  The last row may be short of workgroups to do.
+constexpr int64_t F32_ROW = 1 << 16;
+static dim3 f32_rows(int64_t n, unsigned z = 1) {
+  return dim3((unsigned)(n < F32_ROW ? n : F32_ROW), (unsigned)((n + F32_ROW - 1) / F32_ROW), z);
+}
+__device__ __forceinline__ int f32_workgroup() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+
 // N consecutive floats (N = 1, 2, 4; 4 N bytes aligned)
 template <int N> __device__ __forceinline__ void load_floats(const float* p, float* x) {
   if constexpr (N == 4) { const float4 v = *(const float4*)p; x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
@@ -49,15 +57,17 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
   constexpr int ROW = D + 2;
   constexpr int RED = F32_NW * 16 * QB * ROW, SEL = select_body_smem_words(F32_NW * 64, 1);
   __shared__ __attribute__((aligned(16))) float smem[RED > SEL ? RED : SEL];
-  if ((int)blockIdx.x < n_sel) {
-    select_reg_body<F32_SEL_MAXR, F32_NW * 64, 1>(sel, blockIdx.x, (uint32_t*)smem);
+  const int wg = f32_workgroup();
+  if (wg < n_sel) {
+    select_reg_body<F32_SEL_MAXR, F32_NW * 64, 1>(sel, wg, (uint32_t*)smem);
     return;
   }
   float (*red)[16 * QB][ROW] = (float (*)[16 * QB][ROW])smem;             // O, max, sum of every wavefront
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, kg = lane >> 4;
-  const int item = (int)blockIdx.x - n_sel, j = item / n_ttiles, m = j / g;
+  const int item = wg - n_sel, j = item / n_ttiles, m = j / g;
+  if (j >= h) return;
   const int n_c = head_len(n_c_h, m, n_c_common);
   const int t0 = (n_ttiles - 1 - item % n_ttiles) * (16 * QB);            // longest key ranges first
   const int n_keys = n_c + min(Tn, t0 + 16 * QB);
@@ -196,7 +206,7 @@ static void attn_f32_launch(const Dims& Dm, const float* q, const float* Kx, con
   const int n_sel = sel ? Dm.h_kv : 0;
   const bool two = (int64_t)((T + 31) / 32) * Dm.h >= 256;
   const int n_ttiles = two ? (T + 31) / 32 : (T + 15) / 16;
-  const dim3 grid((unsigned)(n_sel + n_ttiles * Dm.h));
+  const dim3 grid = f32_rows(n_sel + (int64_t)n_ttiles * Dm.h);
   if (two)
     launch_kernel((attn_f32_kernel<D, 2>), grid, dim3(F32_NW * 64), 0, st, q, Kx, V, out, T, Dm.h, Dm.g, Dm.cap, n_c, c_log2, hl,
                   n_ttiles, sa, n_sel);
@@ -248,7 +258,8 @@ __global__ __launch_bounds__(F32_NW * 64) void score_f32_kernel(const float* __r
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, kg = lane >> 4;
-  const int t0 = blockIdx.x * F32_TB, nb = blockIdx.y, n0 = nb * F32_HB;
+  const int t0 = f32_workgroup() * F32_TB, nb = blockIdx.z, n0 = nb * F32_HB;
+  if (t0 >= Tn) return;
   const int t = min(t0 + i16, Tn - 1);
   const float* wp[4];                          // hidden units past the last repeat it (no weight of W2 is applied to them)
 #pragma unroll
@@ -303,7 +314,7 @@ int score_parts_f32(const Dims& D) { return (D.d_R + F32_HB - 1) / F32_HB; }
 
 void launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
                       float* part, hipStream_t st) {
-  launch_kernel(score_f32_kernel, dim3((T + F32_TB - 1) / F32_TB, (D.d_R + F32_HB - 1) / F32_HB), dim3(F32_NW * 64), 0, st,
+  launch_kernel(score_f32_kernel, f32_rows((T + F32_TB - 1) / F32_TB, (D.d_R + F32_HB - 1) / F32_HB), dim3(F32_NW * 64), 0, st,
                 (const float*)q, (const float*)k, (const float*)v, T, D.h * D.d, D.h_kv * D.d, (const float*)W1t, W2f, D.K, D.d_R,
                 D.h_kv, part, T);
 }

@@ -203,6 +203,34 @@ def test_float32_attention_at_the_edges_of_its_tiles(d):
     layer.close()
 
 
+def test_float32_launches_of_more_than_one_row_of_workgroups():
+    """The float32 launches number their workgroups in rows of 65536: 1024 heads x 2100 tokens are 67586 of them, with the selections of
+    two KV heads in front; 1048613 tokens are 65539 for the retaining head.  Against float64 on some heads, and all scores."""
+    w = synth.tiny(name="f32_rows", dtype="f32", h=1024, h_kv=2, d=16, N=2100, B=2100, b=2000, n_s=20, d_R=64, rope=False)
+    layer, _, _ = make_layer(w)
+    q, k, v = synth.tokens(w, 0, w.N)
+    sc_in = np.random.default_rng(5).standard_normal((2, w.N)).astype(np.float32)
+    out, _, kept = layer.prefill_chunk(dev(q, w), dev(k, w), dev(v, w), w.n_s, scores_in=torch.from_numpy(sc_in).to(DEV), want_scores=False)
+    hidden = torch.ones(w.N, w.N, dtype=torch.bool).triu(1)
+    for j in (0, 1, 511, 512, 992, 993, 1022, 1023):      # (the second row begins with a token tile of head 992)
+        x, kk, vv = (torch.from_numpy(t).double() for t in (q[:, j], k[:, j // 512], v[:, j // 512]))
+        ref = torch.softmax((x @ kk.T / 4.0).masked_fill(hidden, -np.inf), 1) @ vv
+        assert_close(host(out[:, j]), ref.numpy(), "f32", f"head {j}")
+    for m in range(2):
+        order = np.argsort(-sc_in[m, :w.N - w.n_s], kind="stable")[:w.b - w.n_s]
+        np.testing.assert_array_equal(kept[m].cpu().numpy(), np.concatenate([np.sort(order), np.arange(w.N - w.n_s, w.N)]))
+    layer.close()
+    w = synth.tiny(name="f32_score_rows", dtype="f32", h=1, h_kv=1, d=16, N=1 << 20, B=(1 << 20) + 37, b=64, n_s=1, d_R=64, rope=False)
+    layer, W1, W2 = make_layer(w)
+    gen = torch.Generator().manual_seed(3)
+    q, k, v = (torch.randn(w.B, 1, 16, generator=gen) for _ in range(3))
+    sc = layer.score(q.to(DEV), k.to(DEV), v.to(DEV))
+    z = torch.cat([q, k, v], 2)[:, 0].double() @ torch.from_numpy(W1).double()
+    ref = (z * z.sigmoid()) @ torch.from_numpy(W2).double()
+    assert_close(sc.cpu().numpy(), ref.T.numpy(), "f32", "scores")
+    layer.close()
+
+
 @pytest.mark.parametrize("n_z", ["0", "2", "5", "8"])
 def test_contraction_split_of_the_retaining_head(n_z, monkeypatch):
     # short chunks give the retaining head too few tiles for the CUs; the launcher then slices the
