@@ -702,7 +702,8 @@ bool launch_attention_bf16_pp(const Dims& Dm, LaunchTimer tm, const void* q, con
   order.n_ttiles = n_ttiles;
   order.gph = g / hpw;
   order.n_sel = n_sel;
-  order.spread = (hl.ragged && Dm.tune.pp_spread != 0) || Dm.tune.pp_spread == 1;
+  // (equal lengths take the spread order only when told to, and the order lists MAX_HEAD_BUDGETS heads)
+  order.spread = (hl.ragged && Dm.tune.pp_spread != 0) || (Dm.tune.pp_spread == 1 && Dm.h_kv <= MAX_HEAD_BUDGETS);
   order.heads = longest_first(hl, Dm.h_kv);
   const PPCut cut = plan_cut(Dm, order, hl, T, n_c, TW, split_part ? split_floats : 0);
   const bool parted = cut.n_donors > 0;

@@ -199,6 +199,22 @@ def test_short_chunk_on_long_caches_with_head_budgets(tail):
     layer.close()
 
 
+@pytest.mark.parametrize("h_kv", [64, 65])
+def test_spread_order_asked_for_at_the_number_of_heads_it_lists(h_kv, monkeypatch):
+    # the order lists 64 KV heads; with more of them the launch keeps the plain order
+    monkeypatch.setenv("LOCRET_PP_SPREAD", "1")
+    w = synth.tiny(name=f"spread_{h_kv}", dtype="bf16", h=h_kv, h_kv=h_kv, d=64, N=3 * 300, B=300, b=500, n_s=8, d_R=128)
+    layer, W1, W2 = make_layer(w)
+    o = _oracle(w, W1, W2, [w.b] * h_kv)
+    for c in range(w.n_chunks):
+        q, k, v = synth.chunk(w, c)
+        out_ref, sc_ref, kept_ref = o.prefill_chunk(q, k, v, w.n_s)
+        out, _, kept = layer.prefill_chunk(dev(q, w), dev(k, w), dev(v, w), w.n_s, scores_in=torch.from_numpy(sc_ref).to(DEV))
+        assert_close(host(out), out_ref, w.dtype, f"chunk {c} attention", per_row=True)
+        _assert_kept_equal(kept, kept_ref, f"chunk {c}")
+    layer.close()
+
+
 def test_key_split_with_head_budgets(monkeypatch):
     monkeypatch.setenv("LOCRET_PP_SPLIT", "4")         # 8 token tiles x 4 key ranges, dealt over the XCDs longest head first
     w = synth.tiny(**SPREAD)
