@@ -98,7 +98,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
 
   const int split = blockIdx.x, m = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if constexpr (SCORED && std::is_same<T, bf16_t>::value) {
+  static_assert(!SCORED || std::is_same<T, bf16_t>::value, "only bf16 layers' scores are formed here");
+  if constexpr (SCORED) {
     if (split >= n_splits) {
       const TokenScore& sc = tk.score;
       const int r = ((split - n_splits) * (int)gridDim.y + m) * (DEC_THREADS / 64) + wave;
@@ -566,16 +567,29 @@ static void decode_launch(const Dims& D, DecodeToken& tk, T* out, float* part, h
     const dim3 grid(n_part + (scored && g0 == 0 ? (D.d_R + per_x - 1) / per_x : 0), D.h_kv);
 #define LOCRET_DEC_ATTN(GG, SC)                                                                                         \
   hipLaunchKernelGGL((decode_attn_kernel<T, DD, GG, SC>), grid, dim3(DEC_THREADS), 0, st, Kx, g0, kpw, part, tk)
-    const bool sc = scored && g0 == 0;
-    if (left >= 3) { if (sc) LOCRET_DEC_ATTN(4, true); else LOCRET_DEC_ATTN(4, false); }
-    else if (left == 2) { if (sc) LOCRET_DEC_ATTN(2, true); else LOCRET_DEC_ATTN(2, false); }
-    else { if (sc) LOCRET_DEC_ATTN(1, true); else LOCRET_DEC_ATTN(1, false); }
+    if constexpr (std::is_same<T, bf16_t>::value) {       // float32 layers hand over no score to form
+      if (scored && g0 == 0) {
+        if (left >= 3) LOCRET_DEC_ATTN(4, true);
+        else if (left == 2) LOCRET_DEC_ATTN(2, true);
+        else LOCRET_DEC_ATTN(1, true);
+        continue;
+      }
+    }
+    if (left >= 3) LOCRET_DEC_ATTN(4, false);
+    else if (left == 2) LOCRET_DEC_ATTN(2, false);
+    else LOCRET_DEC_ATTN(1, false);
 #undef LOCRET_DEC_ATTN
   }
 #define LOCRET_DEC_MERGE(SC)                                                                                              \
   hipLaunchKernelGGL((decode_merge_kernel<T, SC>), dim3(D.h + (SC ? D.h_kv : 0)), dim3(DEC_MERGE_THREADS), 0, st,          \
                      (const float*)part, n_part, D.d, out, D.h, tk.score, tk.S, D.cap, tk.n_c, tk.n_c_h)
-  if (scored) LOCRET_DEC_MERGE(true); else LOCRET_DEC_MERGE(false);
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    if (scored) {
+      LOCRET_DEC_MERGE(true);
+      return;
+    }
+  }
+  LOCRET_DEC_MERGE(false);
 #undef LOCRET_DEC_MERGE
 }
 

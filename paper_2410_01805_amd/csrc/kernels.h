@@ -241,10 +241,8 @@ void launch_score_reduce(const float* part, int n_parts, int part_stride_T, int 
 
 // Stabilizer-masked top-k per KV head over S[m][0..L): keeps the first n_pin, the last n_stab and the
 // best (n_keep - n_stab - n_pin) of the rest (score desc, index asc); kept[m][0..n_keep) ascending.
-// Requires n_pin + n_stab <= min(L, n_keep).  kept2 (optional, row stride stride2) receives a copy.
-void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_stab, int n_pin, int32_t* kept,
-                   int kept_stride, int32_t* kept2, int stride2, hipStream_t st);
-// The same from a filled SelectArgs (head-wise budgets: L and n_keep are the largest over the heads).
+// Requires n_pin + n_stab <= min(L, n_keep).  kept2 (optional, row stride stride2) receives a copy.  (Head-wise
+// budgets: L and n_keep are the largest over the heads.)
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st);
 // True when launch_select is the place to sum partial scores of T tokens (SelectArgs::part).
 bool select_sums_partials(int T);

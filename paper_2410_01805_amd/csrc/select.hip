@@ -33,15 +33,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_reg_kernel(SelectArgs a) {
   select_reg_body<MAXR, SEL_THREADS, 2, TAIL>(a, blockIdx.x, smem);
 }
 
-void launch_select(const float* S, int cap, int h_kv, int L, int n_keep, int n_stab, int n_pin, int32_t* kept,
-                   int kept_stride, int32_t* kept2, int stride2, hipStream_t st) {
-  SelectArgs a = {S, cap, L, n_keep, n_stab, n_pin, kept, kept_stride, kept2, stride2,
-                  nullptr, 0, 0, 0, 0, nullptr, nullptr};
-  a.L_h.ragged = 0;
-  a.keep_h.ragged = 0;
-  launch_select(a, h_kv, st);
-}
-
 // keys of a thread
 static int select_reg_rounds(int n_cand) { return ((n_cand + SEL_WAVES - 1) / SEL_WAVES + 63) / 64; }
 

@@ -12,9 +12,9 @@ namespace locret {
 // Key tiles of 64 slots are staged in LDS; thread (r, c) computes the logits of keys c, c+8, ...
 // with the whole query row in registers, then owns output dims [c*D/8, (c+1)*D/8).
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ q, const T* __restrict__ Kx,
-                                                          const T* __restrict__ V, T* __restrict__ out, int Tn,
+template <int D>
+__global__ __launch_bounds__(256) void attn_simple_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kx,
+                                                          const bf16_t* __restrict__ V, bf16_t* __restrict__ out, int Tn,
                                                           int h, int g, int cap, int n_c_common, float scale,
                                                           HeadLens n_c_h) {
   constexpr int KT = (D > 64) ? 32 : 64;   // keeps K, V, P tiles under 64 KB of LDS
@@ -39,17 +39,17 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
 
   float qreg[D];
   {
-    const T* qp = q + ((int64_t)(row_ok ? t : t_last) * h + j) * D;
+    const bf16_t* qp = q + ((int64_t)(row_ok ? t : t_last) * h + j) * D;
 #pragma unroll
-    for (int e = 0; e < D; ++e) qreg[e] = Elem<T>::ld(qp + e) * scale;
+    for (int e = 0; e < D; ++e) qreg[e] = bf2f(qp[e]) * scale;
   }
   float acc[DC];
 #pragma unroll
   for (int e = 0; e < DC; ++e) acc[e] = 0.f;
   float mrun = -INFINITY, lrun = 0.f;
 
-  const T* Kb = Kx + (int64_t)m * cap * D;
-  const T* Vb = V + (int64_t)m * cap * D;
+  const bf16_t* Kb = Kx + (int64_t)m * cap * D;
+  const bf16_t* Vb = V + (int64_t)m * cap * D;
 
   for (int k0 = 0; k0 < n_keys; k0 += KT) {
     __syncthreads();
@@ -58,8 +58,8 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
       int slot = k0 + kk;
       float kv = 0.f, vv = 0.f;
       if (slot < n_keys) {
-        kv = Elem<T>::ld(Kb + (int64_t)slot * D + e);
-        vv = Elem<T>::ld(Vb + (int64_t)slot * D + e);
+        kv = bf2f(Kb[(int64_t)slot * D + e]);
+        vv = bf2f(Vb[(int64_t)slot * D + e]);
       }
       Ks[kk * DP + e] = kv;
       Vs[kk * DP + e] = vv;
@@ -114,21 +114,20 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* __restrict__ 
     }
   }
   if (row_ok) {
-    T* op = out + ((int64_t)t * h + j) * D + c * DC;
+    bf16_t* op = out + ((int64_t)t * h + j) * D + c * DC;
     float inv = 1.f / lrun;
 #pragma unroll
-    for (int e = 0; e < DC; ++e) Elem<T>::st(op + e, acc[e] * inv);
+    for (int e = 0; e < DC; ++e) op[e] = f2bf(acc[e] * inv);
   }
 }
 
-template <typename T>
 static void attn_simple_dispatch(const Dims& D, const void* q, const void* Kx, const void* V, void* out, int Tn,
                                  int n_c, float scale, hipStream_t st, const HeadLens& hl) {
   dim3 grid((Tn + 31) / 32, D.h);
 #define LOCRET_ATTN_CASE(DD)                                                                                    \
   case DD:                                                                                                      \
-    launch_kernel((attn_simple_kernel<T, DD>), grid, dim3(256), 0, st, (const T*)q, (const T*)Kx, (const T*)V,  \
-                  (T*)out, Tn, D.h, D.g, D.cap, n_c, scale, hl);                                                \
+    launch_kernel(attn_simple_kernel<DD>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)Kx,          \
+                  (const bf16_t*)V, (bf16_t*)out, Tn, D.h, D.g, D.cap, n_c, scale, hl);                         \
     break;
   switch (D.d) {
     LOCRET_ATTN_CASE(16)
@@ -144,7 +143,7 @@ static void attn_simple_dispatch(const Dims& D, const void* q, const void* Kx, c
 void launch_attention_simple(const Dims& D, const void* q, const void* Kx, const void* V, void* out, int T,
                              int n_c, float scale, hipStream_t st, const HeadLens* n_c_h, const SelectArgs* sel) {
   const HeadLens hl = head_lens_or_common(n_c_h);
-  if (D.bf16) attn_simple_dispatch<bf16_t>(D, q, Kx, V, out, T, n_c, scale, st, hl);
+  if (D.bf16) attn_simple_dispatch(D, q, Kx, V, out, T, n_c, scale, st, hl);
   else launch_attention_f32(D, q, Kx, V, out, T, n_c, scale, st, hl, sel);
 }
 
@@ -156,10 +155,9 @@ void launch_attention_simple(const Dims& D, const void* q, const void* Kx, const
 // ------------------------------------------------------------------------------------------------
 constexpr int SC_TM = 64, SC_TN = 64, SC_TK = 16;
 
-template <typename T>
-__global__ __launch_bounds__(256) void score_simple_kernel(const T* __restrict__ q, const T* __restrict__ k,
-                                                           const T* __restrict__ v, int Tn, int hd, int kvd,
-                                                           const T* __restrict__ W1t, const float* __restrict__ W2f,
+__global__ __launch_bounds__(256) void score_simple_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                           const bf16_t* __restrict__ v, int Tn, int hd, int kvd,
+                                                           const bf16_t* __restrict__ W1t, const float* __restrict__ W2f,
                                                            int K, int d_R, int h_kv, float* __restrict__ part,
                                                            int part_T) {
   __shared__ float As[SC_TK][SC_TM + 4];
@@ -173,7 +171,7 @@ __global__ __launch_bounds__(256) void score_simple_kernel(const T* __restrict__
   float acc[4][4] = {};
   for (int k0 = 0; k0 < K; k0 += SC_TK) {
     // the 16 input columns of this step lie in one of q, k, v (hd and kvd are multiples of 16)
-    const T* src; int cw, c0;
+    const bf16_t* src; int cw, c0;
     if (k0 < hd) { src = q; cw = hd; c0 = k0; }
     else if (k0 < hd + kvd) { src = k; cw = kvd; c0 = k0 - hd; }
     else { src = v; cw = kvd; c0 = k0 - hd - kvd; }
@@ -181,9 +179,9 @@ __global__ __launch_bounds__(256) void score_simple_kernel(const T* __restrict__
     for (int idx = tid; idx < SC_TM * SC_TK; idx += 256) {
       int row = idx / SC_TK, kk = idx % SC_TK;
       int t = t0 + row;
-      As[kk][row] = (t < Tn) ? Elem<T>::ld(src + (int64_t)t * cw + c0 + kk) : 0.f;
+      As[kk][row] = (t < Tn) ? bf2f(src[(int64_t)t * cw + c0 + kk]) : 0.f;
       int n = n0 + row;
-      Bs[kk][row] = (n < d_R) ? Elem<T>::ld(W1t + (int64_t)n * K + k0 + kk) : 0.f;
+      Bs[kk][row] = (n < d_R) ? bf2f(W1t[(int64_t)n * K + k0 + kk]) : 0.f;
     }
     __syncthreads();
 #pragma unroll
@@ -224,7 +222,7 @@ void launch_score_simple(const Dims& D, const void* q, const void* k, const void
     return;
   }
   dim3 grid((T + SC_TM - 1) / SC_TM, (D.d_R + SC_TN - 1) / SC_TN);
-  launch_kernel(score_simple_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, T,
+  launch_kernel(score_simple_kernel, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, T,
                 D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, W2f, D.K, D.d_R, D.h_kv, part, T);
 }
 
