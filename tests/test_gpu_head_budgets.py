@@ -58,10 +58,10 @@ EVICT_CASES = [
      [3000, 1000, 2000, 1300], 777, "specials"),
     ("odd_chunks", dict(dtype="f32", h=3, h_kv=3, d=32, N=3000, B=700, b=900, n_s=33, rope=True),
      [900, 34, 411], 0, "specials"),
-    # the longest head sizes the launch: keys staged in LDS, or re-read from global memory, beside a short head
-    ("keys_in_lds", dict(dtype="f32", h=2, h_kv=2, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False),
+    # the longest head decides the form of the selection: 36 keys a thread, or more of them read again, beside a short head
+    ("36_keys_a_thread", dict(dtype="f32", h=2, h_kv=2, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False),
      [26000, 500], 0, "ties"),
-    ("keys_in_global", dict(dtype="f32", h=2, h_kv=2, d=16, N=50000, B=2000, b=40000, n_s=7, rope=False),
+    ("keys_read_again", dict(dtype="f32", h=2, h_kv=2, d=16, N=50000, B=2000, b=40000, n_s=7, rope=False),
      [700, 40000], 0, "specials"),
 ]
 
@@ -166,9 +166,10 @@ def test_other_launch_orders_with_head_budgets(env, monkeypatch):
     layer.close()
 
 
-# The matrix-core attention kernels deal their workgroups differently when the heads differ in length: every XCD
-# takes every eighth token tile of every head, longest head first, instead of one head per XCD (8 token tiles here:
-# whole rounds of the 8 XCDs; the other streams of this file have tile counts that leave the last round short).  LOCRET_PP_SPREAD (read when the context is created) = 0 keeps one head per XCD, 1 forces the other order.
+# The matrix-core attention kernels deal their workgroups differently when the heads differ in length: the token tiles go
+# round the XCDs head after head, longest head first, instead of one head per XCD (8 token tiles here: whole rounds
+# of the 8 XCDs; the other streams of this file have tile counts that are no multiple of 8).  LOCRET_PP_SPREAD (read when the
+# context is created) = 0 keeps one head per XCD, 1 forces the other order.
 SPREAD = dict(name="hb_spread", dtype="bf16", h=16, h_kv=4, d=128, N=3584, B=512, b=1100, n_s=64, d_R=128)
 
 
@@ -182,8 +183,11 @@ def test_workgroup_orders_of_the_head_dim_128_kernel(spread, budgets, monkeypatc
     layer.close()
 
 
-def test_workgroup_order_of_the_other_head_dims_with_head_budgets():
-    # head_dim 96 (register-staged kernel, 256 tokens per workgroup): 8 token tiles
+@pytest.mark.parametrize("variant", [None, "regstaged"])
+def test_workgroup_order_of_the_other_head_dims_with_head_budgets(variant, monkeypatch):
+    # head_dim 96 (256 tokens per workgroup): 8 token tiles; the register-staged kernel gives every XCD every eighth of them
+    if variant is not None:
+        monkeypatch.setenv("LOCRET_ATTN_VARIANT", variant)
     w = synth.tiny(name="hb_spread_d96", dtype="bf16", h=4, h_kv=4, d=96, N=3 * 2048, B=2048, b=2500, n_s=64, d_R=128)
     layer, o = _run_stream(w, [2500, 300, 1200, 64])
     _assert_caches_equal(layer, o, w)
@@ -276,7 +280,7 @@ def test_equal_head_budgets_give_the_single_budget_results_bit_for_bit():
 @pytest.mark.parametrize("kw,budgets", [STREAMS[0], STREAMS[2], STREAMS[4]],
                          ids=[STREAMS[i][0]["name"] for i in (0, 2, 4)])
 def test_decode_steps_with_head_budgets(kw, budgets):
-    # the decode step appends behind every head's own cache and attends over that head's units only
+    # the decode step appends behind every head's own cache, the token's score included, and attends over that head's units only
     w = synth.tiny(**kw)
     n_dec = 5
     w_pre = synth.tiny(**dict(kw, N=w.N - n_dec))
@@ -290,6 +294,9 @@ def test_decode_steps_with_head_budgets(kw, budgets):
         assert_close(host(out), out_ref, w.dtype, f"{w.name} token {i} attention", per_row=True)
         assert_close(sc.cpu().numpy(), sc_ref[:, 0], w.dtype, f"{w.name} token {i} score")
         assert layer.cache_lens == [n + i + 1 for n in lens0]
+        S = layer.cache_tensors()[2]
+        for m, n in enumerate(lens0):                      # the stored score is the returned one, bit for bit
+            assert S[m, n + i].item() == sc[m].item()
     _assert_caches_equal(layer, o, w, check_scores=False)
     # a later evicting chunk brings every head back to its own budget
     T = w.B - n_dec                                       # what the capacity b + B still takes

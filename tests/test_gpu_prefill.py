@@ -142,8 +142,8 @@ def test_key_split_of_the_head_dim_128_kernel_forced(n_split, monkeypatch):
 
 
 def test_key_split_chosen_for_short_chunks_behind_a_long_cache():
-    # 4 items per launch at 128-token chunks: the launcher splits the keys 8 ways once the cache is long enough
-    # (every range at least 8 key tiles), and not before; the tail pass of Algorithm 1 (evict = 0) as well
+    # 4 items per launch at 128-token chunks: the launcher cuts them along the keys once the cache is long enough, and
+    # not before; the tail pass of Algorithm 1 (evict = 0) as well
     w = synth.tiny(name="short_chunks", dtype="bf16", h=8, h_kv=2, d=128, N=6 * 1024 + 5 * 128 + 100, B=1024, b=4600,
                    n_s=100, d_R=128)
     sizes = [1024] * 6 + [128] * 5 + [100]
@@ -427,9 +427,9 @@ def test_stage_times_of_the_other_kernels(dtype, d, d_R, select_rides):
 
 @pytest.mark.parametrize("n_s", [24, 23], ids=["fits_the_fused_selection", "one_candidate_too_many"])
 def test_selection_inside_attention_at_its_size_limit(n_s):
-    # the head_dim-128 attention launch carries the selection while a wavefront's share of the candidates fits
-    # 48 rounds of 64 (24576 per head); one candidate more and the step launches the separate kernel (here its
-    # keys-in-LDS form).  Same kept indices either way; the oracle only scores and evicts (teacher-forced).
+    # the direct-to-LDS attention launch carries the selection while a wavefront's share of the candidates fits
+    # 48 rounds of 64 (24576 per head); one candidate more and the step launches the separate kernel (here with
+    # 36 keys a thread).  Same kept indices either way; the oracle only scores and evicts (teacher-forced).
     w = synth.tiny(name=f"sel_limit_{n_s}", dtype="bf16", h=4, h_kv=1, d=128, N=6 * 4600, B=4600, b=20000, n_s=n_s,
                    d_R=128)
     layer, W1, W2 = make_layer(w)

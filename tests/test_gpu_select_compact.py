@@ -49,10 +49,10 @@ CASES = [
     # rows of 96 dims: 21 rows per workgroup, heads in pairs with one left over
     ("rows_of_96_dims", dict(dtype="bf16", h=5, h_kv=5, d=96, N=852, B=300, b=190, n_s=11), [1, 20, 21, 22, 63, 64, 1, 170, 190, 300], "normal"),
     ("rows_of_96_dims_norope", dict(dtype="bf16", h=3, h_kv=3, d=96, N=1000, B=250, b=400, n_s=20, rope=False), None, "ties"),
-    # more candidates than the register-resident select holds: keys staged in LDS ...
-    ("keys_in_lds", dict(dtype="f32", h=1, h_kv=1, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False), None, "ties"),
-    # ... and more than LDS holds: keys re-read from global memory in every pass
-    ("keys_in_global", dict(dtype="f32", h=1, h_kv=1, d=16, N=50000, B=2000, b=40000, n_s=7, rope=False), None, "specials"),
+    # the 36-key register form of the selection ...
+    ("36_keys_a_thread", dict(dtype="f32", h=1, h_kv=1, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False), None, "ties"),
+    # ... and more candidates than it holds: the others are read again in every pass
+    ("keys_read_again", dict(dtype="f32", h=1, h_kv=1, d=16, N=50000, B=2000, b=40000, n_s=7, rope=False), None, "specials"),
 ]
 
 
@@ -131,8 +131,8 @@ PIN_CASES = [
     ("pin_one", dict(dtype="bf16", h=2, h_kv=2, d=64, N=5000, B=1000, b=1500, n_s=10), 1, "ties"),
     ("pin_fills_budget", dict(dtype="f32", h=2, h_kv=2, d=16, N=3000, B=300, b=512, n_s=12, rope=False), 500, "normal"),
     ("pin_gt_first_chunk", dict(dtype="bf16", h=2, h_kv=1, d=96, N=6000, B=256, b=2000, n_s=700), 900, "ties"),
-    ("pin_keys_in_lds", dict(dtype="f32", h=1, h_kv=1, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False), 333, "ties"),
-    ("pin_keys_in_global", dict(dtype="f32", h=1, h_kv=1, d=16, N=50000, B=2000, b=40000, n_s=7, rope=False), 64, "specials"),
+    ("pin_36_keys_a_thread", dict(dtype="f32", h=1, h_kv=1, d=16, N=34000, B=2000, b=26000, n_s=100, rope=False), 333, "ties"),
+    ("pin_keys_read_again", dict(dtype="f32", h=1, h_kv=1, d=16, N=50000, B=2000, b=40000, n_s=7, rope=False), 64, "specials"),
 ]
 
 
