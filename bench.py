@@ -275,9 +275,9 @@ def main():
     evict_gbs = by_evict / (evict_ms * 1e-3) / 1e9 if evict_ms > 0 else 0.0
     # in the step as it runs (timed region) only the compaction's own time is exposed: the same bytes over that
     compact_gbs = by_evict / (ms["compact"] * 1e-3) / 1e9 if ms["compact"] > 0 else 0.0
-    # the library carries the selection inside the attention launch for bf16 head dims 128 and 96 while the
-    # candidates of a head fit the register-resident form (24576)
-    sel_fused = fuse_before != "0" and w.dtype == "bf16" and w.d in (96, 128) and (w.b + w.B - w.n_s) <= 24576
+    # the library carries the selection inside the attention launch while the candidates of a head fit the
+    # registers of its workgroups: 24576 on bf16 head dims 64, 96 and 128, 12288 on float32 layers
+    sel_fused = fuse_before != "0" and (w.b + w.B - w.n_s) <= (12288 if w.dtype == "f32" else 24576 if w.d in (64, 96, 128) else 0)
     extra = {
         "stage_ms_per_step": {k: round(v / max(1, n_prof), 4) for k, v in ms.items()},
         "retaining_head": {"achieved": round(mlp_tflops, 2), "unit": "TFLOP/s", "frac": round(mlp_tflops / peak, 4)},
