@@ -507,7 +507,15 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
     float l = l_run + __shfl_xor(l_run, 32, 64);
     if (GENERAL && n_parts > 1) {
       // partial result of this part: O un-normalised, running max (log2 units) and sum; a query that saw no key
-      // leaves sum 0.  The accumulators go out as they lie in the registers, 1 KB in a row per store.
+      // leaves sum 0 and O 0 (its accumulators hold 0, or NaN where a key of the part that it must not see has a value that is
+      // not finite: 0 times it).  The accumulators go out as they lie in the registers, 1 KB in a row per store.
+      if (__any(l == 0.f)) {
+        const bool none = l == 0.f;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[db][r] = none ? 0.f : oacc[db][r];
+      }
       const int64_t slot = (int64_t)layer * cut.n_donors + item;
       float4* op = (float4*)part + (slot * NW + wave) * (NDB * 4 * 64) + lane;
 #pragma unroll
@@ -534,8 +542,8 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
 }
 
 // out[t][j][:] = sum_p w_p O_p / sum_p w_p l_p with w_p = 2^(m_p - max m) over the parts of a cut item.  A part whose
-// sum is 0 saw no key of that row and is left out: its O is 0, or NaN where a key that the row must not see has a value
-// that is not finite (0 times it).  One workgroup per (donor, 32 dims), its threads as in the attention kernel.
+// sum is 0 saw no key of that row (a sum that is NaN makes the row NaN).  One workgroup per (donor, 32 dims), its threads as
+// in the attention kernel.
 template <int D>
 __global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* __restrict__ part, bf16_t* __restrict__ out,
                                                                    int Tn, int h, int g, int n_c_common, int hpw, PPOrder order,
@@ -565,11 +573,7 @@ __global__ __launch_bounds__(PP_NW * 64) void attn_pp_merge_kernel(const float* 
     float4 o[4];
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) o[rq] = op[slot * (NW * NDB * 4 * 64) + rq * 64];
-    const bool seen = x.y != 0.f;                // (a sum that is NaN counts: the row's result is NaN)
-    const float w = seen ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;
-    // (the loads are not put behind a branch: the parts' chains overlap)
-#pragma unroll
-    for (int rq = 0; rq < 4; ++rq) o[rq] = seen ? o[rq] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float w = x.y > 0.f ? __builtin_amdgcn_exp2f(x.x - M) : 0.f;     // such a part's O is 0 too
     den = fmaf(w, x.y, den);
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {
