@@ -487,7 +487,9 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
       int parts = 0;
       run_score(c, q, k, v, T, nullptr, n_c, nullptr, st, /*reduce=*/false, &parts);
       const float* part = (const float*)(c->ws + c->L.part);
-      if (!in_attention ? select_sums_partials(T) : c->mfma_attn ? attention_bf16_sums_partials(parts, T) : attention_f32_sums_partials(D, parts, T)) {
+      const bool sums = !in_attention ? select_sums_partials(T)
+                        : c->mfma_attn ? attention_bf16_sums_partials(parts, T) : attention_f32_sums_partials(D, parts, T);
+      if (sums) {
         sel->part = part;
         sel->n_parts = parts;
         sel->part_T = T;
@@ -607,8 +609,11 @@ int locret_evict_compact(locret_ctx* c, const float* chunk_scores, const void* k
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);
   const SelectArgs sa = select_args(c, c->n_c + T, n_stab, kept_idx_out);
-  // (the append's threads write the list of a step that evicts nothing while that is at most 16 entries each)
-  const bool keep = !D.kv_bits && !over_budget(c, sa) && sa.L <= 16 * T;
+  // The append's threads write the list of a step that evicts nothing up to 16 times as long as the chunk: per head a
+  // thread writes 16 / (threads of a row) entries at most, for every head it serves.  (A step, mean over L = T ... 16 T, with the
+  // list in the append or in a launch of its own: 8 heads x 16 dims, one thread a row, T = 16: 7.6, 9.9 us, T = 4096: 7.1, 9.5;
+  // 32 x 16, T = 4096: 7.7, 9.8; 32 x 96, T = 4096: 21.5, 24.1; 8 x 128, T = 4096: 8.3, 10.1.)
+  const bool keep = !D.kv_bits && !over_budget(c, sa) && sa.L <= (int64_t)16 * T;
   if (D.kv_bits) {
     launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st);
     launch_score_reduce(chunk_scores, 1, T, D.h_kv, T, A.S, D.cap, c->n_c, nullptr, st, hl);

@@ -97,8 +97,9 @@ __device__ __forceinline__ void pp_item(const PPOrder& o, bool spread, int i, in
     // (Measured on 8 heads of 28672 ... 4096 units, mean 16384: 1.61 ms per step with one head
     // per XCD, 1.39 ms with the heads interleaved item by item, 1.14 ms in this order; equal heads 1.07 ms.)
     // Heads follow one another without padding: with every head starting on the first XCD a chunk of one token tile
-    // put all of its items there (32 heads of 96 dims with up to 16278 units, 20439 tokens in chunks of 4047 and 45 more,
-    // which is two such chunks: 3839 us a prompt, 3381 us in this order).
+    // puts all of its items there.  (32 heads of 96 dims with up to 16278 units, 20439 tokens in chunks of 4047 and 45 more,
+    // which is two such chunks: 3381 us a prompt in this order, 3839 us padded; 3486 us before items were cut at the
+    // mean load, when every item of such a chunk was cut into eight equal parts, one for each XCD.)
     const int r = i / o.n_ttiles;                          // rank of the head group, longest first
     hgroup = o.heads.v[r / o.gph] * o.gph + r % o.gph;
     tt = i % o.n_ttiles;

@@ -1,6 +1,6 @@
 // Decode step: attention of ONE new token over the retained cache (Eq. 1 with B = 1; the generate
 // step that closes Algorithm 1).  The work is a single pass over K and V of every KV head, so the
-// kernel is built for HBM bandwidth: no matrix cores, no LDS staging.
+// kernel is built for HBM bandwidth: rows go from memory to registers, not through LDS.
 //
 // Split-K over the key axis: workgroup (split, m) owns DEC_KEYS keys of KV head m and serves the
 // query heads of its group (G at a time).  A key row is spread over LPR lanes (16 bytes per lane,
@@ -26,9 +26,10 @@
 // product in the token's workgroup, a 611-token prompt and 8 scored tokens took 181 us, 152 us in this form.
 // The token's own row and the query are requested before anything is computed, and the token's workgroup skips the
 // merge of its empty row slots: 152 -> 145 us there, 16 tokens on 8 x 6144 x 128 units 231 -> 227 us, on
-// 8 x 16384 x 64 268 -> 266 us.  (Requesting the first keys and values there too, or those of the next iteration
-// before the current one is worked on, costs the fourth workgroup of a CU: 8 x 16384 x 128 337 to 357 us against 360, but
-// 8 x 16384 x 64 280 against 268 and 8 x 6144 x 128 233 against 231.)
+// 8 x 16384 x 64 268 -> 266 us.  (Requesting the first keys and values there too gives 337 us against
+// 360 on 8 x 16384 x 128, but 280 against 268 on 8 x 16384 x 64 and 233 against 231 on 8 x 6144 x 128; requesting those of
+// the next iteration before the current one is worked on 357, and on 64 dims 5 % more.  Why 64 dims lose is not known: it is not
+// the fourth workgroup of a CU that the registers then exclude, a launch has 2.7 a CU.)
 // A separate append launch cost 15 % of the step.
 #include <stdlib.h>
 

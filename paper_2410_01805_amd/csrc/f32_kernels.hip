@@ -5,9 +5,10 @@
 // B[k = lane / 16][j = lane % 16], and leaves C[4 (lane / 16) + r][lane % 16] in register r.  A contraction may run over
 // its terms in any order as long as both operands agree, so every operand is fetched 16 bytes at a time straight
 // from memory: a lane's four consecutive elements feed four instructions.  Nothing is staged in LDS: the wavefronts
-// of a workgroup divide the contraction (attention: the keys) among themselves, so no element is read twice
-// by a workgroup, and meet in LDS at the end.  That also fills the chip at the small sizes float32 layers have: 512 tokens x 8
-// heads are 256 workgroups of 8 wavefronts.
+// of a workgroup divide the contraction (attention: the keys) among themselves, so no element of W1 and of the inputs
+// (attention: of keys and values; every wavefront reads the queries) is read twice by a workgroup, and meet in LDS at the
+// end.  That also fills the chip at the small sizes float32 layers have: 512 tokens x 8 heads are 256 workgroups of 8
+// wavefronts.
 #include "device_util.h"
 #include "kernels.h"
 #include "select_body.h"
