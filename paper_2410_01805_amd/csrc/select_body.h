@@ -112,10 +112,10 @@ __device__ __forceinline__ bool select_radix_pass(const uint32_t (&k)[MAXR], int
   return remaining == ws[18];
 }
 
-// REP1: replicas per bin of the first pass (4 where 64 KB of LDS are at hand, else 2)
+// REP1: replicas per bin of the first pass, by the LDS at hand (4: 64 KB, 2: 32 KB, 1: 16 KB)
 template <int MAXR, int NT, int REP1, bool TAIL = false>
 __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint32_t* smem) {
-  static_assert(NT == 512 || NT == 1024, "workgroup sizes of the two callers");
+  static_assert(NT == 512 || NT == 1024, "workgroup sizes of the callers");
   constexpr int NWAVES = NT / 64;
   // a histogram per pass, all cleared at once beside the loads of the keys: [bins][replicas]
   constexpr int H1 = SEL_NB1 * REP1, H2 = SEL_NB2 * SEL_REP2;
