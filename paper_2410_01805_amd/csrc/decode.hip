@@ -2,20 +2,29 @@
 // step that closes Algorithm 1).  The work is a single pass over K and V of every KV head, so the
 // kernel is built for HBM bandwidth: rows go from memory to registers, not through LDS.
 //
-// Split-K over the key axis: workgroup (split, m) owns DEC_KEYS keys of KV head m and serves the
-// query heads of its group (G at a time).  A key row is spread over LPR lanes (16 bytes per lane,
-// padded to a power of two), so one load instruction of a wavefront fetches 64 / LPRP whole rows,
-// contiguous in memory.  Logits: with bf16 storage and head dims that are multiples of 32 the wavefront's 16
-// (or 32) rows of an iteration form one S^T = K Q^T product on the matrix cores (v_mfma_f32_16x16x32_bf16:
-// rows = keys, fetched from memory straight into the A-operand layout; columns = the G query heads, padded to
-// 16), and the logits reach the lanes that own the rows through 256 bytes of LDS per wavefront; the matrix cores
-// idle most of the time here, but the G dot products per row with their butterflies over the row's lanes were
-// more than half of the vector instructions and kept the kernel from overlapping them with its loads.  Other
-// types: each lane keeps the query values of its own dims for G heads and a logit is G short dot products plus a
-// butterfly over the lanes of the row.  Either way the lanes of a row then share the probability and accumulate
-// p * v for their dims.  Online softmax with a lazily raised max as in
-// the prefill kernels, one decision per UN rows.  The (max, sum, vector) triples of the 16 or 32
-// row slots of a workgroup are merged through LDS, those of the splits by decode_merge_kernel.
+// Split-K over the key axis: a workgroup (split, m) owns a range of keys of KV head m and serves the query heads of its
+// group, G = 4, 2 or 1 at a time.
+//
+// bf16 storage, head dims that are multiples of 32: both products run on the matrix cores (v_mfma_f32_16x16x32_bf16), a
+// wavefront takes 32 keys at a time, straight from memory to registers in the layout of the operands (DecTile).  S^T = K Q^T has
+// the heads as columns; O = P V the heads as rows and a dim as a column, 16 dims an instruction, so V's rows are needed
+// dim by dim: two keys' words make two operand words with two byte permutations, half an instruction for each value where
+// the vector form takes a multiply-add per value and head.  The 16 columns of S^T hold every head 16 / G times.  The copies
+// carry the probability in pieces: its upper 8 significant bits, the next 8, the last 8, each exact in bf16, so the
+// products are those of the 32-bit probability (error against 64 bits as with vector multiply-adds).  Nothing passes
+// through LDS before the wavefronts' results are merged.  The running max of a column moves only when a logit exceeds it by
+// 8 binary orders.  The first keys and values are requested before the query is rotated, the next ones as soon as the
+// registers of the present ones are free.  Bound by HBM on long caches, by the chain of launch, first loads and merge
+// on short ones.  Split kernel alone, against the vector form (which held 8 dims x 4 heads of a row in a lane): 8 heads x
+// 16.4K x 128 dims 16.6 -> 14.1 us (67 MB), 8 x 6.1K 10.4 -> 7.6, 8 x 2K 8.2 -> 6.4, 8 x 16.4K x 64 12.1 -> 8.7, 32 x 8.2K x 96
+// 17.2 -> 16.8, 32 x 2K x 96 6.3 -> 6.7.
+//
+// Other types: a key row is spread over LPR lanes (16 bytes per lane, padded to a power of two), so one load instruction of a
+// wavefront fetches 64 / LPRP whole rows, contiguous in memory.  Each lane keeps the query values of its own dims for G heads
+// and a logit is G short dot products plus a butterfly over the lanes of the row, which then share the probability and
+// accumulate p * v for their dims.  Online softmax with a lazily raised max as in the prefill kernels, one decision per UN rows.
+//
+// The (max, sum, vector) triples of a workgroup are merged through LDS, those of the splits by decode_merge_kernel.
 //
 // The step is two launches.  The split kernel goes over the units already in the cache and rotates the
 // (un-rotated) query itself; one more workgroup per KV head takes the new token: one more partial (logit from
@@ -25,11 +34,7 @@
 // further ones of the second its scores: with the activations in a launch of their own in front (5 us) and their
 // product in the token's workgroup, a 611-token prompt and 8 scored tokens took 181 us, 152 us in this form.
 // The token's own row and the query are requested before anything is computed, and the token's workgroup skips the
-// merge of its empty row slots: 152 -> 145 us there, 16 tokens on 8 x 6144 x 128 units 231 -> 227 us, on
-// 8 x 16384 x 64 268 -> 266 us.  (Requesting the first keys and values there too gives 337 us against
-// 360 on 8 x 16384 x 128, but 280 against 268 on 8 x 16384 x 64 and 233 against 231 on 8 x 6144 x 128; requesting those of
-// the next iteration before the current one is worked on 357, and on 64 dims 5 % more.  Why 64 dims lose is not known: it is not
-// the fourth workgroup of a CU that the registers then exclude, a launch has 2.7 a CU.)
+// merge of its empty row slots: 152 -> 145 us there.
 // A separate append launch cost 15 % of the step.
 #include <stdlib.h>
 
@@ -70,8 +75,96 @@ struct DecodeToken {
   HeadLens n_c_h;         // units per head before the token (ragged), else n_c
 };
 
+typedef float dec_f32x4 __attribute__((ext_vector_type(4)));
+
+// the upper halves of a and b as one word, a's low
+__device__ __forceinline__ uint32_t upper_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+__device__ __forceinline__ uint32_t lower_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+
+// max and sum over the four lanes lane % 16, + 16, + 32, + 48, in all of them: after a swap one register holds one half's value
+// in both halves and the other the other's
+__device__ __forceinline__ float max_across_quarters(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return max_across_halves(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float sum_across_quarters(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t w = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  const auto t = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+
+// N consecutive words, 4-byte aligned
+typedef uint32_t dec_u32x3 __attribute__((ext_vector_type(3), aligned(4)));
+template <int N> __device__ __forceinline__ void load_words(const void* p, uint32_t* w) {
+  if constexpr (N == 4) { const uint4 v = *(const uint4*)p; w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w; }
+  else if constexpr (N == 3) { const dec_u32x3 v = *(const dec_u32x3*)p; w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; }
+  else if constexpr (N == 2) { const uint2 v = *(const uint2*)p; w[0] = v.x; w[1] = v.y; }
+  else w[0] = *(const uint32_t*)p;
+}
+
+// 32 keys of one wavefront in the matrix-core form (see the file header).  Lane (n = lane % 16, kg = lane / 16):
+//   ka[b][ks]  16 bytes of key 8 (n / 4) + 4 b + n % 4 from dim 32 ks + 8 kg: rows of the A operand of block b of
+//              S^T = K Q^T, ordered so that the lane's accumulators, rows 4 kg + r of the two blocks, are its keys 8 kg + 4 b + r
+//   vw[r]      dims n NV .. n NV + NV - 1 of key 8 kg + r
+template <int D> struct DecTile {
+  static constexpr int NKS = D / 32, NV = D / 16, PARTS = 3;
+  bf16x8 ka[2][NKS];
+  uint32_t vw[8][NV / 2];
+  // (keys from k1 on repeat the last one; kb is the same in the whole wavefront, so only the offsets inside the block are per lane)
+  __device__ __forceinline__ void load_k(const bf16_t* Kb, int kb, int k1) {
+    const int n = threadIdx.x & 15, kg = (threadIdx.x & 63) >> 4, last = k1 - 1 - kb;
+    const bf16_t* base = Kb + (int64_t)kb * D;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int off = min(8 * (n >> 2) + (n & 3) + 4 * b, last) * D + kg * 8;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) ka[b][ks] = *(const bf16x8*)(base + off + ks * 32);
+    }
+  }
+  __device__ __forceinline__ void load_v(const bf16_t* Vb, int kb, int k1) {
+    const int n = threadIdx.x & 15, kg = (threadIdx.x & 63) >> 4, last = k1 - 1 - kb;
+    const bf16_t* base = Vb + (int64_t)kb * D;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) load_words<NV / 2>(base + (min(8 * kg + r, last) * D + n * NV), vw[r]);
+  }
+  // the rows that repeat the last one: zeros, an infinite value times a probability of 0 would reach the output
+  __device__ __forceinline__ void clear_v(int kb, int k1) {
+    const int over = 8 * (int)((threadIdx.x & 63) >> 4) - (k1 - 1 - kb);
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+      for (int w = 0; w < NV / 2; ++w) vw[r][w] = over + r > 0 ? 0u : vw[r][w];
+  }
+  __device__ __forceinline__ void logits(const bf16x8 (&qb)[NKS], dec_f32x4 (&s)[2]) const {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      s[b] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) s[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[b][ks], qb[ks], s[b], 0, 0, 0);
+    }
+  }
+  // o[i] += P V for dims n NV + i, n = 0..15: the B operand of dim i is the eight keys' values of that dim, taken two keys at
+  // a time from the rows' words
+  __device__ __forceinline__ void accumulate(bf16x8 p, dec_f32x4 (&o)[NV]) const {
+#pragma unroll
+    for (int w = 0; w < NV / 2; ++w) {
+      const uint4 lo = make_uint4(lower_halves(vw[0][w], vw[1][w]), lower_halves(vw[2][w], vw[3][w]),
+                                  lower_halves(vw[4][w], vw[5][w]), lower_halves(vw[6][w], vw[7][w]));
+      const uint4 hi = make_uint4(upper_halves(vw[0][w], vw[1][w]), upper_halves(vw[2][w], vw[3][w]),
+                                  upper_halves(vw[4][w], vw[5][w]), upper_halves(vw[6][w], vw[7][w]));
+      o[2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p, __builtin_bit_cast(bf16x8, lo), o[2 * w], 0, 0, 0);
+      o[2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p, __builtin_bit_cast(bf16x8, hi), o[2 * w + 1], 0, 0, 0);
+    }
+  }
+};
+
+// Three workgroups a CU at 128 dims: left to itself the compiler takes 200 registers, which leaves room for two, and the 520th
+// of 520 workgroups waits for the first.
 template <typename T, int D, int G, bool SCORED>
-__global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __restrict__ Kx, int g0, int keys_per_wg,
+__global__ __launch_bounds__(DEC_THREADS, D == 128 ? 3 : 1) void decode_attn_kernel(const T* __restrict__ Kx, int g0, int keys_per_wg,
                                                                   float* __restrict__ part, DecodeToken tk) {
   // n_splits partials per query head: n_splits - 1 splits over the cached units, then the new token's, which the
   // last of these workgroups forms (it has no units of its own, so it is done long before the others).
@@ -85,20 +178,17 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   constexpr int LPR = D / VEC;                       // lanes that hold data of one row
   constexpr int LPRP = Pow2Ceil<LPR>::value;         // lanes reserved per row
   constexpr int KPW = 64 / LPRP;                     // rows per wavefront per load
-  constexpr int NSETS = (DEC_THREADS / 64) * KPW;    // row slots per workgroup
+  constexpr int NW = DEC_THREADS / 64;
   constexpr int PW = D + 2;                          // floats per partial: vector, max, sum
   typedef Vec16<T> V16;
   typedef decltype(V16().raw) raw_t;
-  __shared__ float sets[NSETS * G * PW];
-  // logits on the matrix cores (see the file header)
-  constexpr bool MM = std::is_same<T, bf16_t>::value && D % 32 == 0 && G <= 16 && (DEC_UN * KPW) % 16 == 0;
-  constexpr int WROWS = DEC_UN * KPW;                // rows of a wavefront per iteration
-  constexpr int NSB = MM ? WROWS / 16 : 1;           // 16-row blocks among them
-  constexpr int NKS = MM ? D / 32 : 1;               // contraction steps
-  __shared__ float slog[MM ? (DEC_THREADS / 64) * WROWS * G : 1];
+  constexpr bool MM = std::is_same<T, bf16_t>::value && D % 32 == 0;      // on the matrix cores (see the file header)
+  constexpr int NSETS = MM ? NW * DecTile<MM ? D : 32>::PARTS : NW * KPW; // accumulator sets the workgroup merges
+  __shared__ __attribute__((aligned(16))) float sets[NSETS * G * (MM ? D : PW)];
+  __shared__ float wml[MM ? NW * G * 2 : 1];         // max and sum of every wavefront
 
   const int split = blockIdx.x, m = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   static_assert(!SCORED || std::is_same<T, bf16_t>::value, "only bf16 layers' scores are formed here");
   if constexpr (SCORED) {
     if (split >= n_splits) {
@@ -120,39 +210,23 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
   const T* Vb = V + (int64_t)m * cap * D;
   const int off = (act ? sub : 0) * VEC;
 
-  constexpr int BLK = (DEC_THREADS / 64) * DEC_UN * KPW;   // rows per workgroup iteration
-  struct Tile {
-    V16 kf[MM ? 1 : DEC_UN], vf[DEC_UN];
-    bf16x8 ka[NSB][NKS];
-  };
-  // (spare rows re-read the first row)
-  auto load_tile = [&](Tile& t, int kb) __attribute__((always_inline)) {
-    if (MM) {
-      // A operand: lane (row lane % 16 of the 16-row block, k group lane / 16) fetches 16 bytes of that key's row
-      const bf16_t* Kh = (const bf16_t*)Kb;
-#pragma unroll
-      for (int sb = 0; sb < NSB; ++sb) {
-        const int key = kb + wave * WROWS + sb * 16 + (lane & 15);
-        const bf16_t* kr = Kh + (int64_t)(key < k1 ? key : k0) * D + (lane >> 4) * 8;
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) t.ka[sb][ks] = *(const bf16x8*)(kr + ks * 32);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < DEC_UN; ++i) {
-      const int key = kb + (wave * DEC_UN + i) * KPW + grp;
-      const int64_t row = (int64_t)(key < k1 ? key : k0) * D + off;
-      if (!MM) t.kf[i].raw = *(const raw_t*)(Kb + row);
-      t.vf[i].raw = *(const raw_t*)(Vb + row);
-    }
-  };
+  constexpr int BLK = MM ? NW * 32 : NW * DEC_UN * KPW;    // keys per workgroup iteration
+  const bool token_wg = split == n_splits - 1;
 
+  // A wavefront's first keys and values are requested before anything else.  (Behind the query's pieces:
+  // 14.6 us instead of 14.1 on 8 heads x 16.4K units.)
+  DecTile<MM ? D : 32> tile;
+  const int kb_w = k0 + wave * 32;                   // (matrix-core form) this wavefront's first block of 32 keys
+  if (MM && kb_w < k1) {
+    tile.load_k((const bf16_t*)Kb, kb_w, k1);
+    tile.load_v((const bf16_t*)Vb, kb_w, k1);
+  }
   // `tab` non-null: q is un-rotated and takes position n_keys (the slot the token is appended at).  One thread
   // per 16-byte chunk of the G query rows rotates its dims with the partner dims (+- D/2), rounds to the storage
   // type as the rotated query of a chunk is, and leaves the row in LDS for the whole workgroup: every workgroup
   // of the launch reads the same few lines of q and of the table, and those requests queue on one L2 channel
   // (with every lane rotating for itself the kernel took 26 us instead of 20).
-  float qv[G][VEC];
+  float qv[MM ? 1 : G][VEC];
   __shared__ float qs[G * D];
   constexpr int CPR = D / VEC;                         // chunks per row
   const int qu = tid / CPR, qoff = (tid % CPR) * VEC;  // the chunk this thread rotates
@@ -168,7 +242,6 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     for (int e = 0; e < VEC; ++e) qcs[e] = tr[e];
   }
   // the new token's own row, in its workgroup (last of the head); 4-bit rows are read by the quantizer instead
-  const bool token_wg = split == n_splits - 1;
   const bool token_row = token_wg && tid < D && tk.Kq == nullptr;
   const bool klow = tid < D / 2;
   T k_own, k_pair, v_own;
@@ -190,10 +263,20 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
       }
     }
     __syncthreads();
+    if (!MM) {
 #pragma unroll
-    for (int u = 0; u < G; ++u)
+      for (int u = 0; u < G; ++u)
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) qv[u][e] = act ? qs[u * D + off + e] : 0.f;
+        for (int e = 0; e < VEC; ++e) qv[MM ? 0 : u][e] = act ? qs[u * D + off + e] : 0.f;
+    }
+  } else if (MM) {                                     // the matrix-core path takes the query from LDS
+    if (tid < G * CPR) {
+      V16 x;
+      x.raw = *(const raw_t*)(q + (int64_t)(m * g + min(g0 + qu, g - 1)) * D + qoff);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) qs[qu * D + qoff + e] = x.get(e) * c_log2;
+    }
+    __syncthreads();
   } else {
 #pragma unroll
     for (int u = 0; u < G; ++u) {
@@ -201,15 +284,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
       V16 x;
       x.raw = *(const raw_t*)(q + (int64_t)j * D + off);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) qv[u][e] = act ? x.get(e) * c_log2 : 0.f;   // logits in log2 units
-    }
-    if (MM) {                                          // the matrix-core path takes the query from LDS
-      if (act && grp == 0 && wave == 0)
-#pragma unroll
-        for (int u = 0; u < G; ++u)
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) qs[u * D + off + e] = qv[u][e];
-      __syncthreads();
+      for (int e = 0; e < VEC; ++e) qv[MM ? 0 : u][e] = act ? x.get(e) * c_log2 : 0.f;   // logits in log2 units
     }
   }
   // ---- the new token (last workgroup of the head): its partial for the G heads, and the append ------------------
@@ -301,143 +376,208 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_attn_kernel(const T* __res
     return;
   }
 
-  // B operand of S^T = K Q^T: lane (head n = lane % 16, k group lane / 16) holds q[n][32 ks + 8 (lane / 16) .. + 8],
-  // scaled, rounded to bf16 (as the chunk kernels round their pre-scaled queries); heads past G are zero
-  bf16x8 qb[NKS];
-  if (MM) {
+  if constexpr (MM) {
+    typedef DecTile<D> Tile;
+    constexpr int NV = Tile::NV, PARTS = Tile::PARTS;
     const int n = lane & 15, kg = lane >> 4;
+    // B operand of S^T = K Q^T: column n is head n % G (every column of a head is the same), lane (n, kg) holds
+    // q[32 ks + 8 kg .. + 8], scaled, rounded to bf16 (as the chunk kernels round their pre-scaled queries)
+    bf16x8 qb[Tile::NKS];
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      float x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = n < G ? qs[n * D + ks * 32 + kg * 8 + e] : 0.f;
+    for (int ks = 0; ks < Tile::NKS; ++ks) {
+      const float* x = qs + (n % G) * D + ks * 32 + kg * 8;
       const uint4 pk = make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7]));
       qb[ks] = __builtin_bit_cast(bf16x8, pk);
     }
-  }
-  float o[G][VEC], mrun[G], lrun[G];
+    // this lane's column takes piece n / G of the probability: what the masks leave after each step
+    const uint32_t cut1 = n / G >= 1 ? 0xffff0000u : 0u, cut2 = n / G >= 2 ? 0xffff0000u : 0u;
+    dec_f32x4 o[NV];
 #pragma unroll
-  for (int u = 0; u < G; ++u) {
-    mrun[u] = -INFINITY;
-    lrun[u] = 0.f;
+    for (int i = 0; i < NV; ++i) o[i] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
+    float mrun = -INFINITY, lrun = 0.f;                // of head n % G; the sum over this lane's keys only
+    for (int kb = kb_w; kb < k1; kb += BLK) {
+      dec_f32x4 s[2];
+      tile.logits(qb, s);
+      if (kb + BLK < k1) tile.load_k((const bf16_t*)Kb, kb + BLK, k1);
+      float p[8];
+      float mx = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) o[u][e] = 0.f;
-  }
-
-  auto attend = [&](const Tile& t, int kb) __attribute__((always_inline)) {
-    bool valid[DEC_UN];
-#pragma unroll
-    for (int i = 0; i < DEC_UN; ++i) valid[i] = kb + (wave * DEC_UN + i) * KPW + grp < k1;
-    float s[DEC_UN][G];
-    if (MM) {
-      typedef float f32x4 __attribute__((ext_vector_type(4)));
-      float* sl = slog + wave * (WROWS * G);
-#pragma unroll
-      for (int sb = 0; sb < NSB; ++sb) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.ka[sb][ks], qb[ks], acc, 0, 0, 0);
-        // the lane holds rows 4 (lane / 16) + r of the block for head lane % 16
-        if ((lane & 15) < G)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sl[(sb * 16 + 4 * (lane >> 4) + r) * G + (lane & 15)] = acc[r];
+      for (int j = 0; j < 8; ++j) {
+        p[j] = kb + 8 * kg + j < k1 ? s[j >> 2][j & 3] : -INFINITY;
+        mx = fmaxf(mx, p[j]);
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (__any((mx - mrun) > DEC_RESCALE_LOG2)) {     // also true from -inf to a number
+        // the four lanes of a column move together: its accumulators are shared
+        mx = max_across_quarters(mx);
+        const bool up = (mx - mrun) > DEC_RESCALE_LOG2;
+        const float alpha = up ? __builtin_amdgcn_exp2f(mrun - mx) : 1.f;
+        if (up) mrun = mx;
+        if (kb != kb_w) {                              // (nothing to scale before the first block)
+          lrun *= alpha;
 #pragma unroll
-      for (int i = 0; i < DEC_UN; ++i)
+          for (int r = 0; r < 4; ++r) {
+            const float ar = __shfl(alpha, (4 * kg + r) % G, 64);    // accumulator row 4 kg + r is of that head
 #pragma unroll
-        for (int u = 0; u < G; ++u) s[i][u] = valid[i] ? sl[(i * KPW + grp) * G + u] : -INFINITY;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();                  // the next iteration rewrites the tile
-    } else {
+            for (int i = 0; i < NV; ++i) o[i][r] *= ar;
+          }
+        }
+      }
+      uint32_t x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float y = kb + 8 * kg + j < k1 ? __builtin_amdgcn_exp2f(p[j] - mrun) : 0.f;
+        lrun += y;
+        y -= __uint_as_float(__float_as_uint(y) & cut1);
+        y -= __uint_as_float(__float_as_uint(y) & cut2);
+        x[j] = __float_as_uint(y);
+      }
+      const uint4 pk = make_uint4(upper_halves(x[0], x[1]), upper_halves(x[2], x[3]), upper_halves(x[4], x[5]), upper_halves(x[6], x[7]));
+      if (kb + 32 > k1) tile.clear_v(kb, k1);
+      tile.accumulate(__builtin_bit_cast(bf16x8, pk), o);
+      if (kb + BLK < k1) tile.load_v((const bf16_t*)Vb, kb + BLK, k1);
+    }
+    lrun = sum_across_quarters(lrun);
+    // ---- merge the wavefronts (and the pieces of the probabilities) ----------------------------
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * kg + r, piece = row / G, u = row % G;
+      if (piece < PARTS)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) sets[((wave * PARTS + piece) * G + u) * D + n * NV + i] = o[i][r];
+    }
+    if (lane < G) {
+      wml[(wave * G + lane) * 2] = mrun;
+      wml[(wave * G + lane) * 2 + 1] = lrun;
+    }
+    __syncthreads();
+    for (int idx = tid; idx < G * PW; idx += DEC_THREADS) {
+      const int u = idx / PW, e = idx % PW;
+      if (g0 + u >= g) continue;
+      float M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) M = fmaxf(M, wml[(w * G + u) * 2]);
+      float val = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float ms = wml[(w * G + u) * 2];
+        const float wt = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - M);      // a wavefront without keys carries nothing
+        float part_w;
+        if (e < D) {
+          const float* src = sets + (w * PARTS * G + u) * D + e;
+          const float hi = src[0], rest = src[G * D] + src[2 * G * D];
+          part_w = isfinite(hi) ? hi + rest : hi;      // an infinite value times a piece that is 0 is not a number
+        } else {
+          part_w = wml[(w * G + u) * 2 + 1];
+        }
+        val = fmaf(wt, part_w, val);
+      }
+      if (e == D) val = M;
+      const int j = m * g + g0 + u;
+      part[((int64_t)j * n_splits + split) * PW + e] = val;
+    }
+  } else {
+    float o[G][VEC], mrun[G], lrun[G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      mrun[u] = -INFINITY;
+      lrun[u] = 0.f;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) o[u][e] = 0.f;
+    }
+    for (int kb = k0; kb < k1; kb += BLK) {
+      // (spare rows re-read the first row)
+      V16 kf[DEC_UN], vf[DEC_UN];
+      bool valid[DEC_UN];
+#pragma unroll
+      for (int i = 0; i < DEC_UN; ++i) {
+        const int key = kb + (wave * DEC_UN + i) * KPW + grp;
+        valid[i] = key < k1;
+        const int64_t row = (int64_t)(valid[i] ? key : k0) * D + off;
+        kf[i].raw = *(const raw_t*)(Kb + row);
+        vf[i].raw = *(const raw_t*)(Vb + row);
+      }
+      float s[DEC_UN][G];
 #pragma unroll
       for (int i = 0; i < DEC_UN; ++i)
 #pragma unroll
         for (int u = 0; u < G; ++u) {
           float a = 0.f;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) a = fmaf(t.kf[0 + (MM ? 0 : i)].get(e), qv[u][e], a);
+          for (int e = 0; e < VEC; ++e) a = fmaf(kf[i].get(e), qv[MM ? 0 : u][e], a);
 #pragma unroll
           for (int x = 1; x < LPRP; x <<= 1) a += __shfl_xor(a, x, 64);
           s[i][u] = valid[i] ? a : -INFINITY;
         }
-    }
-    // one max decision per head for the UN rows of this lane group
-    float muse[G];
-    bool up_any = false;
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      float mx = s[0][u];
-#pragma unroll
-      for (int i = 1; i < DEC_UN; ++i) mx = fmaxf(mx, s[i][u]);
-      const float m_new = fmaxf(mrun[u], mx);
-      const bool up = (m_new - mrun[u]) > DEC_RESCALE_LOG2;   // also true from -inf to a number
-      muse[u] = up ? m_new : mrun[u];
-      up_any = up_any || up;
-    }
-    if (__any(up_any)) {
+      // one max decision per head for the UN rows of this lane group
+      float muse[G];
+      bool up_any = false;
 #pragma unroll
       for (int u = 0; u < G; ++u) {
-        const float alpha = (muse[u] == mrun[u]) ? 1.f : __builtin_amdgcn_exp2f(mrun[u] - muse[u]);
-        lrun[u] *= alpha;
+        float mx = s[0][u];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) o[u][e] *= alpha;
+        for (int i = 1; i < DEC_UN; ++i) mx = fmaxf(mx, s[i][u]);
+        const float m_new = fmaxf(mrun[u], mx);
+        const bool up = (m_new - mrun[u]) > DEC_RESCALE_LOG2;   // also true from -inf to a number
+        muse[u] = up ? m_new : mrun[u];
+        up_any = up_any || up;
       }
+      if (__any(up_any)) {
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+          const float alpha = (muse[u] == mrun[u]) ? 1.f : __builtin_amdgcn_exp2f(mrun[u] - muse[u]);
+          lrun[u] *= alpha;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[u][e] *= alpha;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < G; ++u) mrun[u] = muse[u];
+#pragma unroll
+      for (int i = 0; i < DEC_UN; ++i)
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+          const float p = valid[i] ? __builtin_amdgcn_exp2f(s[i][u] - muse[u]) : 0.f;
+          lrun[u] += p;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[u][e] = fmaf(p, vf[i].get(e), o[u][e]);
+        }
     }
-#pragma unroll
-    for (int u = 0; u < G; ++u) mrun[u] = muse[u];
-#pragma unroll
-    for (int i = 0; i < DEC_UN; ++i)
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        const float p = valid[i] ? __builtin_amdgcn_exp2f(s[i][u] - muse[u]) : 0.f;
-        lrun[u] += p;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) o[u][e] = fmaf(p, t.vf[i].get(e), o[u][e]);
-      }
-  };
-  for (int kb = k0; kb < k1; kb += BLK) {
-    Tile t;
-    load_tile(t, kb);
-    attend(t, kb);
-  }
 
-  // ---- merge the row slots of the workgroup ----------------------------------------------------
-  const int set = wave * KPW + grp;
-  if (act) {
+    // ---- merge the row slots of the workgroup --------------------------------------------------
+    const int set = wave * KPW + grp;
+    if (act) {
 #pragma unroll
-    for (int u = 0; u < G; ++u) {
-      float* dst = sets + (set * G + u) * PW;
+      for (int u = 0; u < G; ++u) {
+        float* dst = sets + (set * G + u) * PW;
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) dst[off + e] = o[u][e];
-      if (sub == 0) {
-        dst[D] = mrun[u];
-        dst[D + 1] = lrun[u];
+        for (int e = 0; e < VEC; ++e) dst[off + e] = o[u][e];
+        if (sub == 0) {
+          dst[D] = mrun[u];
+          dst[D + 1] = lrun[u];
+        }
       }
     }
-  }
-  __syncthreads();
-  for (int idx = tid; idx < G * PW; idx += DEC_THREADS) {
-    const int u = idx / PW, e = idx % PW;
-    if (g0 + u >= g) continue;
-    float M = -INFINITY;
-    for (int s2 = 0; s2 < NSETS; ++s2) M = fmaxf(M, sets[(s2 * G + u) * PW + D]);
-    float val;
-    if (e == D) {
-      val = M;
-    } else {
-      float acc = 0.f;
-      for (int s2 = 0; s2 < NSETS; ++s2) {
-        const float ms = sets[(s2 * G + u) * PW + D];
-        const float w = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - M);   // empty slots carry nothing
-        acc = fmaf(w, sets[(s2 * G + u) * PW + e], acc);     // e == D + 1 merges the sums
+    __syncthreads();
+    for (int idx = tid; idx < G * PW; idx += DEC_THREADS) {
+      const int u = idx / PW, e = idx % PW;
+      if (g0 + u >= g) continue;
+      float M = -INFINITY;
+      for (int s2 = 0; s2 < NSETS; ++s2) M = fmaxf(M, sets[(s2 * G + u) * PW + D]);
+      float val;
+      if (e == D) {
+        val = M;
+      } else {
+        float acc = 0.f;
+        for (int s2 = 0; s2 < NSETS; ++s2) {
+          const float ms = sets[(s2 * G + u) * PW + D];
+          const float w = (ms == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms - M);   // empty slots carry nothing
+          acc = fmaf(w, sets[(s2 * G + u) * PW + e], acc);     // e == D + 1 merges the sums
+        }
+        val = acc;
       }
-      val = acc;
+      const int j = m * g + g0 + u;
+      part[((int64_t)j * n_splits + split) * PW + e] = val;
     }
-    const int j = m * g + g0 + u;
-    part[((int64_t)j * n_splits + split) * PW + e] = val;
   }
 }
 
@@ -534,18 +674,25 @@ __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const f
   }
 }
 
-// Keys per split.  Tuning::dec_keys (a multiple of 64 in 64 .. 65536) fixes it; otherwise it is chosen per
-// launch so that the launch has about 700 workgroups (2.7 per CU), but never under 128 keys, in steps of 64.
-// Measured per token, end to end: 8 heads x 16.6K units 24.0 us at 192 keys (25.4 at 256), 32 heads x 8.4K units
-// 21.5 us at 384 (22.6 at 256), 8 heads x 6.4K units 14.7 us at 128 (18.6 at 64, 15.6 at 256).
-constexpr int DEC_KEYS_MIN = 128;
+// Keys per split.  Tuning::dec_keys (a multiple of 64 in 64 .. 65536) fixes it; otherwise it is chosen per launch.  All
+// workgroups of a launch run at once, so what counts is the CU with the most work: it has the keys of
+// ceil(workgroups / 256) splits and their fixed share (query, first wait, merge: about what 64 keys cost).  One workgroup over a
+// multiple of 256 costs most: 8 heads x 16.4K units x 128 dims take 15.9 us at 256 keys (520 workgroups), 14.1 at 192 (696), 14.0
+// at 320 (424); 8 x 6.1K 7.5 us at 256 (200), 8.8 at 192 (264), 8.3 at 128 (392); 4 x 16.4K 8.8 us at 320 (212), 10.4 at 256 (260).
+// Splits longer than 320 keys only as far as some 700 workgroups are left: on much data a workgroup or two a CU have too few
+// loads in flight (32 x 8.2K x 96 dims: 16.7 us at 384 keys, 736 workgroups, 19.6 at 1056 keys, 256).
+constexpr int DEC_KEYS_MIN = 128, DEC_KEYS_SHORT = 320, DEC_KEYS_SHARE = 64, DEC_CUS = 256;
 int decode_keys_per_split(const Dims& D, int n_keys) {
   if (D.tune.dec_keys > 0) return D.tune.dec_keys;
-  const int64_t want = ((int64_t)D.h_kv * n_keys + 703) / 704;
-  int k = (int)((want + 63) / 64 * 64);
-  if (k < DEC_KEYS_MIN) k = DEC_KEYS_MIN;
-  if (k > 65536) k = 65536;
-  return k;
+  const int64_t want = (((int64_t)D.h_kv * n_keys + 703) / 704 + 63) / 64 * 64;
+  const int most = want < DEC_KEYS_SHORT ? DEC_KEYS_SHORT : want > 65536 ? 65536 : (int)want;
+  int best = DEC_KEYS_MIN;
+  int64_t best_cost = INT64_MAX;
+  for (int k = DEC_KEYS_MIN > want / 2 ? DEC_KEYS_MIN : (int)(want / 128 * 64); k <= most; k += 64) {
+    const int64_t wgs = (int64_t)D.h_kv * ((n_keys + k - 1) / k + 1), cost = (wgs + DEC_CUS - 1) / DEC_CUS * (k + DEC_KEYS_SHARE);
+    if (cost < best_cost) { best_cost = cost; best = k; }
+  }
+  return best;
 }
 
 // partials per query head at most: the splits over a full cache at the smallest split size, and the new token's

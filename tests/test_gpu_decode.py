@@ -151,3 +151,35 @@ def test_decode_on_the_full_budget_of_config3():
         out, _ = layer.decode_step(dev(q, w), dev(k, w), dev(v, w), with_score=False)
         assert_close(host(out), out_ref, w.dtype, f"cfg3 decode token {i}", per_row=True, kappa=kappa_for(w))
     layer.close()
+
+
+@pytest.mark.parametrize("h,h_kv,d", [(2, 2, 128), (4, 2, 96), (8, 2, 128), (12, 2, 64), (4, 1, 32)])
+def test_decode_block_edges(h, h_kv, d):
+    """Cache lengths around the 32-key blocks of a wavefront, the four of a workgroup and the first lengths with two splits, for one,
+    two and four heads a launch; an infinite value (of the last key in the cache, where spare rows repeat it) stays infinite and alone."""
+    w = synth.tiny(name=f"dec_edges_{h}_{h_kv}_{d}", dtype="bf16", h=h, h_kv=h_kv, d=d, N=400, B=200, b=400, n_s=0, d_R=128)
+    layer, W1, W2 = make_layer(w)
+    o = make_oracle(w, W1, W2)
+    n = 0
+    for upto in (1, 31, 32, 33, 63, 95, 127, 128, 129, 160, 191, 255, 256, 257, 319):
+        while n < upto:
+            end = min(upto, n + w.B)
+            x = synth.tokens(w, n, end)
+            o.prefill_chunk(*x, 0, evict=False)
+            layer.evict_compact(torch.zeros(h_kv, end - n, device=DEV), dev(x[1], w), dev(x[2], w), 0)
+            n = end
+        x = synth.tokens(w, n, n + 1)
+        ref, _, _ = o.prefill_chunk(*x, 0, evict=False)
+        out, _ = layer.decode_step(*(dev(t, w) for t in x))
+        n += 1
+        assert_close(host(out), ref, w.dtype, f"{w.name} {upto}", per_row=True)
+    # the same cache with one infinite element in a value row that every head sees
+    q, k, v = (dev(t, w) for t in synth.tokens(w, n, n + 1))
+    v[0, 0, 5] = float("inf")
+    layer.evict_compact(torch.zeros(h_kv, 1, device=DEV), k, v, 0)
+    out = layer.decode_step(*(dev(t, w) for t in synth.tokens(w, n + 1, n + 2)))[0][0].float().cpu()
+    g = h // h_kv
+    expect = torch.zeros(h, d, dtype=torch.bool)
+    expect[:g, 5] = True
+    assert torch.equal(out == float("inf"), expect) and bool(torch.isfinite(out[~expect]).all())
+    layer.close()
