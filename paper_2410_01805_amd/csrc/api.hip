@@ -608,20 +608,29 @@ int locret_evict_compact(locret_ctx* c, const float* chunk_scores, const void* k
   const float2* tab = D.rope ? (const float2*)(c->ws + c->L.tab) : nullptr;
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);
-  const SelectArgs sa = select_args(c, c->n_c + T, n_stab, kept_idx_out);
+  SelectArgs sa = select_args(c, c->n_c + T, n_stab, kept_idx_out);
   // The append's threads write the list of a step that evicts nothing up to 16 times as long as the chunk: per head a
   // thread writes 16 / (threads of a row) entries at most, for every head it serves.  (A step, mean over L = T ... 16 T, with the
   // list in the append or in a launch of its own: 8 heads x 16 dims, one thread a row, T = 16: 7.6, 9.9 us, T = 4096: 7.1, 9.5;
   // 32 x 16, T = 4096: 7.7, 9.8; 32 x 96, T = 4096: 21.5, 24.1; 8 x 128, T = 4096: 8.3, 10.1.)
   const bool keep = !D.kv_bits && !over_budget(c, sa) && sa.L <= (int64_t)16 * T;
-  if (D.kv_bits) {
+  // A step that evicts selects beside the append: the caller has the scores.
+  const bool beside = !D.kv_bits && D.tune.fuse_select && over_budget(c, sa);
+  if (beside) {
+    sa.part = chunk_scores;
+    sa.n_parts = 1;
+    sa.part_T = sa.red_T = T;
+    sa.h_kv = D.h_kv;
+    sa.S_w = A.S;
+    launch_append_select(D, k, v, T, c->n_c, c->seen, A, tab, st, hl, sa);
+  } else if (D.kv_bits) {
     launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st);
     launch_score_reduce(chunk_scores, 1, T, D.h_kv, T, A.S, D.cap, c->n_c, nullptr, st, hl);
   } else {
     launch_append(D, nullptr, k, v, T, c->n_c, c->seen, A, nullptr, tab, st, chunk_scores, hl, keep ? kept_idx_out : nullptr,
                   sa.stride2);
   }
-  run_evict(c, sa, st, false, keep);
+  run_evict(c, sa, st, /*select_done=*/beside, keep);
   c->seen += T;
   return hipGetLastError() == hipSuccess ? LOCRET_OK : LOCRET_EHIP;
 }

@@ -2,8 +2,10 @@
 // chunk append (Algorithm 1 "Concat") and order-preserving compaction (Algorithm 1 gather).
 // Every thread moves 16-byte vectors; a row of d elements is shared by (d/2)/VEC threads, each of
 // which owns VEC rotary pairs (i, i + d/2), so the rotated shadow of K is produced from registers.
+#include "append_body.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "select_body.h"
 
 namespace locret {
 
@@ -71,231 +73,68 @@ void launch_prep_weights(const Dims& D, int expand, const void* W1, const void* 
 }
 
 // ------------------------------------------------------------------------------------------------
-// 16-byte loads and stores that bypass the caches' retention: compaction touches every byte once
-typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4)));
-template <typename R>
-__device__ __forceinline__ R nt_load16(const void* p) {
-  static_assert(sizeof(R) == 16, "16-byte lanes");
-  nt_u32x4 v = __builtin_nontemporal_load((const nt_u32x4*)p);
-  return __builtin_bit_cast(R, v);
-}
-template <typename R>
-__device__ __forceinline__ void nt_store16(void* p, R r) {
-  static_assert(sizeof(R) == 16, "16-byte lanes");
-  __builtin_nontemporal_store(__builtin_bit_cast(nt_u32x4, r), (nt_u32x4*)p);
+template <typename T, bool RAGGED, bool ROWS>
+__global__ __launch_bounds__(256) void append_kernel(AppendArgs<T> a) {
+  append_any<T, RAGGED, ROWS>(a, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
-// Append: a thread owns token t and VEC rotary pairs of its rows, for `hpb` consecutive KV heads (blockIdx.y), so
-// the rotary-table row of the token's slot is read once for all of them and the loads of two heads are in flight
-// together.  Bound by HBM: 12 us for 4096 tokens x 8 heads x 128 dims = 42 MB.  Scores that the caller has already
-// (S_src) travel with the rows.  With one thread per row piece, each with its own table reads, that cost as much as
-// the launch of their own it saves: 48000 tokens in 12 eviction-only steps 538 us with the separate launch, 537 us
-// with one thread per piece, 500 us in this form.  With q != NULL further blocks of blockIdx.y rotate the queries
-// into qr (storage types whose attention kernel does not do it itself).
-// An eviction-only step that evicts nothing has the caller's list 0, 1, 2, ... written here as well (keep), every thread a
-// share of it: a launch of its own for that took 4.2 us
-// (48000 tokens into 8 x 32768 units in 12 steps, 8 of which evict nothing: 499 -> 486 us).
-// K un-rotated is next read by a compaction, long after it has left the caches: its stores do not stay in them.
-__device__ __forceinline__ void keep_all(int32_t* __restrict__ out, int n, int first, int step) {
-  for (int i = first; i < n; i += step) out[i] = i;
-}
-
-template <typename T, bool RAGGED>
-__global__ __launch_bounds__(256) void append_kernel(const T* __restrict__ q, const T* __restrict__ k,
-                                                     const T* __restrict__ v, int Tn, int n_c_common, int seen, int h,
-                                                     int h_kv, int d, int cap, T* __restrict__ Kc,
-                                                     T* __restrict__ Vc, T* __restrict__ Krc,
-                                                     int32_t* __restrict__ Pc, T* __restrict__ qr,
-                                                     const float2* __restrict__ tab, int rope, int hpb, int kv_blocks,
-                                                     float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h,
-                                                     int32_t* __restrict__ keep, int keep_stride) {
-  constexpr int VEC = Vec16<T>::N;
-  typedef Vec16<T> V16;
-  typedef decltype(V16().raw) raw_t;
-  const int half = d / 2;
-  const int tpr = half / VEC;
-  const int rows = 256 / tpr;                    // tokens per workgroup
-  const int lr = (int)threadIdx.x / tpr, part = (int)threadIdx.x % tpr;
-  const int t = (int)blockIdx.x * rows + lr;
-  if (lr >= rows || t >= Tn) return;
-  const int off = part * VEC;
-  float2 cs[VEC];
-  auto table_row = [&](int n_c) {
-    const float2* tr = tab + (int64_t)(n_c + t) * half + off;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) cs[i] = tr[i];
-  };
-  auto rotate = [&](const V16& lo, const V16& hi, V16& olo, V16& ohi) {
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-      const float a = lo.get(i), b = hi.get(i);
-      olo.set(i, a * cs[i].x - b * cs[i].y);
-      ohi.set(i, b * cs[i].x + a * cs[i].y);
-    }
-  };
-  if (rope && !RAGGED) table_row(n_c_common);
-  if ((int)blockIdx.y >= kv_blocks) {
-    const int j0 = ((int)blockIdx.y - kv_blocks) * hpb;
-    for (int j = j0; j < min(h, j0 + hpb); ++j) {
-      if (RAGGED) table_row(n_c_h.v[j / (h / h_kv)]);      // a query sits behind its own KV head's cache
-      const int64_t row = ((int64_t)t * h + j) * d;
-      V16 lo, hi, olo, ohi;
-      lo.raw = *(const raw_t*)(q + row + off);
-      hi.raw = *(const raw_t*)(q + row + half + off);
-      rotate(lo, hi, olo, ohi);
-      *(raw_t*)(qr + row + off) = olo.raw;
-      *(raw_t*)(qr + row + half + off) = ohi.raw;
-    }
+// Append and selection of an eviction-only step in one launch: the first n_sel workgroups select, one KV head each, on the scores
+// that the caller has (they also store the chunk's), the others append, four of the append's workgroups each.  Neither
+// needs the other, and alone the selection keeps h_kv of the 256 CUs busy.  The launch takes what the selection takes beside
+// the append's traffic, 28 us for 8 x 34.8K candidates against 12 + 22 us of two launches: 48000 tokens into 8 x 32768 units 486 -> 463
+// us, 9000 into 8 x 4096 129 -> 116, 33900 into 8 x 32768 in chunks of 300 1085 -> 1024, 32 x 8192 x 96 dims 373 -> 346.
+// Two replicas of the first histogram, as in the selection's own launch; 4 or 8 are no faster (463, 469 us).
+template <typename T, bool RAGGED, bool ROWS, int MAXR, bool TAIL>
+__global__ __launch_bounds__(1024) void append_select_kernel(AppendArgs<T> a, SelectArgs sel, int n_sel) {
+  __shared__ __attribute__((aligned(16))) uint32_t smem[select_body_smem_words(1024, 2)];
+  if ((int)blockIdx.x < n_sel) {
+    select_reg_body<MAXR, 1024, 2, TAIL, true>(sel, blockIdx.x, smem);
     return;
   }
-  const int m_lo = (int)blockIdx.y * hpb, m_hi = min(h_kv, m_lo + hpb);
-  for (int m0 = m_lo; m0 < m_hi; m0 += 2) {
-    V16 klo[2], khi[2], vlo[2], vhi[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t row = ((int64_t)t * h_kv + min(m0 + u, m_hi - 1)) * d;    // a spare head repeats the last one (not stored)
-      klo[u].raw = *(const raw_t*)(k + row + off);
-      khi[u].raw = *(const raw_t*)(k + row + half + off);
-      vlo[u].raw = *(const raw_t*)(v + row + off);
-      vhi[u].raw = *(const raw_t*)(v + row + half + off);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int m = m0 + u;
-      if (m >= m_hi) break;
-      const int n_c = RAGGED ? n_c_h.v[m] : n_c_common;
-      const int64_t slot = (int64_t)m * cap + n_c + t, drow = slot * d;
-      *(raw_t*)(Vc + drow + off) = vlo[u].raw;
-      *(raw_t*)(Vc + drow + half + off) = vhi[u].raw;
-      if (rope) {
-        if (RAGGED) table_row(n_c);
-        V16 olo, ohi;
-        rotate(klo[u], khi[u], olo, ohi);
-        *(raw_t*)(Krc + drow + off) = olo.raw;
-        *(raw_t*)(Krc + drow + half + off) = ohi.raw;
-        nt_store16(Kc + drow + off, klo[u].raw);
-        nt_store16(Kc + drow + half + off, khi[u].raw);
-      } else {
-        *(raw_t*)(Kc + drow + off) = klo[u].raw;
-        *(raw_t*)(Kc + drow + half + off) = khi[u].raw;
-      }
-      if (part == 0) {
-        Pc[slot] = seen + t;
-        if (S_src) S[slot] = S_src[(int64_t)m * Tn + t];
-      }
-      if (keep) keep_all(keep + (int64_t)m * keep_stride, n_c + Tn, t * tpr + part, Tn * tpr);
-    }
-  }
+  const int wg = ((int)blockIdx.x - n_sel) * 4 + (int)(threadIdx.x >> 8);
+  if (wg < a.gx * a.gy) append_any<T, RAGGED, ROWS>(a, wg % a.gx, wg / a.gx, threadIdx.x & 255);
 }
-
-// Rows of 96 bf16, whose halves are not whole 128-byte lines: a thread owns one 16-byte piece of the row
-// instead of a rotary pair of pieces, and fetches the partner piece of K as well (a line its neighbours have just
-// fetched).  A wavefront then stores 1 KB in a row; in pairs of pieces it stores runs of half a row, which end inside
-// lines.  (32 heads x 96: append of 4096 tokens 36 -> 30 us, compaction of 8192 units 70 -> 58 us.  Rows of 64 dims,
-// whose halves are half a line, gain nothing from it: append of 2048 tokens on 8 heads 5.3 against 5.8 us.)
-__device__ __forceinline__ uint4 rotate_piece(uint4 own, uint4 partner, const float2 (&cs)[8], bool low) {
-  Vec16<bf16_t> x, y, r;
-  x.raw = own;
-  y.raw = partner;
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-    r.set(i, low ? x.get(i) * cs[i].x - y.get(i) * cs[i].y : x.get(i) * cs[i].x + y.get(i) * cs[i].y);
-  return r.raw;
-}
-
-template <bool RAGGED>
-__global__ __launch_bounds__(256) void append_rows_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int Tn,
-                                                          int n_c_common, int seen, int h_kv, int d, int cap,
-                                                          bf16_t* __restrict__ Kc, bf16_t* __restrict__ Vc,
-                                                          bf16_t* __restrict__ Krc, int32_t* __restrict__ Pc,
-                                                          const float2* __restrict__ tab, int rope, int hpb,
-                                                          float* __restrict__ S, const float* __restrict__ S_src, HeadLens n_c_h,
-                                                          int32_t* __restrict__ keep, int keep_stride) {
-  constexpr int HB = 2;
-  const int half = d / 2, ppr = d / 8, rows = 256 / ppr;       // pieces of a row, tokens per workgroup
-  const int lr = (int)threadIdx.x / ppr, piece = (int)threadIdx.x % ppr;
-  const int t = (int)blockIdx.x * rows + lr;
-  if (lr >= rows || t >= Tn) return;
-  const int off = piece * 8;
-  const bool low = off < half;
-  const int poff = low ? off + half : off - half, coff = low ? off : off - half;
-  float2 cs[8];
-  auto table_row = [&](int n_c) {
-    const float2* tr = tab + (int64_t)(n_c + t) * half + coff;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) cs[i] = tr[i];
-  };
-  if (rope && !RAGGED) table_row(n_c_common);
-  const int m_lo = (int)blockIdx.y * hpb, m_hi = min(h_kv, m_lo + hpb);
-  for (int m0 = m_lo; m0 < m_hi; m0 += HB) {
-    uint4 kx[HB], ky[HB], vx[HB];
-#pragma unroll
-    for (int u = 0; u < HB; ++u) {
-      const int64_t row = ((int64_t)t * h_kv + min(m0 + u, m_hi - 1)) * d;    // a spare head repeats the last one (not stored)
-      kx[u] = *(const uint4*)(k + row + off);
-      ky[u] = *(const uint4*)(k + row + poff);
-      vx[u] = *(const uint4*)(v + row + off);
-    }
-#pragma unroll
-    for (int u = 0; u < HB; ++u) {
-      const int m = m0 + u;
-      if (m >= m_hi) break;
-      const int n_c = RAGGED ? n_c_h.v[m] : n_c_common;
-      const int64_t slot = (int64_t)m * cap + n_c + t, drow = slot * d;
-      *(uint4*)(Vc + drow + off) = vx[u];
-      if (rope) {
-        if (RAGGED) table_row(n_c);
-        *(uint4*)(Krc + drow + off) = rotate_piece(kx[u], ky[u], cs, low);
-        nt_store16(Kc + drow + off, kx[u]);
-      } else {
-        *(uint4*)(Kc + drow + off) = kx[u];
-      }
-      if (piece == 0) {
-        Pc[slot] = seen + t;
-        if (S_src) S[slot] = S_src[(int64_t)m * Tn + t];
-      }
-      if (keep) keep_all(keep + (int64_t)m * keep_stride, n_c + Tn, t * ppr + piece, Tn * ppr);
-    }
-  }
-}
-
-// storage and head dim of the kernels above and below
-static bool row_pieces(const Dims& D) { return D.bf16 && D.d == 96; }
 
 void launch_append(const Dims& D, const void* q, const void* k, const void* v, int T, int n_c, int64_t seen,
                    const CacheBuf& c, void* qr, const float2* tab, hipStream_t st, const float* scores,
                    const HeadLens* n_c_h, int32_t* keep, int keep_stride) {
-  const HeadLens hl = head_lens_or_common(n_c_h);
-  if (row_pieces(D) && q == nullptr) {
-    const int rows = 256 / (D.d / 8), gx = (T + rows - 1) / rows;
-    int hpb = D.h_kv;
-    while (hpb > 2 && (int64_t)gx * ((D.h_kv + hpb - 1) / hpb) < 768) hpb = (hpb + 1) / 2;
-    const dim3 grid((unsigned)gx, (unsigned)((D.h_kv + hpb - 1) / hpb));
-#define LOCRET_APPEND_ROWS(RG)                                                                                           \
-  launch_kernel((append_rows_kernel<RG>), grid, dim3(256), 0, st, (const bf16_t*)k, (const bf16_t*)v, T, n_c, (int)seen,   \
-                D.h_kv, D.d, D.cap, (bf16_t*)c.K, (bf16_t*)c.V, (bf16_t*)c.Kr, c.P, tab, D.rope, hpb, c.S, scores, hl,      \
-                keep, keep_stride)
-    if (hl.ragged) LOCRET_APPEND_ROWS(true); else LOCRET_APPEND_ROWS(false);
-#undef LOCRET_APPEND_ROWS
-    return;
-  }
-  const int vec = D.bf16 ? 8 : 4;
-  const int tpr = (D.d / 2) / vec;
-  const int rows = 256 / tpr;
-  const int q_rows = (D.rope && q != nullptr) ? D.h : 0;
-  const int gx = (T + rows - 1) / rows;
-  // as few heads per thread as give the chip about three workgroups per CU
-  int hpb = D.h_kv;
-  while (hpb > 1 && (int64_t)gx * ((D.h_kv + hpb - 1) / hpb) < 768) hpb = (hpb + 1) / 2;
-  const int kv_blocks = (D.h_kv + hpb - 1) / hpb;
-  dim3 grid((unsigned)gx, (unsigned)(kv_blocks + (q_rows + hpb - 1) / hpb));
-#define LOCRET_APPEND(TT, RG)                                                                                          \
-  launch_kernel((append_kernel<TT, RG>), grid, dim3(256), 0, st, (const TT*)q, (const TT*)k, (const TT*)v, T, n_c,     \
-                (int)seen, D.h, D.h_kv, D.d, D.cap, (TT*)c.K, (TT*)c.V, (TT*)c.Kr, c.P, (TT*)qr, tab, D.rope, hpb,     \
-                kv_blocks, c.S, scores, hl, keep, keep_stride)
-  if (D.bf16) { if (hl.ragged) LOCRET_APPEND(bf16_t, true); else LOCRET_APPEND(bf16_t, false); }
-  else { if (hl.ragged) LOCRET_APPEND(float, true); else LOCRET_APPEND(float, false); }
+#define LOCRET_APPEND(TT, RG, ROWS)                                                                            \
+  do {                                                                                                         \
+    const AppendArgs<TT> a = append_args<TT>(D, q, k, v, T, n_c, seen, c, qr, tab, scores, n_c_h, keep, keep_stride); \
+    launch_kernel((append_kernel<TT, RG, ROWS>), dim3(a.gx, a.gy), dim3(256), 0, st, a);                       \
+  } while (0)
+  const bool ragged = n_c_h && n_c_h->ragged;
+  if (row_pieces(D) && q == nullptr) { if (ragged) LOCRET_APPEND(bf16_t, true, true); else LOCRET_APPEND(bf16_t, false, true); }
+  else if (D.bf16) { if (ragged) LOCRET_APPEND(bf16_t, true, false); else LOCRET_APPEND(bf16_t, false, false); }
+  else { if (ragged) LOCRET_APPEND(float, true, false); else LOCRET_APPEND(float, false, false); }
 #undef LOCRET_APPEND
+}
+
+template <typename T, bool RAGGED, bool ROWS>
+static void append_select_launch(const AppendArgs<T>& a, const SelectArgs& sel, hipStream_t st) {
+  const dim3 grid((unsigned)(a.h_kv + (a.gx * a.gy + 3) / 4));
+  const int rounds = select_rounds(sel, 16);
+#define LOCRET_AS(R, TAIL)                                                                                              \
+  do {                                                                                                                  \
+    launch_kernel((append_select_kernel<T, RAGGED, ROWS, R, TAIL>), grid, dim3(1024), 0, st, a, sel, a.h_kv);             \
+    return;                                                                                                             \
+  } while (0)
+  if (rounds <= 12) LOCRET_AS(12, false);
+  if (rounds <= 24) LOCRET_AS(24, false);
+  if (rounds <= 36) LOCRET_AS(36, false);
+  LOCRET_AS(36, true);
+#undef LOCRET_AS
+}
+
+void launch_append_select(const Dims& D, const void* k, const void* v, int T, int n_c, int64_t seen, const CacheBuf& c, const float2* tab,
+                          hipStream_t st, const HeadLens* n_c_h, const SelectArgs& sel) {
+#define LOCRET_AS(TT, RG, ROWS) \
+  append_select_launch<TT, RG, ROWS>(append_args<TT>(D, nullptr, k, v, T, n_c, seen, c, nullptr, tab, nullptr, n_c_h, nullptr, 0), sel, st)
+  const bool ragged = n_c_h && n_c_h->ragged;
+  if (row_pieces(D)) { if (ragged) LOCRET_AS(bf16_t, true, true); else LOCRET_AS(bf16_t, false, true); }
+  else if (D.bf16) { if (ragged) LOCRET_AS(bf16_t, true, false); else LOCRET_AS(bf16_t, false, false); }
+  else { if (ragged) LOCRET_AS(float, true, false); else LOCRET_AS(float, false, false); }
+#undef LOCRET_AS
 }
 
 // ------------------------------------------------------------------------------------------------

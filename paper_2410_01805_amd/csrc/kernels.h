@@ -151,6 +151,11 @@ void launch_append(const Dims& D, const void* q, const void* k, const void* v, i
                    int64_t seen, const CacheBuf& c, void* qr, const float2* tab, hipStream_t st,
                    const float* scores = nullptr, const HeadLens* n_c_h = nullptr, int32_t* keep = nullptr, int keep_stride = 0);
 
+// Append of k and v and, in the same launch, the selection `sel` over the rows that the append completes: its first step
+// (SelectArgs::part) stores the chunk's scores.  Not for 4-bit rows.
+void launch_append_select(const Dims& D, const void* k, const void* v, int T, int n_c, int64_t seen, const CacheBuf& c, const float2* tab,
+                          hipStream_t st, const HeadLens* n_c_h, const SelectArgs& sel);
+
 // 4-bit rows.  Append: quantize the chunk's k, v rows into the packed arrays of `c` at slots [n_c, n_c+T) and write
 // their dequantized values (K rotated to n_c+t) into the staging arrays; P as launch_append.
 // Compact: dst packed rows r = src packed rows kept[m][r], S, P likewise, staging rows r rewritten for slot r.

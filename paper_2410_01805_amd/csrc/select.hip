@@ -33,9 +33,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_reg_kernel(SelectArgs a) {
   select_reg_body<MAXR, SEL_THREADS, 2, TAIL>(a, blockIdx.x, smem);
 }
 
-// keys of a thread
-static int select_reg_rounds(int n_cand) { return ((n_cand + SEL_WAVES - 1) / SEL_WAVES + 63) / 64; }
-
 // One token a thread: the thread's chain of loads is then the one a thread of the reduction has, and its launch (4 us) is
 // saved.  With a second token a thread it is lost again.  A step, selection in a launch of its own, summed there or
 // reduced before it: float32, 2 heads, T = 512: 32 partials 88.0, 89.1 us, 128 partials 199.4, 202.1; T = 1024, 32 partials 144.8,
@@ -45,10 +42,7 @@ bool select_sums_partials(int T) { return T <= SEL_THREADS; }
 
 // The form is chosen for the longest head; every form takes shorter heads as they come.
 void launch_select(const SelectArgs& a, int h_kv, hipStream_t st) {
-  const int ns = a.n_stab < a.L ? a.n_stab : a.L;
-  const int npin = a.n_pin < a.L - ns ? a.n_pin : a.L - ns;
-  const int n_cand = a.L - ns - npin;
-  const int rounds = select_reg_rounds(n_cand);
+  const int rounds = select_rounds(a, SEL_WAVES);
 #define LOCRET_SEL_REG(R)                                                                         \
   if (rounds <= R) {                                                                              \
     launch_kernel((select_reg_kernel<R, false>), dim3(h_kv), dim3(SEL_THREADS), 0, st, a);                 \

@@ -28,6 +28,13 @@ __device__ __forceinline__ HeadSel head_sel(const SelectArgs& a, int m) {
   return r;
 }
 
+// rounds of 64 candidates that a wavefront of `waves` has to go through for the longest head
+inline int select_rounds(const SelectArgs& a, int waves) {
+  const int ns = a.n_stab < a.L ? a.n_stab : a.L;
+  const int npin = a.n_pin < a.L - ns ? a.n_pin : a.L - ns;
+  return ((a.L - ns - npin + waves - 1) / waves + 63) / 64;
+}
+
 // Digits of the register-resident form: 12 + 10 + 10 bits, most significant first.  Score keys share their sign
 // and most exponent bits, so an 8-bit first digit leaves a third of the candidates in the threshold's bin and
 // the second pass as heavy as the first; a 12-bit one (sign, exponent, 3 mantissa bits) leaves a few percent,
@@ -112,8 +119,9 @@ __device__ __forceinline__ bool select_radix_pass(const uint32_t (&k)[MAXR], int
   return remaining == ws[18];
 }
 
-// REP1: replicas per bin of the first pass, by the LDS at hand (4: 64 KB, 2: 32 KB, 1: 16 KB)
-template <int MAXR, int NT, int REP1, bool TAIL = false>
+// REP1: replicas per bin of the first pass, by the LDS at hand (4: 64 KB, 2: 32 KB, 1: 16 KB).  WHOLE: a.part is a single part, the
+// chunk's scores themselves.
+template <int MAXR, int NT, int REP1, bool TAIL = false, bool WHOLE = false>
 __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint32_t* smem) {
   static_assert(NT == 512 || NT == 1024, "workgroup sizes of the callers");
   constexpr int NWAVES = NT / 64;
@@ -130,12 +138,16 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
     // the chunk's scores first: the same sum, in the same order, as score_reduce_kernel
     for (int t = tid; t < a.red_T; t += NT) {
       float sum = a.part[(int64_t)m * a.part_T + t];   // a single part is copied bit for bit (-0 stays -0)
-      for (int p = 1; p < a.n_parts; ++p) sum += a.part[((int64_t)p * a.h_kv + m) * a.part_T + t];
+      if constexpr (!WHOLE)
+        for (int p = 1; p < a.n_parts; ++p) sum += a.part[((int64_t)p * a.h_kv + m) * a.part_T + t];
       a.S_w[(int64_t)m * a.cap + red_n_c + t] = sum;
       if (a.red_out) a.red_out[(int64_t)m * a.red_T + t] = sum;
     }
-    __syncthreads();   // workgroup-scope release/acquire: the keys below are read back from S by other threads
+    if constexpr (!WHOLE) __syncthreads();   // workgroup-scope release/acquire: the keys below are read back from S by other threads
   }
+  // WHOLE: candidates from n_old on are read where the caller has them
+  const int n_old = WHOLE ? hs.L - a.red_T - hs.n_pin : 0;
+  const float* fresh = WHOLE ? a.part + (int64_t)m * a.part_T - n_old : s;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int L = hs.L, n_pin = hs.n_pin;
@@ -151,7 +163,10 @@ __device__ __forceinline__ void select_reg_body(const SelectArgs& a, int m, uint
   {
     float f[MAXR];
 #pragma unroll
-    for (int j = 0; j < MAXR; ++j) f[j] = (j < nvalid) ? s[first + j * 64] : 0.f;
+    for (int j = 0; j < MAXR; ++j) {
+      const int c = first + j * 64;
+      f[j] = (j < nvalid) ? (WHOLE && c >= n_old ? fresh : s)[c] : 0.f;
+    }
     for (int i = tid; i < (H1 + 2 * H2) / 4; i += NT) ((uint4*)hist)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 #pragma unroll

@@ -188,3 +188,36 @@ def test_pinned_prefix_argument_errors_and_reset():
     layer.set_pinned_prefix(0)
     layer.evict_compact(sc, dev(k, w), dev(v, w), 20)
     layer.close()
+
+
+@pytest.mark.parametrize("kw,n_pin,budgets", [
+    (dict(dtype="bf16", h=4, h_kv=4, d=128, B=700, b=1500, n_s=40), 0, None),
+    (dict(dtype="bf16", h=5, h_kv=5, d=96, B=333, b=500, n_s=7), 480, None),                # the pinned prefix reaches into the chunk
+    (dict(dtype="bf16", h=3, h_kv=3, d=64, B=900, b=1800, n_s=100, rope=False), 0, [1800, 700, 1300]),
+    (dict(dtype="f32", h=2, h_kv=2, d=32, B=257, b=600, n_s=600), 0, None),                 # no candidate
+    (dict(dtype="f32", h=1, h_kv=1, d=16, B=3000, b=39000, n_s=9, rope=False), 0, None),    # more candidates than registers hold
+], ids=["bf16", "rows_of_96_pinned", "head_budgets", "f32_all_stabilizers", "read_again"])
+def test_selection_beside_the_append_matches_the_separate_launches(kw, n_pin, budgets, monkeypatch):
+    """Eviction-only steps with the selection in the append's launch and (LOCRET_FUSE_SELECT=0) in one of its own: the same lists
+    and caches, chunks of 1, 2 and B tokens."""
+    w = synth.tiny(name="beside", N=kw["b"] + 3 * kw["B"], **kw)
+    beside, _, _ = make_layer(w)
+    monkeypatch.setenv("LOCRET_FUSE_SELECT", "0")
+    plain, _, _ = make_layer(w)
+    rng = np.random.default_rng(5)
+    for layer in (beside, plain):
+        layer.set_head_budgets(budgets)
+        layer.set_pinned_prefix(n_pin)
+    lo, full = 0, [w.B] * (w.b // w.B)
+    for T in full + [1, w.B, 2, w.B]:
+        _, k, v = synth.tokens(w, lo, lo + T)
+        sc = torch.from_numpy(_scores(rng, w.h_kv, T, "specials")).to(DEV)
+        a, b = (layer.evict_compact(sc, dev(k, w), dev(v, w), w.n_s).cpu().numpy() for layer in (beside, plain))
+        np.testing.assert_array_equal(a, b)
+        lo += T
+    assert beside.cache_lens == plain.cache_lens
+    for x, y in zip(beside.cache_tensors(), plain.cache_tensors()):
+        for m, n in enumerate(plain.cache_lens):
+            assert torch.equal(x[m, :n].contiguous().view(torch.int8), y[m, :n].contiguous().view(torch.int8))
+    beside.close()
+    plain.close()
