@@ -201,8 +201,8 @@ __global__ __launch_bounds__(256) void compact_kernel(const T* __restrict__ Ks, 
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
           float a = klo[u].get(i), b = khi[u].get(i);
-          olo.set(i, a * cs[i].x - b * cs[i].y);
-          ohi.set(i, b * cs[i].x + a * cs[i].y);
+          olo.set(i, fmaf(a, cs[i].x, -(b * cs[i].y)));
+          ohi.set(i, fmaf(b, cs[i].x, a * cs[i].y));
         }
         nt_store16(Krd + drow + off, olo.raw);
         nt_store16(Krd + drow + half + off, ohi.raw);

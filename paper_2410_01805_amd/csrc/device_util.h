@@ -9,13 +9,9 @@ typedef uint16_t bf16_t;  // raw bf16 bits
 
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-// round-to-nearest-even, NaN kept quiet
-__device__ __forceinline__ bf16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
+// round to nearest even, a NaN stays one: v_cvt_pk_bf16_f32.  (Rounding with integer instructions and a branch for NaN was half of
+// the instructions of the append and of the compaction: 4096 tokens into 8 x 128-dim heads as 4-bit rows 9.0 -> 7.6 us.)
+__device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
