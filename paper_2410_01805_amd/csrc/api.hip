@@ -137,6 +137,7 @@ inline bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
 // own address, until the process ends.  First the partial scores part[blocks][h_kv][T], then the partial
 // pre-activations of launches that split the contraction.  In host code the array's name is only a handle
 // for hipGetSymbolAddress; kernels and launchers get the looked-up address.
+static_assert(SCORE_FINE_FLOATS <= LOCRET_STATIC_PART_FLOATS, "the finer partials fit the static scratch too");
 constexpr size_t STATIC_PART_FLOATS = LOCRET_STATIC_PART_FLOATS;     // 4 MiB
 constexpr size_t STATIC_ZPART_FLOATS = (size_t)4 << 20;              // 16 MiB
 static __device__ __align__(256) float scratch[STATIC_PART_FLOATS + STATIC_ZPART_FLOATS];

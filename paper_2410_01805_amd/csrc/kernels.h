@@ -227,6 +227,9 @@ void launch_decode_step(const Dims& D, const void* q, const void* k, const void*
                         bool mark_unscored, const HeadLens* n_c_h = nullptr,
                         const TokenScore* score = nullptr);
 
+// Short chunks are worked on in smaller blocks of hidden units, which leave twice as many partials, as long as those are at most
+// this many floats (the entry points without and with a workspace then choose alike).
+constexpr size_t SCORE_FINE_FLOATS = (size_t)1 << 20;
 // Retaining head: partial scores part[nb][h_kv][T] over hidden-unit blocks; returns the number of
 // blocks nb through *n_parts.  `part` must hold (d_R/score_part_width) * h_kv * chunk_max floats.
 int score_parts_simple(const Dims& D);

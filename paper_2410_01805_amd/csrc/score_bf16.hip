@@ -4,12 +4,18 @@
 // The hidden pre-activations are formed transposed, H^T[r][t] = W1t[r][:] . x[t][:], with
 // v_mfma_f32_32x32x16_bf16 (A = rows of the transposed weight, B = token rows; both contiguous
 // along the contraction).  A workgroup owns 128 hidden units x 128 tokens (2 x 2 wavefronts of
-// 64 x 64), or x 64 tokens (wavefronts of 64 x 32) for chunks too short to give every CU a 128-token tile.
+// 64 x 64), x 64 tokens (wavefronts of 64 x 32) for chunks too short to give every CU a 128-token tile, or 64 x 64 (32 x 32)
+// for those too short for that.
 // The input row is never materialised: each stage of 64 contraction elements lies inside
 // one of q, k, v and is fetched from that tensor directly.
 //
 // Operand staging goes global -> LDS without passing through registers (buffer_load ... lds,
-// 16 bytes per lane) into a ring of four stages, so three stages are always in flight.  A direct load
+// 16 bytes per lane) into a ring of stages, four of 32 KB or six of 24 or 16 KB, all but one of them in flight.
+// What bounds the kernel is this path.  Taken apart (32q/8kv x 128, d_R = 1024, 2048 tokens in 128 x 64 tiles, inputs in the
+// last-level cache): 35 us; without the loads 21; the loads alone 29.6, with the same four stages over and over, which stay
+// in the L2, 23 (55 B/clk and CU), weights alone 21.6, tokens alone 17.9.  Fewer distinct bytes per XCD (another
+// order of the tiles: 20 % less), contiguous tiles of W1 and stages offset between the XCDs change 0 to 5 % of that; what counts is the
+// bytes a CU requests, and how long each is on its way (inputs from HBM: 41 us).  A direct load
 // holds its wavefront's issue slot for 60-80 cycles while the CU's vector-memory path (64 B/clk) is
 // busy, and a stage needs 32 of them: issued by the computing wavefronts they cost as much time as the
 // stage's 16 MFMAs.  So the workgroup has eight wavefronts: 0..3 only compute, 4..7 (their SIMD mates)
@@ -36,19 +42,20 @@ namespace locret {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int RT_M = 128;      // hidden units per workgroup
-constexpr int RT_N = 128;      // tokens per workgroup
+constexpr int RT_M = 128;      // hidden units per workgroup at most
+constexpr int RT_N = 128;      // tokens per workgroup at most
 constexpr int RT_K = 64;       // contraction elements per stage (128 bytes per row)
-constexpr int RT_STAGES = 4;
-constexpr int RT_TILE_B = RT_M * RT_K * 2;            // bytes of one operand tile (16 KB)
-constexpr int RT_STAGE_B = 2 * RT_TILE_B;             // A then B
 
+// MT hidden units x NT tokens
+template <int MT, int NT>
 struct ScoreSmem {
+  static constexpr int TILE_A = MT * RT_K * 2, STAGE_B = TILE_A + NT * RT_K * 2;       // bytes of a stage: weights, then tokens
+  static constexpr int STAGES = NT == 64 ? 6 : 4;
   union {
-    unsigned char ring[RT_STAGES * RT_STAGE_B];       // 128 KB
+    unsigned char ring[STAGES * STAGE_B];
     struct {
-      float W2s[RT_M * 32];          // [hidden][m-chunk of up to 32]
-      float red[2 * RT_N * 33];      // [wm][token][m-chunk], rows padded to 33 floats (bank spread)
+      float W2s[MT * 32];            // [hidden][m-chunk of up to 32]
+      float red[2 * NT * 33];        // [wm][token][m-chunk], rows padded to 33 floats (bank spread)
     } ep;
   };
 };
@@ -68,44 +75,47 @@ __device__ __forceinline__ float sum_across_halves(float x) {
 // applies SiLU and W2.  KSPLIT = false: the whole contraction, epilogue below.
 // NT = tokens per workgroup: 128 (2 x 2 wavefronts of 64 hidden units x 64 tokens), or 64 (64 x 32 each) for chunks
 // that would leave half of the CUs without a 128-token tile; the hidden block stays 128 wide.
-template <bool KSPLIT, int NT>
+template <bool KSPLIT, int MT, int NT>
 __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ v, int Tn, int hd, int kvd,
                                                          const bf16_t* __restrict__ W1t,
                                                          const float* __restrict__ W2f, int K, int h_kv,
                                                          float* __restrict__ part, int part_T,
                                                          float* __restrict__ zpart, int d_R) {
-  __shared__ __attribute__((aligned(1024))) ScoreSmem sm;
+  typedef ScoreSmem<MT, NT> Smem;
+  __shared__ __attribute__((aligned(1024))) Smem sm;
+  constexpr int RT_STAGES = Smem::STAGES, RT_STAGE_B = Smem::STAGE_B, RT_TILE_B = Smem::TILE_A;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31, hi = lane >> 5;
   const bool producer = wave >= 4;               // wave-uniform
-  const int pw = wave & 3;                       // producer: fills rows pw*32 .. pw*32+31 of both tiles
-  const int wm = (wave >> 1) & 1, wn = wave & 1; // consumer: 64 x 64 sub-tile
-  static_assert(NT == 128 || NT == 64, "token tile");
+  const int pw = wave & 3;                       // producer: fills a quarter of both tiles
+  const int wm = (wave >> 1) & 1, wn = wave & 1; // consumer: a quarter of the products
+  static_assert((MT == 128 || MT == 64) && (NT == 128 || NT == 64), "tiles");
+  constexpr int NBA = MT / 64;                   // 32-unit blocks per wavefront
+  constexpr int A_LOADS = MT / 32;               // direct loads of a producer for the weight tile of a stage
   constexpr int NBT = NT / 64;                   // 32-token blocks per wavefront
   constexpr int B_LOADS = NT / 32;               // direct loads of a producer for the token tile of a stage
   const int t0 = blockIdx.x * NT;
   const int nb = blockIdx.y;
-  const int r0 = nb * RT_M;
+  const int r0 = nb * MT;
 
-  f32x16 acc[2][NBT];
+  f32x16 acc[NBA][NBT];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NBA; ++a)
 #pragma unroll
     for (int b = 0; b < NBT; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-  // ---- loads: producer p fills rows p*32 .. p*32+31 of the weight tile and its quarter of the token tile, 8 rows
-  // per instruction ----
+  // ---- loads: producer p fills its quarters of the weight tile and of the token tile, 8 rows per instruction ----
   const int l_row = lane >> 3;                           // row inside the instruction's 8 rows
   // byte offset of the chunk this lane fetches: row = 8 * instruction + l_row, so (row >> 1) & 7 is
   // (l_row >> 1) for even instructions and (l_row >> 1) ^ 4 for odd ones (ii & 1 below)
   const int l_csw0 = ((lane & 7) ^ (l_row >> 1)) * 16;
   const int l_csw1 = ((lane & 7) ^ (l_row >> 1) ^ 4) * 16;
-  const int a_vo = (pw * 32 + l_row) * (K * 2);        // + ii * 8 rows + chunk offset
+  const int a_vo = (pw * (MT / 4) + l_row) * (K * 2);        // + ii * 8 rows + chunk offset
   const int b_row = pw * (NT / 4) + l_row;               // + ii * 8
   const int n_stages_all = K / RT_K;
   // this workgroup's stages: [s_lo, s_lo + n_stages)
@@ -122,11 +132,11 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
     const int s = s_lo + s_rel;
     {
       __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(W1t + (int64_t)r0 * K + (int64_t)s * RT_K), 0, live ? (RT_M * K * 2 - s * RT_K * 2) : 0, 0x00020000);
+          (void*)(W1t + (int64_t)r0 * K + (int64_t)s * RT_K), 0, live ? (MT * K * 2 - s * RT_K * 2) : 0, 0x00020000);
 #pragma unroll
-      for (int ii = 0; ii < 4; ++ii)
+      for (int ii = 0; ii < A_LOADS; ++ii)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            ar, (lds_ptr_t)(sm.ring + buf * RT_STAGE_B + (pw * 4 + ii) * 1024), 16, a_vo + ii * 8 * (K * 2) + ((ii & 1) ? l_csw1 : l_csw0), 0, 0, 0);
+            ar, (lds_ptr_t)(sm.ring + buf * RT_STAGE_B + (pw * A_LOADS + ii) * 1024), 16, a_vo + ii * 8 * (K * 2) + ((ii & 1) ? l_csw1 : l_csw0), 0, 0, 0);
     }
     {
       const bf16_t* src;
@@ -151,7 +161,7 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int pos = ((2 * ks + hi) ^ ((n32 >> 1) & 7)) * 16;
-    a_rd[ks] = (wm * 64 + n32) * 128 + pos;
+    a_rd[ks] = (wm * (MT / 2) + n32) * 128 + pos;
     b_rd[ks] = RT_TILE_B + (wn * (NT / 2) + n32) * 128 + pos;
   }
 
@@ -160,29 +170,35 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
   // MFMA, so every read has a full stage to arrive.  (Measured equal to reading six MFMAs ahead: a computing
   // wavefront takes about 720 cycles per stage for 512 cycles of MFMAs either way, almost none of them at the
   // barrier.)
-  constexpr int NFR = 4 * (2 + NBT);             // fragments of a stage: per contraction step 2 of W1, NBT of tokens
+  constexpr int NFK = NBA + NBT, NFR = 4 * NFK;  // fragments of a stage: per contraction step NBA of W1, NBT of tokens
   bf16x8 fr[2][NFR];
   auto fetch = [&](bf16x8 (&f)[NFR], int buf) {
     const unsigned char* base = sm.ring + buf * RT_STAGE_B;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      f[ks * (2 + NBT) + 0] = *(const bf16x8*)(base + a_rd[ks]);
-      f[ks * (2 + NBT) + 1] = *(const bf16x8*)(base + a_rd[ks] + 32 * 128);
-      f[ks * (2 + NBT) + 2] = *(const bf16x8*)(base + b_rd[ks]);
-      if (NBT == 2) f[ks * (2 + NBT) + 3] = *(const bf16x8*)(base + b_rd[ks] + 32 * 128);
+      f[ks * NFK + 0] = *(const bf16x8*)(base + a_rd[ks]);
+      if (NBA == 2) f[ks * NFK + 1] = *(const bf16x8*)(base + a_rd[ks] + 32 * 128);
+      f[ks * NFK + NBA] = *(const bf16x8*)(base + b_rd[ks]);
+      if (NBT == 2) f[ks * NFK + NBA + 1] = *(const bf16x8*)(base + b_rd[ks] + 32 * 128);
     }
   };
   auto compute = [&](bf16x8 (&f)[NFR], bf16x8 (&fn)[NFR], int next_buf) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < NBA; ++a)
 #pragma unroll
         for (int b = 0; b < NBT; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks * (2 + NBT) + a], f[ks * (2 + NBT) + 2 + b], acc[a][b], 0, 0, 0);
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks * NFK + a], f[ks * NFK + NBA + b], acc[a][b], 0, 0, 0);
     fetch(fn, next_buf);
-    // issue order: the fragment reads spread evenly behind the MFMAs (16 for 16, or 12 for 8)
-    if (NBT == 2) {
+    // issue order: the fragment reads spread evenly behind the MFMAs (16 for 16, 12 for 8, 8 for 4)
+    if (NBA == 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+    } else if (NBT == 2) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -202,37 +218,49 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
   // The load wavefronts fetch the W2 rows of this hidden block (first 32 KV heads, zero beyond h_kv) before the
   // pipeline starts and hold them until the epilogue: 16 registers they have to spare, and the epilogue does not
   // begin with a trip to memory.  Element i = hidden unit i / 32, KV head i % 32.
-  float w2pre[16];
+  constexpr int W2_PRE = MT * 32 / 256;
+  float w2pre[W2_PRE];
   if (!KSPLIT && producer) {
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
+    for (int jj = 0; jj < W2_PRE; ++jj) {
       const int i = (tid - 256) + 256 * jj, hh = i >> 5, mm = i & 31;
       const float x = W2f[(int64_t)(r0 + hh) * h_kv + min(mm, h_kv - 1)];     // address clamped, value masked: no branch
       w2pre[jj] = mm < h_kv ? x : 0.f;
     }
   }
 
-  // One barrier per stage.  Invariant at barrier s: stages up to s+1 are in LDS (a producer arrives once at
-  // most one stage = 8 of its loads is still in flight) and every consumer has left stage s-1.  Behind it a
-  // producer starts stage s+3 in the buffer of stage s-1; a consumer computes stage s and then requests the
+  // One barrier per stage.  Invariant at barrier s: stages up to s+1 are in LDS (a producer arrives once only its loads of
+  // stages s+2 .. s+RT_STAGES-2 are still in flight) and every consumer has left stage s-1.  Behind it a producer starts
+  // stage s+RT_STAGES-1 in the buffer of stage s-1; a consumer computes stage s and then requests the
   // first fragments of stage s+1.  A bare s_barrier: __syncthreads() would first drain every load in flight.
+  constexpr int PER_STAGE = A_LOADS + B_LOADS;
+  auto wait_all_but = [&](int stages) __attribute__((always_inline)) {      // wave-uniform
+    if (stages >= 5) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(5 * PER_STAGE) : "memory");
+    else if (stages == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * PER_STAGE) : "memory");
+    else if (stages == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * PER_STAGE) : "memory");
+    else if (stages == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER_STAGE) : "memory");
+    else if (stages == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_STAGE) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  static_assert(RT_STAGES - 3 <= 5 && RT_STAGES % 2 == 0, "waits; two register sets in turn");
   if (n_stages == 0) {
     // an empty slice (the host does not launch one): both roles skip the pipeline, the partial is zero
   } else if (producer) {
-    issue(0, 0);
-    if (1 < n_stages) issue(1, 1);
-    if (2 < n_stages) issue(2, 2);
+#pragma unroll
+    for (int u = 0; u < RT_STAGES - 1; ++u)
+      if (u < n_stages) issue(u, u);
     for (int s0 = 0; s0 < n_stages; s0 += RT_STAGES) {
 #pragma unroll
-      for (int u = 0; u < RT_STAGES; ++u)
-        if (s0 + u < n_stages) {
-          // at most stage s+2 may still be in flight; past the end nothing more is issued, and then the
-          // count has to drop to zero for stage s+1 to be known complete
-          if (s0 + u + 2 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + B_LOADS) : "memory");
-          else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      for (int u = 0; u < RT_STAGES; ++u) {
+        const int s = s0 + u;
+        if (s < n_stages) {
+          // (past the end nothing more is issued, and fewer stages are in flight)
+          if (s + RT_STAGES - 2 < n_stages) wait_all_but(RT_STAGES - 3);
+          else wait_all_but(n_stages - 2 - s);
           asm volatile("s_barrier" ::: "memory");
-          if (s0 + u + RT_STAGES - 1 < n_stages) issue(s0 + u + RT_STAGES - 1, (u + RT_STAGES - 1) % RT_STAGES);
+          if (s + RT_STAGES - 1 < n_stages) issue(s + RT_STAGES - 1, (u + RT_STAGES - 1) % RT_STAGES);
         }
+      }
     }
   } else {
     asm volatile("s_barrier" ::: "memory");
@@ -255,10 +283,10 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
         const int t = t0 + wn * (NT / 2) + b * 32 + n32;
         if (t >= Tn) continue;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < NBA; ++a)
 #pragma unroll
           for (int rq = 0; rq < 4; ++rq)
-            *(float4*)(zp + (int64_t)t * d_R + r0 + wm * 64 + a * 32 + rq * 8 + hi * 4) =
+            *(float4*)(zp + (int64_t)t * d_R + r0 + wm * (MT / 2) + a * 32 + rq * 8 + hi * 4) =
                 make_float4(acc[a][b][rq * 4 + 0], acc[a][b][rq * 4 + 1], acc[a][b][rq * 4 + 2], acc[a][b][rq * 4 + 3]);
       }
     }
@@ -266,7 +294,7 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
   }
   // ---- epilogue: SiLU in place, then W2 in chunks of up to 32 KV heads ---------------------------
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NBA; ++a)
 #pragma unroll
     for (int b = 0; b < NBT; ++b)
 #pragma unroll
@@ -281,9 +309,9 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
     __syncthreads();                               // ring / previous chunk no longer read
     if (m0 == 0 && producer) {
 #pragma unroll
-      for (int jj = 0; jj < 16; ++jj) sm.ep.W2s[(tid - 256) + 256 * jj] = w2pre[jj];
+      for (int jj = 0; jj < W2_PRE; ++jj) sm.ep.W2s[(tid - 256) + 256 * jj] = w2pre[jj];
     } else if (m0 > 0) {
-      for (int i = tid; i < RT_M * 32; i += 512) {
+      for (int i = tid; i < MT * 32; i += 512) {
         const int hh = i >> 5, mm = i & 31;
         sm.ep.W2s[i] = mm < mc ? W2f[(int64_t)(r0 + hh) * h_kv + m0 + mm] : 0.f;
       }
@@ -297,10 +325,10 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
 #pragma unroll
         for (int i = 0; i < 4; ++i) sb[b][i] = 0.f;
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < NBA; ++a)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int hh = wm * 64 + a * 32 + (r >> 2) * 8 + hi * 4 + (r & 3);
+          const int hh = wm * (MT / 2) + a * 32 + (r >> 2) * 8 + hi * 4 + (r & 3);
           const float4 w = *(const float4*)&sm.ep.W2s[hh * 32 + mq];
 #pragma unroll
           for (int b = 0; b < NBT; ++b) {
@@ -435,8 +463,10 @@ int score_parts_bf16(const Dims& D) {
 // launch split the contraction (short chunks: at most half as many tiles as CUs; each slice keeps at least 8
 // stages; Tuning::score_split: 0 = never, k = k slices).  Measured on 32q/8kv x 128, d_R = 1024, in microseconds
 // (hot caches): chunks of 2048 tokens 42.4 with 128-token tiles, 37.3 with 64-token tiles, 49.6 with those and two
-// slices; chunks of 1024 tokens 32.9 (128-token tiles, 4 slices), 33.3 (64-token tiles), 29.4 (64-token tiles,
-// 2 slices); chunks of 3072 or 4096 tokens are a third slower with 64-token tiles (more LDS traffic per MFMA).
+// slices; chunks of 3072 or 4096 tokens are a third slower with 64-token tiles (more LDS traffic per MFMA).  128 x 64 tiles with a
+// ring of six stages instead of four: 1500 tokens 33.0 -> 31.0, 2048 35.0 -> 33.0.  Where 128 x 64 tiles would need two or more slices
+// and their finish kernel, 64 x 64 tiles: 1024 tokens 26.1 -> 23.1, 800 33.4 -> 28.6, 611 26.7 -> 22.9 (inputs from HBM 29.7 -> 29.2,
+// 33.7 -> 30.0, 26.7 -> 27.3) and as many partials again to sum; split as well below that, 300 tokens 21.6 -> 20.0, 100 12.1 -> 11.2.
 int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
                       const float* W2f, float* part, hipStream_t st, float* zpart, size_t zpart_floats, float* single) {
   if (T == 1 && zpart != nullptr && D.tune.score_nt == 0 && D.tune.score_split < 0) {
@@ -450,10 +480,13 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
   // d_R = 1024).  Tuning::score_nt: 0 = this rule, 64 / 128 = always.
   const int tiles128 = ((T + 127) / 128) * (D.d_R / RT_M);
   const int nt = D.tune.score_nt == 64 || D.tune.score_nt == 128 ? D.tune.score_nt : (tiles128 <= 128 ? 64 : 128);
-  dim3 grid((T + nt - 1) / nt, D.d_R / RT_M);
+  const int forced = D.tune.score_split;
+  // Hidden tile: 64 where 64 x 64 tiles are at most one a CU (T <= 1024 at d_R = 1024) and their partials fit.
+  const int tiles64 = ((T + 63) / 64) * (D.d_R / 64);
+  const int mt = nt == 64 && forced < 0 && D.tune.score_nt == 0 && tiles64 <= 256 && (size_t)(D.d_R / 64) * D.h_kv * T <= SCORE_FINE_FLOATS ? 64 : RT_M;
+  dim3 grid((T + nt - 1) / nt, D.d_R / mt);
   int n_z = 1;
   if (zpart != nullptr) {
-    const int forced = D.tune.score_split;
     const int tiles = (int)(grid.x * grid.y), stages = D.K / RT_K;
     n_z = forced >= 0 ? forced : (256 / tiles >= 2 ? 256 / tiles : 1);
     n_z = n_z > 8 ? 8 : n_z;
@@ -462,16 +495,21 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
     if (n_z < 1) n_z = 1;
   }
   grid.z = n_z;
-  if (single && (n_z > 1 || D.d_R == RT_M)) part = single;
-#define LOCRET_SCORE_LAUNCH(KS, NTT)                                                                                  \
-  launch_kernel(score_mfma_kernel<KS, NTT>, grid, dim3(512), 0, st, (const bf16_t*)q, (const bf16_t*)k,                \
+  if (single && (n_z > 1 || D.d_R == mt)) part = single;
+#define LOCRET_SCORE_LAUNCH(KS, MTT, NTT)                                                                             \
+  launch_kernel(score_mfma_kernel<KS, MTT, NTT>, grid, dim3(512), 0, st, (const bf16_t*)q, (const bf16_t*)k,           \
                 (const bf16_t*)v, T, D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, W2f, D.K, D.h_kv, part, T,          \
                 KS ? zpart : (float*)nullptr, D.d_R)
+#define LOCRET_SCORE_TILE(KS)                            \
+  if (mt == 64) LOCRET_SCORE_LAUNCH(KS, 64, 64);         \
+  else if (nt == 64) LOCRET_SCORE_LAUNCH(KS, 128, 64);   \
+  else LOCRET_SCORE_LAUNCH(KS, 128, 128)
   if (n_z == 1) {
-    if (nt == 64) LOCRET_SCORE_LAUNCH(false, 64); else LOCRET_SCORE_LAUNCH(false, 128);
-    return D.d_R / RT_M;
+    LOCRET_SCORE_TILE(false);
+    return D.d_R / mt;
   }
-  if (nt == 64) LOCRET_SCORE_LAUNCH(true, 64); else LOCRET_SCORE_LAUNCH(true, 128);
+  LOCRET_SCORE_TILE(true);
+#undef LOCRET_SCORE_TILE
 #undef LOCRET_SCORE_LAUNCH
   launch_kernel(score_finish_kernel, dim3(T, (D.h_kv + 7) / 8), dim3(FIN_THREADS), 0, st, (const float*)zpart, n_z, T, D.d_R, W2f,
                      D.h_kv, part, T);

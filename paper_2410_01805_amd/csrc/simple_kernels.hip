@@ -233,8 +233,19 @@ __global__ void score_reduce_kernel(const float* __restrict__ part, int n_parts,
   int gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= h_kv * Tn) return;
   int m = gid / Tn, t = gid % Tn;
-  float sum = part[(int64_t)m * part_T + t];   // a single part is copied bit for bit (-0 stays -0)
-  for (int p = 1; p < n_parts; ++p) sum += part[((int64_t)p * h_kv + m) * part_T + t];
+  const float* src = part + (int64_t)m * part_T + t;
+  const int64_t step = (int64_t)h_kv * part_T;
+  float sum = src[0];   // a single part is copied bit for bit (-0 stays -0)
+  // in ascending order, eight loads under way together (a chain of latencies: 8 partials of 1500 tokens 4.6 -> 4.0 us)
+  constexpr int UN = 8;
+  for (int p = 1; p < n_parts; p += UN) {
+    float x[UN];
+#pragma unroll
+    for (int i = 0; i < UN; ++i) x[i] = src[min(p + i, n_parts - 1) * step];
+#pragma unroll
+    for (int i = 0; i < UN; ++i)
+      if (p + i < n_parts) sum += x[i];
+  }
   if (S) S[(int64_t)m * cap + head_len(n_c_h, m, n_c) + t] = sum;
   if (out) out[(int64_t)m * Tn + t] = sum;
 }

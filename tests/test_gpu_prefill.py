@@ -507,3 +507,14 @@ def test_partial_scores_are_summed_to_the_same_bits_wherever_that_is_done(dtype,
     for layer in (fused, plain):
         np.testing.assert_array_equal(layer.cache_tensors()[2][0].cpu().numpy(), S_ref)
         layer.close()
+
+
+@pytest.mark.parametrize("d_R,T", [(1024, 64), (1024, 65), (1024, 127), (1024, 513), (1024, 1024), (1024, 1025), (128, 2), (128, 1100), (256, 2048), (256, 2049)])
+def test_retaining_head_at_the_edges_of_its_tiles(d_R, T):
+    """64-unit tiles, split or whole, where there are at most 256 of 64 x 64, 128-unit tiles beyond; a last token tile of one token."""
+    w = synth.tiny(name=f"tiles_{d_R}_{T}", dtype="bf16", h=6, h_kv=3, d=64, N=T, B=T, b=T, n_s=0, d_R=d_R)
+    layer, W1, W2 = make_layer(w)
+    x = synth.tokens(w, 0, T)
+    sc = layer.score(*(dev(t, w) for t in x)).cpu().numpy()
+    assert_close(sc, make_oracle(w, W1, W2).score(*x), w.dtype, w.name)
+    layer.close()
