@@ -87,8 +87,8 @@ void fill_dims(const locret_config* c, Dims* D) {
 }
 
 int max_score_parts(const Dims& D) {
-  int a = score_parts_simple(D), b = score_parts_bf16(D);
-  return a > b ? a : b;
+  const int a = score_parts_simple(D), b = score_parts_bf16(D), c = D.bf16 ? 0 : score_parts_f32_most(D);
+  return a > b && a > c ? a : b > c ? b : c;
 }
 
 void make_layout(const locret_config* c, const Dims& D, Layout* L) {
@@ -344,7 +344,7 @@ int locret_reset(locret_ctx* c) {
 // workspace's buffers
 static void run_score(locret_ctx* c, const void* q, const void* k, const void* v, int T, float* S_dst, int n_c,
                       float* out, hipStream_t st, bool reduce = true, int* n_parts = nullptr, float* part = nullptr,
-                      float* zpart = nullptr, size_t zpart_floats = 0) {
+                      float* zpart = nullptr, size_t zpart_floats = 0, const ChunkAppend* app = nullptr) {
   HeadLens hl_tmp;
   if (!part) {
     part = (float*)(c->ws + c->L.part);
@@ -361,8 +361,7 @@ static void run_score(locret_ctx* c, const void* q, const void* k, const void* v
                               zpart_floats ? zpart : nullptr, zpart_floats, single);
     done = single && parts == 1;
   } else {
-    launch_score_simple(c->D, q, k, v, T, c->ws + c->L.W1t, (const float*)(c->ws + c->L.W2f), part, st);
-    parts = score_parts_simple(c->D);
+    parts = launch_score_simple(c->D, q, k, v, T, c->ws + c->L.W1t, (const float*)(c->ws + c->L.W2f), part, st, app);
   }
   if (n_parts) *n_parts = parts;
   if (reduce && !done) launch_score_reduce(part, parts, T, c->D.h_kv, T, S_dst, c->D.cap, n_c, out, st, c->lens(&hl_tmp));
@@ -454,8 +453,12 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
   HeadLens hl_tmp;
   const HeadLens* hl = c->lens(&hl_tmp);      // per-head cache lengths before this chunk, or NULL
   c->mark(0, 0, st);
+  // float32 layers: the append rides in the launch of the retaining head, which then comes before the attention (except in a profiled
+  // call, whose stages have times of their own)
+  const bool ride = !D.bf16 && c->prof_calls >= c->prof_max;
+  const ChunkAppend app = {fused_q ? nullptr : q, c->n_c, c->seen, A, qr, tab, hl};
   if (D.kv_bits) launch_append_q4(D, k, v, T, c->n_c, c->seen, A, tab, st);
-  else launch_append(D, fused_q ? nullptr : q, k, v, T, c->n_c, c->seen, A, qr, tab, st, nullptr, hl);
+  else if (!ride) launch_append(D, fused_q ? nullptr : q, k, v, T, c->n_c, c->seen, A, qr, tab, st, nullptr, hl);
   c->mark(0, 1, st);
   const void* qx = (D.rope && !fused_q) ? qr : q;
   const void* Kx = D.rope ? A.Kr : A.K;
@@ -486,7 +489,7 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     c->mark(2, 0, st);
     if (sel && !scores_in) {
       int parts = 0;
-      run_score(c, q, k, v, T, nullptr, n_c, nullptr, st, /*reduce=*/false, &parts);
+      run_score(c, q, k, v, T, nullptr, n_c, nullptr, st, /*reduce=*/false, &parts, nullptr, nullptr, 0, ride ? &app : nullptr);
       const float* part = (const float*)(c->ws + c->L.part);
       const bool sums = !in_attention ? select_sums_partials(T)
                         : c->mfma_attn ? attention_bf16_sums_partials(parts, T) : attention_f32_sums_partials(D, parts, T);
@@ -502,7 +505,7 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
         launch_score_reduce(part, parts, T, D.h_kv, T, A.S, D.cap, n_c, scores_out, st, hl);
       }
     } else {
-      run_score(c, q, k, v, T, scores_in ? nullptr : A.S, n_c, scores_out, st);
+      run_score(c, q, k, v, T, scores_in ? nullptr : A.S, n_c, scores_out, st, true, nullptr, nullptr, nullptr, 0, ride ? &app : nullptr);
       if (scores_in) launch_score_reduce(scores_in, 1, T, D.h_kv, T, A.S, D.cap, n_c, nullptr, st, hl);
     }
     c->mark(2, 1, st);
@@ -531,8 +534,9 @@ int locret_prefill_chunk(locret_ctx* c, const void* q, const void* k, const void
     attention(&sa);
     run_evict(c, sa, st, /*select_done=*/true);
   } else {
-    attention(nullptr);
+    if (!ride) attention(nullptr);
     scores(evict && over_budget(c, sa) ? &sa : nullptr, false);
+    if (ride) attention(nullptr);
     if (evict) run_evict(c, sa, st);
     else {
       grow(c, T);

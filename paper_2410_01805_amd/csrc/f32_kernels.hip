@@ -9,6 +9,7 @@
 // (attention: of keys and values; every wavefront reads the queries) is read twice by a workgroup, and meet in LDS at the
 // end.  That also fills the chip at the small sizes float32 layers have: 512 tokens x 8 heads are 256 workgroups of 8
 // wavefronts.
+#include "append_body.h"
 #include "device_util.h"
 #include "kernels.h"
 #include "select_body.h"
@@ -246,63 +247,75 @@ void launch_attention_f32(const Dims& Dm, const void* q, const void* Kx, const v
 }
 
 // ---- retaining head ------------------------------------------------------------------------------------------------
-// Workgroup = 64 hidden units x 16 tokens; wavefront w takes contraction steps w, w + 8, ... of 16 elements (each inside one
+// Workgroup = HB hidden units x 16 tokens; wavefront w takes contraction steps w, w + 8, ... of 16 elements (each inside one
 // of q, k, v: the [q;k;v] row is read in place).  The wavefronts' sums are added in a fixed order, then SiLU and
-// the product with W2; each workgroup writes its hidden block's partial part[nb][m][t].
-// 512 tokens x 768 inputs x 256 hidden: 10.6 us against 95.7 of 64 x 64 vector-ALU tiles.
-constexpr int F32_HB = 64, F32_TB = 16;
+// the product with W2; each workgroup writes its hidden block's partial part[nb][m][t].  HB = 32 for chunks whose 64-unit
+// workgroups would leave CUs without one, else 64, which reads the tokens half as often: 768 inputs x 256 hidden, 512 tokens
+// 12.7 us with 64, 11 with 32 (1536 inputs 19.0, 13.0), 1024 tokens 13.1, 16.4, 4096 tokens 34.5, 49.8; vector-ALU tiles
+// of 64 x 64 took 95.7 at 512 tokens.  (Two steps' loads under way ahead of the present one: 512 tokens 14.4 us, 4096 43.)
+// APPEND 1 (2: with head-wise lengths): workgroups behind the n_nb hidden blocks, two of the append's each, append the chunk, which
+// depends on nothing this launch does: a launch of 3.4 us less (4096 tokens in chunks of 512, 2 x 64 dims: 280 -> 272 us, with HB = 32 238).
+constexpr int F32_TB = 16;
+template <int HB, int APPEND>
 __global__ __launch_bounds__(F32_NW * 64) void score_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                                                                 const float* __restrict__ v, int Tn, int hd, int kvd,
                                                                 const float* __restrict__ W1t, const float* __restrict__ W2f,
-                                                                int K, int d_R, int h_kv, float* __restrict__ part, int part_T) {
-  __shared__ float hs[F32_NW][F32_TB][F32_HB + 1];
+                                                                int K, int d_R, int h_kv, float* __restrict__ part, int part_T,
+                                                                int n_nb, AppendArgs<float> ap) {
+  if (APPEND && (int)blockIdx.z >= n_nb) {
+    const int64_t wg = ((int64_t)((int)blockIdx.z - n_nb) * (gridDim.x * gridDim.y) + f32_workgroup()) * (F32_NW / 4) + (threadIdx.x >> 8);
+    if (wg < (int64_t)ap.gx * ap.gy) append_any<float, APPEND == 2, false>(ap, (int)(wg % ap.gx), (int)(wg / ap.gx), threadIdx.x & 255);
+    return;
+  }
+  constexpr int NA = HB / 16, UNITS = HB / 8;      // blocks of hidden units; units of a lane in the product with W2
+  __shared__ float hs[F32_NW][F32_TB][HB + 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, kg = lane >> 4;
-  const int t0 = f32_workgroup() * F32_TB, nb = blockIdx.z, n0 = nb * F32_HB;
+  const int t0 = f32_workgroup() * F32_TB, nb = blockIdx.z, n0 = nb * HB;
   if (t0 >= Tn) return;
   const int t = min(t0 + i16, Tn - 1);
-  const float* wp[4];                          // hidden units past the last repeat it (no weight of W2 is applied to them)
+  const float* wp[NA];                          // hidden units past the last repeat it (no weight of W2 is applied to them)
 #pragma unroll
-  for (int a = 0; a < 4; ++a) wp[a] = W1t + (int64_t)min(n0 + a * 16 + i16, d_R - 1) * K + kg * 4;
+  for (int a = 0; a < NA; ++a) wp[a] = W1t + (int64_t)min(n0 + a * 16 + i16, d_R - 1) * K + kg * 4;
   auto x_ptr = [&](int c) -> const float* {
     if (c < hd) return q + (int64_t)t * hd + c + kg * 4;
     if (c < hd + kvd) return k + (int64_t)t * kvd + (c - hd) + kg * 4;
     return v + (int64_t)t * kvd + (c - hd - kvd) + kg * 4;
   };
-  f32x4 acc[4];
+  f32x4 acc[NA];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int a = 0; a < NA; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int c = wave * 16; c < K; c += F32_NW * 16) {
-    float x[4], w[4][4];
+    float x[4], w[NA][4];
     load_floats<4>(x_ptr(c), x);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) load_floats<4>(wp[a] + c, w[a]);
+    for (int a = 0; a < NA; ++a) load_floats<4>(wp[a] + c, w[a]);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[a][e], x[e], acc[a], 0, 0, 0);
+      for (int a = 0; a < NA; ++a) acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[a][e], x[e], acc[a], 0, 0, 0);
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) hs[wave][i16][a * 16 + 4 * kg + r] = acc[a][r];
   __syncthreads();
-  for (int i = tid; i < F32_TB * F32_HB; i += F32_NW * 64) {
-    const int tl = i / F32_HB, n = i % F32_HB;
+  for (int i = tid; i < F32_TB * HB; i += F32_NW * 64) {
+    const int tl = i / HB, n = i % HB;
     float z = hs[0][tl][n];
 #pragma unroll
     for (int w = 1; w < F32_NW; ++w) z += hs[w][tl][n];
     hs[0][tl][n] = z / (1.f + expf(-z));
   }
   __syncthreads();
-  // eight lanes per score, eight hidden units each
-  const int n_out = F32_TB * h_kv, hh_end = min(F32_HB, d_R - n0);
+  // eight lanes per score, UNITS hidden units each
+  const int n_out = F32_TB * h_kv, hh_end = min(HB, d_R - n0);
   for (int i = tid; i < n_out * 8; i += F32_NW * 64) {
-    const int o8 = i >> 3, tl = o8 % F32_TB, m = o8 / F32_TB, n1 = (i & 7) * 8;
+    const int o8 = i >> 3, tl = o8 % F32_TB, m = o8 / F32_TB, n1 = (i & 7) * UNITS;
     float sum = 0.f;
 #pragma unroll
-    for (int n = 0; n < 8; ++n)
+    for (int n = 0; n < UNITS; ++n)
       if (n1 + n < hh_end) sum = fmaf(hs[0][tl][n1 + n], W2f[(int64_t)(n0 + n1 + n) * h_kv + m], sum);
     sum += __shfl_xor(sum, 1, 64);
     sum += __shfl_xor(sum, 2, 64);
@@ -311,13 +324,35 @@ __global__ __launch_bounds__(F32_NW * 64) void score_f32_kernel(const float* __r
   }
 }
 
-int score_parts_f32(const Dims& D) { return (D.d_R + F32_HB - 1) / F32_HB; }
+int score_parts_f32(const Dims& D) { return (D.d_R + 63) / 64; }
+int score_parts_f32_most(const Dims& D) { return (D.d_R + 31) / 32; }
+// Hidden units of a workgroup: 32 where 64 would leave CUs without one.
+static int f32_hidden_block(const Dims& D, int T) {
+  return (int64_t)((T + F32_TB - 1) / F32_TB) * score_parts_f32(D) < 256 &&
+         (size_t)score_parts_f32_most(D) * D.h_kv * T <= SCORE_FINE_FLOATS ? 32 : 64;
+}
 
-void launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
-                      float* part, hipStream_t st) {
-  launch_kernel(score_f32_kernel, f32_rows((T + F32_TB - 1) / F32_TB, (D.d_R + F32_HB - 1) / F32_HB), dim3(F32_NW * 64), 0, st,
-                (const float*)q, (const float*)k, (const float*)v, T, D.h * D.d, D.h_kv * D.d, (const float*)W1t, W2f, D.K, D.d_R,
-                D.h_kv, part, T);
+int launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
+                     float* part, hipStream_t st, const ChunkAppend* app) {
+  const int hb = f32_hidden_block(D, T), nb = (D.d_R + hb - 1) / hb;
+  dim3 grid = f32_rows((T + F32_TB - 1) / F32_TB, nb);
+  AppendArgs<float> ap = {};
+  if (app) {
+    ap = append_args<float>(D, app->q, k, v, T, app->n_c, app->seen, app->c, app->qr, app->tab, nullptr, app->n_c_h, nullptr, 0);
+    const int64_t layer = (int64_t)grid.x * grid.y * (F32_NW / 4);
+    grid.z += (unsigned)(((int64_t)ap.gx * ap.gy + layer - 1) / layer);
+  }
+#define LOCRET_SCORE(HB, AP)                                                                                                     \
+  launch_kernel((score_f32_kernel<HB, AP>), grid, dim3(F32_NW * 64), 0, st, (const float*)q, (const float*)k, (const float*)v, T, \
+                D.h * D.d, D.h_kv * D.d, (const float*)W1t, W2f, D.K, D.d_R, D.h_kv, part, T, nb, ap)
+#define LOCRET_SCORE_AP(HB)                          \
+  if (!app) LOCRET_SCORE(HB, 0);                     \
+  else if (ap.n_c_h.ragged) LOCRET_SCORE(HB, 2);     \
+  else LOCRET_SCORE(HB, 1)
+  if (hb == 32) { LOCRET_SCORE_AP(32); } else { LOCRET_SCORE_AP(64); }
+#undef LOCRET_SCORE_AP
+#undef LOCRET_SCORE
+  return nb;
 }
 
 }  // namespace locret

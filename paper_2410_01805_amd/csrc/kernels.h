@@ -180,9 +180,21 @@ void launch_attention_f32(const Dims& D, const void* q, const void* Kx, const vo
 bool attention_f32_fuses_select(const Dims& D, int n_cand);
 // True when that selection is also the place to sum n_parts partial scores of T tokens (SelectArgs::part).
 bool attention_f32_sums_partials(const Dims& D, int n_parts, int T);
-int score_parts_f32(const Dims& D);
-void launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
-                      float* part, hipStream_t st);
+int score_parts_f32(const Dims& D);            // of long chunks
+int score_parts_f32_most(const Dims& D);       // of short ones
+// app: an append to carry out in the same launch (as launch_append with these arguments), or NULL
+struct ChunkAppend {
+  const void* q;          // queries to rotate into qr, or NULL
+  int n_c;
+  int64_t seen;
+  CacheBuf c;
+  void* qr;
+  const float2* tab;
+  const HeadLens* n_c_h;
+};
+// Returns the number of partials it wrote.
+int launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
+                     float* part, hipStream_t st, const ChunkAppend* app = nullptr);
 // bf16 MFMA kernel with K/V staged global -> LDS directly and the two wavefronts of every SIMD held one S block
 // apart (attention_pp.hip; d = 128, 96 or 64); false if the shape is not covered.
 bool launch_attention_bf16_pp(const Dims& D, LaunchTimer tm, const void* q, const float2* tab, const void* Kx,
@@ -234,8 +246,9 @@ constexpr size_t SCORE_FINE_FLOATS = (size_t)1 << 20;
 // blocks nb through *n_parts.  `part` must hold (d_R/score_part_width) * h_kv * chunk_max floats.
 int score_parts_simple(const Dims& D);
 int score_parts_bf16(const Dims& D);
-void launch_score_simple(const Dims& D, const void* q, const void* k, const void* v, int T,
-                         const void* W1t, const float* W2f, float* part, hipStream_t st);
+// Returns the number of partials it wrote.
+int launch_score_simple(const Dims& D, const void* q, const void* k, const void* v, int T,
+                        const void* W1t, const float* W2f, float* part, hipStream_t st, const ChunkAppend* app = nullptr);
 // Returns the number of partials it wrote (1 when it split the contraction instead, which needs `zpart`).  A single one is
 // the scores themselves and goes to `single` [h_kv][T] if that is not NULL.
 int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v, int T,

@@ -215,15 +215,13 @@ __global__ __launch_bounds__(256) void score_simple_kernel(const bf16_t* __restr
 
 int score_parts_simple(const Dims& D) { return D.bf16 ? (D.d_R + SC_TN - 1) / SC_TN : score_parts_f32(D); }
 
-void launch_score_simple(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
-                         const float* W2f, float* part, hipStream_t st) {
-  if (!D.bf16) {
-    launch_score_f32(D, q, k, v, T, W1t, W2f, part, st);
-    return;
-  }
+int launch_score_simple(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
+                        const float* W2f, float* part, hipStream_t st, const ChunkAppend* app) {
+  if (!D.bf16) return launch_score_f32(D, q, k, v, T, W1t, W2f, part, st, app);
   dim3 grid((T + SC_TM - 1) / SC_TM, (D.d_R + SC_TN - 1) / SC_TN);
   launch_kernel(score_simple_kernel, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, T,
                 D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, W2f, D.K, D.d_R, D.h_kv, part, T);
+  return score_parts_simple(D);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -518,3 +518,29 @@ def test_retaining_head_at_the_edges_of_its_tiles(d_R, T):
     sc = layer.score(*(dev(t, w) for t in x)).cpu().numpy()
     assert_close(sc, make_oracle(w, W1, W2).score(*x), w.dtype, w.name)
     layer.close()
+
+
+@pytest.mark.parametrize("kw,budgets,evict", [
+    (dict(h=4, h_kv=2, d=64, B=300, b=500, n_s=20, d_R=100), None, True),
+    (dict(h=4, h_kv=2, d=16, B=1, b=6, n_s=2, d_R=64), None, True),
+    (dict(h=4, h_kv=4, d=32, B=200, b=600, n_s=20, d_R=256), [600, 100, 300, 250], True),
+    (dict(h=2, h_kv=1, d=96, B=130, b=700, n_s=20, d_R=64), None, False),
+], ids=["rope", "one_token", "head_budgets", "no_eviction"])
+def test_float32_append_in_the_launch_of_the_retaining_head(kw, budgets, evict):
+    """A profiled call launches the append by itself: the same bits throughout."""
+    from paper_2410_01805_amd import binding as B
+    w = synth.tiny(name="ride", dtype="f32", N=5 * kw["B"], **kw)
+    riding, _, _ = make_layer(w)
+    alone, _, _ = make_layer(w)
+    B.locret_profile_enable(alone.ctx, 5)
+    for layer in (riding, alone):
+        layer.set_head_budgets(budgets)
+    for c in range(5):
+        x = [dev(t, w) for t in synth.chunk(w, c)]
+        for a, b in zip(riding.prefill_chunk(*x, w.n_s, evict=evict), alone.prefill_chunk(*x, w.n_s, evict=evict)):
+            assert (a is None and b is None) or torch.equal(a, b)
+    for a, b in zip(riding.cache_tensors(), alone.cache_tensors()):
+        for m, n in enumerate(riding.cache_lens):
+            assert torch.equal(a[m, :n], b[m, :n])
+    riding.close()
+    alone.close()
