@@ -183,3 +183,31 @@ def test_decode_block_edges(h, h_kv, d):
     expect[:g, 5] = True
     assert torch.equal(out == float("inf"), expect) and bool(torch.isfinite(out[~expect]).all())
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 96), ("bf16", 128), ("bf16", 64)])
+def test_decode_merge_of_many_splits(dtype, d, monkeypatch):
+    """Splits of 64 keys (LOCRET_DEC_KEYS), 3 ... 260 of them, around what the merge requests at once (96) and holds the weights of
+    (128), against splits at least four times as long.  Same arithmetic on the keys, so float32 results differ by the order
+    of sums of convex weights (2^-20 is 16 roundings), bf16 ones by that before one rounding (2^-7: two neighbours)."""
+    w = synth.tiny(name="merge", dtype=dtype, h=4, h_kv=2, d=d, N=17000, B=17000, b=17000, n_s=0, d_R=128)
+    layers = []
+    for keys in ("64", "320"):
+        monkeypatch.setenv("LOCRET_DEC_KEYS", keys)
+        layers.append(make_layer(w)[0])
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    rnd = lambda *s: torch.randn(*s, device=DEV, generator=gen).to(tdt)
+    n = 0
+    for splits in (2, 63, 64, 65, 94, 95, 96, 97, 126, 127, 128, 129, 130, 191, 259):
+        k, v = rnd(64 * splits - n, 2, d), rnd(64 * splits - n, 2, d)
+        token = rnd(1, 4, d), rnd(1, 2, d), rnd(1, 2, d)
+        outs = []
+        for layer in layers:
+            layer.evict_compact(torch.zeros(2, len(k), device=DEV), k, v, 0)
+            outs.append(layer.decode_step(*token)[0].float())
+        n = 64 * splits + 1
+        err = (outs[0] - outs[1]).abs().max() / outs[1].abs().max()
+        assert err <= (2.0 ** -20 if dtype == "f32" else 2.0 ** -7), (splits, float(err))
+    for layer in layers:
+        layer.close()
