@@ -3,9 +3,9 @@
 //
 // The instruction takes one float per lane of each operand, A[i = lane % 16][k = lane / 16] and
 // B[k = lane / 16][j = lane % 16], and leaves C[4 (lane / 16) + r][lane % 16] in register r.  A contraction may run over
-// its terms in any order as long as both operands agree, so every operand is fetched 16 bytes at a time straight
-// from memory: a lane's four consecutive elements feed four instructions.  Nothing is staged in LDS: the wavefronts
-// of a workgroup divide the contraction (attention: the keys) among themselves, so no element of W1 and of the inputs
+// its terms in any order as long as both operands agree, so every operand is fetched 16 bytes at a time: a lane's four
+// consecutive elements feed four instructions.  Operands come straight from memory, only the keys by way of LDS.  The wavefronts of
+// a workgroup divide the contraction (attention: the keys) among themselves, so no element of W1 and of the inputs
 // (attention: of keys and values; every wavefront reads the queries) is read twice by a workgroup, and meet in LDS at the
 // end.  That also fills the chip at the small sizes float32 layers have: 512 tokens x 8 heads are 256 workgroups of 8
 // wavefronts.
@@ -44,9 +44,19 @@ template <int N> __device__ __forceinline__ void load_floats(const float* p, flo
 // one query block, by the L2 (a key row is read once per 16 queries): 512 tokens on 1024 + 512 units,
 // 8 heads x 64: 21 us against 199 of a vector-ALU kernel with K, V and P tiles in LDS; the error against 64 bits halved.
 // QB = 2 where that still gives every CU a workgroup.
+// The keys pass through LDS, two tiles of the wavefront's own: straight into the operand's layout 16 neighbouring lanes read 16 rows, a cache
+// line each (4096 tokens in chunks of 512 on 64 dims 236 -> 227 us, 2900 tokens in chunks of 921 with rotary 205 -> 195, 128 dims
+// 719 -> 680).  What is left is not memory: without any load in the loop a step on 1536 keys takes 19.2 us instead of 21.0, without either
+// product 16.5.  (Two tiles ahead in registers 245 us, 16 wavefronts 255, the next tile's S beside the softmax 230.)
 // The first n_sel workgroups of the launch do not attend: each carries out the selection of one KV head, which depends on
 // the scores only, and sums their partials.  As a launch of its own it took 8.4 us behind 20 us of attention (2 heads, 1472
 // candidates): 4096 tokens in chunks of 512 333 us, 279 us in this form.
+typedef __attribute__((address_space(3))) void* f32_lds_ptr;
+// Rows of D floats in LDS: what the pieces of row r are exchanged by, so that 16 lanes that read the same piece of 16 rows meet 16
+// different groups of four banks (row r starts at group (r D / 4) mod 16)
+template <int D> __device__ __forceinline__ int f32_swizzle(int r) {
+  return D == 16 ? (r >> 2) & 3 : D == 32 || D == 96 ? (r >> 1) & 7 : r & 15;
+}
 constexpr int F32_SEL_MAXR = 24;               // keys per thread of a selection workgroup: up to 12288 candidates per head
 template <int D, int QB>
 __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ Kx,
@@ -57,8 +67,9 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
   constexpr int V4 = D / 64 * 64;              // dims fetched four (then two, one) per lane
   constexpr int V2 = (D - V4) / 32 * 32;
   constexpr int ROW = D + 2;
-  constexpr int RED = F32_NW * 16 * QB * ROW, SEL = select_body_smem_words(F32_NW * 64, 1);
-  __shared__ __attribute__((aligned(16))) float smem[RED > SEL ? RED : SEL];
+  constexpr int TILE = 16 * D;                 // floats of a key tile
+  constexpr int RED = F32_NW * 16 * QB * ROW, SEL = select_body_smem_words(F32_NW * 64, 1), KEYS = F32_NW * 2 * TILE;
+  __shared__ __attribute__((aligned(1024))) float smem[RED > SEL ? (RED > KEYS ? RED : KEYS) : (SEL > KEYS ? SEL : KEYS)];
   const int wg = f32_workgroup();
   if (wg < n_sel) {
     select_reg_body<F32_SEL_MAXR, F32_NW * 64, 1>(sel, wg, (uint32_t*)smem);
@@ -100,12 +111,29 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
     for (int c = 0; c < NC; ++c) o[b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   float kf[NC][4], vf[4][NC];
-  auto load_k = [&](int k0) {                  // rows past the end repeat the last one (masked below)
-    const float* kp = Kb + (int64_t)min(k0 + i16, n_keys - 1) * D + kg * 4;
+  // This wavefront's two key tiles in LDS.  Position p of row r holds the row's 16-byte piece p ^ f32_swizzle(r).
+  float* const keys = smem + wave * (2 * TILE);
+  constexpr int PIECES = D / 4;                // of a row
+  int piece[NC];                               // where in the tile the pieces that this lane requests lie (bytes)
 #pragma unroll
-    for (int c = 0; c < NC; ++c) load_floats<4>(kp + c * 16, kf[c]);
+  for (int i = 0; i < NC; ++i) {
+    const int x = i * 64 + lane, r = x / PIECES;
+    piece[i] = (r * PIECES + ((x % PIECES) ^ f32_swizzle<D>(r))) * 16;
+  }
+  auto request_k = [&](int k0, int buf) __attribute__((always_inline)) {      // rows past the end arrive as zeros (masked below)
+    __amdgpu_buffer_rsrc_t src =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(Kb + (int64_t)k0 * D), 0, min(16, n_keys - k0) * (D * 4), 0x00020000);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int at = piece[i];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (f32_lds_ptr)(keys + buf * TILE + i * 256), 16, at, 0, 0, 0);
+    }
   };
-  auto load_v = [&](int k0) {
+  auto read_k = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) load_floats<4>(keys + buf * TILE + i16 * D + (((4 * c + kg) ^ f32_swizzle<D>(i16)) * 4), kf[c]);
+  };
+  auto load_v = [&](int k0) {                  // rows past the end repeat the last one
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float* vp = Vb + (int64_t)min(k0 + 4 * kg + r, n_keys - 1) * D;
@@ -115,10 +143,14 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
       if constexpr (D - V4 - V2 > 0) load_floats<1>(vp + V4 + V2 + i16, &vf[r][(V4 + V2) / 16]);
     }
   };
-  int k0 = wave * 16;
-  if (k0 < n_keys) load_k(k0);
-  for (; k0 < n_keys; k0 += F32_NW * 16) {
+  int k0 = wave * 16, buf = 0;
+  if (k0 < n_keys) request_k(k0, 0);
+  for (; k0 < n_keys; k0 += F32_NW * 16, buf ^= 1) {
+    // all that is in flight here is this tile's keys, requested a tile ago (the tiles are the wavefront's own: no barrier)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    read_k(buf);
     load_v(k0);
+    if (k0 + F32_NW * 16 < n_keys) request_k(k0 + F32_NW * 16, buf ^ 1);
     f32x4 s[QB][2];
 #pragma unroll
     for (int b = 0; b < QB; ++b) s[b][0] = s[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -128,7 +160,6 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int b = 0; b < QB; ++b) s[b][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[b][c][e], s[b][e & 1], 0, 0, 0);
-    if (k0 + F32_NW * 16 < n_keys) load_k(k0 + F32_NW * 16);
     float p[QB][4];
 #pragma unroll
     for (int b = 0; b < QB; ++b) {
@@ -163,6 +194,7 @@ __global__ __launch_bounds__(F32_NW * 64) void attn_f32_kernel(const float* __re
 #pragma unroll
         for (int b = 0; b < QB; ++b) o[b][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][c], p[b][r], o[b][c], 0, 0, 0);
   }
+  __syncthreads();                             // the results go where the key tiles were
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
     l_run[b] += __shfl_xor(l_run[b], 16, 64);
