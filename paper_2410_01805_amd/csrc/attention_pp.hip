@@ -26,7 +26,7 @@
 // so the matrix pipe sees S_A, S_B, PV_A, PV_B back to back while each softmax runs beside the
 // other group's MFMAs.  Group B issues all direct loads (8 per wavefront per tile) in the slot in
 // which it waits for A's S block; group A uses its slot at the end of the tile to fetch the first K
-// fragments of the next one.  A passes Y four MFMAs before the end of its S block (all its fragment reads
+// fragments of the next one.  A passes Y some MFMAs before the end of its S block (four with 128 dims; all its fragment reads
 // are out by then), so B's first MFMAs queue behind A's last ones instead of meeting an idle pipe.
 //
 // The first workgroups of the launch can carry the step's selection (and the sum of the retaining head's
@@ -62,7 +62,10 @@ __host__ __device__ constexpr int pp_tile_keys(int d) { return d == 64 ? 2 * PP_
 constexpr int PP_STAGE_B = 2 * PP_TILE_B;      // K then V
 constexpr int PP_NW = 8;
 constexpr int PP_KPRE = 4;                     // K fragments fetched ahead of the S block
-constexpr int PP_YTAIL = 4;                    // MFMAs of group A's S block issued behind barrier Y
+// MFMAs of group A's S block issued behind barrier Y.  Fewer where the softmax takes the longer part of a tile: 96 dims, 20480 tokens on
+// 32 heads of 8192 units, with 1, 2, 3, 4: 2474, 2460, 2491, 2478 us a prompt (head-wise budgets 1032, 1044, 1045, 1049); 64 dims, 10000
+// tokens on 8 heads of 4096: 513, 516, 517, 518 (cut items 1052, 1055, 1056, 1056); 128 dims, 15900 tokens on 8 of 6144 with 2, 4, 6: 1825, 1820, 1848.
+constexpr int pp_ytail(int d, bool general) { return d == 128 ? 4 : d == 96 && !general ? 2 : 1; }
 constexpr int PP_SEL_MAXR = 48;                // keys per thread of a selection workgroup (512 threads)
 constexpr int PP_MAX_PARTS = 16;               // key ranges per (head group, token tile) item at most
 constexpr int PP_MAX_SLOTS = 256;              // partial results (256 query rows each) the buffer holds at most
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(PP_NW * 64, 2) void attn_pp_kernel(const bf16_t* __
       const int sb_off = (t & 3) * PP_STAGE_B;
       wg_barrier();                                              // X(t)
       f32x16 sacc[NKB];
-      s_block(sacc, sb_off, wg_barrier, IntC<PP_YTAIL>());        // Y(t), passed PP_YTAIL MFMAs before the end of the block
+      s_block(sacc, sb_off, wg_barrier, IntC<pp_ytail(D, GENERAL)>());        // Y(t), passed that many MFMAs before the end of the block
       softmax_pv(sacc, t_lo + t, sb_off);
       prefetch_k(((t + 1) & 3) * PP_STAGE_B);
     }
