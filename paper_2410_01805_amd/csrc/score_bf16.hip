@@ -101,13 +101,18 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
   const int nb = blockIdx.y;
   const int r0 = nb * MT;
 
-  f32x16 acc[NBA][NBT];
+  // One product a step would be a single chain of sums over the whole contraction: four chains, one for each step of a stage, keep
+  // the error where slices of the contraction have it.
+  constexpr int CHAINS = NBA * NBT == 1 ? 4 : 1;
+  f32x16 sums[CHAINS][NBA][NBT];
 #pragma unroll
-  for (int a = 0; a < NBA; ++a)
+  for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
-    for (int b = 0; b < NBT; ++b)
+    for (int a = 0; a < NBA; ++a)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+      for (int b = 0; b < NBT; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sums[c][a][b][r] = 0.f;
 
   // ---- loads: producer p fills its quarters of the weight tile and of the token tile, 8 rows per instruction ----
   const int l_row = lane >> 3;                           // row inside the instruction's 8 rows
@@ -189,7 +194,7 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
       for (int a = 0; a < NBA; ++a)
 #pragma unroll
         for (int b = 0; b < NBT; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks * NFK + a], f[ks * NFK + NBA + b], acc[a][b], 0, 0, 0);
+          sums[ks % CHAINS][a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[ks * NFK + a], f[ks * NFK + NBA + b], sums[ks % CHAINS][a][b], 0, 0, 0);
     fetch(fn, next_buf);
     // issue order: the fragment reads spread evenly behind the MFMAs (16 for 16, 12 for 8, 8 for 4)
     if (NBA == 1) {
@@ -274,6 +279,9 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
         }
     }
   }
+
+  f32x16 (&acc)[NBA][NBT] = sums[0];
+  if (CHAINS == 4) acc[0][0] = (sums[0][0][0] + sums[1 % CHAINS][0][0]) + (sums[2 % CHAINS][0][0] + sums[3 % CHAINS][0][0]);
 
   if (KSPLIT) {
     if (!producer) {
