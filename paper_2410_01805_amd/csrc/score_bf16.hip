@@ -467,7 +467,7 @@ int score_parts_bf16(const Dims& D) {
   return D.d_R / RT_M;
 }
 
-// Returns the number of partial score tensors written to `part` (the caller sums them): d_R / 128, or 1 when the
+// Returns the number of partial score tensors written to `part` (the caller sums them): d_R / 128 (64 x 64 tiles: d_R / 64), or 1 when the
 // launch split the contraction (short chunks: at most half as many tiles as CUs; each slice keeps at least 8
 // stages; Tuning::score_split: 0 = never, k = k slices).  Measured on 32q/8kv x 128, d_R = 1024, in microseconds
 // (hot caches): chunks of 2048 tokens 42.4 with 128-token tiles, 37.3 with 64-token tiles, 49.6 with those and two
@@ -490,7 +490,7 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
   const int nt = D.tune.score_nt == 64 || D.tune.score_nt == 128 ? D.tune.score_nt : (tiles128 <= 128 ? 64 : 128);
   const int forced = D.tune.score_split;
   // Hidden tile: 64 where 64 x 64 tiles are at most one a CU (T <= 1024 at d_R = 1024) and their partials fit.
-  const int tiles64 = ((T + 63) / 64) * (D.d_R / 64);
+  const int64_t tiles64 = (int64_t)((T + 63) / 64) * (D.d_R / 64);
   const int mt = nt == 64 && forced < 0 && D.tune.score_nt == 0 && tiles64 <= 256 && (size_t)(D.d_R / 64) * D.h_kv * T <= SCORE_FINE_FLOATS ? 64 : RT_M;
   dim3 grid((T + nt - 1) / nt, D.d_R / mt);
   int n_z = 1;
