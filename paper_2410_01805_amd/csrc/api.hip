@@ -72,6 +72,13 @@ Tuning tuning_from_env() {
   return t;
 }
 
+// the partial scores of the retaining head and the partial results of a decode step
+size_t part_floats(const Dims& D, int chunk_max) {
+  const int a = score_parts_simple(D), b = score_parts_bf16(D);
+  return (size_t)(a > b ? a : b) * D.h_kv * chunk_max;
+}
+size_t dpart_floats(const Dims& D) { return (size_t)D.h * decode_max_splits(D) * (D.d + 2); }
+
 void fill_dims(const locret_config* c, Dims* D) {
   D->tune = tuning_from_env();
   D->h = c->n_q_heads;
@@ -84,11 +91,7 @@ void fill_dims(const locret_config* c, Dims* D) {
   D->K = (D->h + 2 * D->h_kv) * D->d;
   D->d_R = c->d_hidden;
   D->kv_bits = c->kv_bits;
-}
-
-int max_score_parts(const Dims& D) {
-  const int a = score_parts_simple(D), b = score_parts_bf16(D), c = D.bf16 ? 0 : score_parts_f32_most(D);
-  return a > b && a > c ? a : b > c ? b : c;
+  D->part_floats = part_floats(*D, c->chunk_max) + dpart_floats(*D);
 }
 
 void make_layout(const locret_config* c, const Dims& D, Layout* L) {
@@ -120,9 +123,10 @@ void make_layout(const locret_config* c, const Dims& D, Layout* L) {
   L->tab = D.rope ? take((size_t)D.cap * (D.d / 2) * sizeof(float2)) : 0;
   L->W1t = take((size_t)D.d_R * D.K * es);
   L->W2f = take((size_t)D.d_R * D.h_kv * sizeof(float));
-  L->part = take((size_t)max_score_parts(D) * D.h_kv * c->chunk_max * sizeof(float));
+  // neighbours: the retaining head may go on into the decode step's, which is never in use at the same time (Dims::part_floats)
+  L->part = take(part_floats(D, c->chunk_max) * sizeof(float));
+  L->dpart = take(dpart_floats(D) * sizeof(float));
   L->kept = take((size_t)D.h_kv * c->budget * sizeof(int32_t));
-  L->dpart = take((size_t)D.h * decode_max_splits(D) * (D.d + 2) * sizeof(float));
   L->apart_floats = attention_pp_split_floats(D, c->chunk_max);
   L->apart = take(L->apart_floats * sizeof(float));
   L->zpart_floats = score_bf16_split_floats(D, c->chunk_max);

@@ -357,11 +357,11 @@ __global__ __launch_bounds__(F32_NW * 64) void score_f32_kernel(const float* __r
 }
 
 int score_parts_f32(const Dims& D) { return (D.d_R + 63) / 64; }
-int score_parts_f32_most(const Dims& D) { return (D.d_R + 31) / 32; }
-// Hidden units of a workgroup: 32 where 64 would leave CUs without one.
+// Hidden units of a workgroup: 32 where 64 would leave CUs without one, as far as the partials fit (into the workspace, which is not
+// larger for them, and into the static scratch).
 static int f32_hidden_block(const Dims& D, int T) {
-  return (int64_t)((T + F32_TB - 1) / F32_TB) * score_parts_f32(D) < 256 &&
-         (size_t)score_parts_f32_most(D) * D.h_kv * T <= SCORE_FINE_FLOATS ? 32 : 64;
+  const size_t fine = (size_t)((D.d_R + 31) / 32) * D.h_kv * T;
+  return (int64_t)((T + F32_TB - 1) / F32_TB) * score_parts_f32(D) < 256 && fine <= SCORE_FINE_FLOATS && fine <= D.part_floats ? 32 : 64;
 }
 
 int launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,

@@ -118,6 +118,7 @@ struct Dims {
   int K;        // retaining-head input width after folding: (h + 2 h_kv) d
   int d_R;      // retaining-head hidden width
   int kv_bits;  // 0: cache rows in the storage type; 4: packed 4-bit rows plus one bf16 staging copy (quant_rows.hip)
+  size_t part_floats;   // that the workspace holds for partial scores, with the decode step's partial results behind them
 };
 
 // One copy of the cache (the library ping-pongs between two).
@@ -180,8 +181,7 @@ void launch_attention_f32(const Dims& D, const void* q, const void* Kx, const vo
 bool attention_f32_fuses_select(const Dims& D, int n_cand);
 // True when that selection is also the place to sum n_parts partial scores of T tokens (SelectArgs::part).
 bool attention_f32_sums_partials(const Dims& D, int n_parts, int T);
-int score_parts_f32(const Dims& D);            // of long chunks
-int score_parts_f32_most(const Dims& D);       // of short ones
+int score_parts_f32(const Dims& D);            // of long chunks; short ones have twice as many where Dims::part_floats holds them
 // app: an append to carry out in the same launch (as launch_append with these arguments), or NULL
 struct ChunkAppend {
   const void* q;          // queries to rotate into qr, or NULL

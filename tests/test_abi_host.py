@@ -47,6 +47,21 @@ def test_workspace_bytes_covers_both_cache_copies():
     assert n3 < 1 << 30
 
 
+@pytest.mark.parametrize("kw", [
+    dict(), dict(n_q_heads=32, n_kv_heads=32, head_dim=128, chunk_max=16384, budget=16384, d_hidden=4096, rope_mode=1, rope_theta=1e4),
+    dict(n_q_heads=2, n_kv_heads=2, head_dim=16, chunk_max=256, budget=64, d_hidden=512), dict(chunk_max=1, budget=1, d_hidden=33),
+])
+def test_float32_layers_need_no_workspace_for_the_finer_partial_scores(kw):
+    """Region by region, with partial scores of 64 hidden units: the 32-unit form uses what is there."""
+    c = _cfg(**kw)
+    up = lambda n: -(-n // 256) * 256
+    cap, h, m, d, B_, b, dR = c.budget + c.chunk_max, c.n_q_heads, c.n_kv_heads, c.head_dim, c.chunk_max, c.budget, c.d_hidden
+    copy = [m * cap * d * 4] * (3 if c.rope_mode else 2) + [m * cap * 4] * 2
+    rest = [dR * (h + 2 * m) * d * 4, dR * m * 4, -(-dR // 64) * m * B_ * 4, m * b * 4, h * (-(-cap // 128) + 1) * (d + 2) * 4]
+    rope = [B_ * h * d * 4, cap * (d // 2) * 8] if c.rope_mode else []
+    assert B.locret_workspace_bytes(c) <= sum(map(up, 2 * copy + rest + rope))
+
+
 BAD = [
     dict(n_q_heads=0), dict(n_kv_heads=0), dict(n_q_heads=8, n_kv_heads=3), dict(head_dim=80), dict(head_dim=0),
     dict(chunk_max=0), dict(budget=0), dict(d_hidden=0), dict(dtype=2), dict(rope_mode=2), dict(rh_kv_expand=5),

@@ -544,3 +544,25 @@ def test_float32_append_in_the_launch_of_the_retaining_head(kw, budgets, evict):
             assert torch.equal(a[m, :n], b[m, :n])
     riding.close()
     alone.close()
+
+
+@pytest.mark.parametrize("T", [128, 132, 133, 256])
+def test_float32_partial_scores_up_to_the_end_of_their_room(T):
+    """32-unit partials of 128 tokens fill the workspace's partial scores, of 132 the decode step's results behind them as well (this
+    layer holds 4240 floats); from 133 on they are of 64 units."""
+    w = synth.tiny(name=f"room_{T}", dtype="f32", h=2, h_kv=2, d=16, N=2 * T, B=256, b=64, n_s=8, d_R=512)
+    layer, W1, W2 = make_layer(w)
+    o = make_oracle(w, W1, W2)
+    for lo in (0, T):
+        x = synth.tokens(w, lo, lo + T)
+        ref, sc_ref, kept_ref = o.prefill_chunk(*x, w.n_s)
+        out, sc, kept = layer.prefill_chunk(*(dev(t, w) for t in x), w.n_s, scores_in=torch.from_numpy(sc_ref).to(DEV))
+        np.testing.assert_array_equal(kept.cpu().numpy()[:, :w.b], kept_ref)
+        assert_close(sc.cpu().numpy(), sc_ref, w.dtype, w.name)
+        assert_close(host(out), ref, w.dtype, w.name, per_row=True)
+    x = synth.tokens(w, 2 * T, 2 * T + 1)
+    ref, sc_ref, _ = o.prefill_chunk(*x, 0, evict=False)
+    out, sc = layer.decode_step(*(dev(t, w) for t in x), with_score=True)
+    assert_close(host(out), ref, w.dtype, w.name, per_row=True)
+    assert_close(sc.cpu().numpy().reshape(sc_ref.shape), sc_ref, w.dtype, w.name)
+    layer.close()
