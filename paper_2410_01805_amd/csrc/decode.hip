@@ -42,6 +42,7 @@
 
 #include "attn_common.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "quant_row.h"
 #include "token_score.h"
 
@@ -667,26 +668,8 @@ __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const f
   }
 }
 
-// Keys per split.  Tuning::dec_keys (a multiple of 64 in 64 .. 65536) fixes it; otherwise it is chosen per launch.  All
-// workgroups of a launch run at once, so what counts is the CU with the most work: it has the keys of
-// ceil(workgroups / 256) splits and their fixed share (query, first wait, merge: about what 64 keys cost).  One workgroup over a
-// multiple of 256 costs most: 8 heads x 16.4K units x 128 dims take 15.9 us at 256 keys (520 workgroups), 14.1 at 192 (696), 14.0
-// at 320 (424); 8 x 6.1K 7.5 us at 256 (200), 8.8 at 192 (264), 8.3 at 128 (392); 4 x 16.4K 8.8 us at 320 (212), 10.4 at 256 (260).
-// Splits longer than 320 keys only as far as some 700 workgroups are left: on much data a workgroup or two a CU have too few
-// loads in flight (32 x 8.2K x 96 dims: 16.7 us at 384 keys, 736 workgroups, 19.6 at 1056 keys, 256).
-constexpr int DEC_KEYS_MIN = 128, DEC_KEYS_SHORT = 320, DEC_KEYS_SHARE = 64, DEC_CUS = 256;
-int decode_keys_per_split(const Dims& D, int n_keys) {
-  if (D.tune.dec_keys > 0) return D.tune.dec_keys;
-  const int64_t want = (((int64_t)D.h_kv * n_keys + 703) / 704 + 63) / 64 * 64;
-  const int most = want < DEC_KEYS_SHORT ? DEC_KEYS_SHORT : want > 65536 ? 65536 : (int)want;
-  int best = DEC_KEYS_MIN;
-  int64_t best_cost = INT64_MAX;
-  for (int k = DEC_KEYS_MIN > want / 2 ? DEC_KEYS_MIN : (int)(want / 128 * 64); k <= most; k += 64) {
-    const int64_t wgs = (int64_t)D.h_kv * ((n_keys + k - 1) / k + 1), cost = (wgs + DEC_CUS - 1) / DEC_CUS * (k + DEC_KEYS_SHARE);
-    if (cost < best_cost) { best_cost = cost; best = k; }
-  }
-  return best;
-}
+// Keys per split.  Tuning::dec_keys (a multiple of 64 in 64 .. 65536) fixes it; otherwise it is chosen per launch.
+int decode_keys_per_split(const Dims& D, int n_keys) { return D.tune.dec_keys > 0 ? D.tune.dec_keys : decode_split_keys(D.h_kv, n_keys); }
 
 // partials per query head at most: the splits over a full cache at the smallest split size, and the new token's
 int decode_max_splits(const Dims& D) {

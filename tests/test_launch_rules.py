@@ -1,0 +1,37 @@
+"""The rules that shape launches (csrc/launch_rules.h), compiled for the host and evaluated over the sizes that contexts accept."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SHIM = """
+#include "launch_rules.h"
+extern "C" {
+int split_keys(int h_kv, int n_keys) { return locret::decode_split_keys(h_kv, n_keys); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "shim.cpp").write_text(SHIM)
+    so = d / "shim.so"
+    inc = os.path.join(ROOT, "paper_2410_01805_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", inc, str(d / "shim.cpp"), "-o", str(so)], check=True)
+    return C.CDLL(str(so))
+
+
+def test_decode_splits_grow_with_the_cache(rules):
+    """Around 700 workgroups on long caches, at every size up to the largest cache a context takes."""
+    rng = random.Random(0)
+    cases = [(32, 2_900_000), (1024, 131_072), (1024, (1 << 28) - 1), (1, (1 << 28) - 1), (8, 0), (8, 1), (1024, 1)]
+    cases += [(rng.randint(1, 1024), int(2 ** rng.uniform(0, 28))) for _ in range(3000)]
+    for h_kv, n in cases:
+        k = rules.split_keys(h_kv, n)
+        want = min(65536, h_kv * n // 704)
+        assert k % 64 == 0 and max(128, want // 2 - 64) <= k <= max(320, want + 64), (h_kv, n, k)
