@@ -669,7 +669,9 @@ __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const f
 }
 
 // Keys per split.  Tuning::dec_keys (a multiple of 64 in 64 .. 65536) fixes it; otherwise it is chosen per launch.
-int decode_keys_per_split(const Dims& D, int n_keys) { return D.tune.dec_keys > 0 ? D.tune.dec_keys : decode_split_keys(D.h_kv, n_keys); }
+int decode_keys_per_split(const Dims& D, int n_keys) {
+  return D.tune.dec_keys > 0 ? D.tune.dec_keys : decode_split_keys(D.bf16 != 0, D.h_kv, n_keys);
+}
 
 // partials per query head at most: the splits over a full cache at the smallest split size, and the new token's
 int decode_max_splits(const Dims& D) {

@@ -13,10 +13,15 @@ constexpr int RULE_CUS = 256;
 // at 320 (424); 8 x 6.1K 7.5 us at 256 (200), 8.8 at 192 (264), 8.3 at 128 (392); 4 x 16.4K 8.8 us at 320 (212), 10.4 at 256 (260).
 // Splits longer than 320 keys only as far as some 700 workgroups are left: on much data a workgroup or two a CU have too few
 // loads in flight (32 x 8.2K x 96 dims: 16.7 us at 384 keys, 736 workgroups, 19.6 at 1056 keys, 256).
+// float32 rows: some 700 workgroups of at least 128 keys.  A workgroup has half as many rows in flight and takes the longer for
+// them, so two short ones on a CU cost less than a long one.  A token, caches from HBM, by this and by the search: 8 heads x 4.1K x
+// 128 dims 20.4, 22.8 us, 8.2K 24.7, 34.1; 32 x 2K x 128 21.1, 24.6; 8 x 8.2K x 64 13.9, 15.1.  (bf16 rows of 16 dims, the same
+// kernel: 8 heads x 8.2K 12.2, 10.3.)
 constexpr int DEC_KEYS_MIN = 128, DEC_KEYS_SHORT = 320, DEC_KEYS_SHARE = 64, DEC_KEYS_MAX = 65536;
-inline int decode_split_keys(int h_kv, int n_keys) {
+inline int decode_split_keys(bool bf16, int h_kv, int n_keys) {
   int64_t want = (((int64_t)h_kv * n_keys + 703) / 704 + 63) / 64 * 64;
   if (want > DEC_KEYS_MAX) want = DEC_KEYS_MAX;        // (both ends of the search below follow it)
+  if (!bf16) return (int)(want < DEC_KEYS_MIN ? DEC_KEYS_MIN : want);
   const int64_t most = want < DEC_KEYS_SHORT ? DEC_KEYS_SHORT : want;
   int64_t best = DEC_KEYS_MIN, best_cost = INT64_MAX;
   for (int64_t k = DEC_KEYS_MIN > want / 2 ? DEC_KEYS_MIN : want / 128 * 64; k <= most; k += 64) {

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "launch_rules.h"
 extern "C" {
-int split_keys(int h_kv, int n_keys) { return locret::decode_split_keys(h_kv, n_keys); }
+int split_keys(int bf16, int h_kv, int n_keys) { return locret::decode_split_keys(bf16 != 0, h_kv, n_keys); }
 }
 """
 
@@ -32,6 +32,8 @@ def test_decode_splits_grow_with_the_cache(rules):
     cases = [(32, 2_900_000), (1024, 131_072), (1024, (1 << 28) - 1), (1, (1 << 28) - 1), (8, 0), (8, 1), (1024, 1)]
     cases += [(rng.randint(1, 1024), int(2 ** rng.uniform(0, 28))) for _ in range(3000)]
     for h_kv, n in cases:
-        k = rules.split_keys(h_kv, n)
+        k = rules.split_keys(1, h_kv, n)
         want = min(65536, h_kv * n // 704)
         assert k % 64 == 0 and max(128, want // 2 - 64) <= k <= max(320, want + 64), (h_kv, n, k)
+        k = rules.split_keys(0, h_kv, n)
+        assert k % 64 == 0 and max(128, want) <= k <= max(128, want + 64), (h_kv, n, k)
