@@ -12,6 +12,7 @@
 #include "append_body.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "select_body.h"
 
 namespace locret {
@@ -281,10 +282,9 @@ void launch_attention_f32(const Dims& Dm, const void* q, const void* Kx, const v
 // ---- retaining head ------------------------------------------------------------------------------------------------
 // Workgroup = HB hidden units x 16 tokens; wavefront w takes contraction steps w, w + 8, ... of 16 elements (each inside one
 // of q, k, v: the [q;k;v] row is read in place).  The wavefronts' sums are added in a fixed order, then SiLU and
-// the product with W2; each workgroup writes its hidden block's partial part[nb][m][t].  HB = 32 for chunks whose 64-unit
-// workgroups would leave CUs without one, else 64, which reads the tokens half as often: 768 inputs x 256 hidden, 512 tokens
-// 12.7 us with 64, 11 with 32 (1536 inputs 19.0, 13.0), 1024 tokens 13.1, 16.4, 4096 tokens 34.5, 49.8; vector-ALU tiles
-// of 64 x 64 took 95.7 at 512 tokens.  (Two steps' loads under way ahead of the present one: 512 tokens 14.4 us, 4096 43.)
+// the product with W2; each workgroup writes its hidden block's partial part[nb][m][t].  HB = 32 or 64 by f32_hidden_units(): 768
+// inputs x 256 hidden, 512 tokens 9.4 us with 32, 4096 tokens 34.5 with 64, 49.8 with 32; vector-ALU tiles of 64 x 64 took 95.7 at
+// 512 tokens.  (Two steps' loads under way ahead of the present one: 64 units, 512 tokens 12.7 -> 14.4 us, 4096 34.5 -> 43.)
 // APPEND 1 (2: with head-wise lengths): workgroups behind the n_nb hidden blocks, two of the append's each, append the chunk, which
 // depends on nothing this launch does: a launch of 3.4 us less (4096 tokens in chunks of 512, 2 x 64 dims: 280 -> 272 us, with HB = 32 238).
 constexpr int F32_TB = 16;
@@ -357,16 +357,12 @@ __global__ __launch_bounds__(F32_NW * 64) void score_f32_kernel(const float* __r
 }
 
 int score_parts_f32(const Dims& D) { return (D.d_R + 63) / 64; }
-// Hidden units of a workgroup: 32 where 64 would leave CUs without one, as far as the partials fit (into the workspace, which is not
-// larger for them, and into the static scratch).
-static int f32_hidden_block(const Dims& D, int T) {
-  const size_t fine = (size_t)((D.d_R + 31) / 32) * D.h_kv * T;
-  return (int64_t)((T + F32_TB - 1) / F32_TB) * score_parts_f32(D) < 256 && fine <= SCORE_FINE_FLOATS && fine <= D.part_floats ? 32 : 64;
-}
 
 int launch_score_f32(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t, const float* W2f,
                      float* part, hipStream_t st, const ChunkAppend* app) {
-  const int hb = f32_hidden_block(D, T), nb = (D.d_R + hb - 1) / hb;
+  // the partials have to fit into the workspace, which is not larger for them, and into the static scratch
+  const size_t room = D.part_floats < SCORE_FINE_FLOATS ? D.part_floats : SCORE_FINE_FLOATS;
+  const int hb = f32_hidden_units(T, D.h_kv, D.d_R, (int64_t)room), nb = (D.d_R + hb - 1) / hb;
   dim3 grid = f32_rows((T + F32_TB - 1) / F32_TB, nb);
   AppendArgs<float> ap = {};
   if (app) {

@@ -31,4 +31,14 @@ inline int decode_split_keys(bool bf16, int h_kv, int n_keys) {
   return (int)best;
 }
 
+// ---- retaining head, float32: hidden units of a workgroup ------------------------------------------------------------------
+// 32 while that leaves at most one workgroup (of 16 tokens) a CU, else 64, which reads the tokens half as often.  `room`: floats
+// that the partial scores may take.  locret_score on 768 inputs x 256 hidden units, 64 against 32 units: 512 tokens 12.6, 9.4 us, 611
+// tokens (312 workgroups of 32) 12.5, 13.2, 900 12.7, 13.2; 1536 inputs: 512 19.2, 13.2, 611 19.5, 22.0; 6144 inputs x 1024: 100 tokens 64.1,
+// 39.6, 200 64.2, 73.1.
+inline int f32_hidden_units(int T, int h_kv, int d_R, int64_t room) {
+  const int64_t wgs = (int64_t)((T + 15) / 16) * ((d_R + 31) / 32), partials = (int64_t)((d_R + 31) / 32) * h_kv * T;
+  return wgs <= RULE_CUS && partials <= room ? 32 : 64;
+}
+
 }  // namespace locret

@@ -12,6 +12,7 @@ SHIM = """
 #include "launch_rules.h"
 extern "C" {
 int split_keys(int bf16, int h_kv, int n_keys) { return locret::decode_split_keys(bf16 != 0, h_kv, n_keys); }
+int f32_units(int T, int h_kv, int d_R, int64_t room) { return locret::f32_hidden_units(T, h_kv, d_R, room); }
 }
 """
 
@@ -37,3 +38,15 @@ def test_decode_splits_grow_with_the_cache(rules):
         assert k % 64 == 0 and max(128, want // 2 - 64) <= k <= max(320, want + 64), (h_kv, n, k)
         k = rules.split_keys(0, h_kv, n)
         assert k % 64 == 0 and max(128, want) <= k <= max(128, want + 64), (h_kv, n, k)
+
+
+@pytest.mark.parametrize("T,h_kv,d_R,units", [
+    (512, 2, 256, 32), (513, 2, 256, 64), (611, 2, 256, 64), (900, 2, 256, 64), (4096, 2, 256, 64), (1, 2, 256, 32),
+    (128, 8, 1024, 32), (129, 8, 1024, 64), (200, 8, 1024, 64), (4096, 1, 32, 32), (4097, 1, 32, 64), (4096, 1, 33, 64), (1, 1, 65536, 64),
+])
+def test_finer_float32_retaining_head_has_one_workgroup_a_cu(rules, T, h_kv, d_R, units):
+    f = rules.f32_units
+    f.argtypes = [C.c_int] * 3 + [C.c_int64]
+    assert f(T, h_kv, d_R, 1 << 20) == units
+    partials = -(-d_R // 32) * h_kv * T
+    assert f(T, h_kv, d_R, partials) == units and f(T, h_kv, d_R, partials - 1) == 64
