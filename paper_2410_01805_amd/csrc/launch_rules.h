@@ -31,6 +31,75 @@ inline int decode_split_keys(bool bf16, int h_kv, int n_keys) {
   return (int)best;
 }
 
+// ---- retaining head, bf16: tiles, slices of the contraction, order of the workgroups -------------------------------------------
+// mt hidden units x nt tokens a workgroup, n_z slices of the contraction (1: none; the finish kernel sums more).  A launch without
+// slices leaves d_R / mt partial scores.
+struct ScorePlan {
+  int mt, nt, n_z;
+  bool hidden_first;      // neighbouring workgroups take the same tokens and the next hidden units (false: the other way round)
+};
+
+constexpr int SCORE_STAGE = 64;       // contraction elements of a stage of the kernel
+
+// Slices: as many as give every CU a workgroup, of 8 stages at least, none of them empty.  zpart_floats: room for
+// the partial pre-activations, 0: no slices.  forced (Tuning::score_split): -1 this rule, 0 never, k always k.
+inline int score_slices(int64_t tiles, int stages, int T, int d_R, int64_t zpart_floats, int forced) {
+  if (zpart_floats == 0) return 1;
+  int64_t n = forced >= 0 ? forced : RULE_CUS / tiles >= 2 ? RULE_CUS / tiles : 1;
+  if (n > 8) n = 8;
+  auto last_empty = [&](int64_t k) { return (k - 1) * ((stages + k - 1) / k) >= stages; };      // slices are ceil(stages / k) long
+  while (n > 1 && (n * T * d_R > zpart_floats || (forced < 0 && stages / n < 8) || last_empty(n))) --n;
+  return n < 1 ? 1 : (int)n;
+}
+
+// Every XCD has an L2 of its own and takes every eighth workgroup.  Of slow x fast tiles (neighbouring workgroups differ in `fast`)
+// those of one XCD need about this much of one stage; w_slow, w_fast: a row's and a column's share of it.
+inline double score_xcd_load(int64_t slow, int64_t fast, double w_slow, double w_fast) {
+  const double n = slow * fast / 8. > 1 ? slow * fast / 8. : 1;              // its workgroups
+  const double f = (double)(fast / (fast % 8 == 0 ? 8 : fast % 4 == 0 ? 4 : fast % 2 == 0 ? 2 : 1));
+  return (f < n ? f : n) * w_fast + (slow < n ? slow : n) * w_slow;
+}
+
+// About what a launch with these tiles costs, in us, a mean over what callers meet (inputs in the last-level cache and in HBM, locret_score
+// and steps whose selection sums the partials beside the attention): the longer of a workgroup's chain of stages and of
+// what the L2s have to fetch (MB), then the finish kernel (8 KV heads a workgroup, whole eights by a faster path) or the sum.
+inline double score_cost(const ScorePlan& p, double xcd_load, int stages, int h_kv) {
+  const double chain = (p.mt == 128 ? 0.38 : 0.212) * ((stages + p.n_z - 1) / p.n_z), fetch = xcd_load * 8 * stages / 1024 / 7.7;
+  const double finish = p.n_z == 1 ? 1.9 : (h_kv % 8 == 0 ? 5.5 : 10.5) + 4.8 * ((h_kv + 7) / 8 - 1) + 0.45 * p.n_z;
+  return (chain > fetch ? chain : fetch) + finish;
+}
+
+// Token tile: 64 when 128-token tiles would leave at least half of the CUs without one (2048 tokens at d_R = 1024).
+// 32q/8kv x 128, d_R = 1024 (hot caches): chunks of 2048 tokens 42.4 us with 128-token tiles, 37.3 with 64-token tiles, 49.6 with those
+// and two slices; chunks of 3072 or 4096 tokens are a third slower with 64-token tiles (more LDS traffic per MFMA).
+//
+// Order, for 64 x 64 tiles: the one by which an XCD needs fewer different tiles.  Tokens first against hidden units first,
+// 32q/8kv x 128, d_R = 512, 900 tokens (15 x 8 tiles) 27.4 / 27.4, 21.8 / 22.9 us (inputs in the last-level cache / from HBM), 1024 tokens
+// (16 x 8) 19.8 / 22.5, 23.0 / 23.4.
+//
+// Hidden tile: 128, or 64 where 64 x 64 tiles are at most one a CU and their partials fit: then there are twice as many workgroups
+// for half as many slices.  locret_score with 128 x 64 tiles against 64 x 64, 32q/8kv x 128, d_R = 1024: 300 tokens 21.9 / 21.6, 15.3 /
+// 16.9 us, 900 35.5 / 35.9, 25.7 / 32.6; 32q/32kv x 96: 900 65.7 / 66.5, 39.1 / 47.8; 16q/4kv x 128, d_R = 512: 2048 25.1 / 25.7, 15.9 / 19.2.
+// But a slice also gets longer by that, a chain of stages that may take more than the finish kernel saved, and 64-unit tiles ask
+// the L2s for more: d_R = 512: 1100 tokens (3 slices, 1) 24.2 / 25.0, 23.9 / 32.3, 1300 (3, 1) 26.4 / 27.1, 24.9 / 33.4; d_R = 384: 900 (4, 2)
+// 19.9 / 21.2, 21.7 / 22.4.  So both are estimated.  Over 450 launches (16 layouts, d_R 128 .. 2048, 64 .. 4096 tokens) the choice takes
+// 0.86 (last-level cache) and 0.92 (HBM) of the time of 128 x 64 tiles, within 0.2 % of always taking the better form.  It is the
+// slower one for locret_score from HBM where the slices of 64 x 64 tiles are long: d_R = 1024, 611 tokens (3, 1) 27.1 / 27.0, 23.9 / 31.9; in a
+// prompt, where the append or the attention has read the inputs before, that launch is the faster one (a 611-token prompt and
+// 8 scored tokens 126.7, 121.4 us).
+// (Tuning::score_nt: 0 = these rules, 64 / 128 = tokens of a workgroup, with 128 hidden units.)
+inline ScorePlan plan_score(int T, int h_kv, int K, int d_R, int64_t zpart_floats, int64_t fine_floats, int tune_nt, int tune_split) {
+  const int stages = K / SCORE_STAGE;
+  const int64_t tiles128 = ((int64_t)T + 127) / 128 * (d_R / 128), t64 = ((int64_t)T + 63) / 64, h64 = d_R / 64, h128 = d_R / 128;
+  const int nt = tune_nt == 64 || tune_nt == 128 ? tune_nt : tiles128 <= RULE_CUS / 2 ? 64 : 128;
+  const ScorePlan wide = {128, nt, score_slices(((int64_t)T + nt - 1) / nt * h128, stages, T, d_R, zpart_floats, tune_split), false};
+  if (nt != 64 || tune_nt != 0 || tune_split >= 0 || t64 * h64 > RULE_CUS || h64 * h_kv * T > fine_floats) return wide;
+  const double tokens_first = score_xcd_load(h64, t64, 8, 8), hidden_first = score_xcd_load(t64, h64, 8, 8);      // KB
+  const ScorePlan fine = {64, 64, score_slices(t64 * h64, stages, T, d_R, zpart_floats, -1), hidden_first < tokens_first};
+  const double wide_us = score_cost(wide, score_xcd_load(h128, t64, 16, 8), stages, h_kv) - (wide.n_z == 1 && h128 == 1 ? 3 : 0);   // (a single partial is the score)
+  return score_cost(fine, fine.hidden_first ? hidden_first : tokens_first, stages, h_kv) <= wide_us ? fine : wide;
+}
+
 // ---- retaining head, float32: hidden units of a workgroup ------------------------------------------------------------------
 // 32 while that leaves at most one workgroup (of 16 tokens) a CU, else 64, which reads the tokens half as often.  `room`: floats
 // that the partial scores may take.  locret_score on 768 inputs x 256 hidden units, 64 against 32 units: 512 tokens 12.6, 9.4 us, 611

@@ -13,9 +13,10 @@
 // 16 bytes per lane) into a ring of stages, four of 32 KB or six of 24 or 16 KB, all but one of them in flight.
 // What bounds the kernel is this path.  Taken apart (32q/8kv x 128, d_R = 1024, 2048 tokens in 128 x 64 tiles, inputs in the
 // last-level cache): 35 us; without the loads 21; the loads alone 29.6, with the same four stages over and over, which stay
-// in the L2, 23 (55 B/clk and CU), weights alone 21.6, tokens alone 17.9.  Fewer distinct bytes per XCD (another
-// order of the tiles: 20 % less), contiguous tiles of W1 and stages offset between the XCDs change 0 to 5 % of that; what counts is the
-// bytes a CU requests, and how long each is on its way (inputs from HBM: 41 us).  A direct load
+// in the L2, 23 (55 B/clk and CU), weights alone 21.6, tokens alone 17.9.  Contiguous tiles of W1 and
+// stages offset between the XCDs change 0 to 5 % of that, and so do 20 % fewer distinct bytes per XCD by another order of these 32 x 8
+// tiles; what counts is the bytes a CU requests, and how long each is on its way (inputs from HBM: 41 us).  (Numbers of token tiles
+// that are no multiple of 8 spread every tile over all XCDs; there the order does count: plan_score().)  A direct load
 // holds its wavefront's issue slot for 60-80 cycles while the CU's vector-memory path (64 B/clk) is
 // busy, and a stage needs 32 of them: issued by the computing wavefronts they cost as much time as the
 // stage's 16 MFMAs.  So the workgroup has eight wavefronts: 0..3 only compute, 4..7 (their SIMD mates)
@@ -35,6 +36,7 @@
 // scores are deterministic.
 #include "device_util.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "token_score.h"
 
 namespace locret {
@@ -44,7 +46,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int RT_M = 128;      // hidden units per workgroup at most
 constexpr int RT_N = 128;      // tokens per workgroup at most
-constexpr int RT_K = 64;       // contraction elements per stage (128 bytes per row)
+constexpr int RT_K = SCORE_STAGE;       // contraction elements per stage (128 bytes per row)
 
 // MT hidden units x NT tokens
 template <int MT, int NT>
@@ -70,18 +72,18 @@ __device__ __forceinline__ float sum_across_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// KSPLIT (short chunks, too few 128 x 128 tiles for the CUs): blockIdx.z takes a slice of the contraction and
+// KSPLIT (short chunks, too few tiles for the CUs): blockIdx.z takes a slice of the contraction and
 // the workgroup leaves its partial pre-activations zpart[z][t][r]; score_finish_kernel sums the slices and
 // applies SiLU and W2.  KSPLIT = false: the whole contraction, epilogue below.
-// NT = tokens per workgroup: 128 (2 x 2 wavefronts of 64 hidden units x 64 tokens), or 64 (64 x 32 each) for chunks
-// that would leave half of the CUs without a 128-token tile; the hidden block stays 128 wide.
+// MT hidden units x NT tokens per workgroup, 2 x 2 wavefronts: 128 x 128 (64 x 64 each), 128 x 64 (64 x 32) or 64 x 64 (32 x 32);
+// which one, how many slices and in which order the workgroups are numbered (hidden_first: along the hidden units) is plan_score()'s.
 template <bool KSPLIT, int MT, int NT>
 __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ v, int Tn, int hd, int kvd,
                                                          const bf16_t* __restrict__ W1t,
                                                          const float* __restrict__ W2f, int K, int h_kv,
                                                          float* __restrict__ part, int part_T,
-                                                         float* __restrict__ zpart, int d_R) {
+                                                         float* __restrict__ zpart, int d_R, int hidden_first) {
   typedef ScoreSmem<MT, NT> Smem;
   __shared__ __attribute__((aligned(1024))) Smem sm;
   constexpr int RT_STAGES = Smem::STAGES, RT_STAGE_B = Smem::STAGE_B, RT_TILE_B = Smem::TILE_A;
@@ -97,8 +99,8 @@ __global__ __launch_bounds__(512) void score_mfma_kernel(const bf16_t* __restric
   constexpr int A_LOADS = MT / 32;               // direct loads of a producer for the weight tile of a stage
   constexpr int NBT = NT / 64;                   // 32-token blocks per wavefront
   constexpr int B_LOADS = NT / 32;               // direct loads of a producer for the token tile of a stage
-  const int t0 = blockIdx.x * NT;
-  const int nb = blockIdx.y;
+  const int t0 = (int)(hidden_first ? blockIdx.y : blockIdx.x) * NT;
+  const int nb = hidden_first ? blockIdx.x : blockIdx.y;
   const int r0 = nb * MT;
 
   // One product a step would be a single chain of sums over the whole contraction: four chains, one for each step of a stage, keep
@@ -467,14 +469,9 @@ int score_parts_bf16(const Dims& D) {
   return D.d_R / RT_M;
 }
 
-// Returns the number of partial score tensors written to `part` (the caller sums them): d_R / 128 (64 x 64 tiles: d_R / 64), or 1 when the
-// launch split the contraction (short chunks: at most half as many tiles as CUs; each slice keeps at least 8
-// stages; Tuning::score_split: 0 = never, k = k slices).  Measured on 32q/8kv x 128, d_R = 1024, in microseconds
-// (hot caches): chunks of 2048 tokens 42.4 with 128-token tiles, 37.3 with 64-token tiles, 49.6 with those and two
-// slices; chunks of 3072 or 4096 tokens are a third slower with 64-token tiles (more LDS traffic per MFMA).  128 x 64 tiles with a
-// ring of six stages instead of four: 1500 tokens 33.0 -> 31.0, 2048 35.0 -> 33.0.  Where 128 x 64 tiles would need two or more slices
-// and their finish kernel, 64 x 64 tiles: 1024 tokens 26.1 -> 23.1, 800 33.4 -> 28.6, 611 26.7 -> 22.9 (inputs from HBM 29.7 -> 29.2,
-// 33.7 -> 30.0, 26.7 -> 27.3) and as many partials again to sum; split as well below that, 300 tokens 21.6 -> 20.0, 100 12.1 -> 11.2.
+// Returns the number of partial score tensors written to `part` (the caller sums them): d_R / the hidden units of a tile, or 1 when
+// the launch split the contraction.  128 x 64 tiles with a ring of six stages instead of four: 1500 tokens (32q/8kv x 128, d_R = 1024)
+// 33.0 -> 31.0 us, 2048 35.0 -> 33.0.
 int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v, int T, const void* W1t,
                       const float* W2f, float* part, hipStream_t st, float* zpart, size_t zpart_floats, float* single) {
   if (T == 1 && zpart != nullptr && D.tune.score_nt == 0 && D.tune.score_split < 0) {
@@ -484,30 +481,15 @@ int launch_score_bf16(const Dims& D, const void* q, const void* k, const void* v
                   single ? single : part);
     return 1;
   }
-  // Token tile: 64 when 128-token tiles would leave at least half of the 256 CUs without one (T <= 2048 at
-  // d_R = 1024).  Tuning::score_nt: 0 = this rule, 64 / 128 = always.
-  const int tiles128 = ((T + 127) / 128) * (D.d_R / RT_M);
-  const int nt = D.tune.score_nt == 64 || D.tune.score_nt == 128 ? D.tune.score_nt : (tiles128 <= 128 ? 64 : 128);
-  const int forced = D.tune.score_split;
-  // Hidden tile: 64 where 64 x 64 tiles are at most one a CU (T <= 1024 at d_R = 1024) and their partials fit.
-  const int64_t tiles64 = (int64_t)((T + 63) / 64) * (D.d_R / 64);
-  const int mt = nt == 64 && forced < 0 && D.tune.score_nt == 0 && tiles64 <= 256 && (size_t)(D.d_R / 64) * D.h_kv * T <= SCORE_FINE_FLOATS ? 64 : RT_M;
-  dim3 grid((T + nt - 1) / nt, D.d_R / mt);
-  int n_z = 1;
-  if (zpart != nullptr) {
-    const int tiles = (int)(grid.x * grid.y), stages = D.K / RT_K;
-    n_z = forced >= 0 ? forced : (256 / tiles >= 2 ? 256 / tiles : 1);
-    n_z = n_z > 8 ? 8 : n_z;
-    auto last_empty = [&](int n) { return (n - 1) * ((stages + n - 1) / n) >= stages; };   // slices are ceil(stages / n) long
-    while (n_z > 1 && ((size_t)n_z * T * D.d_R > zpart_floats || (forced < 0 && stages / n_z < 8) || last_empty(n_z))) --n_z;
-    if (n_z < 1) n_z = 1;
-  }
-  grid.z = n_z;
+  const ScorePlan p = plan_score(T, D.h_kv, D.K, D.d_R, zpart ? (int64_t)zpart_floats : 0, (int64_t)SCORE_FINE_FLOATS, D.tune.score_nt, D.tune.score_split);
+  const int mt = p.mt, nt = p.nt, n_z = p.n_z;
+  const unsigned tiles_t = (unsigned)((T + nt - 1) / nt), tiles_h = (unsigned)(D.d_R / mt);
+  const dim3 grid = p.hidden_first ? dim3(tiles_h, tiles_t, n_z) : dim3(tiles_t, tiles_h, n_z);
   if (single && (n_z > 1 || D.d_R == mt)) part = single;
 #define LOCRET_SCORE_LAUNCH(KS, MTT, NTT)                                                                             \
   launch_kernel(score_mfma_kernel<KS, MTT, NTT>, grid, dim3(512), 0, st, (const bf16_t*)q, (const bf16_t*)k,           \
                 (const bf16_t*)v, T, D.h * D.d, D.h_kv * D.d, (const bf16_t*)W1t, W2f, D.K, D.h_kv, part, T,          \
-                KS ? zpart : (float*)nullptr, D.d_R)
+                KS ? zpart : (float*)nullptr, D.d_R, (int)p.hidden_first)
 #define LOCRET_SCORE_TILE(KS)                            \
   if (mt == 64) LOCRET_SCORE_LAUNCH(KS, 64, 64);         \
   else if (nt == 64) LOCRET_SCORE_LAUNCH(KS, 128, 64);   \

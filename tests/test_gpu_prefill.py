@@ -566,3 +566,14 @@ def test_float32_partial_scores_up_to_the_end_of_their_room(T):
     assert_close(host(out), ref, w.dtype, w.name, per_row=True)
     assert_close(sc.cpu().numpy().reshape(sc_ref.shape), sc_ref, w.dtype, w.name)
     layer.close()
+
+
+@pytest.mark.parametrize("d_R,T", [(512, 300), (512, 65), (1024, 833), (256, 450)])
+def test_retaining_head_numbered_along_the_hidden_units(d_R, T):
+    """64 x 64 tiles whose workgroups are numbered along the hidden units, with and without slices of the contraction, a last token
+    tile of one token among them."""
+    w = synth.tiny(name=f"order_{d_R}_{T}", dtype="bf16", h=24, h_kv=8, d=64, N=T, B=T, b=T, n_s=0, d_R=d_R)
+    layer, W1, W2 = make_layer(w)
+    x = synth.tokens(w, 0, T)
+    assert_close(layer.score(*(dev(t, w) for t in x)).cpu().numpy(), make_oracle(w, W1, W2).score(*x), w.dtype, w.name)
+    layer.close()
