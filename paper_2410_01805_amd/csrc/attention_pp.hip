@@ -62,9 +62,11 @@ __host__ __device__ constexpr int pp_tile_keys(int d) { return d == 64 ? 2 * PP_
 constexpr int PP_STAGE_B = 2 * PP_TILE_B;      // K then V
 constexpr int PP_NW = 8;
 constexpr int PP_KPRE = 4;                     // K fragments fetched ahead of the S block
-// MFMAs of group A's S block issued behind barrier Y.  Fewer where the softmax takes the longer part of a tile: 96 dims, 20480 tokens on
-// 32 heads of 8192 units, with 1, 2, 3, 4: 2474, 2460, 2491, 2478 us a prompt (head-wise budgets 1032, 1044, 1045, 1049); 64 dims, 10000
-// tokens on 8 heads of 4096: 513, 516, 517, 518 (cut items 1052, 1055, 1056, 1056); 128 dims, 15900 tokens on 8 of 6144 with 2, 4, 6: 1825, 1820, 1848.
+// MFMAs of group A's S block issued behind barrier Y.  Fewer than four where the softmax takes the longer part of a tile.  Steps of 300 to
+// 4096 tokens on 4096 and 8192 units, five runs in turn (the runs of one side differ by 1 to 3 %, by 0.6 % with head-wise budgets), means over
+// the ten shapes against four: 96 dims with two 0.992 on 32 heads, 0.986 on 8, with one 0.993, 0.991 (20480 tokens on 32 heads of 8192
+// units, in turn: one 2509, two 2494 us); 96 dims with head-wise budgets, one 0.984, in every shape; 64 dims, one 0.993 on 8 heads, 0.998
+// on 32, 1.000 with budgets.  128 dims, 15900 tokens on 8 heads of 6144, with two, four, six: 1825, 1820, 1848 us.
 constexpr int pp_ytail(int d, bool general) { return d == 128 ? 4 : d == 96 && !general ? 2 : 1; }
 constexpr int PP_SEL_MAXR = 48;                // keys per thread of a selection workgroup (512 threads)
 constexpr int PP_MAX_PARTS = 16;               // key ranges per (head group, token tile) item at most
