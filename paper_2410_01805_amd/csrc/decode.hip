@@ -617,6 +617,7 @@ template <typename T, int ND, bool SCORED>
 __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const float* __restrict__ part, int n_splits,
                                                                          int d, T* __restrict__ out, int h, TokenScore score,
                                                                          float* __restrict__ S, int cap, int n_c, HeadLens n_c_h) {
+  static_assert(ND == 1 || ND == 2, "head dims up to 128");
   constexpr int NW = DEC_MERGE_THREADS / 64, SG = NW / ND, PRE = DEC_MERGE_PRE / SG;
   __shared__ float acc_s[NW][64];
   const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -649,16 +650,24 @@ __global__ __launch_bounds__(DEC_MERGE_THREADS) void decode_merge_kernel(const f
   float l = fmaf(w1, lane + 64 < n_splits ? ml[1].y : 0.f, w0 * (lane < n_splits ? ml[0].y : 0.f));
   for (int s = lane + 128; s < n_splits; s += 64) l = fmaf(__builtin_amdgcn_exp2f(p[s * pw + d] - M), p[s * pw + d + 1], l);
   const float inv = 1.f / wave_sum(l);
-  float a0 = 0.f;
+  // eight chains of sums over the splits for every head dim: SG wavefronts with ND each
+  float a[ND];
+#pragma unroll
+  for (int c = 0; c < ND; ++c) a[c] = 0.f;
 #pragma unroll
   for (int i = 0; i < PRE; ++i) {
     const int s = sg + i * SG;                           // below 64 for i < 64 / SG, below 128 for all
     const float w = i < 64 / SG ? lane_value(w0, s) : lane_value(w1, s - 64);      // 0 past the last split
-    if (s < n_splits) a0 = fmaf(w, pv[i], a0);
+    if (s < n_splits) a[i % ND] = fmaf(w, pv[i], a[i % ND]);
   }
-  for (int s = sg + PRE * SG; s < n_splits; s += SG)
-    a0 = fmaf(s < 128 ? lane_value(w1, s - 64) : __builtin_amdgcn_exp2f(p[s * pw + d] - M), p[s * pw + e], a0);
-  acc_s[wave][lane] = a0;
+  static_assert(PRE % ND == 0, "the chains go on in turn");
+  for (int s0 = sg + PRE * SG; s0 < n_splits; s0 += ND * SG)
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      const int s = s0 + c * SG;
+      if (s < n_splits) a[c] = fmaf(s < 128 ? lane_value(w1, s - 64) : __builtin_amdgcn_exp2f(p[s * pw + d] - M), p[s * pw + e], a[c]);
+    }
+  acc_s[wave][lane] = ND == 1 ? a[0] : a[0] + a[ND - 1];
   __syncthreads();
   if (tid < d) {
     float t = 0.f;

@@ -211,3 +211,20 @@ def test_decode_merge_of_many_splits(dtype, d, monkeypatch):
         assert err <= (2.0 ** -20 if dtype == "f32" else 2.0 ** -7), (splits, float(err))
     for layer in layers:
         layer.close()
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+def test_decode_merge_sums_the_splits_in_eight_chains(d, monkeypatch):
+    """64 splits of equal weight whose results are odd whole numbers near 2^21, of alternating sign: split s in the chain s mod 8 meets
+    eight of one sign, which stay below 2^24 and therefore exact, and so do all sums of chains; sixteen of one sign would not."""
+    monkeypatch.setenv("LOCRET_DEC_KEYS", "64")
+    w = synth.tiny(name=f"chains_{d}", dtype="f32", h=2, h_kv=1, d=d, N=4096, B=4095, b=4096, n_s=0, d_R=64, rope=False)
+    layer, _, _ = make_layer(w)
+    V = torch.zeros(4095, 1, d, dtype=torch.float64)
+    s = torch.arange(64)[:, None]
+    V[::64, 0] = ((-1.0) ** s) * (2 ** 21 - 1 - 2 * ((s * 37 + torch.arange(d) * 11) % 512))
+    layer.evict_compact(torch.zeros(1, 4095, device=DEV), torch.zeros(4095, 1, d, device=DEV), V.float().to(DEV), 0)
+    zero = lambda n: torch.zeros(1, n, d, device=DEV)
+    out = layer.decode_step(zero(2), zero(1), zero(1))[0].cpu().double()       # the token's own value is 0, its weight that of any unit
+    assert torch.equal(out[0, 0], V.sum(0)[0] / 4096) and torch.equal(out[0, 1], out[0, 0])
+    layer.close()
