@@ -17,7 +17,8 @@
 // registers of the present ones are free.  Bound by HBM on long caches, by the chain of launch, first loads and merge
 // on short ones.  Split kernel alone, against the vector form (which held 8 dims x 4 heads of a row in a lane): 8 heads x
 // 16.4K x 128 dims 16.6 -> 14.1 us (67 MB), 8 x 6.1K 10.4 -> 7.6, 8 x 2K 8.2 -> 6.4, 8 x 16.4K x 64 12.1 -> 8.7, 32 x 8.2K x 96
-// 17.2 -> 16.8, 32 x 2K x 96 6.3 -> 6.7.
+// 17.2 -> 16.8, 32 x 2K x 96 6.3 -> 6.7 (a token there, with the merge, 9.4 -> 8.8; one query head fills a sixteenth of the matrix
+// form's columns, and the vector form is still the slower one: 11.0).
 //
 // Other types: a key row is spread over LPR lanes (16 bytes per lane, padded to a power of two), so one load instruction of a
 // wavefront fetches 64 / LPRP whole rows, contiguous in memory.  Each lane keeps the query values of its own dims for G heads
@@ -589,8 +590,9 @@ __global__ __launch_bounds__(DEC_THREADS, D == 128 ? 3 : 1) void decode_attn_ker
 // The kernel is a chain of memory latencies, not of bytes (45 KB per head): every load that does not depend on another is
 // requested up front, and the wavefronts meet once.  A wavefront owns 64 dims of splits sg, sg + SG, ..., and forms the
 // weights of all splits itself, one or two a lane (their maxima and sums cost it two loads), from where a split's weight comes
-// as a scalar.  With a thread per (dim, eighth of the splits) of 1024 and three meetings in LDS the launch took 3.9 us, in this
-// form 3.1 (2.2 at best): 16 tokens on 8 x 16.4K x 128 dims 312 -> 298 us, 32 tokens on 8 x 6.2K 4-bit rows 1047 -> 991 with the prompt.
+// as a scalar.  Against a thread per (dim, eighth of the splits) of 1024 and three meetings in LDS a token (both launches, tokens back to back)
+// takes 0.8 us less: 8 heads x 128 dims, 2K units 9.1 -> 8.3 us, 16.4K 17.5 -> 16.7, 32 x 8.2K x 96 20.7 -> 19.9; by the kernel trace, which
+// sees the launch from its first wavefront on, this kernel takes 3.9 -> 2.6 to 3.2 us on 1K and 6K units, 3.8 as before on 16.4K.
 constexpr int DEC_MERGE_THREADS = 512;
 constexpr int DEC_MERGE_PRE = 96;       // splits requested before anything else
 
