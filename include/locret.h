@@ -169,15 +169,16 @@ int locret_score(locret_ctx* ctx, const void* q, const void* k, const void* v, i
 
 /* locret_score for callers that cannot allocate device memory or hand over a workspace region for scratch:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
- * kernels and bit-identical scores, but the kernels' scratch (partial scores per block of 128 hidden units,
+ * kernels and bit-identical scores, but the kernels' scratch (partial scores per block of hidden units,
  * and for short chunks the partial pre-activations of a split contraction) lies in a fixed array that is
  * part of the library's device code: 20 MiB per GPU that runs the library, held until the process ends,
  * looked up once per device in locret_create.  The call allocates nothing and frees nothing.
  * Limit: blocks * n_kv_heads * T <= LOCRET_STATIC_PART_FLOATS with blocks = d_hidden / 128 on the matrix-core path
  * (bf16, d_hidden a multiple of 128) and d_hidden / 64 rounded up otherwise,
  * else LOCRET_ELIMIT and nothing is launched (the five named configurations fit at their chunk sizes).  Short
- * chunks split the contraction as locret_score does as long as the slices fit 4 Mi floats; beyond that they run
- * unsplit (same scores up to summation order).
+ * chunks may use blocks half as wide, here and in locret_score, as long as those partial scores are at most
+ * LOCRET_STATIC_PART_FLOATS too; the limit does not depend on it.  They split the contraction as locret_score does
+ * as long as the slices fit 4 Mi floats; beyond that they run unsplit (same scores up to summation order).
  * Every call on a GPU, from any context, shares that GPU's array and nothing in it has to start at zero (a call
  * writes every element before reading it): calls that overlap in time on one GPU (two streams, two threads)
  * race and must be ordered by the caller.  LOCRET_ESTATE if the context was created on a device index >= 64. */
@@ -227,7 +228,9 @@ int locret_cache_view_q4(const locret_ctx* ctx, const void** Kq, const void** Vq
  * Mode 0 (default) times every stage with events between the kernels.  Mode 2 times every stage through the
  * dispatches of its own kernels (first kernel's begin to last kernel's end; no extra packets, so the figures are
  * pure kernel durations, as a profiler's kernel trace reports them; where the selection rides in the attention
- * launch its entry is 0 and the attention entry covers it).  The mode can be changed while no recorded call is
+ * launch its entry is 0 and the attention entry covers it).  On float32 layers a recorded call launches the append by
+ * itself in front of the attention; an unrecorded one carries it in the retaining head's launch, which then comes before
+ * the attention (same results, a few microseconds less).  The mode can be changed while no recorded call is
  * unread (LOCRET_ESTATE otherwise). */
 #define LOCRET_PROF_STAGES 5
 int locret_profile_mode(locret_ctx* ctx, int32_t mode);

@@ -79,3 +79,24 @@ def test_static_scratch_limit_and_argument_errors():
     ctx = B.locret_create(cfg, ws)
     assert call(ctx, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), 16, sc.data_ptr(), None) == B.LOCRET_ESTATE   # no weights
     B.locret_destroy(ctx)
+
+
+@pytest.mark.parametrize("kw,Ts", [
+    (dict(dtype="bf16", h=96, h_kv=96, d=16, B=700), (682, 683)),         # 16 x 96 x 682 floats are the last below 2^20
+    (dict(dtype="f32", h=320, h_kv=320, d=16, B=256), (102, 103)),        # 32 x 320 x 102
+], ids=["bf16", "f32"])
+def test_static_scratch_takes_the_finer_partials_as_far_as_the_workspace_does(kw, Ts):
+    """On both sides of the most partial scores of half-wide hidden blocks, which fill the static array."""
+    w = synth.tiny(name="static_fine", N=sum(Ts), b=kw["B"], n_s=0, d_R=1024, theta=10000.0, **kw)
+    layer, W1, W2 = make_layer(w)
+    lo = 0
+    for T in Ts:
+        x = synth.tokens(w, lo, lo + T)
+        got, ref = _scores_both_ways(layer, w, *x)
+        np.testing.assert_array_equal(got.view(np.uint32), ref.view(np.uint32))
+        z = np.concatenate([t.reshape(T, -1) for t in x], 1).astype(np.float64) @ W1.astype(np.float64)
+        exact = (z / (1 + np.exp(-z)) @ W2.astype(np.float64)).T
+        # float32 sums of up to 15360 products, then of 1024: sqrt(15360) + sqrt(1024) roundings of 2^-24 in the mean, 1e-5; ten times that
+        assert np.abs(got - exact).max() <= 1e-4 * np.abs(exact).max()
+        lo += T
+    layer.close()
