@@ -83,7 +83,7 @@ inline double score_cost(const ScorePlan& p, double xcd_load, int stages, int h_
 // But a slice also gets longer by that, a chain of stages that may take more than the finish kernel saved, and 64-unit tiles ask
 // the L2s for more: d_R = 512: 1100 tokens (3 slices, 1) 24.2 / 25.0, 23.9 / 32.3, 1300 (3, 1) 26.4 / 27.1, 24.9 / 33.4; d_R = 384: 900 (4, 2)
 // 19.9 / 21.2, 21.7 / 22.4.  So both are estimated.  Over 450 launches (16 layouts, d_R 128 .. 2048, 64 .. 4096 tokens) the choice takes
-// 0.86 (last-level cache) and 0.92 (HBM) of the time of 128 x 64 tiles, within 0.2 % of always taking the better form.  It is the
+// 0.86 (last-level cache) and 0.92 (HBM) of the time of 128 x 64 tiles, 0.2 % more than the better form of each would in the mean.  It is the
 // slower one for locret_score from HBM where the slices of 64 x 64 tiles are long: d_R = 1024, 611 tokens (3, 1) 27.1 / 27.0, 23.9 / 31.9; in a
 // prompt, where the append or the attention has read the inputs before, that launch is the faster one (a 611-token prompt and
 // 8 scored tokens 126.7, 121.4 us).
