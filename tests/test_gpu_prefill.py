@@ -568,7 +568,7 @@ def test_float32_partial_scores_up_to_the_end_of_their_room(T):
     layer.close()
 
 
-@pytest.mark.parametrize("d_R,T", [(512, 300), (512, 65), (1024, 833), (256, 450)])
+@pytest.mark.parametrize("d_R,T", [(512, 300), (1024, 65), (1024, 833), (256, 385)])
 def test_retaining_head_numbered_along_the_hidden_units(d_R, T):
     """64 x 64 tiles whose workgroups are numbered along the hidden units, with and without slices of the contraction, a last token
     tile of one token among them."""
